@@ -46,58 +46,32 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
   return p;
 }
 
-// Maxima as single instructions.  (fmaxf on raw matrix-instruction results makes the compiler add a
-// canonicalising v_max per input.)  The inputs are logits or -inf, never NaN.  The instructions read
-// results of matrix instructions issued at least a whole softmax slice plus a stage prologue earlier,
-// far beyond the wait states such a read needs.
-__device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ float max2(float a, float b) {
-  float r;
-  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-
-// QT = 32-row query tiles per wave.  With QT = 2 every K / V^T fragment read from LDS feeds two
-// matrix instructions, which halves the LDS bytes per matrix instruction, but at d = 128 the
-// accumulators then need the whole register file, i.e. one wave per SIMD.  Measured: the lone wave runs
-// at a higher clock (2.1 against 1.8 GHz, it draws less power) but keeps the matrix cores busy only
-// 43 % of the cycles against 57 % for two waves: a wave issues in order, about one instruction per five
-// cycles, and one wave's stream of ~9 instructions per matrix instruction cannot fill the pipe alone.
-// Net 960 against 1070 TFLOP/s on cache-resident keys, so QT = 1 is what is launched.
-//
 // XLSE: the caller wants the log-sum-exp.  The normaliser of O sums the probabilities as rounded to bf16
-// (see `pack` below), which is right for O but leaves ln(sum) off by up to bf16's unit roundoff 2^-8; with
+// (see the row sums below), which is right for O but leaves ln(sum) off by up to bf16's unit roundoff 2^-8; with
 // XLSE a second running sum of the unrounded fp32 probabilities is kept for the log-sum-exp alone.
 //
 // Waves per SIMD: two at d = 128 (about 250 registers each).  At d = 64 the kernel needs about 160 registers, so
 // three waves fit (measured 36 -> 43 % of the matrix cycles, +8 % throughput on the 17 550- and 75 600-token
 // shapes); the variants that would have to spill for that (64-row blocks, log-sum-exp output) stay at two.
-template <int D, int QT, int BM, bool XLSE>
-constexpr int attn_waves() { return D == 64 && QT == 1 && BM == 128 && !XLSE ? 3 : 2 / QT; }
-template <int D, int BM, int QT, bool XLSE>
-__global__ void __launch_bounds__(BM * 2 / QT)
-__attribute__((amdgpu_waves_per_eu(attn_waves<D, QT, BM, XLSE>(), attn_waves<D, QT, BM, XLSE>())))
+template <int D, int BM, bool XLSE>
+constexpr int attn_waves() { return D == 64 && BM == 128 && !XLSE ? 3 : 2; }
+template <int D, int BM, bool XLSE>
+__global__ void __launch_bounds__(BM * 2)
+__attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE>(), attn_waves<D, BM, XLSE>())))
 attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                  const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
                  float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
                  int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe) {
-  constexpr int NW = BM / (32 * QT);               // waves: one per 32 QT query rows
+  constexpr int NW = BM / 32;                      // waves: one per 32 query rows
   constexpr int CH = D / 8;                        // 16-byte chunks per row
   constexpr int TILE = KN * D;                     // elements per tile
   constexpr int LPW = KN * CH / (64 * NW);         // load instructions per wave and tile
   constexpr int RJ = NW * 64 / CH;                 // tile rows between two load instructions of a wave
   constexpr int STEPS = BM / KN;                   // tiles per key block
   constexpr int NF = D / 8;                        // operand fragments per stage: D/16 of V^T, D/16 of K
-  constexpr int SLOTS = NF * QT;                   // matrix instructions per stage
-  constexpr int ESL = 12;                          // slices the sixteen exponentials of a query tile are spread over
-  constexpr int SL = 5 + ESL;                      // softmax slices per query tile: 4 for the maximum, ESL, 1 to close
-  constexpr int SLICES = SL * QT;                  // softmax slices per stage
-  constexpr int STAGE_LEN = SLOTS > SLICES ? SLOTS : SLICES;
-  constexpr float TAU = 8.f;                       // rescale only when the row maximum grows by > 2^TAU
+  constexpr int ESL = NF - 1;                      // matrix instructions the sixteen exponentials of a half tile are spread over
+  constexpr float HEADROOM = 16.f;                 // exponents of two: see "No maximum is taken" below
+  constexpr float SUM_HIGH = 65536.f, SUM_LIMIT = 281474976710656.f;      // 2^16, 2^48
   // Two K and two V tile buffers (tile t lives in the pair of parity t & 1).
   __shared__ __attribute__((aligned(16))) uint16_t sK0[TILE];
   __shared__ __attribute__((aligned(16))) uint16_t sK1[TILE];
@@ -149,43 +123,36 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   const int64_t head_off = int64_t(head) * N_pad * D;
   const uint16_t* kh = k + head_off;
   const uint16_t* vh = v + head_off;
-  const int64_t q_row0 = int64_t(u) * BM + wave * (32 * QT) + n;      // query tile a adds 32 a
+  const int64_t q_row0 = int64_t(u) * BM + wave * 32 + n;
 
   // Where this lane's query rows live.  With row_index (the permutation) Q is read from, and O written to,
   // the tensors in source order, which spares the reorder passes of Q and O; -1 marks a pad row.
-  int64_t io_row[QT];
-#pragma unroll
-  for (int a = 0; a < QT; ++a) {
-    const int64_t pos = q_row0 + 32 * a;
-    io_row[a] = row_index ? int64_t(row_index[pos]) : pos;
-    if (row_index && io_row[a] >= N_src) io_row[a] = -1;
-  }
+  int64_t io_row = row_index ? int64_t(row_index[q_row0]) : q_row0;
+  if (row_index && io_row >= N_src) io_row = -1;
   const int64_t io_off = int64_t(head) * (row_index ? N_src : N_pad) * D;
 
   // Q rows as the B operand of S^T = K Q^T: lane (n, h) holds Q[row][16 kk + 8 h .. + 7]
-  bf16x8 qf[QT][D / 16];
+  bf16x8 qf[D / 16];
+  {
+    const u32x4* qp = reinterpret_cast<const u32x4*>(q + io_off + (io_row < 0 ? 0 : io_row) * D);
 #pragma unroll
-  for (int a = 0; a < QT; ++a) {
-    const u32x4* qp = reinterpret_cast<const u32x4*>(q + io_off + (io_row[a] < 0 ? 0 : io_row[a]) * D);
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk)
-      qf[a][kk] = __builtin_bit_cast(bf16x8, io_row[a] < 0 ? u32x4{0u, 0u, 0u, 0u} : qp[2 * kk + h]);
+    for (int kk = 0; kk < D / 16; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, io_row < 0 ? u32x4{0u, 0u, 0u, 0u} : qp[2 * kk + h]);
   }
 
-  f32x16 oacc[QT][D / 32];
+  f32x16 oacc[D / 32];
 #pragma unroll
-  for (int a = 0; a < QT; ++a)
+  for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) oacc[a][dt][i] = 0.f;
-  float m_run[QT], l_run[QT], x_run[QT];           // x_run: unrounded normaliser (XLSE only)
-  // m_run is the reference maximum in the base-2 exponent's units (logit x c2).  It starts at a large
-  // finite negative value instead of -inf, so that a row that has only met pad keys (all logits -inf)
-  // needs no special case: its differences stay finite and its probabilities are exp2(-inf) = 0.
-  constexpr float M_START = -1.0e30f;
-#pragma unroll
-  for (int a = 0; a < QT; ++a) { m_run[a] = M_START; l_run[a] = 0.f; x_run[a] = 0.f; }
+    for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
+  float m_run = 0.f, x_run = 0.f;                  // reference in the base-2 exponent's units (logit x c2); unrounded normaliser (XLSE only)
+  // Row sums of the probabilities as rounded to bf16 (numerator and denominator then use exactly the same weights, so
+  // a dominant key leaves no systematic rounding bias), on the matrix cores: a 16x16x32 product takes the same B operand
+  // registers as the 32x32x16 one, but reads lanes 16 g + n as keys 8 g .. 8 g + 7 of column n.  With ones where the
+  // parity of the key group equals that of the result row's group, every lane's result is the sum over both lane
+  // halves of its own query row.
+  f32x4 lsum = {0.f, 0.f, 0.f, 0.f};
+  const uint32_t one_pair = (((lane >> 4) ^ (lane >> 2)) & 1) == 0 ? 0x3F803F80u : 0u;
+  const bf16x8 row_ones = __builtin_bit_cast(bf16x8, u32x4{one_pair, one_pair, one_pair, one_pair});
   const float c2 = scale * 1.4426950408889634f;     // softmax in base 2
 
   // Tile loads, global memory straight into LDS: instruction j of this wave fills the 64 consecutive
@@ -259,18 +226,12 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(p0 + 8 * D));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  auto logits = [&](const uint16_t* kbuf, int half, f32x16 (&sx)[QT]) {
+  auto logits = [&](const uint16_t* kbuf, int half, f32x16& sx) {
     const uint16_t* tK = kbuf + (32 * half + n) * D;
 #pragma unroll
-    for (int a = 0; a < QT; ++a)
+    for (int i = 0; i < 16; ++i) sx[i] = 0.f;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sx[a][i] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
-      const bf16x8 f = k_frag(tK, kk);
-#pragma unroll
-      for (int a = 0; a < QT; ++a) sx[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[a][kk], sx[a], 0, 0, 0);
-    }
+    for (int kk = 0; kk < D / 16; ++kk) sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(tK, kk), qf[kk], sx, 0, 0, 0);
   };
   // pad keys of a ragged block never count.  Only two blocks can be ragged, the last video block and the last text
   // block; their ids and real-row counts are worked out once, so that the check per half tile is two scalar compares
@@ -279,145 +240,124 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   const int real_v_last = block_real_rows(M_v - 1, BM, M_v, N_v, n_text);
   const int real_x_last = M > M_v ? block_real_rows(M - 1, BM, M_v, N_v, n_text) : BM;
   const int ragged_v = real_v_last < BM ? M_v - 1 : -1, ragged_x = real_x_last < BM ? M - 1 : -1;
-  auto mask_pads = [&](int blk, int tile, int half, f32x16 (&sx)[QT]) {
+  auto mask_pads = [&](int blk, int tile, int half, f32x16& sx) {
     if (__builtin_expect(blk == ragged_v || blk == ragged_x, 0)) {
       asm volatile("");                               // keeps this a branch: turned into selects it would run on every half tile
       const int real = blk == ragged_v ? real_v_last : real_x_last;
       const int base = (tile % STEPS) * KN + 32 * half;
 #pragma unroll
-      for (int a = 0; a < QT; ++a)
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (base + 8 * (i / 4) + 4 * h + (i % 4) >= real) sx[a][i] = -INFINITY;
+      for (int i = 0; i < 16; ++i)
+        if (base + 8 * (i / 4) + 4 * h + (i % 4) >= real) sx[i] = -INFINITY;
     }
   };
 
-  // One pipeline stage, written out in issue order.  Fragments alternate between V^T of the previous
-  // half tile (products O^T += V^T P^T with its probabilities `pp`) and K of the next half tile (logit
-  // chains into `sn`); every fragment feeds one matrix instruction per query tile.  In the shadow of
-  // the matrix instructions the vector units run slices of the online softmax of the current half tile
-  // `sx` (this lane and lane^32 hold the two halves of a query row's keys), producing `pc`.  The
-  // reference maximum only moves when the row maximum outgrows it by more than 2^TAU, so the
-  // accumulators are rescaled rarely; probabilities stay below 2^TAU, which is exact in the final
-  // ratio.  Scheduling fences and empty asm statements keep the compiler from separating the matrix and
-  // vector work again.  alpha[a] is the factor accumulator a must be multiplied by after the stage.
-  auto stage = [&](auto do_pv, auto do_s, const uint16_t* vbuf, int pv_half, const u32x4 (&pp)[QT][2], const uint16_t* kbuf,
-                   int s_half, f32x16 (&sn)[QT], const f32x16 (&sx)[QT], u32x4 (&pc)[QT][2], float (&alpha)[QT], bool (&moved)[QT]) {
+  // One pipeline stage, written out in issue order.  Fragments alternate between K of the next half tile (logit chain
+  // into `sn`) and V^T of the previous half tile (products O^T += V^T P^T with its probabilities `pp`, and their row
+  // sums).  In the shadow of the matrix instructions the vector units turn the logits `sx` of the current half tile
+  // into probabilities `pc`.  Scheduling fences and empty asm statements keep the compiler from separating the matrix
+  // and vector work again.
+  //
+  // No maximum is taken on the way.  The final ratio does not depend on a row's reference m_run, and floating-point
+  // weights lose nothing by being small or large, so the reference is the maximum of the row's first half tile times
+  // 2^HEADROOM and stays until the row sum says that it is outgrown: every two tiles `rebase` looks whether a sum has
+  // reached SUM_HIGH (2^32 times what the first half tile's maximum alone gives) and if so, rarely, divides
+  // everything by a power of two.  A sum at SUM_LIMIT or beyond is left alone, can only grow, and makes the work-group
+  // do its work again from the true maximum at the end.  A half tile is then forty vector instructions (sixteen
+  // fused multiply-adds and exponentials, eight packs) instead of sixty-seven with its maximum, the factor
+  // 2^(m_old - m_new) and a row sum on the vector unit.  Measured with the row sums on the matrix cores: d = 64,
+  // 17 550 tokens x 48 heads, 743 -> 675 us; d = 128, 75 600 tokens x 40 heads, 60 of 591 blocks, 11.9 -> 11.3 ms
+  // (the matrix cores are busy 63.5 instead of 60 % of the cycles, and the clock falls from 1.66 to 1.60 GHz).
+  auto half_max = [&](const f32x16& x) __attribute__((always_inline)) {      // row maximum of a half tile, in both lane halves
+    float mx = x[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, x[i]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  };
+  auto pack = [&](float a, float b) __attribute__((always_inline)) {
+    const bf16x2 pk = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, pk);
+  };
+  auto rebase = [&](u32x4 (&pc)[2]) __attribute__((always_inline)) {         // pc: probabilities not yet summed
+    const bool high = lsum[0] >= SUM_HIGH && lsum[0] < SUM_LIMIT;           // the same in both lane halves of a row
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(high) != 0, 0)) {
+      const float shift = high ? HEADROOM + float(int(__float_as_uint(lsum[0]) >> 23) - 127) : 0.f;
+      const float alpha = __builtin_amdgcn_exp2f(-shift);                    // a power of two
+      m_run += shift;
+      x_run *= alpha;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) lsum[i] *= alpha;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t u = pc[i / 4][i % 4];
+        pc[i / 4][i % 4] = pack(__uint_as_float(u << 16) * alpha, __uint_as_float(u & 0xFFFF0000u) * alpha);
+      }
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          float y = oacc[dt][i];                      // in place: the accumulators keep one home across the branch
+          asm volatile("v_mul_f32 %0, %1, %0" : "+v"(y) : "v"(alpha));
+          oacc[dt][i] = y;
+        }
+    }
+  };
+  auto stage = [&](auto do_pv, auto do_s, const uint16_t* vbuf, int pv_half, const u32x4 (&pp)[2], const uint16_t* kbuf,
+                   int s_half, f32x16& sn, const f32x16& sx, u32x4 (&pc)[2]) __attribute__((always_inline)) {
     constexpr bool DO_PV = decltype(do_pv)::value, DO_S = decltype(do_s)::value;
     const uint16_t* tV = vbuf + (32 * pv_half + v_row) * D + v_b;
     const uint16_t* tK = kbuf + (32 * s_half + n) * D;
     bf16x8 frag[NF];
     auto load = [&](int f) {
-      if (f % 2 == 0) {
+      if (f % 2 == 1) {
         if (DO_PV) frag[f] = v_frag(tV, f / 2);
       } else if (DO_S) {
         frag[f] = k_frag(tK, f / 2);
       }
     };
-    float mx_a = 0.f, mx_b = 0.f, mx_c = 0.f, mx_d = 0.f, mx = 0.f, mc = 0.f, psum = 0.f, xsum = 0.f;
-    bool move = false;
-    float pe[16];
-    // Rounds a pair of probabilities to bf16 and adds them, as rounded, to the normaliser: numerator and
-    // denominator then use exactly the same weights, so a dominant key leaves no systematic rounding bias.
-    // The pair is one 32-bit register of the next product's B operand.
-    auto pack = [&](int a, int i) {
-      const bf16x2 pk = {(__bf16)pe[i], (__bf16)pe[i + 1]};
-      psum = __builtin_amdgcn_fdot2_f32_bf16(pk, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, psum, false);
-      if (XLSE) xsum += pe[i] + pe[i + 1];
-      pc[a][i / 8][(i % 8) / 2] = __builtin_bit_cast(uint32_t, pk);
-    };
+    float pe[16], xsum = 0.f;
     if (DO_S) {
 #pragma unroll
-      for (int a = 0; a < QT; ++a)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sn[a][i] = 0.f;
+      for (int i = 0; i < 16; ++i) sn[i] = 0.f;
     }
-    constexpr int AHEAD = 3;                          // fragments requested ahead of their matrix instruction (2: 1 % slower;
-                                                      // 4 needs two registers more than there are)
+    constexpr int AHEAD = 3;                          // fragments requested ahead of their matrix instruction
 #pragma unroll
     for (int f = 0; f < AHEAD; ++f) load(f);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int m = 0; m < STAGE_LEN; ++m) {
-      if (m < SLOTS) {
-        const int f = m / QT, a = m % QT;
-        if (a == 0 && f + AHEAD < NF) load(f + AHEAD);
-        if (f % 2 == 0) {
-          if (DO_PV) {
-            const int j = f / 2, s2 = j / (D / 32), dt = j % (D / 32);
-            oacc[a][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[f], __builtin_bit_cast(bf16x8, pp[a][s2]), oacc[a][dt], 0, 0, 0);
-          }
-        } else if (DO_S) {
-          sn[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[f], qf[a][f / 2], sn[a], 0, 0, 0);
+    for (int f = 0; f < NF; ++f) {
+      if (f + AHEAD < NF) load(f + AHEAD);
+      if (f % 2 == 1) {
+        if (DO_PV) {
+          const int j = f / 2, s2 = j / (D / 32), dt = j % (D / 32);
+          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[f], __builtin_bit_cast(bf16x8, pp[s2]), oacc[dt], 0, 0, 0);
+          if (dt == D / 64) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, __builtin_bit_cast(bf16x8, pp[s2]), lsum, 0, 0, 0);
+        }
+      } else if (DO_S) {
+        sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[f], qf[f / 2], sn, 0, 0, 0);
+      }
+      if (f < ESL) {
+#pragma unroll
+        for (int i = f * 16 / ESL; i < (f + 1) * 16 / ESL; ++i) {
+          pe[i] = __builtin_amdgcn_exp2f(fmaf(sx[i], c2, -m_run));
+          asm volatile("" : "+v"(pe[i]));
         }
       }
-      if (m < SLICES) {
-        const int a = m / SL, ph = m % SL;
-        const f32x16& x = sx[a];
-        if (ph == 0) {
-          mx_a = max3(x[0], x[1], x[2]);
-          mx_b = max3(x[3], x[4], x[5]);
-          mx_c = max3(x[6], x[7], x[8]);
-          mx_d = max3(x[9], x[10], x[11]);
-          psum = 0.f;
-          xsum = 0.f;
-        } else if (ph == 1) {
-          mx_a = max3(mx_a, mx_b, mx_c);
-          mx_d = max3(mx_d, x[12], x[13]);
-          mx_a = max3(mx_a, x[14], x[15]);
-          mx = max2(mx_a, mx_d);
-          asm volatile("" : "+v"(mx));                 // keeps the slice in its slot (its result is needed only later)
-        } else if (ph == 2) {
-          const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-          mx = max2(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c2;
-          asm volatile("" : "+v"(mx));
-        } else if (ph == 3) {
-          move = mx - m_run[a] > TAU;                  // true on the first real half tile (m_run = M_START)
-          mc = move ? mx : m_run[a];
-          asm volatile("" : "+v"(mc));
-        } else if (ph < 4 + ESL) {                    // the sixteen probabilities, spread evenly over ESL slices
-          const int eb = (ph - 4) * 16 / ESL, ee = (ph - 3) * 16 / ESL;
+      if (f > 0 && f <= ESL) {                        // pairs completed in the slot before: their exponentials have retired
 #pragma unroll
-          for (int i = eb; i < ee; ++i) {
-            pe[i] = __builtin_amdgcn_exp2f(fmaf(x[i], c2, -mc));
-            asm volatile("" : "+v"(pe[i]));
+        for (int i = (f - 1) * 16 / ESL; i < f * 16 / ESL; ++i)
+          if (i % 2 == 1) {
+            pc[i / 8][(i % 8) / 2] = pack(pe[i - 1], pe[i]);
+            if (XLSE) xsum += pe[i - 1] + pe[i];
           }
-          if (ph > 4) {                               // pairs completed by the previous slice: its exponentials have retired
-            const int pb = (ph - 5) * 16 / ESL, pe_ = (ph - 4) * 16 / ESL;
+      }
+      if (f == NF - 1) {
 #pragma unroll
-            for (int i = pb; i < pe_; ++i)
-              if (i % 2 == 1) pack(a, i - 1);
-          }
-        } else {
-#pragma unroll
-          for (int i = (ESL - 1) * 16 / ESL; i < 16; ++i)
-            if (i % 2 == 1) pack(a, i - 1);
-          alpha[a] = __builtin_amdgcn_exp2f(m_run[a] - mc);              // 1 unless the maximum moved
-          moved[a] = __builtin_amdgcn_ballot_w64(move) != 0;
-          m_run[a] = mc;
-          l_run[a] = l_run[a] * alpha[a] + psum;
-          if (XLSE) x_run[a] = x_run[a] * alpha[a] + xsum;
-          asm volatile("" : "+v"(l_run[a]), "+v"(alpha[a]));
-        }
+        for (int i = (ESL - 1) * 16 / ESL; i < 16; ++i) asm volatile("" : "+v"(pc[i / 8][(i % 8) / 2]));
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-  };
-  // accumulators *= alpha, in place (the multiply is tied to its register so that the accumulators keep
-  // one home across the rarely taken branch)
-  auto rescale = [&](const float (&alpha)[QT], const bool (&moved)[QT]) {
-#pragma unroll
-    for (int a = 0; a < QT; ++a)
-      if (moved[a]) {
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            float x = oacc[a][dt][i];
-            asm volatile("v_mul_f32 %0, %1, %0" : "+v"(x) : "v"(alpha[a]));
-            oacc[a][dt][i] = x;
-          }
-      }
+    if (XLSE) x_run += xsum;
   };
   using yes = std::true_type;
   using no = std::false_type;
@@ -425,20 +365,17 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // Software pipeline over half tiles.  K(t+2) and V(t+1) are requested once per tile, right after the
   // barrier in the middle of tile t, into the buffers K(t) and V(t-1) have just left; they are first
   // read a full tile later.
-  f32x16 s0[QT], s1[QT];
-  u32x4 p0[QT][2], p1[QT][2];                      // probabilities as bf16 pairs: B operands of the products
+  f32x16 s0, s1;
+  u32x4 p0[2], p1[2];                              // probabilities as bf16 pairs: B operands of the products
   int b_cur = 0, b_nxt = 0;                        // key blocks of tiles t and t + 1: one list lookup per tile (that of tile t + 2)
-  auto tile_step = [&](auto parity, auto first, auto last, int t) {
+  auto tile_step = [&](auto parity, auto first, auto last, int t) __attribute__((always_inline)) {
     constexpr bool ODD = decltype(parity)::value, FIRST = decltype(first)::value, LAST = decltype(last)::value;
     uint16_t* k_cur = ODD ? sK1 : sK0;             // K(t); K(t+2) goes here
     uint16_t* k_nxt = ODD ? sK0 : sK1;             // K(t+1)
     uint16_t* v_cur = ODD ? sV1 : sV0;             // V(t)
     uint16_t* v_nxt = ODD ? sV0 : sV1;             // V(t-1); V(t+1) goes here
-    float alpha[QT];
-    bool moved[QT];
-    // first half: products of (t-1, 1), logits of (t, 1), softmax of (t, 0)
-    stage(std::integral_constant<bool, !FIRST>{}, yes{}, v_nxt, 1, p1, k_cur, 1, s1, s0, p0, alpha, moved);
-    rescale(alpha, moved);
+    // first half: products of (t-1, 1), logits of (t, 1), probabilities of (t, 0)
+    stage(std::integral_constant<bool, !FIRST>{}, yes{}, v_nxt, 1, p1, k_cur, 1, s1, s0, p0);
     mask_pads(b_cur, t, 1, s1);
     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wave's parts of K(t+1) and V(t) landed
     __syncthreads();                                 // all parts landed; every wave is past the first half of tile t
@@ -450,12 +387,20 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       }
       issue(vh, v_nxt, true, t + 1, b_nxt);
     }
-    // second half: products of (t, 0), logits of (t+1, 0), softmax of (t, 1)
-    stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1, alpha, moved);
-    rescale(alpha, moved);
+    // second half: products of (t, 0), logits of (t+1, 0), probabilities of (t, 1)
+    stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1);
     if (!LAST) mask_pads(b_nxt, t + 1, 0, s0);
     b_cur = b_nxt;
     b_nxt = b_new;
+  };
+  auto products = [&](const uint16_t* vbuf, int half, const u32x4 (&pp)[2]) __attribute__((always_inline)) {    // O^T += V^T P^T
+    const uint16_t* tV = vbuf + (32 * half + v_row) * D + v_b;
+#pragma unroll
+    for (int j = 0; j < 2 * (D / 32); ++j) {
+      const bf16x8 pj = __builtin_bit_cast(bf16x8, pp[j / (D / 32)]);
+      oacc[j % (D / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(tV, j), pj, oacc[j % (D / 32)], 0, 0, 0);
+      if (j % (D / 32) == 0) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, pj, lsum, 0, 0, 0);
+    }
   };
   if (n_tiles > 0) {
     b_cur = tile_block(0);
@@ -467,6 +412,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     if (n_tiles > 1) issue(kh, sK1, false, 1, b_nxt);
     logits(sK0, 0, s0);
     mask_pads(b_cur, 0, 0, s0);
+    m_run = fmaf(half_max(s0), c2, HEADROOM);        // finite: the first row of a block is never a pad
     if (n_tiles == 1) {
       tile_step(no{}, yes{}, yes{}, 0);
     } else {
@@ -475,19 +421,49 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       for (; t + 2 < n_tiles; t += 2) {              // middle tiles in pairs: buffer parities are compile-time
         tile_step(yes{}, no{}, no{}, t);
         tile_step(no{}, no{}, no{}, t + 1);
+        rebase(p1);
       }
       if (t + 1 < n_tiles) { tile_step(yes{}, no{}, no{}, t); ++t; }
       if (t & 1) tile_step(yes{}, no{}, yes{}, t);
       else tile_step(no{}, no{}, yes{}, t);
     }
-    // drain: products of the last half tile
-    const uint16_t* tV = ((n_tiles - 1) & 1 ? sV1 : sV0) + (32 + v_row) * D + v_b;
+    products((n_tiles - 1) & 1 ? sV1 : sV0, 1, p1);  // drain: the last half tile
+    if (__builtin_expect(__syncthreads_or(!(lsum[0] < SUM_LIMIT)), 0)) {
+      // Once more in plain order, with the reference at the row's true maximum: first that maximum, then the sums.
+      x_run = 0.f;
+      lsum = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < 2 * (D / 32); ++j) {
-      const bf16x8 f = v_frag(tV, j);
+      for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-      for (int a = 0; a < QT; ++a)
-        oacc[a][j % (D / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, __builtin_bit_cast(bf16x8, p1[a][j / (D / 32)]), oacc[a][j % (D / 32)], 0, 0, 0);
+        for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
+      float mx = -INFINITY;
+#pragma unroll 1
+      for (int step = 0; step < 2 * n_tiles; ++step) {
+        const bool sums = step >= n_tiles;
+        const int t = sums ? step - n_tiles : step, blk = tile_block(t);
+        issue(kh, sK0, false, t, blk);
+        issue(vh, sV0, true, t, blk);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+          logits(sK0, half, s0);
+          mask_pads(blk, t, half, s0);
+          if (!sums) {
+            mx = fmaxf(mx, half_max(s0));
+            m_run = fmaf(mx, c2, HEADROOM);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 16; i += 2) {
+              const float a = __builtin_amdgcn_exp2f(fmaf(s0[i], c2, -m_run)), b = __builtin_amdgcn_exp2f(fmaf(s0[i + 1], c2, -m_run));
+              p0[i / 8][(i % 8) / 2] = pack(a, b);
+              x_run += a + b;
+            }
+            products(sV0, half, p0);
+          }
+        }
+        __syncthreads();
+      }
     }
   }
 
@@ -497,28 +473,23 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     atomicAdd(&clock_probe[2], 1ull);
   }
   // epilogue: normalise, round to bf16, store.  Lane (n, h) holds O[row][32 dt + 8 j + 4 h + 0..3].
+  const float inv = lsum[0] > 0.f ? 1.0f / lsum[0] : 0.f;
+  if (io_row >= 0) {
+    uint16_t* orow = o + io_off + io_row * D;
 #pragma unroll
-  for (int a = 0; a < QT; ++a) {
-    const float l_tot = l_run[a] + __shfl_xor(l_run[a], 32, 64);
-    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    uint16_t* orow = o + io_off + (io_row[a] < 0 ? 0 : io_row[a]) * D;
-    if (io_row[a] >= 0) {
+    for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt)
+      for (int j = 0; j < 4; ++j) {
+        bf16x4 w;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          bf16x4 w;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = (__bf16)(oacc[a][dt][4 * j + e] * inv);
-          *reinterpret_cast<u32x2*>(orow + 32 * dt + 8 * j + 4 * h) = __builtin_bit_cast(u32x2, w);
-        }
-    }
-    if (XLSE) {
-      const float x_tot = x_run[a] + __shfl_xor(x_run[a], 32, 64);
-      if (lse && h == 0)
-        lse[int64_t(head) * N_pad + q_row0 + 32 * a] =
-            x_tot > 0.f ? (m_run[a] + __builtin_amdgcn_logf(x_tot)) * 0.6931471805599453f : -INFINITY;
-    }
+        for (int e = 0; e < 4; ++e) w[e] = (__bf16)(oacc[dt][4 * j + e] * inv);
+        *reinterpret_cast<u32x2*>(orow + 32 * dt + 8 * j + 4 * h) = __builtin_bit_cast(u32x2, w);
+      }
+  }
+  if (XLSE) {
+    const float x_tot = x_run + __shfl_xor(x_run, 32, 64);
+    if (lse && h == 0)
+      lse[int64_t(head) * N_pad + q_row0] = x_tot > 0.f ? (m_run + __builtin_amdgcn_logf(x_tot)) * 0.6931471805599453f : -INFINITY;
   }
 }
 
@@ -618,14 +589,14 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     const int mapping = chunk >= 64 ? 2 : 1;
     const int per_xcd = mapping == 2 ? (g->heads * s.M_x + 7) / 8 + g->heads * chunk : int((total + 7) / 8);
     dim3 grid(unsigned(per_xcd * 8));
-#define ATTN_X(DD, BB, QQ, XX)                                                                                                  \
-  attn_bf16_kernel<DD, BB, QQ, XX><<<grid, BB * 2 / QQ, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
-                                                                 static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,          \
-                                                                 static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,  \
-                                                                 g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe)
-#define ATTN(DD, BB, QQ) do { if (lse) ATTN_X(DD, BB, QQ, true); else ATTN_X(DD, BB, QQ, false); } while (0)
-    if (g->d == 64) { if (g->B == 64) ATTN(64, 64, 1); else ATTN(64, 128, 1); }
-    else            { if (g->B == 64) ATTN(128, 64, 1); else ATTN(128, 128, 1); }
+#define ATTN_X(DD, BB, XX)                                                                                                      \
+  attn_bf16_kernel<DD, BB, XX><<<grid, BB * 2, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),       \
+                                                        static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                 \
+                                                        static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,         \
+                                                        g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe)
+#define ATTN(DD, BB) do { if (lse) ATTN_X(DD, BB, true); else ATTN_X(DD, BB, false); } while (0)
+    if (g->d == 64) { if (g->B == 64) ATTN(64, 64); else ATTN(64, 128); }
+    else            { if (g->B == 64) ATTN(128, 64); else ATTN(128, 128); }
 #undef ATTN
 #undef ATTN_X
   } else {
