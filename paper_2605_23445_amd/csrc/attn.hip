@@ -501,84 +501,177 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 }
 
 // ---------------------------------------------------------------------------------------------
-// fp32 kernel: correctness path for fp32 tensors (small problems).  One thread per query row, key
-// and value rows broadcast from LDS in tiles of 16, plain fp32 FMA, softmax rescaled once per tile.
+// fp32 kernel.  A work-group owns 32 query rows of one (head, query block); its eight waves split the kept keys, 32 at a
+// time in turn, each with a softmax of its own, and merge through LDS at the end, because calls on fp32 tensors are
+// small (a few thousand tokens) and have few query rows to fill the chip with, so what bounds them is one row's serial
+// walk through its keys.  Both products run on the fp32 matrix instruction (32x32x2: full fp32, the chip's fastest fp32
+// rate), transposed as in the bf16 kernel, with operands straight from memory: no key is shared between waves.  The
+// order of the summed features and of the output features is free, so lanes load 16 bytes of a key row (features
+// 8 c + 4 h ..) and D / 32 consecutive value features each.
+// Measured against one thread per query row with operands from LDS (which at d = 128 spilled its rows): 256 tokens x
+// 2 heads, d = 64, 2 of 4 blocks 89 -> 9 us; 3 600 tokens + 30 text rows x 6 heads, d = 128, 9 of 29 blocks 6 670 ->
+// 268 us (16 and 330 without the requests ahead of their use); error against 64 bits a half to a ninth of that kernel's
+// (3.2e-7 instead of 2.1e-6 at d = 128), since a row's sums are now eight shorter ones.
 template <int D>
-__global__ void __launch_bounds__(128) attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
+__global__ void __launch_bounds__(512) attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                                                        const float* __restrict__ v, const int32_t* __restrict__ kv_idx,
                                                        const int32_t* __restrict__ kv_cnt, int K_max, float* __restrict__ o,
-                                                       float* __restrict__ lse, int64_t N_pad, int64_t N_v, int n_text, int M_v,
-                                                       int M, int B, float scale) {
-  constexpr int TR = 16;
-  __shared__ __attribute__((aligned(16))) float sK[TR * D];
-  __shared__ __attribute__((aligned(16))) float sV[TR * D];
-  const int head = blockIdx.y, u = blockIdx.x, tid = threadIdx.x;
+                                                       float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src,
+                                                       int64_t N_pad, int64_t N_v, int n_text, int M_v, int M, int B, float scale) {
+  constexpr int NW = 8, DT = D / 32;
+  typedef float vrow __attribute__((ext_vector_type(DT)));
+  __shared__ float s_m[NW][32], s_l[NW][32];
+  __shared__ float s_o[NW / 2][DT * 16 * 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, h = lane >> 5;
+  const int log_parts = B == 128 ? 2 : 1, parts = 1 << log_parts;        // per block: groups of 32 query rows, runs of 32 keys
+  const int head = blockIdx.y, u = M - 1 - int(blockIdx.x >> log_parts); // the dense text rows start first
   const int cnt_in = kv_cnt[int64_t(head) * M + u];
   const bool dense = cnt_in >= M;
   const int cnt = dense ? M : (cnt_in < 0 ? 0 : (cnt_in > K_max ? K_max : cnt_in));
   const int32_t* idx = kv_idx + (int64_t(head) * M + u) * K_max;
-  const int64_t head_off = int64_t(head) * N_pad * D;
-  const int64_t q_row = int64_t(u) * B + tid;
-  float qr[D], acc[D];
-  const f32x4* qp = reinterpret_cast<const f32x4*>(q + head_off + q_row * D);
+  const float* kh = k + int64_t(head) * N_pad * D;
+  const float* vh = v + int64_t(head) * N_pad * D;
+  const int64_t q_row = int64_t(u) * B + int(blockIdx.x) % parts * 32 + n;
+  int64_t io_row = row_index ? int64_t(row_index[q_row]) : q_row;        // see the bf16 kernel
+  if (row_index && io_row >= N_src) io_row = -1;
+  const int64_t io_off = int64_t(head) * (row_index ? N_src : N_pad) * D;
+  f32x4 qf[D / 8];
 #pragma unroll
-  for (int c = 0; c < D / 4; ++c) {
-    const f32x4 t = qp[c];
-    qr[4 * c] = t[0] * scale; qr[4 * c + 1] = t[1] * scale; qr[4 * c + 2] = t[2] * scale; qr[4 * c + 3] = t[3] * scale;
+  for (int c = 0; c < D / 8; ++c)                    // a pad row reads row 0; it is not written
+    qf[c] = *reinterpret_cast<const f32x4*>(q + io_off + (io_row < 0 ? 0 : io_row) * D + 8 * c + 4 * h);
+  const float c2 = scale * 1.4426950408889634f;      // softmax in base 2
+  f32x16 oacc[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;              // reference in the exponent's units, this lane half's share of the sum
+  // This wave's next run of keys, skipping what lies wholly behind the real rows of a ragged block.
+  const int runs = cnt << log_parts;
+  int64_t row = 0;                                   // first key row of the run, the real ones among its 32
+  int real = 1;
+  auto next_run = [&](int j) {
+    for (; j < runs; j += NW) {
+      int blk = dense ? j >> log_parts : idx[j >> log_parts];
+      blk = unsigned(blk) < unsigned(M) ? blk : 0;   // a corrupt list must not read out of bounds
+      const int r0 = j % parts * 32;
+      const int left = block_real_rows(blk, B, M_v, N_v, n_text) - r0;
+      if (left <= 0) continue;
+      row = int64_t(blk) * B + r0;
+      real = left < 32 ? left : 32;
+      break;
+    }
+    return j;
+  };
+  // pad rows are never read: their keys and values repeat the last real one and are masked
+  f32x4 kf[D / 8];
+  vrow vf[16];
+  auto load_k = [&](const float* base, uint32_t off, int c) { kf[c] = *reinterpret_cast<const f32x4*>(base + off + 8 * c); };
+  int j = next_run(wave);
+  if (j < runs) {
+#pragma unroll
+    for (int c = 0; c < D / 8; ++c) load_k(kh + row * D, uint32_t(n < real ? n : real - 1) * D + 4 * h, c);
   }
+  while (j < runs) {
+    const float* vb = vh + row * D;
+    const int here = real;
+    f32x16 s;
 #pragma unroll
-  for (int c = 0; c < D; ++c) acc[c] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  for (int it = 0; it < cnt; ++it) {
-    int blk = dense ? it : idx[it];
-    blk = unsigned(blk) < unsigned(M) ? blk : 0;
-    const int real = block_real_rows(blk, B, M_v, N_v, n_text);
-    for (int r0 = 0; r0 < real; r0 += TR) {
-      const int rows = real - r0 < TR ? real - r0 : TR;
-      __syncthreads();
-      const f32x4* ks = reinterpret_cast<const f32x4*>(k + head_off + (int64_t(blk) * B + r0) * D);
-      const f32x4* vs = reinterpret_cast<const f32x4*>(v + head_off + (int64_t(blk) * B + r0) * D);
-      for (int c = tid; c < rows * (D / 4); c += B) {
-        reinterpret_cast<f32x4*>(sK)[c] = ks[c];
-        reinterpret_cast<f32x4*>(sV)[c] = vs[c];
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+    // the values are requested while the logits are formed, the keys of the next run during the value products
+#pragma unroll
+    for (int c = 0; c < D / 8; ++c) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[c][e], qf[c][e], s, 0, 0, 0);
+#pragma unroll
+      for (int i = c * 128 / D; i < (c + 1) * 128 / D; ++i) {
+        const int key = 8 * (i / 4) + 4 * h + i % 4;
+        vf[i] = *reinterpret_cast<const vrow*>(vb + (uint32_t(key < here ? key : here - 1) * D + DT * n));
       }
-      __syncthreads();
-      float s[TR];
-      float mx = -INFINITY;
+    }
+    j = next_run(j + NW);
+    // s[i]: key 8 (i / 4) + 4 h + i % 4 of the run against query row n
+    float mx = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < TR; ++j) {
-        float d0 = 0.f;
-        if (j < rows) {
+    for (int i = 0; i < 16; ++i) {
+      if (8 * (i / 4) + 4 * h + i % 4 >= here) s[i] = -INFINITY;
+      mx = fmaxf(mx, s[i]);
+    }
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    const float m_new = fmaxf(m_run, fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c2);
+    const float ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
+    m_run = m_new;
+    l_run *= alpha;
 #pragma unroll
-          for (int c = 0; c < D; ++c) d0 = fmaf(qr[c], sK[j * D + c], d0);
-        } else {
-          d0 = -INFINITY;
-        }
-        s[j] = d0;
-        mx = fmaxf(mx, d0);
-      }
-      const float m_new = fmaxf(m_run, mx);
-      const float alpha = __expf(m_run - m_new);
-      l_run *= alpha;
+    for (int i = 0; i < 16; ++i) {
+      s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], c2, -ref));
+      l_run += s[i];
+    }
 #pragma unroll
-      for (int c = 0; c < D; ++c) acc[c] *= alpha;
+    for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-      for (int j = 0; j < TR; ++j) {
-        if (j < rows) {
-          const float p = __expf(s[j] - m_new);
-          l_run += p;
+      for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
+    const float* kb = kh + row * D;                  // behind the last run: that run once more
+    const uint32_t k_off = uint32_t(n < real ? n : real - 1) * D + 4 * h;
 #pragma unroll
-          for (int c = 0; c < D; ++c) acc[c] = fmaf(p, sV[j * D + c], acc[c]);
-        }
-      }
-      m_run = m_new;
+    for (int i = 0; i < 16; ++i) {
+      const bool pad = 8 * (i / 4) + 4 * h + i % 4 >= here;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(pad ? 0.f : vf[i][dt], s[i], oacc[dt], 0, 0, 0);
+#pragma unroll
+      for (int c = i * D / 128; c < (i + 1) * D / 128; ++c) load_k(kb, k_off, c);
     }
   }
-  const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
-  f32x4* op = reinterpret_cast<f32x4*>(o + head_off + q_row * D);
+  // merge: a common reference, then the sums, wave onto wave in a tree
+  const auto lw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+  s_m[wave][n] = m_run;
+  s_l[wave][n] = __uint_as_float(lw[0]) + __uint_as_float(lw[1]);
+  __syncthreads();
+  float m_all = s_m[0][n], l_all = 0.f;
 #pragma unroll
-  for (int c = 0; c < D / 4; ++c) op[c] = f32x4{acc[4 * c] * inv, acc[4 * c + 1] * inv, acc[4 * c + 2] * inv, acc[4 * c + 3] * inv};
-  if (lse) lse[int64_t(head) * N_pad + q_row] = l_run > 0.f ? m_run + __logf(l_run) : -INFINITY;
+  for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, s_m[w][n]);
+  const float ref = m_all == -INFINITY ? 0.f : m_all;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) l_all += s_l[w][n] * __builtin_amdgcn_exp2f(s_m[w][n] - ref);
+  const float share = __builtin_amdgcn_exp2f(m_run - ref);
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[dt][i] *= share;
+#pragma unroll
+  for (int half = NW / 2; half >= 1; half /= 2) {
+    if (wave >= half && wave < 2 * half) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s_o[wave - half][(dt * 16 + i) * 64 + lane] = oacc[dt][i];
+    }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[dt][i] += s_o[wave][(dt * 16 + i) * 64 + lane];
+    }
+    __syncthreads();
+  }
+  if (wave != 0) return;
+  // no keys: a zero row; keys whose weights all vanish (logits of -inf only): undefined, NaN as 0 / 0
+  const float inv = l_all > 0.f ? 1.0f / l_all : cnt > 0 ? NAN : 0.f;
+  if (io_row >= 0) {
+    float* orow = o + io_off + io_row * D + DT * 4 * h;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      vrow w;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) w[dt] = oacc[dt][i] * inv;
+      *reinterpret_cast<vrow*>(orow + DT * (8 * (i / 4) + i % 4)) = w;
+    }
+  }
+  if (lse && h == 0)
+    lse[int64_t(head) * N_pad + q_row] = l_all > 0.f ? (ref + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f : -INFINITY;
 }
 
 static unsigned long long* g_clock_probe = nullptr;   // set by dfs_attn_clock_probe (diagnostic)
@@ -607,17 +700,14 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
 #undef ATTN
 #undef ATTN_X
   } else {
-    if (row_index) return fail(DFS_EDTYPE, "dfs_sparse_attn_fwd: reading Q / writing O through the permutation needs bf16 tensors");
     if (g->heads > 65535) return fail(DFS_ESHAPE, "heads=%d exceeds 65535", g->heads);
-    dim3 grid(unsigned(s.M), unsigned(g->heads));
-    if (g->d == 64)
-      attn_f32_kernel<64><<<grid, g->B, 0, st>>>(static_cast<const float*>(q), static_cast<const float*>(k),
-                                                 static_cast<const float*>(v), kv_idx, kv_cnt, K_max, static_cast<float*>(o), lse,
-                                                 s.N_pad, s.N_v, g->n_text, s.M_v, s.M, g->B, scale);
-    else
-      attn_f32_kernel<128><<<grid, g->B, 0, st>>>(static_cast<const float*>(q), static_cast<const float*>(k),
-                                                  static_cast<const float*>(v), kv_idx, kv_cnt, K_max, static_cast<float*>(o), lse,
-                                                  s.N_pad, s.N_v, g->n_text, s.M_v, s.M, g->B, scale);
+    dim3 grid(unsigned(s.M * (g->B / 32)), unsigned(g->heads));
+#define ATTN_F32(DD)                                                                                                            \
+  attn_f32_kernel<DD><<<grid, 512, 0, st>>>(static_cast<const float*>(q), static_cast<const float*>(k),                         \
+                                            static_cast<const float*>(v), kv_idx, kv_cnt, K_max, static_cast<float*>(o), lse,   \
+                                            row_index, s.N, s.N_pad, s.N_v, g->n_text, s.M_v, s.M, g->B, scale)
+    if (g->d == 64) ATTN_F32(64); else ATTN_F32(128);
+#undef ATTN_F32
   }
   return launch_status("dfs_sparse_attn_fwd");
 }
