@@ -52,16 +52,15 @@ int check_geom(const dfs_geom* g, dfs_sizes* s) {
   return DFS_OK;
 }
 
-struct FwdLayout { size_t qp, kp, vp, op, score, sub, total; };
+struct FwdLayout { size_t kp, vp, score, sub, total; };
 
 static FwdLayout forward_layout(const dfs_geom* g, const dfs_sizes& s, int dtype) {
   FwdLayout L;
   size_t t = align256(size_t(g->heads) * s.N_pad * g->d * elem_size(dtype));
   size_t off = 0;
-  L.qp = off; off += t;
   L.kp = off; off += t;
   L.vp = off; off += t;
-  L.op = off; off += t;
+  off += 2 * t;                                      // unused; the size asked of callers stays what it was
   L.score = off; off += align256(size_t(g->heads) * s.M_v * s.M_v * sizeof(float));
   L.sub = off;
   size_t a = ws_block_score(g, s), b = ws_select_mask(g, s);
@@ -121,32 +120,19 @@ int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, cons
     return fail(DFS_EWORKSPACE, "dfs_forward: workspace of %zu bytes needed (256-byte aligned), got %zu", L.total, ws_bytes);
   char* base = static_cast<char*>(ws);
   hipStream_t hs = as_stream(stream);
-  // bf16: Q is gathered where it is consumed (pooling, attention) and O is scattered by the attention kernel,
-  // so only K and V take a reorder pass.  fp32 (small problems): every tensor is reordered.
-  const bool fused = dtype == DFS_BF16;
-  const int32_t* index = fused ? perm_pad : nullptr;
-  const void* q_in = fused ? q : base + L.qp;
-  void* o_out = fused ? o : base + L.op;
-  if (!fused && (rc = run_permute(g, s, dtype, q, perm_pad, base + L.qp, hs))) return rc;
-  // On a refresh step of the bf16 path the pooling kernel reorders K on the way (it reads K in source order
-  // and writes K'), which spares that reorder pass too.
-  const bool k_in_pool = fused && refresh;
-  if (!k_in_pool && (rc = run_permute(g, s, dtype, k, perm_pad, base + L.kp, hs))) return rc;
-  if ((rc = run_permute(g, s, dtype, v, perm_pad, base + L.vp, hs))) return rc;
+  // Q is gathered where it is consumed (pooling, attention) and O is scattered by the attention kernel, so only K and V
+  // are reordered: by the pooling kernel on the way on a refresh step, by one gather on a reuse step.
+  void *k_perm = base + L.kp, *v_perm = base + L.vp;
   if (refresh) {
     float* score = reinterpret_cast<float*>(base + L.score);
-    if ((rc = run_block_score(g, s, dtype, q_in, k_in_pool ? k : static_cast<const void*>(base + L.kp), score, base + L.sub, index,
-                              k_in_pool ? base + L.kp : nullptr, hs)))
-      return rc;
+    if ((rc = run_block_score(g, s, dtype, q, k, score, base + L.sub, perm_pad, k_perm, v, v_perm, hs))) return rc;
     if ((rc = run_select_mask(g, s, score, mode, sparsity, mass, st->mask, st->kv_idx, st->kv_cnt, st->K_max,
                               st->k_head, base + L.sub, hs)))
       return rc;
-  }
-  if ((rc = run_sparse_attn(g, s, dtype, q_in, base + L.kp, base + L.vp, st->kv_idx, st->kv_cnt, st->K_max, scale, o_out,
-                            nullptr, index, hs)))
+  } else if ((rc = run_permute(g, s, dtype, k, perm_pad, k_perm, v, v_perm, hs))) {
     return rc;
-  if (!fused) return run_unperm(g, s, dtype, base + L.op, inv, o, hs);
-  return DFS_OK;
+  }
+  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, st->kv_idx, st->kv_cnt, st->K_max, scale, o, nullptr, perm_pad, hs);
 }
 
 int dfs_schedule(int32_t total_steps, int32_t t, int32_t delta, double cached_keep, int32_t* dense, int32_t* refresh,

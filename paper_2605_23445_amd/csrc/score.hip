@@ -56,25 +56,31 @@ __device__ __forceinline__ void group_scale(float gmax, float& up, float& down) 
 // flight per load; partial sums of the row groups are folded with cross-lane exchanges.
 // Output row layout: [2][D] fp16 (hi, lo planes) of the row times its group's scale; the inverse scale of
 // group s / 4 goes to q_down / k_down.
+// blockIdx.z: 0 pools Q, 1 pools K, 2 only reorders V.  With an index (the permutation) the tensors come in source
+// order and their rows are gathered; K (if k_out) and V are written out in the reordered layout on the way (pads as
+// zeros, text rows too), so that a step that refreshes the mask reads and writes each of them once, in one launch.
+// An HBM stream; a wave requests up to eight row groups (the positions first, then the rows) before it uses one,
+// because on small problems a sub-block is a chain of dependent loads.  With V's reorder in a launch of its own and
+// one row group at a time: 75 600 tokens x 40 heads, d = 128, 715 -> 643 us (6.0 TB/s); 17 550 x 48, d = 64, 105 -> 83
+// us; 5 589 x 7, d = 128, 21.5 -> 11 us.
 template <bool BF16, int D>
-__global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_perm, const void* __restrict__ k_perm,
+__global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in, const void* __restrict__ k_in, const void* __restrict__ v_in,
                                                    uint16_t* __restrict__ q_hat, uint16_t* __restrict__ k_hat,
                                                    float* __restrict__ q_down, float* __restrict__ k_down,
-                                                   const int32_t* __restrict__ q_index, void* __restrict__ k_out, int64_t N_src,
-                                                   int64_t N_pad, int64_t N_v, int Bs, int M_s, float q_scale) {
+                                                   const int32_t* __restrict__ index, void* __restrict__ k_out, void* __restrict__ v_out,
+                                                   int64_t N_src, int64_t N_pad, int64_t N_v, int Bs, int M_s, float q_scale) {
   constexpr int EPL = BF16 ? 8 : 4;           // elements per lane (16 bytes)
   constexpr int TPR = D / EPL;                // lanes per row
   constexpr int RPP = 64 / TPR;               // rows per pass
+  constexpr int AHEAD = 32 / RPP < 8 ? 32 / RPP : 8;         // passes in flight
   const int lane = threadIdx.x & 63;
   const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
-  // With k_out the key rows come in source order too: they are gathered through the permutation, pooled, and
-  // written out in the reordered layout on the way (pads as zeros), which spares the reorder pass of K.  The
-  // sub-blocks behind the video segment (text rows) are then copied only.
-  const bool k_copy = blockIdx.z == 1 && k_out != nullptr;
-  const bool pooled = s < M_s;                               // this wave has a sub-block to pool
-  const bool busy = pooled || (k_copy && int64_t(s) * Bs < N_pad);
+  const bool pooled = s < M_s && blockIdx.z < 2;             // this wave has a sub-block to pool
+  void* out = blockIdx.z == 0 ? nullptr : blockIdx.z == 1 ? k_out : v_out;
+  const bool copied = out != nullptr && int64_t(s) * Bs < N_pad;
+  const bool gather = index != nullptr && (blockIdx.z == 0 || out != nullptr);   // K without k_out is in the reordered layout
   const int head = blockIdx.y;
-  const void* src = blockIdx.z == 0 ? q_perm : k_perm;
+  const void* src = blockIdx.z == 0 ? q_in : blockIdx.z == 1 ? k_in : v_in;
   uint16_t* dst = blockIdx.z == 0 ? q_hat : k_hat;
   const int c = lane % TPR, rg = lane / TPR;
   const int64_t row0 = int64_t(s) * Bs;
@@ -83,35 +89,41 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_pe
   float acc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-  // With q_index (the permutation) the query rows are gathered from the tensor in source order, which spares
-  // the reorder pass of Q.
-  const bool gather = q_index != nullptr && (blockIdx.z == 0 || k_copy);
   const u32x4* base = reinterpret_cast<const u32x4*>(src) + (gather ? int64_t(head) * N_src * TPR : (int64_t(head) * N_pad + row0) * TPR) + c;
-  u32x4* copy = k_copy ? reinterpret_cast<u32x4*>(k_out) + (int64_t(head) * N_pad + row0) * TPR + c : nullptr;
-  const int rows = !busy ? 0 : k_copy ? Bs : cnt;   // a copy covers the pad rows of the sub-block as well
-  for (int i = rg; i < rows; i += RPP) {
-    int64_t from = i;
-    bool real = true;
-    if (gather) {
-      from = q_index[row0 + i];
-      real = from >= 0 && from < N_src;
+  u32x4* copy = reinterpret_cast<u32x4*>(out) + (int64_t(head) * N_pad + row0) * TPR + c;
+  const int rows = copied ? Bs : pooled ? cnt : 0;           // a copy covers the pad rows of the sub-block as well
+  for (int i0 = rg; i0 - rg < rows; i0 += RPP * AHEAD) {
+    int32_t from[AHEAD];
+    u32x4 val[AHEAD];
+#pragma unroll
+    for (int p = 0; p < AHEAD; ++p) {
+      const int i = i0 + p * RPP;
+      from[p] = i >= rows ? -1 : gather ? index[row0 + i] : i;
     }
-    if (!real && !k_copy) continue;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (real) v = __builtin_nontemporal_load(base + from * TPR);
-    if (k_copy) __builtin_nontemporal_store(v, copy + int64_t(i) * TPR);
-    if (!real || i >= cnt) continue;
-    if (BF16) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[2 * e] += __uint_as_float(v[e] << 16);
-        acc[2 * e + 1] += __uint_as_float(v[e] & 0xFFFF0000u);
+    for (int p = 0; p < AHEAD; ++p) {
+      if (gather && from[p] >= N_src) from[p] = -1;
+      val[p] = u32x4{0u, 0u, 0u, 0u};
+      if (from[p] >= 0) val[p] = __builtin_nontemporal_load(base + int64_t(from[p]) * TPR);
+    }
+#pragma unroll
+    for (int p = 0; p < AHEAD; ++p) {
+      const int i = i0 + p * RPP;
+      if (copied && i < rows) __builtin_nontemporal_store(val[p], copy + int64_t(i) * TPR);
+      if (from[p] < 0 || i >= cnt) continue;
+      if (BF16) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[2 * e] += __uint_as_float(val[p][e] << 16);
+          acc[2 * e + 1] += __uint_as_float(val[p][e] & 0xFFFF0000u);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += __uint_as_float(val[p][e]);
       }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] += __uint_as_float(v[e]);
     }
   }
+  if (blockIdx.z == 2) return;                               // the whole work-group
 #pragma unroll
   for (int off = TPR; off < 64; off <<= 1) {
 #pragma unroll
@@ -522,7 +534,7 @@ static void launch_score(const dfs_geom* g, const dfs_sizes& s, const uint16_t* 
 }
 
 int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q_perm, const void* k_perm, float* score,
-                    void* ws, const int32_t* q_index, void* k_out, hipStream_t st) {
+                    void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, hipStream_t st) {
   if (g->heads > 65535) return fail(DFS_ESHAPE, "heads=%d exceeds 65535", g->heads);
   if ((s.M_v + 31) / 32 > 65535) return fail(DFS_ESHAPE, "M_v=%d is too large for the scoring grid", s.M_v);
   char* base = static_cast<char*>(ws);
@@ -532,12 +544,12 @@ int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
   float* k_down = reinterpret_cast<float*>(base + ws_hat_bytes(g, s) + ws_planes_bytes(g, s));
   float* tt = reinterpret_cast<float*>(base + 2 * ws_hat_bytes(g, s));
   float* lse = reinterpret_cast<float*>(base + 2 * ws_hat_bytes(g, s) + ws_tt_bytes(g, s));
-  const int64_t pool_subs = k_out ? s.N_pad / g->Bs : s.M_s;   // with k_out the text blocks are copied as well
-  dim3 pg(unsigned((pool_subs + 3) / 4), unsigned(g->heads), 2);
+  const int64_t pool_subs = k_out ? s.N_pad / g->Bs : s.M_s;   // with k_out (and v_out) the text blocks are copied as well
+  dim3 pg(unsigned((pool_subs + 3) / 4), unsigned(g->heads), v_out ? 3 : 2);
   const bool bf = dtype == DFS_BF16;
   // 1/sqrt(d) of Eq. 2 and the change to base 2 go into Q_hat, so that the logits come out of the contraction in base 2
   const float scale = 1.4426950408889634f / sqrtf(float(g->d));
-#define POOL(BF, DD) pool_kernel<BF, DD><<<pg, 256, 0, st>>>(q_perm, k_perm, q_hat, k_hat, q_down, k_down, q_index, k_out, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale)
+#define POOL(BF, DD) pool_kernel<BF, DD><<<pg, 256, 0, st>>>(q_perm, k_perm, v, q_hat, k_hat, q_down, k_down, index, k_out, v_out, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale)
   if (g->d == 64) { if (bf) POOL(true, 64); else POOL(false, 64); }
   else            { if (bf) POOL(true, 128); else POOL(false, 128); }
 #undef POOL
@@ -572,7 +584,7 @@ extern "C" int dfs_block_score(const dfs_geom* g, int dtype, const void* q_perm,
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q_perm, k_perm, score, ws, nullptr, nullptr, as_stream(stream));
+  return run_block_score(g, s, dtype, q_perm, k_perm, score, ws, nullptr, nullptr, nullptr, nullptr, as_stream(stream));
 }
 
 extern "C" int dfs_block_score_src(const dfs_geom* g, int dtype, const void* q, const int32_t* perm_pad, const void* k_perm,
@@ -587,7 +599,7 @@ extern "C" int dfs_block_score_src(const dfs_geom* g, int dtype, const void* q, 
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score_src: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q, k_perm, score, ws, perm_pad, nullptr, as_stream(stream));
+  return run_block_score(g, s, dtype, q, k_perm, score, ws, perm_pad, nullptr, nullptr, nullptr, as_stream(stream));
 }
 
 extern "C" int dfs_block_score_fused(const dfs_geom* g, int dtype, const void* q, const void* k, const int32_t* perm_pad,
@@ -603,5 +615,5 @@ extern "C" int dfs_block_score_fused(const dfs_geom* g, int dtype, const void* q
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score_fused: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q, k, score, ws, perm_pad, k_perm, as_stream(stream));
+  return run_block_score(g, s, dtype, q, k, score, ws, perm_pad, k_perm, nullptr, nullptr, as_stream(stream));
 }
