@@ -52,7 +52,7 @@ int check_geom(const dfs_geom* g, dfs_sizes* s) {
   return DFS_OK;
 }
 
-struct FwdLayout { size_t kp, vp, score, sub, total; };
+struct FwdLayout { size_t kp, vp, text, text_bytes, score, sub, total; };
 
 static FwdLayout forward_layout(const dfs_geom* g, const dfs_sizes& s, int dtype) {
   FwdLayout L;
@@ -60,7 +60,7 @@ static FwdLayout forward_layout(const dfs_geom* g, const dfs_sizes& s, int dtype
   size_t off = 0;
   L.kp = off; off += t;
   L.vp = off; off += t;
-  off += 2 * t;                                      // unused; the size asked of callers stays what it was
+  L.text = off; L.text_bytes = 2 * t; off += 2 * t;  // tickets and partial sums of text rows split over work-groups
   L.score = off; off += align256(size_t(g->heads) * s.M_v * s.M_v * sizeof(float));
   L.sub = off;
   size_t a = ws_block_score(g, s), b = ws_select_mask(g, s);
@@ -123,16 +123,19 @@ int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, cons
   // Q is gathered where it is consumed (pooling, attention) and O is scattered by the attention kernel, so only K and V
   // are reordered: by the pooling kernel on the way on a refresh step, by one gather on a reuse step.
   void *k_perm = base + L.kp, *v_perm = base + L.vp;
+  int32_t* tickets = reinterpret_cast<int32_t*>(base + L.text);
+  const int n_tickets = int(text_tickets(g, s));
   if (refresh) {
     float* score = reinterpret_cast<float*>(base + L.score);
-    if ((rc = run_block_score(g, s, dtype, q, k, score, base + L.sub, perm_pad, k_perm, v, v_perm, hs))) return rc;
+    if ((rc = run_block_score(g, s, dtype, q, k, score, base + L.sub, perm_pad, k_perm, v, v_perm, tickets, n_tickets, hs))) return rc;
     if ((rc = run_select_mask(g, s, score, mode, sparsity, mass, st->mask, st->kv_idx, st->kv_cnt, st->K_max,
                               st->k_head, base + L.sub, hs)))
       return rc;
-  } else if ((rc = run_permute(g, s, dtype, k, perm_pad, k_perm, v, v_perm, hs))) {
+  } else if ((rc = run_permute(g, s, dtype, k, perm_pad, k_perm, v, v_perm, tickets, n_tickets, hs))) {
     return rc;
   }
-  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, st->kv_idx, st->kv_cnt, st->K_max, scale, o, nullptr, perm_pad, hs);
+  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, st->kv_idx, st->kv_cnt, st->K_max, scale, o, nullptr, perm_pad,
+                         base + L.text, L.text_bytes, hs);
 }
 
 int dfs_schedule(int32_t total_steps, int32_t t, int32_t delta, double cached_keep, int32_t* dense, int32_t* refresh,

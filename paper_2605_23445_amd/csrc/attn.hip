@@ -53,16 +53,26 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
 // Waves per SIMD: two at d = 128 (about 250 registers each).  At d = 64 the kernel needs about 160 registers, so
 // three waves fit (measured 36 -> 43 % of the matrix cycles, +8 % throughput on the 17 550- and 75 600-token
 // shapes); the variants that would have to spill for that (64-row blocks, log-sum-exp output) stay at two.
-template <int D, int BM, bool XLSE>
-constexpr int attn_waves() { return D == 64 && BM == 128 && !XLSE ? 3 : 2; }
-template <int D, int BM, bool XLSE>
-__global__ void __launch_bounds__(BM * 2)
-__attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE>(), attn_waves<D, BM, XLSE>())))
+//
+// Text rows keep every block and are many times longer than the others; where too few of the others follow to hide
+// them, SPLIT work-groups share one text block, each with a run of its list.  They leave their unnormalised sums in
+// `part`; the one that takes the last ticket merges them, in list order, so the result does not depend on who is last.
+// (Only calls without log-sum-exp are given a `part`.)
+//
+// KS: where the query blocks are too few to give every SIMD its two waves, KS groups of waves share one query block, each
+// with a KS-th of its tiles, tile buffers of its own and a softmax of its own; they merge through LDS at the end.  A lone
+// wave per SIMD waits for LDS at every matrix instruction (43 % of the matrix cycles); see key_split below for the rule.
+template <int D, int BM, bool XLSE, int KS>
+constexpr int attn_waves() { return D == 64 && BM == 128 && !XLSE && KS == 1 ? 3 : 2; }
+template <int D, int BM, bool XLSE, int KS>
+__global__ void __launch_bounds__(BM * 2 * KS)
+__attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE, KS>(), attn_waves<D, BM, XLSE, KS>())))
 attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                  const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
                  float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
-                 int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe) {
-  constexpr int NW = BM / 32;                      // waves: one per 32 query rows
+                 int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
+                 float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks) {
+  constexpr int NW = BM / 32;                      // waves per group: one per 32 query rows
   constexpr int CH = D / 8;                        // 16-byte chunks per row
   constexpr int TILE = KN * D;                     // elements per tile
   constexpr int LPW = KN * CH / (64 * NW);         // load instructions per wave and tile
@@ -72,11 +82,11 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   constexpr int ESL = NF - 1;                      // matrix instructions the sixteen exponentials of a half tile are spread over
   constexpr float HEADROOM = 16.f;                 // exponents of two: see "No maximum is taken" below
   constexpr float SUM_HIGH = 65536.f, SUM_LIMIT = 281474976710656.f;      // 2^16, 2^48
-  // Two K and two V tile buffers (tile t lives in the pair of parity t & 1).
-  __shared__ __attribute__((aligned(16))) uint16_t sK0[TILE];
-  __shared__ __attribute__((aligned(16))) uint16_t sK1[TILE];
-  __shared__ __attribute__((aligned(16))) uint16_t sV0[TILE];
-  __shared__ __attribute__((aligned(16))) uint16_t sV1[TILE];
+  // Two K and two V tile buffers per group (tile t lives in the pair of parity t & 1).
+  __shared__ __attribute__((aligned(16))) uint16_t aK0[KS * TILE];
+  __shared__ __attribute__((aligned(16))) uint16_t aK1[KS * TILE];
+  __shared__ __attribute__((aligned(16))) uint16_t aV0[KS * TILE];
+  __shared__ __attribute__((aligned(16))) uint16_t aV1[KS * TILE];
 
   // Work-group to (head, query block).  Ids are dealt round-robin to the 8 XCDs, so id % 8 names the XCD
   // and id / 8 the order inside it.
@@ -87,25 +97,31 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   //     longest work-groups, come first.
   //   mapping 1 (an eighth of a head would not fill an XCD): each XCD walks whole heads of its own,
   //     query blocks last-first so that the text blocks of a head start first.
-  //   mapping 0: ids in plain order.
-  int head, u;
-  if (mapping == 2) {
+  //   mapping 3: mapping 1 with the text blocks, split, of all heads in front as in mapping 2.
+  int head, u, split = 0;
+  if (mapping >= 2) {
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int M_x = M - M_v, n_heads = total_wg / M;
-    const int text_slots = (n_heads * M_x + 7) / 8;
+    const int text_wgs = n_heads * M_x * text_splits, text_slots = (text_wgs + 7) / 8;
     if (slot < text_slots) {
       const int id = slot * 8 + xcd;
-      if (id >= n_heads * M_x) return;
-      head = id / M_x;
+      if (id >= text_wgs) return;
       u = M_v + id % M_x;
-    } else {
+      split = id / M_x % text_splits;
+      head = id / M_x / text_splits;
+    } else if (mapping == 2) {
       const int C = (M_v + 7) / 8, s2 = slot - text_slots;
       head = s2 / C;
       u = xcd * C + s2 % C;
       if (head >= n_heads || u >= M_v) return;
+    } else {
+      const int logical = xcd * wg_per_xcd + slot - text_slots;
+      if (slot - text_slots >= wg_per_xcd || logical >= n_heads * M_v) return;
+      head = logical / M_v;
+      u = M_v - 1 - logical % M_v;
     }
   } else {
-    const int logical = mapping ? (blockIdx.x % 8) * wg_per_xcd + blockIdx.x / 8 : blockIdx.x;
+    const int logical = (blockIdx.x % 8) * wg_per_xcd + blockIdx.x / 8;
     if (logical >= total_wg) return;
     head = logical / M;
     u = M - 1 - logical % M;
@@ -114,12 +130,17 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // diagnostic: shader-clock cycles and constant-rate (100 MHz) ticks this work-group lives for
   const unsigned long long probe_c0 = clock_probe ? clock64() : 0, probe_w0 = clock_probe ? wall_clock64() : 0;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / (64 * NW)), wave = (tid >> 6) - grp * NW;
+  uint16_t *const sK0 = aK0 + grp * TILE, *const sK1 = aK1 + grp * TILE, *const sV0 = aV0 + grp * TILE, *const sV1 = aV1 + grp * TILE;
   const int n = lane & 31, h = lane >> 5;
   const int cnt_in = kv_cnt[int64_t(head) * M + u];
   const bool dense = cnt_in >= M;
-  const int cnt = dense ? M : (cnt_in < 0 ? 0 : (cnt_in > K_max ? K_max : cnt_in));
-  const int32_t* idx = kv_idx + (int64_t(head) * M + u) * K_max;
+  const bool shared_row = !XLSE && text_splits > 1 && u >= M_v;
+  const int blk_first = shared_row ? split * split_blocks : 0;            // this work-group's run of the list
+  int cnt = dense ? M : (cnt_in < 0 ? 0 : (cnt_in > K_max ? K_max : cnt_in));
+  if (shared_row) cnt = cnt - blk_first < 0 ? 0 : cnt - blk_first < split_blocks ? cnt - blk_first : split_blocks;
+  const int32_t* idx = kv_idx + (int64_t(head) * M + u) * K_max + blk_first;
   const int64_t head_off = int64_t(head) * N_pad * D;
   const uint16_t* kh = k + head_off;
   const uint16_t* vh = v + head_off;
@@ -161,9 +182,15 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   constexpr int PK = swz_period(RJ / (16 / CH) > 0 ? RJ / (16 / CH) : 1, CH);
   constexpr int PV = swz_period(RJ / (16 / CH) > 0 ? RJ / (16 / CH) : 1, CH / 4);
   static_assert(RJ % (16 / CH) == 0 && LPW % PK == 0 && LPW % PV == 0, "tile load pattern");
-  const int n_tiles = cnt * STEPS;
+  // This group's tiles are t_first .. t_first + n_tiles - 1 of the list's, whole key blocks (whose first row is real: the
+  // softmax starts from it) and as many for every group, because the groups share their barriers: what lies behind the
+  // last tile of all is that tile again with every key masked.
+  const int all_tiles = cnt * STEPS;
+  const int n_tiles = (cnt + KS - 1) / KS * STEPS, t_first = grp * n_tiles;
   auto tile_block = [&](int tile) {
-    int blk = dense ? tile / STEPS : idx[tile / STEPS];
+    tile += t_first;
+    if (KS > 1 && tile >= all_tiles) tile = all_tiles - 1;
+    int blk = dense ? blk_first + tile / STEPS : idx[tile / STEPS];
     return unsigned(blk) < unsigned(M) ? blk : 0;     // a corrupt list must not read out of bounds
   };
   auto lane_off = [&](int j, bool is_v) {             // byte offset inside the tile of the chunk this lane fetches
@@ -190,8 +217,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   auto tile_src = [&](const uint16_t* base, int tile, int blk) {
     return reinterpret_cast<uint64_t>(base + (int64_t(blk) * BM + (tile % STEPS) * KN) * D);
   };
-  auto issue_one = [&](uint64_t src, uint16_t* stage, bool is_v, int j) {
-    const uint32_t lds0 = stage == sK0 ? lds_k0 : stage == sK1 ? lds_k1 : stage == sV0 ? lds_v0 : lds_v1;
+  auto issue_one = [&](uint64_t src, uint32_t lds0, bool is_v, int j) {
     const int P = is_v ? PV : PK;
     const uint32_t voff = is_v ? v_off[j % PV] : k_off[j % PK];
     const uint64_t sj = src + uint64_t(j / P) * (P * RJ) * D * 2;
@@ -200,10 +226,10 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint32_t lds = lds0 + uint32_t(j * NW * 1024);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
   };
-  auto issue = [&](const uint16_t* base, uint16_t* stage, bool is_v, int tile, int blk) {
+  auto issue = [&](const uint16_t* base, uint32_t lds0, bool is_v, int tile, int blk) {
     const uint64_t src = tile_src(base, tile, blk);
 #pragma unroll
-    for (int j = 0; j < LPW; ++j) issue_one(src, stage, is_v, j);
+    for (int j = 0; j < LPW; ++j) issue_one(src, lds0, is_v, j);
   };
 
   // LDS read offsets (elements), loop invariant
@@ -245,9 +271,10 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   const int real_x_last = M > M_v ? block_real_rows(M - 1, BM, M_v, N_v, n_text) : BM;
   const int ragged_v = real_v_last < BM ? M_v - 1 : -1, ragged_x = real_x_last < BM ? M - 1 : -1;
   auto mask_pads = [&](int blk, int tile, int half, f32x16& sx) {
-    if (__builtin_expect(blk == ragged_v || blk == ragged_x, 0)) {
+    const bool behind = KS > 1 && t_first + tile >= all_tiles;
+    if (__builtin_expect(blk == ragged_v || blk == ragged_x || behind, 0)) {
       asm volatile("");                               // keeps this a branch: turned into selects it would run on every half tile
-      const int real = blk == ragged_v ? real_v_last : real_x_last;
+      const int real = behind ? 0 : blk == ragged_v ? real_v_last : real_x_last;
       const int base = (tile % STEPS) * KN + 32 * half;
 #pragma unroll
       for (int i = 0; i < 16; ++i)
@@ -394,7 +421,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       if (LAST) return;
 #pragma unroll
       for (int j = f * 2 * LPW / NF; j < (f + 1) * 2 * LPW / NF; ++j)
-        issue_one(j < LPW ? v_src : k_src, j < LPW ? v_nxt : k_cur, j < LPW, j % LPW);
+        issue_one(j < LPW ? v_src : k_src, j < LPW ? (ODD ? lds_v0 : lds_v1) : (ODD ? lds_k1 : lds_k0), j < LPW, j % LPW);
     });
     if (!LAST) mask_pads(b_nxt, t + 1, 0, s0);
     b_cur = b_nxt;
@@ -412,14 +439,14 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   if (n_tiles > 0) {
     b_cur = tile_block(0);
     b_nxt = n_tiles > 1 ? tile_block(1) : b_cur;
-    issue(kh, sK0, false, 0, b_cur);
-    issue(vh, sV0, true, 0, b_cur);
+    issue(kh, lds_k0, false, 0, b_cur);
+    issue(vh, lds_v0, true, 0, b_cur);
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
-    if (n_tiles > 1) issue(kh, sK1, false, 1, b_nxt);
+    if (n_tiles > 1) issue(kh, lds_k1, false, 1, b_nxt);
     logits(sK0, 0, s0);
     mask_pads(b_cur, 0, 0, s0);
-    m_run = fmaf(half_max(s0), c2, HEADROOM);        // finite: the first row of a block is never a pad
+    if (KS == 1 || t_first < all_tiles) m_run = fmaf(half_max(s0), c2, HEADROOM);      // finite: the first row of a block is never a pad
     if (n_tiles == 1) {
       tile_step(no{}, yes{}, yes{}, 0);
     } else {
@@ -448,8 +475,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       for (int step = 0; step < 2 * n_tiles; ++step) {
         const bool sums = step >= n_tiles;
         const int t = sums ? step - n_tiles : step, blk = tile_block(t);
-        issue(kh, sK0, false, t, blk);
-        issue(vh, sV0, true, t, blk);
+        issue(kh, lds_k0, false, t, blk);
+        issue(vh, lds_v0, true, t, blk);
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
 #pragma unroll 1
@@ -458,7 +485,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
           mask_pads(blk, t, half, s0);
           if (!sums) {
             mx = fmaxf(mx, half_max(s0));
-            m_run = fmaf(mx, c2, HEADROOM);
+            if (KS == 1 || t_first < all_tiles) m_run = fmaf(mx, c2, HEADROOM);
           } else {
 #pragma unroll
             for (int i = 0; i < 16; i += 2) {
@@ -470,6 +497,99 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
           }
         }
         __syncthreads();
+      }
+    }
+  }
+
+  if constexpr (KS > 1) {
+    // Merge.  A group's accumulators go where its tiles were (one buffer holds one wave's), its reference and sums beside
+    // them; the first group brings all to the largest reference and adds.  A group without tiles (reference -inf) adds zeros.
+    __shared__ float s_part[KS][NW][3][64];
+    auto acc_buf = [&](int g) {
+      uint16_t* b = (wave == 0 ? aK0 : wave == 1 ? aK1 : wave == 2 ? aV0 : aV1) + g * TILE;
+      return reinterpret_cast<float*>(b) + lane;
+    };
+    static_assert(TILE * 2 == (D / 32) * 16 * 64 * 4, "one tile buffer holds the accumulators of one wave");
+    if (n_tiles == 0) {
+      if (grp > 0) return;
+    } else {
+      if (t_first >= all_tiles) m_run = -INFINITY;
+      __syncthreads();                               // every wave is done with the tiles
+      if (grp > 0) {
+        float* part = acc_buf(grp);
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) part[(dt * 16 + i) * 64] = oacc[dt][i];
+        s_part[grp][wave][0][lane] = m_run;
+        s_part[grp][wave][1][lane] = lsum[0];
+        s_part[grp][wave][2][lane] = x_run;
+      }
+      __syncthreads();
+      if (grp > 0) return;
+      float m_all = m_run;
+#pragma unroll
+      for (int g = 1; g < KS; ++g) m_all = fmaxf(m_all, s_part[g][wave][0][lane]);
+      const float own = __builtin_amdgcn_exp2f(m_run - m_all);
+      m_run = m_all;
+      lsum[0] *= own;
+      x_run *= own;
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[dt][i] *= own;
+#pragma unroll
+      for (int g = 1; g < KS; ++g) {
+        const float share = __builtin_amdgcn_exp2f(s_part[g][wave][0][lane] - m_all);
+        const float* part = acc_buf(g);
+        lsum[0] = fmaf(share, s_part[g][wave][1][lane], lsum[0]);
+        x_run = fmaf(share, s_part[g][wave][2][lane], x_run);
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) oacc[dt][i] = fmaf(share, part[(dt * 16 + i) * 64], oacc[dt][i]);
+      }
+    }
+  }
+
+  if constexpr (!XLSE) {
+    if (shared_row) {
+      // Stores and loads at the chip's scope go past the L2, which belongs to one XCD: a fence instead would write
+      // the whole L2 back.
+      auto put = [](float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+      auto get = [](const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+      constexpr int REGS = D / 2 + 2;                // of a lane: accumulators, reference, row sum
+      const int M_x = M - M_v, row = head * M_x + (u - M_v);
+      float* rows = part + (int64_t(row) * text_splits * NW + wave) * REGS * 64 + lane;
+      float* mine = rows + int64_t(split) * NW * REGS * 64;
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) put(mine + (dt * 16 + i) * 64, oacc[dt][i]);
+      put(mine + (REGS - 2) * 64, n_tiles == 0 ? -INFINITY : m_run);
+      put(mine + (REGS - 1) * 64, lsum[0]);
+      __shared__ int s_ticket;
+      __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wave's sums have reached memory
+      __syncthreads();                               // and every wave's, before the ticket is taken
+      if (tid == 0) s_ticket = __hip_atomic_fetch_add(&tickets[row], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+      if (s_ticket != text_splits - 1) return;
+      float m_all = -INFINITY;
+      for (int sp = 0; sp < text_splits; ++sp) m_all = fmaxf(m_all, get(rows + (int64_t(sp) * NW * REGS + REGS - 2) * 64));
+      const float ref = m_all == -INFINITY ? 0.f : m_all;
+      lsum[0] = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
+      for (int sp = 0; sp < text_splits; ++sp) {
+        const float* p = rows + int64_t(sp) * NW * REGS * 64;
+        const float share = __builtin_amdgcn_exp2f(get(p + (REGS - 2) * 64) - ref);
+        lsum[0] = fmaf(share, get(p + (REGS - 1) * 64), lsum[0]);
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) oacc[dt][i] = fmaf(share, get(p + (dt * 16 + i) * 64), oacc[dt][i]);
       }
     }
   }
@@ -676,9 +796,45 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(const float* __restrict__
 
 static unsigned long long* g_clock_probe = nullptr;   // set by dfs_attn_clock_probe (diagnostic)
 
+// Groups of waves that share a query block (kernel's KS): two where the work-groups leave SIMDs with less than one wave
+// each.  A second wave per SIMD raises the matrix rate by a fifth, the merge costs some 4 us, so short lists of the one
+// shape whose lone waves do well (d = 128, 128 rows) stay whole.  Measured (us, one group -> two), 128 rows: d = 128, 44
+// blocks x 1 head 26.1 -> 29.1 with 9 kept, 78 -> 71 with all kept, 176 work-groups 100 -> 85, 264 136 -> 162; d = 64,
+// 88 work-groups 22.8 -> 21.0, 264 31.6 -> 38.4.  64 rows (two waves per group): d = 64, 164 work-groups 18.6 -> 16.6,
+// 492 25.0 -> 22.5, 656 26.8 -> 29.9; d = 128, 246 25.5 -> 24.6, 328 28.4 -> 35.5.
+static int key_split(int d, int B, int64_t work_groups, int K_max) {
+  if (B == 64 && d == 64) return work_groups <= 512 ? 2 : 1;
+  if (B == 128 && d == 128 && K_max <= 16) return 1;
+  return work_groups <= 256 ? 2 : 1;
+}
+
+// Work-groups per text block, and the key blocks each takes: about as many as a video row keeps (an eighth of all where
+// K_max does not tell), at least eight.  One where the video rows' work, in rounds of the chip's work-group slots, hides
+// the text rows, which start first.  Measured (us a reuse step, whole -> split), 17 550 video + 77 text tokens, 21 of 138
+// blocks kept: d = 64 x 2 heads 185 -> 57, x 12 322 -> 199, x 40 660 -> 652; d = 128 x 2 251 -> 88, x 12 502 -> 348, x 40
+// 1 157 -> 1 166 (work of 1.7 text rows: whole); 75 600 + 256 tokens x 8 heads 2 359 -> 2 385 (work of 0.96: whole).
+// Below 16 blocks there is nothing to win.
+struct TextSplit { int splits, blocks; };
+static TextSplit text_split(const dfs_geom* g, const dfs_sizes& s, int K_max, size_t scratch_bytes) {
+  const TextSplit whole = {1, s.M};
+  if (s.M_x == 0 || s.M < 16 || scratch_bytes == 0) return whole;
+  const int64_t slots = g->B == 128 ? 512 : 1024, kept = K_max < s.M ? K_max : s.M;
+  const int64_t likely = kept == s.M ? kept / 3 : kept;                  // adaptive lists are given room for all
+  if (int64_t(g->heads) * s.M_v * likely * 5 >= 4 * slots * s.M) return whole;
+  int blocks = int(2 * kept <= s.M ? kept : s.M / 8);
+  if (blocks < 8) blocks = 8;
+  const size_t row = size_t(g->B) * (g->d + 4) * sizeof(float) * s.M_x * g->heads;         // one split of every text block
+  const int64_t room = int64_t((scratch_bytes - align256(text_tickets(g, s) * sizeof(int32_t))) / row);
+  if ((s.M + blocks - 1) / blocks > room) {
+    if (room < 2) return whole;
+    blocks = int((s.M + room - 1) / room);
+  }
+  return {(s.M + blocks - 1) / blocks, blocks};
+}
+
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
-                    const int32_t* row_index, hipStream_t st) {
+                    const int32_t* row_index, void* scratch, size_t scratch_bytes, hipStream_t st) {
   if (K_max < 1) return fail(DFS_ESHAPE, "dfs_sparse_attn_fwd: K_max=%d must be positive", K_max);
   if (dtype == DFS_BF16) {
     const int64_t total = int64_t(g->heads) * s.M;
@@ -686,17 +842,25 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     // an eighth of a head's video blocks per XCD once that fills the XCD's 64 work-group slots (measured
     // +3..6 % on the 75 600- and 118 800-token shapes, -4 % on the 17 550-token one, which stays on mapping 1)
     const int chunk = (s.M_v + 7) / 8;
-    const int mapping = chunk >= 64 ? 2 : 1;
-    const int per_xcd = mapping == 2 ? (g->heads * s.M_x + 7) / 8 + g->heads * chunk : int((total + 7) / 8);
-    dim3 grid(unsigned(per_xcd * 8));
-#define ATTN_X(DD, BB, XX)                                                                                                      \
-  attn_bf16_kernel<DD, BB, XX><<<grid, BB * 2, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),       \
+    const TextSplit ts = lse ? TextSplit{1, s.M} : text_split(g, s, K_max, scratch_bytes);
+    const int mapping = chunk >= 64 ? 2 : ts.splits > 1 ? 3 : 1;
+    const int text_slots = (g->heads * s.M_x * ts.splits + 7) / 8, video_slots = int((int64_t(g->heads) * s.M_v + 7) / 8);
+    const int per_xcd = mapping == 2 ? g->heads * chunk : mapping == 3 ? video_slots : int((total + 7) / 8);
+    dim3 grid(unsigned(8 * (mapping >= 2 ? text_slots + per_xcd : per_xcd)));
+    int32_t* tickets = static_cast<int32_t*>(scratch);
+    float* part = reinterpret_cast<float*>(static_cast<char*>(scratch) + align256(text_tickets(g, s) * sizeof(int32_t)));
+    const int ks = key_split(g->d, g->B, total + int64_t(g->heads) * s.M_x * (ts.splits - 1), K_max);
+#define ATTN_X(DD, BB, XX, KS)                                                                                                  \
+  attn_bf16_kernel<DD, BB, XX, KS><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
                                                         static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                 \
                                                         static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,         \
-                                                        g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe)
-#define ATTN(DD, BB) do { if (lse) ATTN_X(DD, BB, true); else ATTN_X(DD, BB, false); } while (0)
-    if (g->d == 64) { if (g->B == 64) ATTN(64, 64); else ATTN(64, 128); }
-    else            { if (g->B == 64) ATTN(128, 64); else ATTN(128, 128); }
+                                                        g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe, \
+                                                        part, tickets, ts.splits, ts.blocks)
+#define ATTN(DD, BB, KS) do { if (lse) ATTN_X(DD, BB, true, KS); else ATTN_X(DD, BB, false, KS); } while (0)
+#define ATTN_KS(DD, BB) do { if (ks == 2) ATTN(DD, BB, 2); else ATTN(DD, BB, 1); } while (0)
+    if (g->d == 64) { if (g->B == 64) ATTN_KS(64, 64); else ATTN_KS(64, 128); }
+    else            { if (g->B == 64) ATTN_KS(128, 64); else ATTN_KS(128, 128); }
+#undef ATTN_KS
 #undef ATTN
 #undef ATTN_X
   } else {
@@ -733,7 +897,7 @@ extern "C" int dfs_sparse_attn_fwd(const dfs_geom* g, int dtype, const void* q_p
   if (misaligned(16, {q_perm, k_perm, v_perm, o_perm}) || misaligned(4, {kv_idx, kv_cnt, lse}))
     return fail(DFS_EINVAL, "dfs_sparse_attn_fwd: tensors must be 16-byte aligned, index and fp32 arrays 4-byte aligned");
   if (!(scale > 0.f)) return fail(DFS_EINVAL, "dfs_sparse_attn_fwd: scale must be positive");
-  return run_sparse_attn(g, s, dtype, q_perm, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o_perm, lse, nullptr, as_stream(stream));
+  return run_sparse_attn(g, s, dtype, q_perm, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o_perm, lse, nullptr, nullptr, 0, as_stream(stream));
 }
 
 extern "C" int dfs_sparse_attn_fwd_src(const dfs_geom* g, int dtype, const void* q, const int32_t* perm_pad, const void* k_perm,
@@ -747,5 +911,5 @@ extern "C" int dfs_sparse_attn_fwd_src(const dfs_geom* g, int dtype, const void*
   if (misaligned(16, {q, k_perm, v_perm, o}) || misaligned(4, {perm_pad, kv_idx, kv_cnt, lse}))
     return fail(DFS_EINVAL, "dfs_sparse_attn_fwd_src: tensors must be 16-byte aligned, index and fp32 arrays 4-byte aligned");
   if (!(scale > 0.f)) return fail(DFS_EINVAL, "dfs_sparse_attn_fwd_src: scale must be positive");
-  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o, lse, perm_pad, as_stream(stream));
+  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o, lse, perm_pad, nullptr, 0, as_stream(stream));
 }

@@ -27,19 +27,24 @@ inline bool misaligned(size_t a, std::initializer_list<const void*> ps) {
 inline int elem_size(int dtype) { return dtype == DFS_BF16 ? 2 : 4; }
 
 // Stage entry points without argument checks, used by dfs_forward after it has validated once.
-// x2, x2_perm (may be NULL): a second tensor, reordered in the same launch.
+// x2, x2_perm (may be NULL): a second tensor, reordered in the same launch.  n_zero words at `zero` are cleared.
 int run_permute(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* x, const int32_t* perm_pad,
-                void* x_perm, const void* x2, void* x2_perm, hipStream_t st);
+                void* x_perm, const void* x2, void* x2_perm, int32_t* zero, int n_zero, hipStream_t st);
 // index (may be NULL): the permutation; Q is then read in source order and gathered while pooling.  With k_out K comes
-// in source order too and is written out reordered, and so is V with v_out (which needs k_out).
+// in source order too and is written out reordered, and so is V with v_out (which needs k_out).  n_zero words at `zero`
+// are cleared on the way.
 int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q_perm, const void* k_perm,
-                    float* score, void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, hipStream_t st);
+                    float* score, void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, int32_t* zero,
+                    int n_zero, hipStream_t st);
 int run_select_mask(const dfs_geom* g, const dfs_sizes& s, const float* score, int mode, double sparsity,
                     double mass, uint8_t* mask, int32_t* kv_idx, int32_t* kv_cnt, int32_t K_max,
                     int32_t* k_head, void* ws, hipStream_t st);
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
-                    const int32_t* row_index, hipStream_t st);   // row_index (may be NULL): Q and O in source order
+                    const int32_t* row_index, void* scratch, size_t scratch_bytes, hipStream_t st);
+// row_index (may be NULL): Q and O in source order.  scratch (may be NULL): room to split text rows over work-groups; its
+// first text_tickets() words are zero when the kernel starts.
+inline size_t text_tickets(const dfs_geom* g, const dfs_sizes& s) { return size_t(g->heads) * s.M_x; }
 int run_unperm(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* o_perm, const int32_t* inv, void* o,
                hipStream_t st);
 size_t ws_block_score(const dfs_geom* g, const dfs_sizes& s);

@@ -68,7 +68,10 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in
                                                    uint16_t* __restrict__ q_hat, uint16_t* __restrict__ k_hat,
                                                    float* __restrict__ q_down, float* __restrict__ k_down,
                                                    const int32_t* __restrict__ index, void* __restrict__ k_out, void* __restrict__ v_out,
-                                                   int64_t N_src, int64_t N_pad, int64_t N_v, int Bs, int M_s, float q_scale) {
+                                                   int64_t N_src, int64_t N_pad, int64_t N_v, int Bs, int M_s, float q_scale,
+                                                   int32_t* __restrict__ zero, int n_zero) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+    for (int i = threadIdx.x; i < n_zero; i += 256) zero[i] = 0;
   constexpr int EPL = BF16 ? 8 : 4;           // elements per lane (16 bytes)
   constexpr int TPR = D / EPL;                // lanes per row
   constexpr int RPP = 64 / TPR;               // rows per pass
@@ -534,7 +537,7 @@ static void launch_score(const dfs_geom* g, const dfs_sizes& s, const uint16_t* 
 }
 
 int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q_perm, const void* k_perm, float* score,
-                    void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, hipStream_t st) {
+                    void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, int32_t* zero, int n_zero, hipStream_t st) {
   if (g->heads > 65535) return fail(DFS_ESHAPE, "heads=%d exceeds 65535", g->heads);
   if ((s.M_v + 31) / 32 > 65535) return fail(DFS_ESHAPE, "M_v=%d is too large for the scoring grid", s.M_v);
   char* base = static_cast<char*>(ws);
@@ -549,7 +552,7 @@ int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
   const bool bf = dtype == DFS_BF16;
   // 1/sqrt(d) of Eq. 2 and the change to base 2 go into Q_hat, so that the logits come out of the contraction in base 2
   const float scale = 1.4426950408889634f / sqrtf(float(g->d));
-#define POOL(BF, DD) pool_kernel<BF, DD><<<pg, 256, 0, st>>>(q_perm, k_perm, v, q_hat, k_hat, q_down, k_down, index, k_out, v_out, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale)
+#define POOL(BF, DD) pool_kernel<BF, DD><<<pg, 256, 0, st>>>(q_perm, k_perm, v, q_hat, k_hat, q_down, k_down, index, k_out, v_out, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale, zero, n_zero)
   if (g->d == 64) { if (bf) POOL(true, 64); else POOL(false, 64); }
   else            { if (bf) POOL(true, 128); else POOL(false, 128); }
 #undef POOL
@@ -584,7 +587,7 @@ extern "C" int dfs_block_score(const dfs_geom* g, int dtype, const void* q_perm,
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q_perm, k_perm, score, ws, nullptr, nullptr, nullptr, nullptr, as_stream(stream));
+  return run_block_score(g, s, dtype, q_perm, k_perm, score, ws, nullptr, nullptr, nullptr, nullptr, nullptr, 0, as_stream(stream));
 }
 
 extern "C" int dfs_block_score_src(const dfs_geom* g, int dtype, const void* q, const int32_t* perm_pad, const void* k_perm,
@@ -599,7 +602,7 @@ extern "C" int dfs_block_score_src(const dfs_geom* g, int dtype, const void* q, 
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score_src: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q, k_perm, score, ws, perm_pad, nullptr, nullptr, nullptr, as_stream(stream));
+  return run_block_score(g, s, dtype, q, k_perm, score, ws, perm_pad, nullptr, nullptr, nullptr, nullptr, 0, as_stream(stream));
 }
 
 extern "C" int dfs_block_score_fused(const dfs_geom* g, int dtype, const void* q, const void* k, const int32_t* perm_pad,
@@ -615,5 +618,5 @@ extern "C" int dfs_block_score_fused(const dfs_geom* g, int dtype, const void* q
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score_fused: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q, k, score, ws, perm_pad, k_perm, nullptr, nullptr, as_stream(stream));
+  return run_block_score(g, s, dtype, q, k, score, ws, perm_pad, k_perm, nullptr, nullptr, nullptr, 0, as_stream(stream));
 }

@@ -1,0 +1,94 @@
+"""bf16 attention where several waves or work-groups share one query block: key counts below, at and beside the split (a group
+without any block, a ragged last block in the last group, one block more than the groups share evenly), rows that outgrow
+their reference in one group only, and dense text rows split over work-groups in dfs_forward.  Against the oracle."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import dfs_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+P = pytest.importorskip("paper_2605_23445_amd")
+from tests import gpu_util as G  # noqa: E402
+
+# the suite's bounds for bf16 tensors (the weights and the result are rounded to bf16)
+TOL_MAX, TOL_MEAN, TOL_LSE = 2e-2, 2e-3, 1e-4
+
+
+def _bits(x):
+    return torch.from_numpy(x).to(torch.bfloat16).cuda()
+
+
+@pytest.mark.parametrize("steep", [False, True])
+@pytest.mark.parametrize("d,B", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("n_blocks,tail", [(1, 1), (2, 40), (5, 0), (18, 33)])
+def test_waves_that_share_a_query_block(d, B, n_blocks, tail, steep):
+    n_video = (n_blocks - 1) * B + (tail or B)
+    n_text = 0 if n_blocks < 5 else 7
+    W = next(w for w in range(512, 0, -1) if n_video % w == 0 and n_video // w <= 512)
+    g = P.Geom(1, n_video // W, W, n_text, 2, d, B, B // 4)
+    s = P.dfs_geom_sizes(g)
+    rng = np.random.default_rng(n_blocks * B + d)
+    valid = G.gpu_perm(g)[2].cpu().numpy()
+    q, k, v = (rng.standard_normal((2, s.N_pad, d)).astype(np.float32) for _ in range(3))
+    if steep:                                              # the last block far above the first: log2 weights up to 2^90 apart
+        q[:, :, 0], k[:, :, 0] = 8.0, (np.arange(s.N_pad) // B == s.M - 1) * 90 * math.sqrt(d) / (8 * math.log2(math.e))
+    pad = np.concatenate([np.arange(B) >= valid[b] for b in range(s.M)])
+    k[:, pad] = np.nan                                     # keys of pad rows may hold anything, values must be finite
+    v[:, pad] = 0.0
+    qd, kd, vd = (_bits(x) for x in (q, k, v))
+    mask = np.zeros((2, s.M, s.M), dtype=np.uint8)
+    for h in range(2):
+        for u in range(s.M):
+            mask[h, u, rng.permutation(s.M)[:1 + (u + h) % s.M]] = 1
+            mask[h, u, s.M - 1] |= u % 2
+    st = G.upload_mask(mask, K_max=max(17, s.M))           # room that lets every shape share its blocks
+    qf, kf, vf = (G.as_f64_dev(x) for x in (qd, kd, vd))
+    for want_lse in (True, False):
+        o, lse = G.gpu_attn(g, P.DFS_BF16, qd, kd, vd, st, want_lse=want_lse)
+        o = G.as_f64_dev(o)
+        err = []
+        for h in range(2):
+            for u in range(s.M):
+                rows = slice(u * B, u * B + valid[u])
+                want, want_lse_rows = O.sparse_attn_block(qf[h], kf[h], vf[h], np.nonzero(mask[h, u])[0], valid, B, u, 1.0 / math.sqrt(d))
+                err.append(np.abs(o[h, rows] - want[:valid[u]]).ravel())
+                if want_lse:
+                    assert np.abs(lse[h, rows].cpu().numpy() - want_lse_rows[:valid[u]]).max() <= TOL_LSE * (10 if steep else 1)
+        err = np.concatenate(err)
+        assert err.max() <= TOL_MAX and err.mean() <= TOL_MEAN
+
+
+@pytest.mark.parametrize("d,B,H,W,n_text,heads,sparsity", [(64, 64, 32, 32, 1, 3, 0.7), (64, 128, 40, 51, 130, 2, 0.5), (128, 64, 41, 27, 200, 1, 0.9),
+                                                           (128, 128, 90, 80, 128, 3, 0.8), (128, 128, 43, 48, 77, 24, 0.9)])
+def test_text_rows_over_several_work_groups(d, B, H, W, n_text, heads, sparsity):
+    g = P.Geom(1, H, W, n_text, heads, d, B, B // 4)
+    s = P.dfs_geom_sizes(g)
+    assert s.M >= 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H)
+    q, k, v = (torch.randn(heads, s.N, d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    k[:, s.N_v // 2] *= 6.0                                # a key that stands out in one run of the list only
+    perm_pad, inv, _ = G.gpu_perm(g)
+    K_max = P.dfs_keep_count(sparsity, s.M_v) + s.M_x
+    i32 = dict(dtype=torch.int32, device="cuda")
+    st = P.MaskState(torch.zeros((heads, s.M, K_max), **i32), torch.zeros((heads, s.M), **i32), None, None, K_max)
+    ws = G.ws_tensor(P.dfs_workspace_bytes(g, P.DFS_WS_FORWARD_BF16))
+    ws.fill_(255)                                          # tickets and sums start from anything
+    outs = []
+    for refresh in (True, False, False):
+        o = torch.full_like(q, float("nan"))
+        P.dfs_forward(g, P.DFS_BF16, q, k, v, perm_pad, inv, refresh, P.DFS_SELECT_TOPK, sparsity, 0.0, st, 1.0 / math.sqrt(d), o, ws)
+        outs.append(o)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])       # whoever merges, in list order
+    want = torch.softmax(q[:, s.N_v:].double() @ k.double().transpose(1, 2).contiguous() / math.sqrt(d), -1) @ v.double()
+    err = (outs[0][:, s.N_v:].double() - want).abs()
+    assert err.max() <= TOL_MAX and err.mean() <= TOL_MEAN
+    # video rows are not split: as from the staged calls
+    staged = G.gpu_attn(g, P.DFS_BF16, *(G.gpu_permute(g, P.DFS_BF16, x, perm_pad) for x in (q, k, v)), st, want_lse=False)[0]
+    video = G.gpu_unperm(g, P.DFS_BF16, staged, inv)[:, :s.N_v].float()
+    diff = (outs[0][:, :s.N_v].float() - video).abs()
+    assert diff.max() <= TOL_MAX and diff.mean() <= TOL_MEAN
