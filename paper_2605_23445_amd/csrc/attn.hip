@@ -82,11 +82,9 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   constexpr int ESL = NF - 1;                      // matrix instructions the sixteen exponentials of a half tile are spread over
   constexpr float HEADROOM = 16.f;                 // exponents of two: see "No maximum is taken" below
   constexpr float SUM_HIGH = 65536.f, SUM_LIMIT = 281474976710656.f;      // 2^16, 2^48
-  // Two K and two V tile buffers per group (tile t lives in the pair of parity t & 1).
-  __shared__ __attribute__((aligned(16))) uint16_t aK0[KS * TILE];
-  __shared__ __attribute__((aligned(16))) uint16_t aK1[KS * TILE];
-  __shared__ __attribute__((aligned(16))) uint16_t aV0[KS * TILE];
-  __shared__ __attribute__((aligned(16))) uint16_t aV1[KS * TILE];
+  // Two K and two V tile buffers per group (tile t lives in the pair of parity t & 1), at fixed byte offsets.
+  __shared__ __attribute__((aligned(16))) uint16_t tiles[KS * 4 * TILE];
+  constexpr int K0 = 0, K1 = 2 * TILE, V0 = 4 * TILE, V1 = 6 * TILE;
 
   // Work-group to (head, query block).  Ids are dealt round-robin to the 8 XCDs, so id % 8 names the XCD
   // and id / 8 the order inside it.
@@ -132,7 +130,6 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / (64 * NW)), wave = (tid >> 6) - grp * NW;
-  uint16_t *const sK0 = aK0 + grp * TILE, *const sK1 = aK1 + grp * TILE, *const sV0 = aV0 + grp * TILE, *const sV1 = aV1 + grp * TILE;
   const int n = lane & 31, h = lane >> 5;
   const int cnt_in = kv_cnt[int64_t(head) * M + u];
   const bool dense = cnt_in >= M;
@@ -208,60 +205,72 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // flight into another and would wait for every outstanding load before each LDS read.  The waits
   // that are needed are the explicit vmcnt(0) + barrier pairs in the loop below.  (Loads retire in
   // order, so the compiler's own counts for its few other memory operations stay conservative.)
-  // LDS addresses of this wave's first chunk in each tile buffer, as scalars, once (taken from a vector register
-  // inside the loop they cost a vector-to-scalar hand-over per tile)
-  auto lds_base = [&](uint16_t* buf) {
-    return __builtin_amdgcn_readfirstlane(uint32_t(reinterpret_cast<uintptr_t>((LDS_PTR(void))(buf + wave * 512))));
-  };
-  const uint32_t lds_k0 = lds_base(sK0), lds_k1 = lds_base(sK1), lds_v0 = lds_base(sV0), lds_v1 = lds_base(sV1);
+  // LDS address of this wave's first chunk in the first buffer, as a scalar, once (taken from a vector register
+  // inside the loop it costs a vector-to-scalar hand-over per tile)
+  const uint32_t lds_tiles = uint32_t(reinterpret_cast<uintptr_t>((LDS_PTR(void))(tiles))) + uint32_t(grp * 8 * TILE);
+  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_tiles + uint32_t(wave * 1024));
   auto tile_src = [&](const uint16_t* base, int tile, int blk) {
     return reinterpret_cast<uint64_t>(base + (int64_t(blk) * BM + (tile % STEPS) * KN) * D);
   };
-  auto issue_one = [&](uint64_t src, uint32_t lds0, bool is_v, int j) {
+  auto issue_one = [&](uint64_t src, int buf, bool is_v, int j) {
     const int P = is_v ? PV : PK;
     const uint32_t voff = is_v ? v_off[j % PV] : k_off[j % PK];
     const uint64_t sj = src + uint64_t(j / P) * (P * RJ) * D * 2;
     const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(sj)), hi = __builtin_amdgcn_readfirstlane(uint32_t(sj >> 32));
     const uint64_t sbase = (uint64_t(hi) << 32) | lo;
-    const uint32_t lds = lds0 + uint32_t(j * NW * 1024);
+    const uint32_t lds = lds_wave + uint32_t(buf + j * NW * 1024);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
   };
-  auto issue = [&](const uint16_t* base, uint32_t lds0, bool is_v, int tile, int blk) {
+  auto issue = [&](const uint16_t* base, int buf, bool is_v, int tile, int blk) {
     const uint64_t src = tile_src(base, tile, blk);
 #pragma unroll
-    for (int j = 0; j < LPW; ++j) issue_one(src, lds0, is_v, j);
+    for (int j = 0; j < LPW; ++j) issue_one(src, buf, is_v, j);
   };
 
-  // LDS read offsets (elements), loop invariant
+  // LDS byte addresses of this lane's operand reads in the first buffer, loop invariant: one per K fragment and one per
+  // value column group, everything else (buffer, half tile, key rows) is in the instruction's offset.  The empty asm keeps
+  // the compiler from working each out anew per buffer, which took thirty registers more, spilled some and redid eight of
+  // them per tile: 4 heads of 75 600 tokens with log-sum-exp, dense and sparse, 13.5 -> 12.2 ms; d = 64, 17 550 tokens x 48
+  // heads, 667 -> 658 us.
   const int k_sw = swz_k<CH>(n);                                    // rows 32 t + n: swizzle depends on n only
   const int v_r = (lane & 15) >> 2;                                 // row inside the 4-row group
   const int v_row = 4 * h + v_r;
   const int v_sw = swz_v<CH>(v_r);                                  // rows 16 s + 4 h + v_r (+8): same swizzle
   const int v_c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);        // chunk inside the 32-column group
   const int v_b = (lane & 1) * 4;                                   // 8-byte half of the chunk
+  uint32_t k_addr[D / 16], v_addr[D / 32];
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) {
+    k_addr[kk] = lds_tiles + uint32_t(2 * (n * D + ((2 * kk + h) ^ k_sw) * 8));
+    asm volatile("" : "+v"(k_addr[kk]));
+  }
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt) {
+    v_addr[dt] = lds_tiles + uint32_t(2 * (v_row * D + v_b + ((4 * dt + v_c) ^ v_sw) * 8));
+    asm volatile("" : "+v"(v_addr[dt]));
+  }
 
   // The loop works on half tiles (32 key rows).  Logits of a half tile for query tile a:
   // sx[a][i] = logit(key row 32 half + 8 (i/4) + 4 h + i%4, query row 32 a + n).
-  auto k_frag = [&](const uint16_t* tK, int kk) {
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&tK[((2 * kk + h) ^ k_sw) * 8]));
+  auto k_frag = [&](int kbuf, int half, int kk) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<LDS_PTR(const u32x4)>(k_addr[kk] + uint32_t(kbuf + half * 64 * D)));
   };
   // One product piece of O^T += V^T P^T for a half tile: piece j = (D/32) s2 + dt.  Product step s2
   // covers key rows 16 s2 + {4h..4h+3} and 16 s2 + 8 + {4h..4h+3}, which is what registers 8 s2 .. 8 s2 + 7
   // of the logit tile hold; the transposing LDS read hands each lane four consecutive key rows of one
   // value column.
-  auto v_frag = [&](const uint16_t* tV, int j) {
+  auto v_frag = [&](int vbuf, int half, int j) {
     const int s2 = j / (D / 32), dt = j % (D / 32);
-    const uint16_t* p0 = &tV[16 * s2 * D + ((4 * dt + v_c) ^ v_sw) * 8];
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(p0));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(p0 + 8 * D));
+    const uint32_t p0 = v_addr[dt] + uint32_t(vbuf + half * 64 * D + s2 * 32 * D);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_PTR(s16x4)>(p0));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<LDS_PTR(s16x4)>(p0 + 16 * D));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  auto logits = [&](const uint16_t* kbuf, int half, f32x16& sx) {
-    const uint16_t* tK = kbuf + (32 * half + n) * D;
+  auto logits = [&](int kbuf, int half, f32x16& sx) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) sx[i] = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(tK, kk), qf[kk], sx, 0, 0, 0);
+    for (int kk = 0; kk < D / 16; ++kk) sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(kbuf, half, kk), qf[kk], sx, 0, 0, 0);
   };
   // pad keys of a ragged block never count.  Only two blocks can be ragged, the last video block and the last text
   // block; their ids and real-row counts are worked out once, so that the check per half tile is two scalar compares
@@ -333,17 +342,15 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         }
     }
   };
-  auto stage = [&](auto do_pv, auto do_s, const uint16_t* vbuf, int pv_half, const u32x4 (&pp)[2], const uint16_t* kbuf,
+  auto stage = [&](auto do_pv, auto do_s, int vbuf, int pv_half, const u32x4 (&pp)[2], int kbuf,
                    int s_half, f32x16& sn, const f32x16& sx, u32x4 (&pc)[2], auto mem) __attribute__((always_inline)) {
     constexpr bool DO_PV = decltype(do_pv)::value, DO_S = decltype(do_s)::value;
-    const uint16_t* tV = vbuf + (32 * pv_half + v_row) * D + v_b;
-    const uint16_t* tK = kbuf + (32 * s_half + n) * D;
     bf16x8 frag[NF];
     auto load = [&](int f) {
       if (f % 2 == 1) {
-        if (DO_PV) frag[f] = v_frag(tV, f / 2);
+        if (DO_PV) frag[f] = v_frag(vbuf, pv_half, f / 2);
       } else if (DO_S) {
-        frag[f] = k_frag(tK, f / 2);
+        frag[f] = k_frag(kbuf, s_half, f / 2);
       }
     };
     float pe[16], xsum = 0.f;
@@ -402,10 +409,10 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   int b_cur = 0, b_nxt = 0;                        // key blocks of tiles t and t + 1: one list lookup per tile (that of tile t + 2)
   auto tile_step = [&](auto parity, auto first, auto last, int t) __attribute__((always_inline)) {
     constexpr bool ODD = decltype(parity)::value, FIRST = decltype(first)::value, LAST = decltype(last)::value;
-    uint16_t* k_cur = ODD ? sK1 : sK0;             // K(t); K(t+2) goes here
-    uint16_t* k_nxt = ODD ? sK0 : sK1;             // K(t+1)
-    uint16_t* v_cur = ODD ? sV1 : sV0;             // V(t)
-    uint16_t* v_nxt = ODD ? sV0 : sV1;             // V(t-1); V(t+1) goes here
+    constexpr int k_cur = ODD ? K1 : K0;             // K(t); K(t+2) goes here
+    constexpr int k_nxt = ODD ? K0 : K1;             // K(t+1)
+    constexpr int v_cur = ODD ? V1 : V0;             // V(t)
+    constexpr int v_nxt = ODD ? V0 : V1;             // V(t-1); V(t+1) goes here
     // first half: products of (t-1, 1), logits of (t, 1), probabilities of (t, 0)
     stage(std::integral_constant<bool, !FIRST>{}, yes{}, v_nxt, 1, p1, k_cur, 1, s1, s0, p0, [](int) {});
     mask_pads(b_cur, t, 1, s1);
@@ -421,30 +428,29 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       if (LAST) return;
 #pragma unroll
       for (int j = f * 2 * LPW / NF; j < (f + 1) * 2 * LPW / NF; ++j)
-        issue_one(j < LPW ? v_src : k_src, j < LPW ? (ODD ? lds_v0 : lds_v1) : (ODD ? lds_k1 : lds_k0), j < LPW, j % LPW);
+        issue_one(j < LPW ? v_src : k_src, j < LPW ? v_nxt : k_cur, j < LPW, j % LPW);
     });
     if (!LAST) mask_pads(b_nxt, t + 1, 0, s0);
     b_cur = b_nxt;
     b_nxt = b_new;
   };
-  auto products = [&](const uint16_t* vbuf, int half, const u32x4 (&pp)[2]) __attribute__((always_inline)) {    // O^T += V^T P^T
-    const uint16_t* tV = vbuf + (32 * half + v_row) * D + v_b;
+  auto products = [&](int vbuf, int half, const u32x4 (&pp)[2]) __attribute__((always_inline)) {    // O^T += V^T P^T
 #pragma unroll
     for (int j = 0; j < 2 * (D / 32); ++j) {
       const bf16x8 pj = __builtin_bit_cast(bf16x8, pp[j / (D / 32)]);
-      oacc[j % (D / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(tV, j), pj, oacc[j % (D / 32)], 0, 0, 0);
+      oacc[j % (D / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(vbuf, half, j), pj, oacc[j % (D / 32)], 0, 0, 0);
       if (j % (D / 32) == 0) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, pj, lsum, 0, 0, 0);
     }
   };
   if (n_tiles > 0) {
     b_cur = tile_block(0);
     b_nxt = n_tiles > 1 ? tile_block(1) : b_cur;
-    issue(kh, lds_k0, false, 0, b_cur);
-    issue(vh, lds_v0, true, 0, b_cur);
+    issue(kh, K0, false, 0, b_cur);
+    issue(vh, V0, true, 0, b_cur);
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
-    if (n_tiles > 1) issue(kh, lds_k1, false, 1, b_nxt);
-    logits(sK0, 0, s0);
+    if (n_tiles > 1) issue(kh, K1, false, 1, b_nxt);
+    logits(K0, 0, s0);
     mask_pads(b_cur, 0, 0, s0);
     if (KS == 1 || t_first < all_tiles) m_run = fmaf(half_max(s0), c2, HEADROOM);      // finite: the first row of a block is never a pad
     if (n_tiles == 1) {
@@ -461,7 +467,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       if (t & 1) tile_step(yes{}, no{}, yes{}, t);
       else tile_step(no{}, no{}, yes{}, t);
     }
-    products((n_tiles - 1) & 1 ? sV1 : sV0, 1, p1);  // drain: the last half tile
+    products((n_tiles - 1) & 1 ? V1 : V0, 1, p1);  // drain: the last half tile
     if (__builtin_expect(__syncthreads_or(!(lsum[0] < SUM_LIMIT)), 0)) {
       // Once more in plain order, with the reference at the row's true maximum: first that maximum, then the sums.
       x_run = 0.f;
@@ -475,13 +481,13 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       for (int step = 0; step < 2 * n_tiles; ++step) {
         const bool sums = step >= n_tiles;
         const int t = sums ? step - n_tiles : step, blk = tile_block(t);
-        issue(kh, lds_k0, false, t, blk);
-        issue(vh, lds_v0, true, t, blk);
+        issue(kh, K0, false, t, blk);
+        issue(vh, V0, true, t, blk);
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
 #pragma unroll 1
         for (int half = 0; half < 2; ++half) {
-          logits(sK0, half, s0);
+          logits(K0, half, s0);
           mask_pads(blk, t, half, s0);
           if (!sums) {
             mx = fmaxf(mx, half_max(s0));
@@ -493,7 +499,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               p0[i / 8][(i % 8) / 2] = pack(a, b);
               x_run += a + b;
             }
-            products(sV0, half, p0);
+            products(V0, half, p0);
           }
         }
         __syncthreads();
@@ -506,8 +512,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // them; the first group brings all to the largest reference and adds.  A group without tiles (reference -inf) adds zeros.
     __shared__ float s_part[KS][NW][3][64];
     auto acc_buf = [&](int g) {
-      uint16_t* b = (wave == 0 ? aK0 : wave == 1 ? aK1 : wave == 2 ? aV0 : aV1) + g * TILE;
-      return reinterpret_cast<float*>(b) + lane;
+      return reinterpret_cast<float*>(tiles + (g * 4 + wave) * TILE) + lane;
     };
     static_assert(TILE * 2 == (D / 32) * 16 * 64 * 4, "one tile buffer holds the accumulators of one wave");
     if (n_tiles == 0) {
