@@ -10,7 +10,7 @@
 
 #include <mutex>
 
-#include "common.h"
+#include "select_row.h"
 
 namespace dfs {
 
@@ -20,78 +20,16 @@ namespace dfs {
 constexpr size_t STATIC_SCRATCH_BYTES = size_t(1) << 20;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
-constexpr int MASS_FRAC_BITS = 24;
-
-__device__ __forceinline__ uint32_t order_key(float s) {
-  uint32_t b = __float_as_uint(s);
-  if (b == 0x80000000u) b = 0u;                     // -0 ranks with +0
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const uint32_t lo = __shfl_xor(uint32_t(v), off, 64), hi = __shfl_xor(uint32_t(v >> 32), off, 64);
-    v += (static_cast<unsigned long long>(hi) << 32) | lo;
-  }
-  return v;
-}
-
-__device__ __forceinline__ unsigned long long mass_fixed(float s) {
-  const double c = fmin(fmax(double(s), 0.0), 4096.0);   // NaN clamps to 0
-  return static_cast<unsigned long long>(c * double(1 << MASS_FRAC_BITS));
-}
-
 // k_row[head, u] = fewest top-ranked columns whose fixed-point scores reach ceil(mass * row total).
 __global__ void __launch_bounds__(64) mass_count_kernel(const float* __restrict__ score, int M_v, double mass,
                                                         int32_t* __restrict__ k_row) {
-  extern __shared__ uint32_t keys[];
+  extern __shared__ unsigned long long lds[];
+  uint32_t* keys = reinterpret_cast<uint32_t*>(lds + 64);
   const int lane = threadIdx.x;
   const float* row = score + (int64_t(blockIdx.y) * M_v + blockIdx.x) * M_v;
-  unsigned long long tot = 0;
-  for (int j = lane; j < M_v; j += 64) {
-    const float s = row[j];
-    keys[j] = order_key(s);
-    tot += mass_fixed(s);
-  }
-  __syncthreads();
-  tot = wave_sum_u64(tot);
-  const unsigned long long target = static_cast<unsigned long long>(ceil(mass * double(tot)));
-  int k = 1;
-  if (target > 0) {
-    // largest threshold T with sum over {key >= T} >= target
-    uint32_t T = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-      const uint32_t cand = T | (1u << bit);
-      unsigned long long part = 0;
-      for (int j = lane; j < M_v; j += 64)
-        if (keys[j] >= cand) part += mass_fixed(row[j]);
-      if (wave_sum_u64(part) >= target) T = cand;
-    }
-    unsigned long long above = 0, at = 0;
-    uint32_t n_above = 0;
-    for (int j = lane; j < M_v; j += 64) {
-      if (keys[j] > T) { above += mass_fixed(row[j]); ++n_above; }
-      else if (keys[j] == T) at = mass_fixed(row[j]);
-    }
-    above = wave_sum_u64(above);
-    n_above = wave_sum_u32(n_above);
-    // every column at the threshold has the same fixed-point value; take the largest lane's copy
-    unsigned long long at_all = at;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const uint32_t lo = __shfl_xor(uint32_t(at_all), off, 64), hi = __shfl_xor(uint32_t(at_all >> 32), off, 64);
-      const unsigned long long o = (static_cast<unsigned long long>(hi) << 32) | lo;
-      at_all = o > at_all ? o : at_all;
-    }
-    const unsigned long long need = target - above;          // > 0 by choice of T
-    k = int(n_above + (need + at_all - 1) / at_all);
-  }
+  for (int j = lane; j < M_v; j += 64) keys[j] = order_key(row[j]);
+  wave_sync();
+  const int k = mass_count_row(keys, lds, M_v, mass);
   if (lane == 0) k_row[int64_t(blockIdx.y) * M_v + blockIdx.x] = k;
 }
 
@@ -125,11 +63,10 @@ __global__ void __launch_bounds__(64) select_kernel(const float* __restrict__ sc
   const int lane = threadIdx.x;
   const int head = blockIdx.y, u = blockIdx.x;
   const int M = M_v + M_x;
-  uint8_t* mrow = mask ? mask + (int64_t(head) * M + u) * M : nullptr;
-  if (u >= M_v) {                                   // text query block: keeps every key block
-    if (mrow)
-      for (int j = lane; j < M; j += 64) mrow[j] = 1;
-    if (lane == 0) kv_cnt[int64_t(head) * M + u] = M;
+  const int64_t out = int64_t(head) * M + u;
+  uint8_t* mrow = mask ? mask + out * M : nullptr;
+  if (u >= M_v) {
+    select_text_row(M, mrow, kv_cnt + out);
     return;
   }
   int k = k_per_head ? k_per_head[head] : k_fixed;
@@ -140,76 +77,15 @@ __global__ void __launch_bounds__(64) select_kernel(const float* __restrict__ sc
   if (k_head_out && !k_per_head && !k_per_row && u == 0 && lane == 0) k_head_out[head] = k;
   const float* row = score + (int64_t(head) * M_v + u) * M_v;
   for (int j = lane; j < M_v; j += 64) keys[j] = order_key(row[j]);
-  __syncthreads();
-  // T = k-th largest key, found a byte at a time from the top: a 256-bin histogram of the next byte of the keys that
-  // still match the bytes fixed so far, then the bin in which the count from the top reaches what is still wanted.
-  // Four passes instead of one per bit; counts are integers, so the result is the same key.
-  uint32_t* hist = keys + M_v;
-  uint32_t T = 0, fixed = 0, want = uint32_t(k);      // want: rank of the key looked for among the keys matching T on `fixed`
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    for (int b = lane; b < 256; b += 64) hist[b] = 0u;
-    __syncthreads();
-    for (int j = lane; j < M_v; j += 64) {
-      const uint32_t key = keys[j];
-      if ((key & fixed) == T) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    // lane l owns bins 255 - 4 l .. 252 - 4 l, so that lane order is descending key order
-    uint32_t c[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) c[i] = hist[255 - 4 * lane - i];
-    const uint32_t mine = c[0] + c[1] + c[2] + c[3];
-    uint32_t incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t up = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += up;
-    }
-    const unsigned long long reached = __ballot(incl >= want);     // never empty: at least `want` keys match
-    const int sel = __ffsll(reached) - 1;
-    uint32_t left = want - (incl - mine), digit = 0u;              // meaningful in lane `sel` only
-#pragma unroll
-    for (int i = 3; i >= 0; --i) {                                 // the first bin (from the top) whose running count reaches `left`
-      const uint32_t before = (i > 0 ? c[0] : 0u) + (i > 1 ? c[1] : 0u) + (i > 2 ? c[2] : 0u);
-      if (before < left && left <= before + c[i]) digit = uint32_t(255 - 4 * lane - i) | ((left - before) << 8);
-    }
-    digit = __shfl(digit, sel, 64);
-    T |= (digit & 255u) << shift;
-    want = digit >> 8;
-    fixed |= 255u << shift;
-    __syncthreads();                                               // the histogram is cleared next
-  }
-  const uint32_t ties_wanted = want;                               // lowest-index columns equal to T; the k - want keys above T are all kept
-  int32_t* idx = kv_idx + (int64_t(head) * M + u) * K_max;
-  uint32_t ties_seen = 0, written = 0;
-  const unsigned long long below_me = (1ull << lane) - 1ull;
-  for (int j0 = 0; j0 < M_v; j0 += 64) {
-    const int j = j0 + lane;
-    const uint32_t key = j < M_v ? keys[j] : 0u;
-    const bool is_tie = j < M_v && key == T;
-    const unsigned long long tie_ballot = __ballot(is_tie);
-    const uint32_t tie_rank = ties_seen + __popcll(tie_ballot & below_me);
-    const bool keep = j < M_v && (key > T || (is_tie && tie_rank < ties_wanted));
-    const unsigned long long keep_ballot = __ballot(keep);
-    if (keep) idx[written + __popcll(keep_ballot & below_me)] = j;
-    if (mrow && j < M_v) mrow[j] = keep ? 1 : 0;
-    ties_seen += __popcll(tie_ballot);
-    written += __popcll(keep_ballot);
-  }
-  for (int j = lane; j < M_x; j += 64) {             // text key blocks are always kept
-    idx[k + j] = M_v + j;
-    if (mrow) mrow[M_v + j] = 1;
-  }
-  if (lane == 0) kv_cnt[int64_t(head) * M + u] = k + M_x;
+  wave_sync();
+  select_row(keys, keys + M_v, M_v, M_x, k, mrow, kv_idx + out * K_max, kv_cnt + out);
 }
 
 size_t ws_select_mask(const dfs_geom* g, const dfs_sizes& s) {
   return align256(size_t(g->heads) * s.M_v * sizeof(int32_t)) + align256(size_t(g->heads) * sizeof(int32_t));
 }
 
-int run_select_mask(const dfs_geom* g, const dfs_sizes& s, const float* score, int mode, double sparsity, double mass,
-                    uint8_t* mask, int32_t* kv_idx, int32_t* kv_cnt, int32_t K_max, int32_t* k_head, void* ws,
-                    hipStream_t st) {
+int check_select(const dfs_geom* g, const dfs_sizes& s, int mode, double sparsity, double mass, int32_t K_max) {
   if (mode != DFS_SELECT_TOPK && mode != DFS_SELECT_MASS_HEAD && mode != DFS_SELECT_MASS_ROW)
     return fail(DFS_EINVAL, "dfs_select_mask: unknown mode %d", mode);
   if (!(sparsity >= 0.0 && sparsity <= 1.0)) return fail(DFS_EINVAL, "dfs_select_mask: sparsity %g is outside [0,1]", sparsity);
@@ -218,13 +94,22 @@ int run_select_mask(const dfs_geom* g, const dfs_sizes& s, const float* score, i
   const int k_base = dfs_keep_count(sparsity, s.M_v);
   if (K_max < k_base + s.M_x)
     return fail(DFS_ESHAPE, "dfs_select_mask: K_max=%d is below the %d kept blocks per row", K_max, k_base + s.M_x);
-  const size_t lds = size_t(s.M_v) * sizeof(uint32_t);            // the mass count keeps one key per column
-  const size_t lds_sel = lds + 256 * sizeof(uint32_t);           // the selection adds its byte histogram
+  if (mode != DFS_SELECT_TOPK && !(mass > 0.0 && mass <= 1.0)) return fail(DFS_EINVAL, "dfs_select_mask: mass %g is outside (0,1]", mass);
+  return DFS_OK;
+}
+
+int run_select_mask(const dfs_geom* g, const dfs_sizes& s, const float* score, int mode, double sparsity, double mass,
+                    uint8_t* mask, int32_t* kv_idx, int32_t* kv_cnt, int32_t K_max, int32_t* k_head, void* ws,
+                    hipStream_t st) {
+  const int rc = check_select(g, s, mode, sparsity, mass, K_max);
+  if (rc) return rc;
+  const int k_base = dfs_keep_count(sparsity, s.M_v);
+  const size_t lds = size_t(s.M_v) * sizeof(uint32_t) + 64 * sizeof(uint64_t);       // one key per column and the mass bins
+  const size_t lds_sel = size_t(s.M_v) * sizeof(uint32_t) + 256 * sizeof(uint32_t);  // ... or the byte histogram
   dim3 rows(unsigned(s.M), unsigned(g->heads));
   if (mode == DFS_SELECT_TOPK) {
     select_kernel<<<rows, 64, lds_sel, st>>>(score, s.M_v, s.M_x, k_base, nullptr, nullptr, 0, mask, kv_idx, kv_cnt, K_max, k_head);
   } else {
-    if (!(mass > 0.0 && mass <= 1.0)) return fail(DFS_EINVAL, "dfs_select_mask: mass %g is outside (0,1]", mass);
     int32_t* k_row = static_cast<int32_t*>(ws);
     int32_t* k_used = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + align256(size_t(g->heads) * s.M_v * sizeof(int32_t)));
     int k_cap = K_max - s.M_x;
