@@ -127,9 +127,16 @@ int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, cons
   const int n_tickets = int(text_tickets(g, s));
   if (refresh) {
     float* score = reinterpret_cast<float*>(base + L.score);
-    if ((rc = run_block_score(g, s, dtype, q, k, score, base + L.sub, perm_pad, k_perm, v, v_perm, tickets, n_tickets, hs))) return rc;
-    if ((rc = run_select_mask(g, s, score, mode, sparsity, mass, st->mask, st->kv_idx, st->kv_cnt, st->K_max,
-                              st->k_head, base + L.sub, hs)))
+    if ((rc = check_select(g, s, mode, sparsity, mass, st->K_max))) return rc;
+    const int k_room = st->K_max - s.M_x;
+    const SelectPlan sel = {dfs_keep_count(sparsity, s.M_v), k_room < s.M_v ? k_room : s.M_v, mode == DFS_SELECT_MASS_ROW ? mass : 0.0,
+                            st->mask, st->kv_idx, st->kv_cnt, st->K_max, st->k_head};
+    const bool in_fold = can_select_in_fold(s, mode);
+    if ((rc = run_block_score(g, s, dtype, q, k, score, base + L.sub, perm_pad, k_perm, v, v_perm, tickets, n_tickets,
+                              in_fold ? &sel : nullptr, hs)))
+      return rc;
+    if (!in_fold && (rc = run_select_mask(g, s, score, mode, sparsity, mass, st->mask, st->kv_idx, st->kv_cnt, st->K_max, st->k_head,
+                                          base + L.sub, hs)))
       return rc;
   } else if ((rc = run_permute(g, s, dtype, k, perm_pad, k_perm, v, v_perm, tickets, n_tickets, hs))) {
     return rc;

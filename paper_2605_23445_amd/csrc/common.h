@@ -30,12 +30,24 @@ inline int elem_size(int dtype) { return dtype == DFS_BF16 ? 2 : 4; }
 // x2, x2_perm (may be NULL): a second tensor, reordered in the same launch.  n_zero words at `zero` are cleared.
 int run_permute(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* x, const int32_t* perm_pad,
                 void* x_perm, const void* x2, void* x2_perm, int32_t* zero, int n_zero, hipStream_t st);
+// What the selection of a row needs when the scoring does it on the way: the keep count, or with mass > 0 its bounds.
+struct SelectPlan {
+  int k_fixed, k_cap;
+  double mass;
+  uint8_t* mask;
+  int32_t *kv_idx, *kv_cnt;
+  int32_t K_max;
+  int32_t* k_head;
+};
 // index (may be NULL): the permutation; Q is then read in source order and gathered while pooling.  With k_out K comes
 // in source order too and is written out reordered, and so is V with v_out (which needs k_out).  n_zero words at `zero`
-// are cleared on the way.
+// are cleared on the way.  With sel the block lists are written instead of the scores (`score` may be NULL then).
 int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q_perm, const void* k_perm,
                     float* score, void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, int32_t* zero,
-                    int n_zero, hipStream_t st);
+                    int n_zero, const SelectPlan* sel, hipStream_t st);
+// Whether the scoring can select on the way: the rule needs one row's scores only and eight rows fit in 64 KB of LDS.
+bool can_select_in_fold(const dfs_sizes& s, int mode);
+int check_select(const dfs_geom* g, const dfs_sizes& s, int mode, double sparsity, double mass, int32_t K_max);
 int run_select_mask(const dfs_geom* g, const dfs_sizes& s, const float* score, int mode, double sparsity,
                     double mass, uint8_t* mask, int32_t* kv_idx, int32_t* kv_cnt, int32_t K_max,
                     int32_t* k_head, void* ws, hipStream_t st);

@@ -16,7 +16,7 @@
 //                   follows stays an fp32 one); the scaling is undone, exactly, on the fp32 result.
 #include <type_traits>
 
-#include "common.h"
+#include "select_row.h"
 
 namespace dfs {
 
@@ -491,6 +491,72 @@ __global__ void __launch_bounds__(256) score_fold_kernel(const float* __restrict
   }
 }
 
+// Pass 2 and the selection in one, for callers that want the lists only: eight query blocks of a head per work-group.  The
+// scores of their rows (the same sums as above, in the same order) go to LDS as ordered keys, then each wave selects one
+// row.  Eight rows because at R = 4 their query sub-blocks are one 128-byte line of a row of T.  The scores never go to
+// memory and one launch goes: 75 600 tokens x 40 heads 134 -> 71 us, 17 550 x 48 19 -> 14, 2 565 x 12 and its gap 10 + 2 -> 7.
+constexpr int FS_ROWS = 8, FS_T = 64 * FS_ROWS;
+__host__ __device__ inline int fs_stride(int M_v) { return (M_v + 63) / 64 * 64 + 8; }   // lanes (block, row) hit every bank once
+template <int R>
+__global__ void __launch_bounds__(FS_T) fold_select_kernel(const float* __restrict__ tt, const float* __restrict__ lse, int M_s, int M_v,
+                                                           int M_x, int n_live, int ksplit, int k_fixed, int k_cap, double mass,
+                                                           uint8_t* __restrict__ mask, int32_t* __restrict__ kv_idx,
+                                                           int32_t* __restrict__ kv_cnt, int K_max, int32_t* __restrict__ k_head) {
+  extern __shared__ unsigned long long lds64[];
+  uint32_t* hists = reinterpret_cast<uint32_t*>(lds64);                  // 256 words per wave, then the keys
+  uint32_t* keys = hists + FS_ROWS * 256;
+  const int stride = fs_stride(M_v);
+  const int head = blockIdx.y, u0 = blockIdx.x * FS_ROWS;
+  const int TC = t_cols(M_s);
+  const int r = threadIdx.x % FS_ROWS, u = u0 + r;
+  if (u < M_v) {
+    const float* tt_h = tt + int64_t(head) * t_rows(M_s, R) * TC + int64_t(u) * R;
+    const float* lse_h = lse + int64_t(head) * ksplit * M_s;
+    float l[R];
+#pragma unroll
+    for (int a = 0; a < R; ++a) {
+      const int i = u * R + a;
+      float m = LSE_START, z = 0.f;
+      if (i < n_live)
+        for (int sp = 0; sp < ksplit; ++sp) lse_add(m, z, lse_h[int64_t(sp) * M_s + i]);
+      l[a] = z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;
+    }
+    typedef float trow __attribute__((ext_vector_type(R < 4 ? R : 4)));   // R T-values side by side, 4 R bytes aligned
+    constexpr int W = R < 4 ? R : 4;
+#pragma unroll 4
+    for (int v = threadIdx.x / FS_ROWS; v < M_v; v += FS_T / FS_ROWS) {
+      float acc = 0.f;
+#pragma unroll
+      for (int w = 0; w < R / W; ++w) {
+        const trow t = reinterpret_cast<const trow*>(tt_h + int64_t(v) * TC)[w];
+#pragma unroll
+        for (int e = 0; e < W; ++e) acc += __builtin_amdgcn_exp2f(t[e] - l[w * W + e]);
+      }
+      keys[r * stride + v] = order_key(acc);
+    }
+  }
+  __syncthreads();
+  const int wave = threadIdx.x >> 6, uw = u0 + wave, M = M_v + M_x;
+  if (uw >= M) return;
+  const int64_t out = int64_t(head) * M + uw;
+  uint8_t* mrow = mask ? mask + out * M : nullptr;
+  if (uw >= M_v) {
+    select_text_row(M, mrow, kv_cnt + out);
+    return;
+  }
+  const uint32_t* row = keys + wave * stride;
+  uint32_t* hist = hists + wave * 256;
+  int k = k_fixed;
+  if (mass > 0.0) {                                                      // every row its own count, clamped
+    const int ku = mass_count_row(row, reinterpret_cast<unsigned long long*>(hist), M_v, mass);
+    k = ku < k_fixed ? k_fixed : (ku > k_cap ? k_cap : ku);
+  } else if (k_head && uw == 0 && (threadIdx.x & 63) == 0) {
+    k_head[head] = k;
+  }
+  select_row(row, hist, M_v, M_x, k, mrow, kv_idx + out * K_max, kv_cnt + out);
+}
+static size_t fs_lds(int M_v) { return size_t(FS_ROWS) * (256 + fs_stride(M_v)) * sizeof(uint32_t); }
+
 // Workspace: Q_hat, K_hat (two fp16 planes each, followed by the inverse scales of their row groups),
 // T [heads][t_rows][t_cols] fp32 (padded, see t_cols), row log-sum-exp [heads][KSPLIT_MAX][M_s] fp32.
 constexpr int KSPLIT_MAX = 4;
@@ -523,7 +589,7 @@ static int choose_ksplit(int64_t groups_times_heads, int n_tiles) {
 
 template <int D, int R>
 static void launch_score(const dfs_geom* g, const dfs_sizes& s, const uint16_t* q_hat, const uint16_t* k_hat, const float* q_down,
-                         const float* k_down, float* tt, float* lse, float* score, int n_live, hipStream_t st) {
+                         const float* k_down, float* tt, float* lse, float* score, const SelectPlan* sel, int n_live, hipStream_t st) {
   const int groups = (s.M_s + 127) / 128, n_tiles = (n_live + 31) / 32;
   const int ksplit = choose_ksplit(int64_t(groups) * g->heads, n_tiles);
   const int per = (n_tiles + ksplit - 1) / ksplit;
@@ -532,12 +598,20 @@ static void launch_score(const dfs_geom* g, const dfs_sizes& s, const uint16_t* 
   const int per_xcd = int((total + 7) / 8);
   score_lse_kernel<D, R><<<dim3(unsigned(per_xcd * 8)), 256, 0, st>>>(q_hat, k_hat, q_down, k_down, tt, lse, s.M_s, n_live, per, ksplit,
                                                                       wgs_per_head, int(total), per_xcd);
+  if (sel) {
+    fold_select_kernel<R><<<dim3(unsigned((s.M + FS_ROWS - 1) / FS_ROWS), unsigned(g->heads)), FS_T, fs_lds(s.M_v), st>>>(
+        tt, lse, s.M_s, s.M_v, s.M_x, n_live, ksplit, sel->k_fixed, sel->k_cap, sel->mass, sel->mask, sel->kv_idx, sel->kv_cnt, sel->K_max, sel->k_head);
+    return;
+  }
   const unsigned tb = unsigned((s.M_v + 31) / 32);
   score_fold_kernel<R><<<dim3(tb, tb, unsigned(g->heads)), 256, 0, st>>>(tt, lse, score, s.M_s, s.M_v, n_live, ksplit);
 }
 
+bool can_select_in_fold(const dfs_sizes& s, int mode) { return mode != DFS_SELECT_MASS_HEAD && fs_lds(s.M_v) <= 65536; }
+
 int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q_perm, const void* k_perm, float* score,
-                    void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, int32_t* zero, int n_zero, hipStream_t st) {
+                    void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, int32_t* zero, int n_zero, const SelectPlan* sel,
+                    hipStream_t st) {
   if (g->heads > 65535) return fail(DFS_ESHAPE, "heads=%d exceeds 65535", g->heads);
   if ((s.M_v + 31) / 32 > 65535) return fail(DFS_ESHAPE, "M_v=%d is too large for the scoring grid", s.M_v);
   char* base = static_cast<char*>(ws);
@@ -557,7 +631,7 @@ int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
   else            { if (bf) POOL(true, 128); else POOL(false, 128); }
 #undef POOL
   const int n_live = int((s.N_v + g->Bs - 1) / g->Bs);
-#define SCORE(DD, RR) launch_score<DD, RR>(g, s, q_hat, k_hat, q_down, k_down, tt, lse, score, n_live, st)
+#define SCORE(DD, RR) launch_score<DD, RR>(g, s, q_hat, k_hat, q_down, k_down, tt, lse, score, sel, n_live, st)
 #define SCORE_R(DD)                                                                 \
   switch (s.r) {                                                                    \
     case 1: SCORE(DD, 1); break;                                                    \
@@ -587,7 +661,7 @@ extern "C" int dfs_block_score(const dfs_geom* g, int dtype, const void* q_perm,
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q_perm, k_perm, score, ws, nullptr, nullptr, nullptr, nullptr, nullptr, 0, as_stream(stream));
+  return run_block_score(g, s, dtype, q_perm, k_perm, score, ws, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, as_stream(stream));
 }
 
 extern "C" int dfs_block_score_src(const dfs_geom* g, int dtype, const void* q, const int32_t* perm_pad, const void* k_perm,
@@ -602,7 +676,7 @@ extern "C" int dfs_block_score_src(const dfs_geom* g, int dtype, const void* q, 
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score_src: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q, k_perm, score, ws, perm_pad, nullptr, nullptr, nullptr, nullptr, 0, as_stream(stream));
+  return run_block_score(g, s, dtype, q, k_perm, score, ws, perm_pad, nullptr, nullptr, nullptr, nullptr, 0, nullptr, as_stream(stream));
 }
 
 extern "C" int dfs_block_score_fused(const dfs_geom* g, int dtype, const void* q, const void* k, const int32_t* perm_pad,
@@ -618,5 +692,5 @@ extern "C" int dfs_block_score_fused(const dfs_geom* g, int dtype, const void* q
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score_fused: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q, k, score, ws, perm_pad, k_perm, nullptr, nullptr, nullptr, 0, as_stream(stream));
+  return run_block_score(g, s, dtype, q, k, score, ws, perm_pad, k_perm, nullptr, nullptr, nullptr, 0, nullptr, as_stream(stream));
 }
