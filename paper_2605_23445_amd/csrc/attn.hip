@@ -4,8 +4,7 @@
 // bf16 kernel (the hot one).  A work-group owns one query block of one head; each of its waves
 // owns 32 query rows.  Key/value blocks named by kv_idx stream through LDS in tiles of 64 rows.
 // Per tile a wave forms S^T = K Q^T on the matrix cores (32x32x16 bf16), so that every lane holds
-// logits of ONE query row: the online-softmax maximum, normaliser and rescale factor are per-lane
-// scalars and need a single exchange between lane l and l^32.  The probabilities, still in
+// logits of ONE query row: the softmax reference and normaliser are per-lane scalars.  The probabilities, still in
 // registers, are already laid out as the B operand of O^T += V^T P^T; the V^T operand comes out of
 // LDS through the transposing LDS read, so V is stored row-major like K and never transposed in
 // memory.
@@ -61,7 +60,7 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
 //
 // KS: where the query blocks are too few to give every SIMD its two waves, KS groups of waves share one query block, each
 // with a KS-th of its tiles, tile buffers of its own and a softmax of its own; they merge through LDS at the end.  A lone
-// wave per SIMD waits for LDS at every matrix instruction (43 % of the matrix cycles); see key_split below for the rule.
+// wave per SIMD reaches three fifths of the matrix rate, two together three quarters; see key_split below for the rule.
 template <int D, int BM, bool XLSE, int KS>
 constexpr int attn_waves() { return D == 64 && BM == 128 && !XLSE && KS == 1 ? 3 : 2; }
 template <int D, int BM, bool XLSE, int KS>
