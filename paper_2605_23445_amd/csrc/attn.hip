@@ -766,6 +766,7 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(const float* __restrict__
     for (int i = 0; i < 16; ++i) oacc[dt][i] *= share;
 #pragma unroll
   for (int half = NW / 2; half >= 1; half /= 2) {
+    if (runs <= half) continue;                      // the upper waves had no run: nothing to add
     if (wave >= half && wave < 2 * half) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
