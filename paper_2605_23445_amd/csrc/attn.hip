@@ -8,6 +8,7 @@
 // registers, are already laid out as the B operand of O^T += V^T P^T; the V^T operand comes out of
 // LDS through the transposing LDS read, so V is stored row-major like K and never transposed in
 // memory.
+#include <float.h>
 #include <math.h>
 #include <type_traits>
 
@@ -79,8 +80,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   constexpr int STEPS = BM / KN;                   // tiles per key block
   constexpr int NF = D / 8;                        // operand fragments per stage: D/16 of V^T, D/16 of K
   constexpr int ESL = NF - 1;                      // matrix instructions the sixteen exponentials of a half tile are spread over
-  constexpr float HEADROOM = 16.f;                 // exponents of two: see "No maximum is taken" below
-  constexpr float SUM_HIGH = 65536.f, SUM_LIMIT = 281474976710656.f;      // 2^16, 2^48
+  constexpr float HEADROOM = 4.f, SUM_LIMIT = 2.25f;                      // see "A row's reference" below
   // Two K and two V tile buffers per group (tile t lives in the pair of parity t & 1), at fixed byte offsets.
   __shared__ __attribute__((aligned(16))) uint16_t tiles[KS * 4 * TILE];
   constexpr int K0 = 0, K1 = 2 * TILE, V0 = 4 * TILE, V1 = 6 * TILE;
@@ -161,13 +161,13 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
-  float m_run = 0.f, x_run = 0.f;                  // reference in the base-2 exponent's units (logit x c2); unrounded normaliser (XLSE only)
+  // reference in the base-2 exponent's units (logit x c2), row sum, row sum of the unrounded probabilities (XLSE only)
+  float m_run = 0.f, l_run = 0.f, x_run = 0.f;
   // Row sums of the probabilities as rounded to bf16 (numerator and denominator then use exactly the same weights, so
   // a dominant key leaves no systematic rounding bias), on the matrix cores: a 16x16x32 product takes the same B operand
   // registers as the 32x32x16 one, but reads lanes 16 g + n as keys 8 g .. 8 g + 7 of column n.  With ones where the
   // parity of the key group equals that of the result row's group, every lane's result is the sum over both lane
   // halves of its own query row.
-  f32x4 lsum = {0.f, 0.f, 0.f, 0.f};
   const uint32_t one_pair = (((lane >> 4) ^ (lane >> 2)) & 1) == 0 ? 0x3F803F80u : 0u;
   const bf16x8 row_ones = __builtin_bit_cast(bf16x8, u32x4{one_pair, one_pair, one_pair, one_pair});
   const float c2 = scale * 1.4426950408889634f;     // softmax in base 2
@@ -249,8 +249,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     asm volatile("" : "+v"(v_addr[dt]));
   }
 
-  // The loop works on half tiles (32 key rows).  Logits of a half tile for query tile a:
-  // sx[a][i] = logit(key row 32 half + 8 (i/4) + 4 h + i%4, query row 32 a + n).
+  // The loop works on half tiles (32 key rows).  Logits of a half tile:
+  // sx[i] = logit(key row 32 half + 8 (i/4) + 4 h + i%4, query row n of the wave).
   auto k_frag = [&](int kbuf, int half, int kk) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<LDS_PTR(const u32x4)>(k_addr[kk] + uint32_t(kbuf + half * 64 * D)));
   };
@@ -291,21 +291,22 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   };
 
   // One pipeline stage, written out in issue order.  Fragments alternate between K of the next half tile (logit chain
-  // into `sn`) and V^T of the previous half tile (products O^T += V^T P^T with its probabilities `pp`, and their row
-  // sums).  In the shadow of the matrix instructions the vector units turn the logits `sx` of the current half tile
-  // into probabilities `pc`.  Scheduling fences and empty asm statements keep the compiler from separating the matrix
+  // into `sn`) and V^T of the previous half tile (products O^T += V^T P^T with its probabilities `pp`).  In the shadow of the matrix instructions the vector units turn the logits `sx` of the current half tile
+  // into probabilities `pc` and sum them.  Scheduling fences and empty asm statements keep the compiler from separating the matrix
   // and vector work again.
   //
-  // No maximum is taken on the way.  The final ratio does not depend on a row's reference m_run, and floating-point
-  // weights lose nothing by being small or large, so the reference is the maximum of the row's first half tile times
-  // 2^HEADROOM and stays until the row sum says that it is outgrown: every two tiles `rebase` looks whether a sum has
-  // reached SUM_HIGH (2^32 times what the first half tile's maximum alone gives) and if so, rarely, divides
-  // everything by a power of two.  A sum at SUM_LIMIT or beyond is left alone, can only grow, and makes the work-group
-  // do its work again from the true maximum at the end.  A half tile is then forty vector instructions (sixteen
-  // fused multiply-adds and exponentials, eight packs) instead of sixty-seven with its maximum, the factor
-  // 2^(m_old - m_new) and a row sum on the vector unit.  Measured with the row sums on the matrix cores: d = 64,
-  // 17 550 tokens x 48 heads, 743 -> 675 us; d = 128, 75 600 tokens x 40 heads, 60 of 591 blocks, 11.9 -> 11.3 ms
-  // (the matrix cores are busy 63.5 instead of 60 % of the cycles, and the clock falls from 1.66 to 1.60 GHz).
+  // A row's reference m_run is a maximum of its logits times 2^HEADROOM: to start with that of its first half tile and of
+  // its own 32 keys, where many rows have their largest logit; later that of a half tile whose weights sum to more than
+  // SUM_LIMIT.  32 weights of 2^-HEADROOM sum to 2, so a row moves when one weight has grown by 2^5.2 or many have by less,
+  // and raises its reference by at least an eighth.  The sums come from the matrix cores, so that watching them costs two
+  // vector instructions per half tile, an addition and a comparison (a running maximum and its factor: some fifteen), and
+  // `settle` does the half tile again when a row moves: about 1 % of the half tiles of a wave at 75 600 tokens, 2 % at
+  // 17 550, 5 % in rows of 13 blocks of 64.
+  // Weights are then below SUM_LIMIT whatever comes, and exact in bf16 where they are largest, which is what the reference
+  // is followed for: with that of the first half tile kept, the outputs' error against 64 bits was 1.86e-3 of the result
+  // instead of 1.77e-3 (75 600 tokens, 60 of 591 blocks), 2.29e-3 instead of 2.17e-3 (17 550 tokens, dense, d = 64,
+  // logits of standard deviation 2).  What it costs against keeping it, on one box: d = 64, 17 550 tokens x 48 heads 659 ->
+  // 680 us; d = 128, 75 600 tokens, 40 heads, 60 of 591 blocks 11.43 -> 11.61 ms, 8 heads dense 19.30 -> 19.47.
   auto half_max = [&](const f32x16& x) __attribute__((always_inline)) {      // row maximum of a half tile, in both lane halves
     float mx = x[0];
 #pragma unroll
@@ -317,32 +318,47 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const bf16x2 pk = {(__bf16)a, (__bf16)b};
     return __builtin_bit_cast(uint32_t, pk);
   };
-  auto rebase = [&](u32x4 (&pc)[2]) __attribute__((always_inline)) {         // pc: probabilities not yet summed
-    const bool high = lsum[0] >= SUM_HIGH && lsum[0] < SUM_LIMIT;           // the same in both lane halves of a row
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(high) != 0, 0)) {
-      const float shift = high ? HEADROOM + float(int(__float_as_uint(lsum[0]) >> 23) - 127) : 0.f;
-      const float alpha = __builtin_amdgcn_exp2f(-shift);                    // a power of two
-      m_run += shift;
-      x_run *= alpha;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) lsum[i] *= alpha;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const uint32_t u = pc[i / 4][i % 4];
-        pc[i / 4][i % 4] = pack(__uint_as_float(u << 16) * alpha, __uint_as_float(u & 0xFFFF0000u) * alpha);
-      }
+  auto half_sum = [&](const u32x4& p, f32x4 sum) __attribute__((always_inline)) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, __builtin_bit_cast(bf16x8, p), sum, 0, 0, 0);
+  };
+  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  // Adds a half tile's sums (`sum` of the rounded weights pc, xsum of the unrounded) to the row's.  If a row of the wave has
+  // outgrown its reference, the rows that have grown at all move first (logits sx).
+  auto settle = [&](const f32x16& sx, u32x4 (&pc)[2], f32x4 sum, float xsum) __attribute__((always_inline)) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(sum[0] <= SUM_LIMIT)) != 0, 0)) {
+      const float mx = fmaf(half_max(sx), c2, HEADROOM);
+      const float m_new = mx > m_run ? mx : m_run;   // not fmaxf: a NaN leaves the reference where it is
+      float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      // The accumulators are scaled in place, so that they keep one home across the branch.  The compiler does not see what
+      // these statements read, so the waits for the matrix instructions in flight (at most 19 states) and for the
+      // exponential (one) are written out, in a statement that they depend on.
+      asm volatile("s_nop 15\n\ts_nop 3" : "+v"(alpha));
+      m_run = m_new;
+      l_run *= alpha;
+      if (XLSE) x_run *= alpha;
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          float y = oacc[dt][i];                      // in place: the accumulators keep one home across the branch
+          float y = oacc[dt][i];
           asm volatile("v_mul_f32 %0, %1, %0" : "+v"(y) : "v"(alpha));
           oacc[dt][i] = y;
         }
+      xsum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        const float a = __builtin_amdgcn_exp2f(fmaf(sx[i], c2, -m_run)), b = __builtin_amdgcn_exp2f(fmaf(sx[i + 1], c2, -m_run));
+        pc[i / 8][(i % 8) / 2] = pack(a, b);
+        if (XLSE) xsum += a + b;
+      }
+      sum = half_sum(pc[1], half_sum(pc[0], zero4));
+      asm volatile("" : "+v"(sum));                   // one home as well
     }
+    l_run += sum[0];
+    if (XLSE) x_run += xsum;
   };
   auto stage = [&](auto do_pv, auto do_s, int vbuf, int pv_half, const u32x4 (&pp)[2], int kbuf,
-                   int s_half, f32x16& sn, const f32x16& sx, u32x4 (&pc)[2], auto mem) __attribute__((always_inline)) {
+                   int s_half, f32x16& sn, const f32x16& sx, u32x4 (&pc)[2], f32x4& sum, float& xsum, auto mem) __attribute__((always_inline)) {
     constexpr bool DO_PV = decltype(do_pv)::value, DO_S = decltype(do_s)::value;
     bf16x8 frag[NF];
     auto load = [&](int f) {
@@ -352,7 +368,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         frag[f] = k_frag(kbuf, s_half, f / 2);
       }
     };
-    float pe[16], xsum = 0.f;
+    float pe[16];
+    xsum = 0.f;
     if (DO_S) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) sn[i] = 0.f;
@@ -369,7 +386,6 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         if (DO_PV) {
           const int j = f / 2, s2 = j / (D / 32), dt = j % (D / 32);
           oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[f], __builtin_bit_cast(bf16x8, pp[s2]), oacc[dt], 0, 0, 0);
-          if (dt == D / 64) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, __builtin_bit_cast(bf16x8, pp[s2]), lsum, 0, 0, 0);
         }
       } else if (DO_S) {
         sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[f], qf[f / 2], sn, 0, 0, 0);
@@ -393,9 +409,10 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 #pragma unroll
         for (int i = (ESL - 1) * 16 / ESL; i < 16; ++i) asm volatile("" : "+v"(pc[i / 8][(i % 8) / 2]));
       }
+      if (f == NF - 2) sum = half_sum(pc[0], zero4);
+      if (f == NF - 1) sum = half_sum(pc[1], sum);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (XLSE) x_run += xsum;
   };
   using yes = std::true_type;
   using no = std::false_type;
@@ -413,22 +430,26 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     constexpr int v_cur = ODD ? V1 : V0;             // V(t)
     constexpr int v_nxt = ODD ? V0 : V1;             // V(t-1); V(t+1) goes here
     // first half: products of (t-1, 1), logits of (t, 1), probabilities of (t, 0)
-    stage(std::integral_constant<bool, !FIRST>{}, yes{}, v_nxt, 1, p1, k_cur, 1, s1, s0, p0, [](int) {});
+    f32x4 sum;
+    float xsum;
+    stage(std::integral_constant<bool, !FIRST>{}, yes{}, v_nxt, 1, p1, k_cur, 1, s1, s0, p0, sum, xsum, [](int) {});
     mask_pads(b_cur, t, 1, s1);
     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wave's parts of K(t+1) and V(t) landed
     __syncthreads();                                 // all parts landed; every wave is past the first half of tile t
+    settle(s0, p0, sum, xsum);
     // Second half: products of (t, 0), logits of (t+1, 0), probabilities of (t, 1); between its matrix instructions the
     // loads of K(t+2) and V(t+1) (in one run behind the barrier they kept the matrix cores waiting for some fifty
     // instructions: +2.0 % on lists that hit in L2, +2.5 % on scattered ones, +4.7 % dense at d = 128).  Behind the
     // last tile K(t+2) is that tile once more, into a buffer that nothing reads.
     const int b_new = tile_block(t + 2 < n_tiles ? t + 2 : n_tiles - 1);
     const uint64_t k_src = tile_src(kh, t + 2, b_new), v_src = tile_src(vh, t + 1, b_nxt);
-    stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1, [&](int f) {
+    stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1, sum, xsum, [&](int f) {
       if (LAST) return;
 #pragma unroll
       for (int j = f * 2 * LPW / NF; j < (f + 1) * 2 * LPW / NF; ++j)
         issue_one(j < LPW ? v_src : k_src, j < LPW ? v_nxt : k_cur, j < LPW, j % LPW);
     });
+    settle(s1, p1, sum, xsum);
     if (!LAST) mask_pads(b_nxt, t + 1, 0, s0);
     b_cur = b_nxt;
     b_nxt = b_new;
@@ -438,7 +459,6 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     for (int j = 0; j < 2 * (D / 32); ++j) {
       const bf16x8 pj = __builtin_bit_cast(bf16x8, pp[j / (D / 32)]);
       oacc[j % (D / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(vbuf, half, j), pj, oacc[j % (D / 32)], 0, 0, 0);
-      if (j % (D / 32) == 0) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, pj, lsum, 0, 0, 0);
     }
   };
   if (n_tiles > 0) {
@@ -446,12 +466,37 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     b_nxt = n_tiles > 1 ? tile_block(1) : b_cur;
     issue(kh, K0, false, 0, b_cur);
     issue(vh, V0, true, 0, b_cur);
+    // The keys of this wave's own rows, for the reference to start from if their block is among this group's
+    const int own_first = t_first / STEPS, own_end = own_first + n_tiles / STEPS < cnt ? own_first + n_tiles / STEPS : cnt;
+    bool own = dense && u - blk_first >= own_first && u - blk_first < own_end;
+    if (!dense) {
+      for (int i = own_first + lane; i < own_end; i += 64) own |= idx[i] == u;
+      own = __builtin_amdgcn_ballot_w64(own) != 0;
+    }
+    bf16x8 own_k[D / 16];
+    {
+      const u32x4* kp = reinterpret_cast<const u32x4*>(kh + q_row0 * D);
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk) own_k[kk] = __builtin_bit_cast(bf16x8, kp[2 * kk + h]);
+    }
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
     if (n_tiles > 1) issue(kh, K1, false, 1, b_nxt);
     logits(K0, 0, s0);
     mask_pads(b_cur, 0, 0, s0);
-    if (KS == 1 || t_first < all_tiles) m_run = fmaf(half_max(s0), c2, HEADROOM);      // finite: the first row of a block is never a pad
+    m_run = half_max(s0);
+    if (own) {                                       // as logits and mask_pads, with the keys from registers
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s1[i] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk) s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(own_k[kk], qf[kk], s1, 0, 0, 0);
+      const int real = block_real_rows(u, BM, M_v, N_v, n_text) - wave * 32;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (8 * (i / 4) + 4 * h + (i % 4) >= real) s1[i] = -INFINITY;
+      m_run = fmaxf(m_run, half_max(s1));
+    }
+    m_run = fmaxf(fmaf(m_run, c2, HEADROOM), -FLT_MAX);              // finite: logits of -inf have weight 0, not NaN
     if (n_tiles == 1) {
       tile_step(no{}, yes{}, yes{}, 0);
     } else {
@@ -460,50 +505,12 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       for (; t + 2 < n_tiles; t += 2) {              // middle tiles in pairs: buffer parities are compile-time
         tile_step(yes{}, no{}, no{}, t);
         tile_step(no{}, no{}, no{}, t + 1);
-        rebase(p1);
       }
       if (t + 1 < n_tiles) { tile_step(yes{}, no{}, no{}, t); ++t; }
       if (t & 1) tile_step(yes{}, no{}, yes{}, t);
       else tile_step(no{}, no{}, yes{}, t);
     }
     products((n_tiles - 1) & 1 ? V1 : V0, 1, p1);  // drain: the last half tile
-    if (__builtin_expect(__syncthreads_or(!(lsum[0] < SUM_LIMIT)), 0)) {
-      // Once more in plain order, with the reference at the row's true maximum: first that maximum, then the sums.
-      x_run = 0.f;
-      lsum = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
-      float mx = -INFINITY;
-#pragma unroll 1
-      for (int step = 0; step < 2 * n_tiles; ++step) {
-        const bool sums = step >= n_tiles;
-        const int t = sums ? step - n_tiles : step, blk = tile_block(t);
-        issue(kh, K0, false, t, blk);
-        issue(vh, V0, true, t, blk);
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        __syncthreads();
-#pragma unroll 1
-        for (int half = 0; half < 2; ++half) {
-          logits(K0, half, s0);
-          mask_pads(blk, t, half, s0);
-          if (!sums) {
-            mx = fmaxf(mx, half_max(s0));
-            if (KS == 1 || t_first < all_tiles) m_run = fmaf(mx, c2, HEADROOM);
-          } else {
-#pragma unroll
-            for (int i = 0; i < 16; i += 2) {
-              const float a = __builtin_amdgcn_exp2f(fmaf(s0[i], c2, -m_run)), b = __builtin_amdgcn_exp2f(fmaf(s0[i + 1], c2, -m_run));
-              p0[i / 8][(i % 8) / 2] = pack(a, b);
-              x_run += a + b;
-            }
-            products(V0, half, p0);
-          }
-        }
-        __syncthreads();
-      }
-    }
   }
 
   if constexpr (KS > 1) {
@@ -526,7 +533,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 #pragma unroll
           for (int i = 0; i < 16; ++i) part[(dt * 16 + i) * 64] = oacc[dt][i];
         s_part[grp][wave][0][lane] = m_run;
-        s_part[grp][wave][1][lane] = lsum[0];
+        s_part[grp][wave][1][lane] = l_run;
         s_part[grp][wave][2][lane] = x_run;
       }
       __syncthreads();
@@ -536,7 +543,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       for (int g = 1; g < KS; ++g) m_all = fmaxf(m_all, s_part[g][wave][0][lane]);
       const float own = __builtin_amdgcn_exp2f(m_run - m_all);
       m_run = m_all;
-      lsum[0] *= own;
+      l_run *= own;
       x_run *= own;
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
@@ -546,7 +553,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       for (int g = 1; g < KS; ++g) {
         const float share = __builtin_amdgcn_exp2f(s_part[g][wave][0][lane] - m_all);
         const float* part = acc_buf(g);
-        lsum[0] = fmaf(share, s_part[g][wave][1][lane], lsum[0]);
+        l_run = fmaf(share, s_part[g][wave][1][lane], l_run);
         x_run = fmaf(share, s_part[g][wave][2][lane], x_run);
 #pragma unroll
         for (int dt = 0; dt < D / 32; ++dt)
@@ -571,7 +578,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 #pragma unroll
         for (int i = 0; i < 16; ++i) put(mine + (dt * 16 + i) * 64, oacc[dt][i]);
       put(mine + (REGS - 2) * 64, n_tiles == 0 ? -INFINITY : m_run);
-      put(mine + (REGS - 1) * 64, lsum[0]);
+      put(mine + (REGS - 1) * 64, l_run);
       __shared__ int s_ticket;
       __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wave's sums have reached memory
       __syncthreads();                               // and every wave's, before the ticket is taken
@@ -581,7 +588,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       float m_all = -INFINITY;
       for (int sp = 0; sp < text_splits; ++sp) m_all = fmaxf(m_all, get(rows + (int64_t(sp) * NW * REGS + REGS - 2) * 64));
       const float ref = m_all == -INFINITY ? 0.f : m_all;
-      lsum[0] = 0.f;
+      l_run = 0.f;
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
@@ -589,7 +596,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       for (int sp = 0; sp < text_splits; ++sp) {
         const float* p = rows + int64_t(sp) * NW * REGS * 64;
         const float share = __builtin_amdgcn_exp2f(get(p + (REGS - 2) * 64) - ref);
-        lsum[0] = fmaf(share, get(p + (REGS - 1) * 64), lsum[0]);
+        l_run = fmaf(share, get(p + (REGS - 1) * 64), l_run);
 #pragma unroll
         for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
@@ -604,7 +611,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     atomicAdd(&clock_probe[2], 1ull);
   }
   // epilogue: normalise, round to bf16, store.  Lane (n, h) holds O[row][32 dt + 8 j + 4 h + 0..3].
-  const float inv = lsum[0] > 0.f ? 1.0f / lsum[0] : 0.f;
+  const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
   if (io_row >= 0) {
     uint16_t* orow = o + io_off + io_row * D;
 #pragma unroll
