@@ -179,13 +179,11 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   constexpr int PV = swz_period(RJ / (16 / CH) > 0 ? RJ / (16 / CH) : 1, CH / 4);
   static_assert(RJ % (16 / CH) == 0 && LPW % PK == 0 && LPW % PV == 0, "tile load pattern");
   // This group's tiles are t_first .. t_first + n_tiles - 1 of the list's, whole key blocks (whose first row is real: the
-  // softmax starts from it) and as many for every group, because the groups share their barriers: what lies behind the
-  // last tile of all is that tile again with every key masked.
-  const int all_tiles = cnt * STEPS;
-  const int n_tiles = (cnt + KS - 1) / KS * STEPS, t_first = grp * n_tiles;
+  // softmax starts from it).  `rounds`: as many as any group has.
+  const int rounds = (cnt + KS - 1) / KS * STEPS, t_first = grp * rounds;
+  const int own_tiles = cnt * STEPS - t_first, n_tiles = KS == 1 || own_tiles > rounds ? rounds : own_tiles < 0 ? 0 : own_tiles;
   auto tile_block = [&](int tile) {
     tile += t_first;
-    if (KS > 1 && tile >= all_tiles) tile = all_tiles - 1;
     int blk = dense ? blk_first + tile / STEPS : idx[tile / STEPS];
     return unsigned(blk) < unsigned(M) ? blk : 0;     // a corrupt list must not read out of bounds
   };
@@ -279,10 +277,9 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   const int real_x_last = M > M_v ? block_real_rows(M - 1, BM, M_v, N_v, n_text) : BM;
   const int ragged_v = real_v_last < BM ? M_v - 1 : -1, ragged_x = real_x_last < BM ? M - 1 : -1;
   auto mask_pads = [&](int blk, int tile, int half, f32x16& sx) {
-    const bool behind = KS > 1 && t_first + tile >= all_tiles;
-    if (__builtin_expect(blk == ragged_v || blk == ragged_x || behind, 0)) {
+    if (__builtin_expect(blk == ragged_v || blk == ragged_x, 0)) {
       asm volatile("");                               // keeps this a branch: turned into selects it would run on every half tile
-      const int real = behind ? 0 : blk == ragged_v ? real_v_last : real_x_last;
+      const int real = blk == ragged_v ? real_v_last : real_x_last;
       const int base = (tile % STEPS) * KN + 32 * half;
 #pragma unroll
       for (int i = 0; i < 16; ++i)
@@ -467,7 +464,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     issue(kh, K0, false, 0, b_cur);
     issue(vh, V0, true, 0, b_cur);
     // The keys of this wave's own rows, for the reference to start from if their block is among this group's
-    const int own_first = t_first / STEPS, own_end = own_first + n_tiles / STEPS < cnt ? own_first + n_tiles / STEPS : cnt;
+    const int own_first = t_first / STEPS, own_end = own_first + n_tiles / STEPS;
     bool own = dense && u - blk_first >= own_first && u - blk_first < own_end;
     if (!dense) {
       for (int i = own_first + lane; i < own_end; i += 64) own |= idx[i] == u;
@@ -512,6 +509,11 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
     products((n_tiles - 1) & 1 ? V1 : V0, 1, p1);  // drain: the last half tile
   }
+  // The groups share their barriers, one in front of the first tile and one per tile: a group with fewer tiles meets the
+  // others at those it has not come to.  (It walked its last tile again with weights of zero instead, which turned
+  // infinite values there into NaN.)
+  if (KS > 1)
+    for (int t = n_tiles > 0 ? n_tiles : -1; t < rounds; ++t) __syncthreads();
 
   if constexpr (KS > 1) {
     // Merge.  A group's accumulators go where its tiles were (one buffer holds one wave's), its reference and sums beside
@@ -521,10 +523,10 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       return reinterpret_cast<float*>(tiles + (g * 4 + wave) * TILE) + lane;
     };
     static_assert(TILE * 2 == (D / 32) * 16 * 64 * 4, "one tile buffer holds the accumulators of one wave");
-    if (n_tiles == 0) {
+    if (rounds == 0) {
       if (grp > 0) return;
     } else {
-      if (t_first >= all_tiles) m_run = -INFINITY;
+      if (n_tiles == 0) m_run = -INFINITY;
       __syncthreads();                               // every wave is done with the tiles
       if (grp > 0) {
         float* part = acc_buf(grp);

@@ -92,3 +92,19 @@ def test_text_rows_over_several_work_groups(d, B, H, W, n_text, heads, sparsity)
     video = G.gpu_unperm(g, P.DFS_BF16, staged, inv)[:, :s.N_v].float()
     diff = (outs[0][:, :s.N_v].float() - video).abs()
     assert diff.max() <= TOL_MAX and diff.mean() <= TOL_MEAN
+
+
+@pytest.mark.parametrize("d,B", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("n_blocks", [1, 3, 5])
+def test_infinite_values_stay_infinite(d, B, n_blocks):
+    """Odd block counts over two wave groups, an infinite value in the last block: a group with less to do adds nothing
+    of it a second time (an infinity times a weight of zero is NaN)."""
+    g = P.Geom(1, 1 if n_blocks * B <= 512 else n_blocks, n_blocks * B if n_blocks * B <= 512 else B, 0, 1, d, B, B // 4)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_blocks)
+    q, k, v = (torch.randn(1, n_blocks * B, d, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    v[0, -3, 5] = float("inf")
+    st = G.upload_mask(np.ones((1, n_blocks, n_blocks), dtype=np.uint8), 17)
+    for want_lse in (False, True):
+        o = G.gpu_attn(g, P.DFS_BF16, q, k, v, st, want_lse=want_lse)[0]
+        assert bool((o[0, :, 5] == float("inf")).all()) and bool(o[0, :, :5].isfinite().all()) and bool(o[0, :, 6:].isfinite().all())
