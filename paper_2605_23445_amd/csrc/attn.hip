@@ -673,7 +673,17 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(const float* __restrict__
 #pragma unroll
   for (int c = 0; c < D / 8; ++c)                    // a pad row reads row 0; it is not written
     qf[c] = *reinterpret_cast<const f32x4*>(q + io_off + (io_row < 0 ? 0 : io_row) * D + 8 * c + 4 * h);
-  const float c2 = scale * 1.4426950408889634f;      // softmax in base 2
+  // Softmax in base 2.  The factor is positive, so that masked logits (-inf) stay what they are and a row's maximum is the
+  // largest exponent; the sign of a scale that is not goes to Q (0 as well: every logit is 0 then).
+  float c2 = scale * 1.4426950408889634f;
+  if (!(scale > 0.f)) {
+    const float sign = scale < 0.f ? -1.f : scale;
+    c2 = scale < 0.f ? -c2 : 1.f;
+#pragma unroll
+    for (int c = 0; c < D / 8; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) qf[c][e] *= sign;
+  }
   f32x16 oacc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)

@@ -45,3 +45,21 @@ def test_f32_attention_edges(d, B, n_video, n_text):
             want, want_lse = O.sparse_attn_block(*(x[h] for x in clean), np.nonzero(mask[h, u])[0], valid, B, u, 1.0 / np.sqrt(d))
             assert np.abs(o[h, rows] - want[:valid[u]]).max() <= 1e-4
             assert np.abs(lse[h, rows] - want_lse[:valid[u]]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale", [0.0, -0.125, 0.125])
+def test_f32_forward_takes_any_scale(d, scale):
+    """dfs_forward takes scales that are not positive; ragged and text blocks, whose pads are masked, among the kept."""
+    g = P.Geom(1, 3, 67, 40, 2, d, 64, 16)
+    s = P.dfs_geom_sizes(g)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    q, k, v = (torch.randn(2, s.N, d, generator=gen, device="cuda") for _ in range(3))
+    perm_pad, inv, _ = G.gpu_perm(g)
+    st = G.upload_mask(np.ones((2, s.M, s.M), dtype=np.uint8))
+    o = torch.full_like(q, float("nan"))
+    P.dfs_forward(g, P.DFS_F32, q, k, v, perm_pad, inv, False, P.DFS_SELECT_TOPK, 0.5, 0.0, st, scale, o,
+                  G.ws_tensor(P.dfs_workspace_bytes(g, P.DFS_WS_FORWARD)))
+    want = torch.softmax(q.double() @ k.double().transpose(1, 2) * scale, -1) @ v.double()
+    assert (o - want).abs().max() <= 1e-4
