@@ -126,6 +126,13 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
   // diagnostic: shader-clock cycles and constant-rate (100 MHz) ticks this work-group lives for
   const unsigned long long probe_c0 = clock_probe ? clock64() : 0, probe_w0 = clock_probe ? wall_clock64() : 0;
+  auto probe_end = [&]() {
+    if (clock_probe && threadIdx.x == 0) {
+      atomicAdd(&clock_probe[0], clock64() - probe_c0);
+      atomicAdd(&clock_probe[1], wall_clock64() - probe_w0);
+      atomicAdd(&clock_probe[2], 1ull);
+    }
+  };
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / (64 * NW)), wave = (tid >> 6) - grp * NW;
@@ -586,7 +593,10 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       __syncthreads();                               // and every wave's, before the ticket is taken
       if (tid == 0) s_ticket = __hip_atomic_fetch_add(&tickets[row], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __syncthreads();
-      if (s_ticket != text_splits - 1) return;
+      if (s_ticket != text_splits - 1) {
+        probe_end();
+        return;
+      }
       float m_all = -INFINITY;
       for (int sp = 0; sp < text_splits; ++sp) m_all = fmaxf(m_all, get(rows + (int64_t(sp) * NW * REGS + REGS - 2) * 64));
       const float ref = m_all == -INFINITY ? 0.f : m_all;
@@ -607,11 +617,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
   }
 
-  if (clock_probe && tid == 0) {
-    atomicAdd(&clock_probe[0], clock64() - probe_c0);
-    atomicAdd(&clock_probe[1], wall_clock64() - probe_w0);
-    atomicAdd(&clock_probe[2], 1ull);
-  }
+  probe_end();
   // epilogue: normalise, round to bf16, store.  Lane (n, h) holds O[row][32 dt + 8 j + 4 h + 0..3].
   const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
   if (io_row >= 0) {

@@ -108,3 +108,24 @@ def test_infinite_values_stay_infinite(d, B, n_blocks):
     for want_lse in (False, True):
         o = G.gpu_attn(g, P.DFS_BF16, q, k, v, st, want_lse=want_lse)[0]
         assert bool((o[0, :, 5] == float("inf")).all()) and bool(o[0, :, :5].isfinite().all()) and bool(o[0, :, 6:].isfinite().all())
+
+
+def test_clock_probe_counts_every_work_group_of_a_split_row():
+    """64 video and 2 text blocks x 2 heads: each video block once, each text block as often as it has work-groups."""
+    g = P.Geom(1, 64, 64, 100, 2, 64, 64, 16)
+    s = P.dfs_geom_sizes(g)
+    q, k, v = (torch.randn(2, s.N, 64, device="cuda").bfloat16() for _ in range(3))
+    perm_pad, inv, _ = G.gpu_perm(g)
+    K_max = P.dfs_keep_count(0.8, s.M_v) + s.M_x
+    i32 = dict(dtype=torch.int32, device="cuda")
+    st = P.MaskState(torch.zeros((2, s.M, K_max), **i32), torch.zeros((2, s.M), **i32), None, None, K_max)
+    probe = torch.zeros(3, dtype=torch.int64, device="cuda")
+    ws = G.ws_tensor(P.dfs_workspace_bytes(g, P.DFS_WS_FORWARD_BF16))
+    P.dfs_attn_clock_probe(probe)
+    try:
+        P.dfs_forward(g, P.DFS_BF16, q, k, v, perm_pad, inv, True, P.DFS_SELECT_TOPK, 0.8, 0.0, st, 0.125, torch.empty_like(q), ws)
+        torch.cuda.synchronize()
+    finally:
+        P.dfs_attn_clock_probe(None)
+    splits, rest = divmod(int(probe[2]) - 2 * s.M_v, 2 * s.M_x)
+    assert splits > 1 and rest == 0, probe.tolist()
