@@ -295,8 +295,9 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   };
 
   // One pipeline stage, written out in issue order.  Fragments alternate between K of the next half tile (logit chain
-  // into `sn`) and V^T of the previous half tile (products O^T += V^T P^T with its probabilities `pp`).  In the shadow of the matrix instructions the vector units turn the logits `sx` of the current half tile
-  // into probabilities `pc` and sum them.  Scheduling fences and empty asm statements keep the compiler from separating the matrix
+  // into `sn`) and V^T of the previous half tile (products O^T += V^T P^T with its probabilities `pp`).  In the shadow
+  // of the matrix instructions the vector units turn the logits `sx` of the current half tile into probabilities `pc`,
+  // which are summed at the end.  Scheduling fences and empty asm statements keep the compiler from separating the matrix
   // and vector work again.
   //
   // A row's reference m_run is a maximum of its logits times 2^HEADROOM: to start with that of its first half tile and of
@@ -574,8 +575,10 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
   if constexpr (!XLSE) {
     if (shared_row) {
-      // Stores and loads at the chip's scope go past the L2, which belongs to one XCD: a fence instead would write
-      // the whole L2 back.
+      // Stores and loads at the chip's scope go past the L2, which belongs to one XCD: a release and an acquire around
+      // the ticket instead would write the whole L2 back and drop it (2 565 + 77 tokens x 12 heads 43 -> 55 us).  The order
+      // that they would give is here: no store is in flight when its wave arrives at the barrier in front of the ticket,
+      // and no load is issued before the ticket has come back.
       auto put = [](float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
       auto get = [](const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
       constexpr int REGS = D / 2 + 2;                // of a lane: accumulators, reference, row sum
@@ -828,10 +831,12 @@ static unsigned long long* g_clock_probe = nullptr;   // set by dfs_attn_clock_p
 
 // Groups of waves that share a query block (kernel's KS): two where the work-groups leave SIMDs with less than one wave
 // each.  A second wave per SIMD raises the matrix rate by a fifth, the merge costs some 4 us, so short lists of the one
-// shape whose lone waves do well (d = 128, 128 rows) stay whole.  Measured (us, one group -> two), 128 rows: d = 128, 44
-// blocks x 1 head 26.1 -> 29.1 with 9 kept, 78 -> 71 with all kept, 176 work-groups 100 -> 85, 264 136 -> 162; d = 64,
-// 88 work-groups 22.8 -> 21.0, 264 31.6 -> 38.4.  64 rows (two waves per group): d = 64, 164 work-groups 18.6 -> 16.6,
-// 492 25.0 -> 22.5, 656 26.8 -> 29.9; d = 128, 246 25.5 -> 24.6, 328 28.4 -> 35.5.
+// shape whose lone waves do well (d = 128, 128 rows) stay whole.  Measured (us a reuse step, one group -> two), 128 rows:
+// d = 128, 44 blocks x 1 head 28.0 -> 29.2 with 9 kept, 83.6 -> 73.0 with all kept, 176 work-groups 92.8 -> 83.0, 264
+// 140 -> 165; d = 64, 88 work-groups 22.5 -> 21.9, 264 31.5 -> 39.5.  64 rows (two waves per group): d = 64, 164
+// work-groups 18.3 -> 16.9, 492 25.1 -> 23.3, 656 26.9 -> 30.7; d = 128, 246 29.4 -> 28.6, 328 31.0 -> 43.1.
+// The host knows a list's room, K_max, not its length, and the two differ: a dense call whose lists have room for 9 blocks
+// stays on one group (83.7 and 92.9 us above instead of 73.0 and 83.0), a list of 9 with room for all 44 takes two.
 static int key_split(int d, int B, int64_t work_groups, int K_max) {
   if (B == 64 && d == 64) return work_groups <= 512 ? 2 : 1;
   if (B == 128 && d == 128 && K_max <= 16) return 1;
@@ -841,9 +846,10 @@ static int key_split(int d, int B, int64_t work_groups, int K_max) {
 // Work-groups per text block, and the key blocks each takes: about as many as a video row keeps (an eighth of all where
 // K_max does not tell), at least eight.  One where the video rows' work, in rounds of the chip's work-group slots, hides
 // the text rows, which start first.  Measured (us a reuse step, whole -> split), 17 550 video + 77 text tokens, 21 of 138
-// blocks kept: d = 64 x 2 heads 185 -> 57, x 12 322 -> 199, x 40 660 -> 652; d = 128 x 2 251 -> 88, x 12 502 -> 348, x 40
-// 1 157 -> 1 166 (work of 1.7 text rows: whole); 75 600 + 256 tokens x 8 heads 2 359 -> 2 385 (work of 0.96: whole).
-// Below 16 blocks there is nothing to win.
+// blocks kept: d = 64 x 2 heads 194 -> 58, x 12 331 -> 199, x 40 679 -> 618; d = 128 x 2 264 -> 88, x 12 519 -> 348, x 40
+// 1 187 -> 1 142 (work of 1.7 text rows: whole by the rule, which is drawn for lists of the room they are given);
+// 75 600 + 256 tokens x 8 heads 2 435 -> 2 436 (work of 0.96: whole).  A dense call with room for 22 blocks is taken for a
+// short one and split: 1 209 -> 1 213 (d = 128, 8 heads).  Below 16 blocks there is nothing to win.
 struct TextSplit { int splits, blocks; };
 static TextSplit text_split(const dfs_geom* g, const dfs_sizes& s, int K_max, size_t scratch_bytes) {
   const TextSplit whole = {1, s.M};
