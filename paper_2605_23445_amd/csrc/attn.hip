@@ -341,6 +341,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       m_run = m_new;
       l_run *= alpha;
       if (XLSE) x_run *= alpha;
+      asm volatile("" : "+v"(l_run), "+v"(x_run));    // not fused with the additions below: the same bits in every instance
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
