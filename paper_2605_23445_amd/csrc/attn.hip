@@ -468,17 +468,15 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
   };
   if (n_tiles > 0) {
+    // The keys of this wave's own rows, for the reference to start from if their block is among this group's.  The list is
+    // requested in front of the tiles: behind them the wave waited for tiles and list before it asked for the keys (44
+    // blocks x 4 heads, 9 kept, 27.8 -> 27.2 us a reuse step).
+    const int own_first = t_first / STEPS, own_blks = n_tiles / STEPS;
+    const int listed = !dense && lane < own_blks ? idx[own_first + lane] : -1;
     b_cur = tile_block(0);
     b_nxt = n_tiles > 1 ? tile_block(1) : b_cur;
     issue(kh, K0, false, 0, b_cur);
     issue(vh, V0, true, 0, b_cur);
-    // The keys of this wave's own rows, for the reference to start from if their block is among this group's
-    const int own_first = t_first / STEPS, own_end = own_first + n_tiles / STEPS;
-    bool own = dense && u - blk_first >= own_first && u - blk_first < own_end;
-    if (!dense) {
-      for (int i = own_first + lane; i < own_end; i += 64) own |= idx[i] == u;
-      own = __builtin_amdgcn_ballot_w64(own) != 0;
-    }
     bf16x8 own_k[D / 16];
     {
       const u32x4* kp = reinterpret_cast<const u32x4*>(kh + q_row0 * D);
@@ -491,15 +489,20 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     logits(K0, 0, s0);
     mask_pads(b_cur, 0, 0, s0);
     m_run = half_max(s0);
-    if (own) {                                       // as logits and mask_pads, with the keys from registers
+    bool own = dense ? u - blk_first >= own_first && u - blk_first < own_first + own_blks : listed == u;
+    if (!dense)
+      for (int i = 64 + lane; i < own_blks; i += 64) own |= idx[own_first + i] == u;
+    if (__builtin_amdgcn_ballot_w64(own) != 0) {     // as logits and mask_pads, with the keys from registers
 #pragma unroll
       for (int i = 0; i < 16; ++i) s1[i] = 0.f;
 #pragma unroll
       for (int kk = 0; kk < D / 16; ++kk) s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(own_k[kk], qf[kk], s1, 0, 0, 0);
-      const int real = block_real_rows(u, BM, M_v, N_v, n_text) - wave * 32;
+      if (u == ragged_v || u == ragged_x) {
+        const int real = u == ragged_v ? real_v_last : real_x_last;
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (8 * (i / 4) + 4 * h + (i % 4) >= real) s1[i] = -INFINITY;
+        for (int i = 0; i < 16; ++i)
+          if (wave * 32 + 8 * (i / 4) + 4 * h + (i % 4) >= real) s1[i] = -INFINITY;
+      }
       m_run = fmaxf(m_run, half_max(s1));
     }
     m_run = fmaxf(fmaf(m_run, c2, HEADROOM), -FLT_MAX);              // finite: logits of -inf have weight 0, not NaN
