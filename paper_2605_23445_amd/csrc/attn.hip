@@ -310,7 +310,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // Weights are then below SUM_LIMIT whatever comes, and exact in bf16 where they are largest, which is what the reference
   // is followed for: with that of the first half tile kept, the outputs' error against 64 bits was 1.86e-3 of the result
   // instead of 1.77e-3 (75 600 tokens, 60 of 591 blocks), 2.29e-3 instead of 2.17e-3 (17 550 tokens, dense, d = 64,
-  // logits of standard deviation 2).  What it costs against keeping it, on one box: d = 64, 17 550 tokens x 48 heads 654 ->
+  // logits of standard deviation 2).  What it costs against keeping it, on one card: d = 64, 17 550 tokens x 48 heads 654 ->
   // 674 us; d = 128, 75 600 tokens, 40 heads, 60 of 591 blocks 10.99 -> 11.16 ms, 8 heads dense 19.56 -> 19.66; against a
   // running maximum it wins 743 -> 674, 11.92 -> 11.16, 21.09 -> 19.66.
   auto half_max = [&](const f32x16& x) __attribute__((always_inline)) {      // row maximum of a half tile, in both lane halves
