@@ -14,6 +14,8 @@
 //                   in fp32 and the dropped lo.lo term is below 2^-22 of the result, so the logits are as
 //                   accurate as an fp32 contraction at several times its speed (the mask decision that
 //                   follows stays an fp32 one); the scaling is undone, exactly, on the fp32 result.
+//   fold_select_kernel : the second of the two with the selection of a row behind it (select_row.h).
+//   score_small_kernel : all of it behind the pooling, for small problems.
 #include <type_traits>
 
 #include "select_row.h"
@@ -557,6 +559,162 @@ __global__ void __launch_bounds__(FS_T) fold_select_kernel(const float* __restri
 }
 static size_t fs_lds(int M_v) { return size_t(FS_ROWS) * (256 + fs_stride(M_v)) * sizeof(uint32_t); }
 
+// Scoring of small problems in one kernel: a work-group owns 32 query sub-blocks (32 / R query blocks) of a head, its eight
+// waves take key tiles in turn, straight from memory, and T and the row sums never leave LDS.  The same sums as the two kernels
+// above, except that a row's keys are summed by eight waves; so one kernel serves the calls that want scores (`score`) and
+// those that want lists (`kv_idx`), and both decide alike.  What bounds it is latency: a tile's rows, its product chain, three
+// barriers, the selection; it saves a launch and the way of T through memory.  256 fp32 tokens x 2 heads 18.6 -> 16.3 us a
+// refresh, 2 565 + 77 tokens x 12 heads, blocks of 64, 42.5 -> 38.6, 2 565 x 1 23.4 -> 21.0 (on one box each).
+constexpr int SS_T = 512, SS_WAVES = SS_T / 64, SS_STRIDE = 33;
+template <int D, int R>
+__global__ void __launch_bounds__(SS_T) score_small_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict__ k_hat,
+                                                           const float* __restrict__ q_down, const float* __restrict__ k_down,
+                                                           float* __restrict__ score, int M_s, int M_v, int M_x, int n_live, int k_fixed,
+                                                           int k_cap, double mass, uint8_t* __restrict__ mask, int32_t* __restrict__ kv_idx,
+                                                           int32_t* __restrict__ kv_cnt, int K_max, int32_t* __restrict__ k_head) {
+  constexpr int RS = 2 * D, KS = D / 16, ROWS = 32 / R;
+  constexpr int G = R < 4 ? R : 4, NG = 16 / G;            // as in score_lse_kernel
+  extern __shared__ unsigned long long lds64[];
+  uint32_t* hists = reinterpret_cast<uint32_t*>(lds64);                  // 256 words per wave
+  float* s_t = reinterpret_cast<float*>(hists + SS_WAVES * 256);         // T [M_v][SS_STRIDE], then keys in the first of R
+  __shared__ float s_m[SS_WAVES][32], s_z[SS_WAVES][32], s_lse[32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, half = lane >> 5;
+  const int head = blockIdx.y, u0 = blockIdx.x * ROWS, i0 = blockIdx.x * 32, M = M_v + M_x;
+  if (u0 < M_v) {
+    const uint16_t* qh = q_hat + int64_t(head) * M_s * RS;
+    const uint16_t* kh = k_hat + int64_t(head) * M_s * RS;
+    const int G4 = (M_s + 3) / 4;
+    const int q_from = i0 + n < M_s ? i0 + n : M_s - 1;    // rows beyond the last repeat it; nothing reads their results
+    const float q_dn = q_down[int64_t(head) * G4 + q_from / 4];
+    f16x8 bq[2][KS];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk)
+        bq[p][kk] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(qh + int64_t(q_from) * RS + p * D + 16 * kk + 8 * half));
+    float m_row = LSE_START, z_row = 0.f;
+    for (int t = wave; t * 32 < n_live; t += SS_WAVES) {
+      const int k_from = t * 32 + n < M_s ? t * 32 + n : M_s - 1;        // beyond the last: masked below
+      const uint16_t* krow = kh + int64_t(k_from) * RS + 8 * half;
+      f16x8 ak[2][KS];
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) ak[p][kk] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + p * D + 16 * kk));
+      float dn[4];
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        const int grp = 8 * t + 2 * gq + half;
+        dn[gq] = k_down[int64_t(head) * G4 + (grp < G4 ? grp : G4 - 1)] * q_dn;
+      }
+      f32x16 c0, c1;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) { c0[i] = 0.f; c1[i] = 0.f; }
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) {                    // hi.hi, hi.lo, lo.hi, dealt to the accumulators as there
+        f32x16& a = kk % 2 ? c1 : c0;
+        f32x16& b = kk % 2 ? c0 : c1;
+        a = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[0][kk], bq[0][kk], a, 0, 0, 0);
+        b = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[0][kk], bq[1][kk], b, 0, 0, 0);
+        a = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[1][kk], bq[0][kk], a, 0, 0, 0);
+      }
+      float c[16], mt = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        c[i] = (c0[i] + c1[i]) * dn[i / 4];
+        if (t * 32 + 8 * (i / 4) + 4 * half + (i % 4) >= n_live) c[i] = -INFINITY;
+        mt = fmaxf(mt, c[i]);
+      }
+      if (R == 8) {                                        // a key block is split over the lane halves: one reference
+        float lo, hi;
+        both_halves(mt, lo, hi);
+        mt = fmaxf(lo, hi);
+      }
+      const float m_new = fmaxf(m_row, mt);
+      z_row *= __builtin_amdgcn_exp2f(m_row - m_new);
+      m_row = m_new;
+#pragma unroll
+      for (int gi = 0; gi < NG; ++gi) {
+        float sg = 0.f;
+#pragma unroll
+        for (int e = 0; e < G; ++e) sg += __builtin_amdgcn_exp2f(c[gi * G + e] - m_new);
+        z_row += sg;
+        if (R == 8) {
+          float lo, hi;
+          both_halves(sg, lo, hi);
+          sg = lo + hi;
+        }
+        const int first = gi * G, v = (t * 32 + 8 * (first / 4) + (R == 8 ? 0 : 4 * half) + first % 4) / R;
+        if (v < M_v) s_t[v * SS_STRIDE + n] = m_new + __builtin_amdgcn_logf(sg);  // R == 8: both halves store the same
+      }
+    }
+    const float m2 = __shfl_xor(m_row, 32, 64), z2 = __shfl_xor(z_row, 32, 64);
+    lse_merge(m_row, z_row, m2, z2);
+    if (half == 0) {
+      s_m[wave][n] = m_row;
+      s_z[wave][n] = z_row;
+    }
+    __syncthreads();
+    if (tid < 32) {
+      float m = s_m[0][tid], z = s_z[0][tid];
+#pragma unroll
+      for (int w = 1; w < SS_WAVES; ++w) lse_merge(m, z, s_m[w][tid], s_z[w][tid]);
+      s_lse[tid] = i0 + tid < n_live && z > 0.f ? m + __builtin_amdgcn_logf(z) : INFINITY;   // an empty query sub-block scores nothing
+    }
+    __syncthreads();
+    for (int x = tid; x < ROWS * M_v; x += SS_T) {
+      const int r = x / M_v, v = x % M_v;
+      float* t = s_t + v * SS_STRIDE + r * R;
+      float acc = 0.f;
+#pragma unroll
+      for (int a = 0; a < R; ++a) acc += __builtin_amdgcn_exp2f(t[a] - s_lse[r * R + a]);
+      if (score) {
+        if (u0 + r < M_v) score[(int64_t(head) * M_v + u0 + r) * M_v + v] = acc;
+      } else {
+        *reinterpret_cast<uint32_t*>(t) = order_key(acc);
+      }
+    }
+    __syncthreads();
+  }
+  if (score) return;
+  for (int r = wave; r < ROWS && u0 + r < M; r += SS_WAVES) {
+    const int u = u0 + r;
+    const int64_t out = int64_t(head) * M + u;
+    uint8_t* mrow = mask ? mask + out * M : nullptr;
+    if (u >= M_v) {
+      select_text_row(M, mrow, kv_cnt + out);
+      continue;
+    }
+    const StridedKeys row = {reinterpret_cast<const uint32_t*>(s_t) + r * R, SS_STRIDE};
+    uint32_t* hist = hists + wave * 256;
+    int k = k_fixed;
+    if (mass > 0.0) {                                      // every row its own count, clamped
+      const int ku = mass_count_row(row, reinterpret_cast<unsigned long long*>(hist), M_v, mass);
+      k = ku < k_fixed ? k_fixed : (ku > k_cap ? k_cap : ku);
+    } else if (k_head && u == 0 && lane == 0) {
+      k_head[head] = k;
+    }
+    select_row(row, hist, M_v, M_x, k, mrow, kv_idx + out * K_max, kv_cnt + out);
+  }
+}
+static size_t ss_lds(int M_v) { return (size_t(SS_WAVES) * 256 + size_t(M_v) * SS_STRIDE) * sizeof(uint32_t); }
+// Where the one kernel is the faster of the two ways.  A wave selects 4 / R .. 1 rows one after the other, and a tile's rows come
+// from memory lane by lane, the more so the longer they are.  Two kernels / one, us a refresh, bf16, one card:
+//   R = 8, d = 64: 250 blocks x 4 heads (252 work-groups) 1.03, x 5 (315) 0.94, 375 x 2 (188) 1.01, 44 x 12 1.13;
+//          d = 128: 16 x 24 1.13, 48 x 6 1.03, 48 x 24 (288) 0.96, 64 x 6 1.01, 72 x 6 1.01, 200 x 1 0.89
+//   R = 4, d = 64: 41 blocks of 64 x 12 1.09, 64 x 48 1.03, 96 x 12 1.04, 86 x 48 (528 work-groups) 0.99;
+//          d = 128: 32 x 24 1.05, 48 x 24 1.01, 64 x 6 0.995, 85 x 40 0.985
+//   R = 2, d = 64: 24 x 24 1.02, 48 x 24 0.99; d = 128: 8 x 6 1.08, 24 x 1 0.998, 48 x 1 0.96
+//   R = 1, d = 64: 16 x 24 1.03, 24 x 24 0.98; d = 128: 8 x 24 1.09, 16 x 1 0.99, 64 x 1 0.79
+static bool score_small(const dfs_geom* g, const dfs_sizes& s) {
+  if (ss_lds(s.M_v) > 61440) return false;                 // 64 KB with the fixed part: 392 blocks
+  const int64_t work_groups = int64_t(g->heads) * ((s.M_s + 31) / 32);
+  if (s.r == 8) return work_groups <= 256 && (g->d == 64 || s.M_v <= 64);
+  if (s.r == 4) return work_groups <= 480 && s.M_v * g->d <= 6144;
+  return s.M_v * g->d <= (s.r == 2 ? 1536 : 1024);
+}
+
 // Workspace: Q_hat, K_hat (two fp16 planes each, followed by the inverse scales of their row groups),
 // T [heads][t_rows][t_cols] fp32 (padded, see t_cols), row log-sum-exp [heads][KSPLIT_MAX][M_s] fp32.
 constexpr int KSPLIT_MAX = 4;
@@ -590,6 +748,14 @@ static int choose_ksplit(int64_t groups_times_heads, int n_tiles) {
 template <int D, int R>
 static void launch_score(const dfs_geom* g, const dfs_sizes& s, const uint16_t* q_hat, const uint16_t* k_hat, const float* q_down,
                          const float* k_down, float* tt, float* lse, float* score, const SelectPlan* sel, int n_live, hipStream_t st) {
+  if (score_small(g, s)) {
+    const int rows = 32 / R, n_rows = sel ? s.M : s.M_v;
+    score_small_kernel<D, R><<<dim3(unsigned((n_rows + rows - 1) / rows), unsigned(g->heads)), SS_T, ss_lds(s.M_v), st>>>(
+        q_hat, k_hat, q_down, k_down, sel ? nullptr : score, s.M_s, s.M_v, s.M_x, n_live, sel ? sel->k_fixed : 0, sel ? sel->k_cap : 0,
+        sel ? sel->mass : 0.0, sel ? sel->mask : nullptr, sel ? sel->kv_idx : nullptr, sel ? sel->kv_cnt : nullptr, sel ? sel->K_max : 0,
+        sel ? sel->k_head : nullptr);
+    return;
+  }
   const int groups = (s.M_s + 127) / 128, n_tiles = (n_live + 31) / 32;
   const int ksplit = choose_ksplit(int64_t(groups) * g->heads, n_tiles);
   const int per = (n_tiles + ksplit - 1) / ksplit;

@@ -43,12 +43,20 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+struct StridedKeys {                                 // a row whose keys lie `stride` words apart
+  const uint32_t* first;
+  int stride;
+  __device__ __forceinline__ uint32_t operator[](int j) const { return first[j * stride]; }
+};
+
 // Fewest top-ranked columns whose fixed-point scores reach ceil(mass * row total).  The column at which the sum from
 // the top reaches the target is found six bits of its key at a time: a 64-bin histogram of the masses of the keys that
 // match the bits fixed so far, one bin per lane, and a scan over the lanes.  Integers throughout, so the result does
 // not depend on any order.  (One bit per pass, each with a sum over the row: 355 us at 75 600 tokens x 40 heads and
 // reading the scores again; this form 101.)
-__device__ __forceinline__ int mass_count_row(const uint32_t* keys, unsigned long long* bins /*[64]*/, int M_v, double mass) {
+// (keys: a pointer, or whatever else gives the key of column j as keys[j].)
+template <class Keys>
+__device__ __forceinline__ int mass_count_row(Keys keys, unsigned long long* bins /*[64]*/, int M_v, double mass) {
   const int lane = threadIdx.x & 63;
   unsigned long long tot = 0;
   for (int j = lane; j < M_v; j += 64) tot += mass_fixed(key_score(keys[j]));
@@ -95,7 +103,8 @@ __device__ __forceinline__ int mass_count_row(const uint32_t* keys, unsigned lon
 // passes instead of one per bit; counts are integers, so the result is the same key.  A row of up to 64 columns is ranked
 // outright, each lane counting the columns ahead of its own (keys four at a time, the same for all lanes): with the fold, 4 columns
 // 5.3 -> 3.0 us, 41 columns 7.4 -> 7.1.
-__device__ __forceinline__ void select_row(const uint32_t* keys, uint32_t* hist /*[256]*/, int M_v, int M_x, int k, uint8_t* mrow,
+template <class Keys>
+__device__ __forceinline__ void select_row(Keys keys, uint32_t* hist /*[256]*/, int M_v, int M_x, int k, uint8_t* mrow,
                                            int32_t* idx, int32_t* cnt) {
   const int lane = threadIdx.x & 63;
   for (int j = lane; j < M_x; j += 64) {             // text key blocks are always kept

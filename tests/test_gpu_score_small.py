@@ -1,0 +1,46 @@
+"""Scoring and selection of small problems in one kernel: scores against the oracle and lists of dfs_forward against the staged
+calls bit for bit, at one block, at the largest row the rule takes for each r and d and one beyond (the two kernels)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dfs_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+P = pytest.importorskip("paper_2605_23445_amd")
+from tests import gpu_util as G  # noqa: E402
+
+
+# blocks of 64; r = 8 is bounded by 256 work-groups of 32 sub-blocks (1024 blocks over the heads) and by 64 blocks at d = 128
+@pytest.mark.parametrize("d,r,M_v,heads", [(64, 1, 1, 3), (64, 1, 16, 2), (64, 1, 17, 2), (64, 2, 1, 1), (64, 2, 24, 2), (64, 2, 25, 2), (64, 4, 2, 2),
+                                           (64, 4, 65, 2), (64, 4, 96, 1), (64, 4, 97, 1), (64, 8, 1, 2), (64, 8, 392, 1), (64, 8, 393, 1), (64, 8, 64, 16),
+                                           (64, 8, 65, 16), (128, 1, 8, 2), (128, 1, 9, 2), (128, 2, 12, 2), (128, 2, 13, 2), (128, 4, 48, 2),
+                                           (128, 4, 49, 2), (128, 8, 64, 2), (128, 8, 65, 2), (128, 8, 5, 1)])
+def test_scores_and_lists(d, r, M_v, heads):
+    N_v = M_v * 64 - (64 // r % 64 + 3 if M_v % 2 else 0) if M_v > 1 else 41     # odd counts: a ragged last block, without its last sub-block if r > 1
+    H, W = next((n // w, w) for n in range(N_v, 0, -1) for w in range(512, 0, -1) if n % w == 0 and n // w <= 512)
+    n_text = 70 if heads == 2 else 0
+    g = P.Geom(1, H, W, n_text, heads, d, 64, 64 // r)
+    s = P.dfs_geom_sizes(g)
+    assert s.M_v == M_v
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M_v * d + r)
+    q, k, v = (torch.randn(heads, s.N, d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    q, k = q * 3, k * 3
+    perm_pad, inv, _ = G.gpu_perm(g)
+    qp, kp = (G.gpu_permute(g, P.DFS_BF16, x, perm_pad) for x in (q, k))
+    score = G.gpu_score(g, P.DFS_BF16, qp, kp)
+    # the bound of the scores everywhere: fp32 contraction, exponentials and sums of at most r x r probabilities
+    want = O.block_score(qp[:1].float().cpu().numpy().astype(np.float64), kp[:1].float().cpu().numpy().astype(np.float64), s.N_v, 64, 64 // r)
+    assert np.abs(score[0].cpu().numpy() - want.reshape(M_v, M_v)).max() <= 1e-5 * r
+    i32 = dict(dtype=torch.int32, device="cuda")
+    for mode, sparsity, mass in ((P.DFS_SELECT_TOPK, 0.7, 0.0), (P.DFS_SELECT_MASS_ROW, 0.95, 0.8)):
+        K_max = s.M if mode != P.DFS_SELECT_TOPK else P.dfs_keep_count(sparsity, s.M_v) + s.M_x
+        mask = torch.full((heads, s.M, s.M), 9, dtype=torch.uint8, device="cuda")
+        st = P.MaskState(torch.full((heads, s.M, K_max), -1, **i32), torch.full((heads, s.M), -1, **i32), mask, torch.full((heads,), -1, **i32), K_max)
+        P.dfs_forward(g, P.DFS_BF16, q, k, v, perm_pad, inv, True, mode, sparsity, mass, st, d ** -0.5, torch.empty_like(q),
+                      G.ws_tensor(P.dfs_workspace_bytes(g, P.DFS_WS_FORWARD_BF16)))
+        ref = G.gpu_select(g, score, mode, sparsity, mass, K_max=K_max)
+        for name in ("kv_idx", "kv_cnt", "mask", "k_head"):
+            assert torch.equal(getattr(st, name), getattr(ref, name)), (name, mode)
