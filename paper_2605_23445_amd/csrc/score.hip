@@ -54,10 +54,19 @@ __device__ __forceinline__ void group_scale(float gmax, float& up, float& down) 
   }
 }
 
+// Layout of Q_hat and K_hat: per head, tiles of 32 sub-blocks (the last one with what is left, `rows`), a tile chunk by chunk as
+// the matrix instructions' operands want it, [2 D / 8][rows][8] fp16: chunks 0 .. D / 8 - 1 are features 8 c .. 8 c + 7 of the hi
+// plane, the others of the lo plane.  The lanes of an operand load, one row each, then read a kilobyte in one piece; with
+// whole rows behind one another they read 16 bytes of 32 rows.  A refresh
+// of 2 565 tokens x 12 heads, d = 64, blocks of 64, 36.5 -> 35.5 us; 75 600 tokens x 40 heads, sub-blocks of 16, 22.9 ms the same.
+__host__ __device__ __forceinline__ int tile_rows(int M_s, int t) { return M_s - 32 * t < 32 ? M_s - 32 * t : 32; }
+template <int D> __device__ __forceinline__ int64_t tile_at(int t) { return int64_t(t) * (32 * 2 * D); }      // elements
+template <int D> __device__ __forceinline__ int chunk_at(int p, int c, int rows, int n) { return ((p * (D / 8) + c) * rows + n) * 8; }
+
 // One wave per sub-block.  Lanes of a row sit side by side (16 bytes each); several rows are in
 // flight per load; partial sums of the row groups are folded with cross-lane exchanges.
-// Output row layout: [2][D] fp16 (hi, lo planes) of the row times its group's scale; the inverse scale of
-// group s / 4 goes to q_down / k_down.
+// Output: the hi and lo fp16 planes of the row times its group's scale (layout above); the inverse scale of group s / 4 goes
+// to q_down / k_down.
 // blockIdx.z: 0 pools Q, 1 pools K, 2 only reorders V.  With an index (the permutation) the tensors come in source
 // order and their rows are gathered; K (if k_out) and V are written out in the reordered layout on the way (pads as
 // zeros, text rows too), so that a step that refreshes the mask reads and writes each of them once, in one launch.
@@ -152,15 +161,20 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in
   group_scale(fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3])), up, down);
   if (threadIdx.x == 0) (blockIdx.z == 0 ? q_down : k_down)[int64_t(head) * ((M_s + 3) / 4) + blockIdx.x] = down;
   if (rg == 0) {
-    uint16_t* o = dst + (int64_t(head) * M_s + s) * (2 * D) + c * EPL;
+    const int in_tile = tile_rows(M_s, s / 32);
+    uint16_t* o = dst + int64_t(head) * M_s * (2 * D) + tile_at<D>(s / 32) + chunk_at<D>(0, c * EPL / 8, in_tile, s % 32) + c * EPL % 8;
     uint16_t hi[EPL], lo[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) split2(acc[e] * up, hi[e], lo[e]);
+    typedef unsigned int pairs __attribute__((ext_vector_type(EPL / 2)));
+    pairs h2, l2;
 #pragma unroll
     for (int e = 0; e < EPL; e += 2) {
-      *reinterpret_cast<uint32_t*>(o + e) = uint32_t(hi[e]) | (uint32_t(hi[e + 1]) << 16);
-      *reinterpret_cast<uint32_t*>(o + D + e) = uint32_t(lo[e]) | (uint32_t(lo[e + 1]) << 16);
+      h2[e / 2] = uint32_t(hi[e]) | (uint32_t(hi[e + 1]) << 16);
+      l2[e / 2] = uint32_t(lo[e]) | (uint32_t(lo[e + 1]) << 16);
     }
+    *reinterpret_cast<pairs*>(o) = h2;
+    *reinterpret_cast<pairs*>(o + chunk_at<D>(1, 0, in_tile, 0)) = l2;
   }
 }
 
@@ -213,11 +227,10 @@ score_lse_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict_
                  const float* __restrict__ k_down, float* __restrict__ tt, float* __restrict__ lse, int M_s, int n_live, int tiles_per_split, int ksplit,
                  int wgs_per_head, int total_wgs, int wgs_per_xcd) {
   constexpr int RS = 2 * D;                   // elements of a centroid row (hi, lo planes)
-  constexpr int RSP = RS + 8;                 // LDS row stride: 16 bytes of skew keep the row-per-lane reads conflict-free
   constexpr int KS = D / 16;                  // product steps of 16 features
-  constexpr int CPT = 32 * RS / 8 / 256;      // 16-byte chunks of a key tile per thread (6 at d=128)
+  constexpr int CPT = 32 * RS / 8 / 256;      // 16-byte chunks of a key tile per thread (4 at d = 128)
   constexpr int G = R < 4 ? R : 4;            // key sub-blocks of one key block that sit in consecutive registers
-  __shared__ __attribute__((aligned(16))) uint16_t s_k[2][32 * RSP];
+  __shared__ __attribute__((aligned(16))) uint16_t s_k[2][32 * RS];      // chunk by chunk, 32 rows each
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = lane & 31, half = lane >> 5;
   // Work-group ids are dealt round-robin to the 8 XCDs, each with an L2 of its own.  Every XCD takes a contiguous
@@ -243,7 +256,7 @@ score_lse_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict_
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
         u32x4 v = {0u, 0u, 0u, 0u};
-        if (row < M_s) v = *reinterpret_cast<const u32x4*>(qh + int64_t(row) * RS + p * D + 16 * kk + 8 * half);
+        if (row < M_s) v = *reinterpret_cast<const u32x4*>(qh + tile_at<D>(i0 / 32) + chunk_at<D>(p, 2 * kk + half, tile_rows(M_s, i0 / 32), n));
         bq[p][kk] = __builtin_bit_cast(f16x8, v);
       }
   }
@@ -251,24 +264,18 @@ score_lse_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict_
   const int t_begin = split * tiles_per_split;
   const int t_end = t_begin + tiles_per_split < n_tiles ? t_begin + tiles_per_split : n_tiles;
 
-  // key tile t (32 centroid rows, contiguous in memory) -> registers -> LDS
+  // key tile t -> registers -> LDS
   u32x4 kreg[CPT];
   auto fetch = [&](int t) {
+    // rows at or beyond M_s re-read the last row instead (no branch): they are at or beyond n_live and masked later
+    const int rows = tile_rows(M_s, t), row = tid % 32 < rows ? tid % 32 : rows - 1;
+    const uint16_t* kt = kh + tile_at<D>(t) + row * 8;
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      // rows at or beyond M_s re-read the last row instead (no branch): they are at or beyond n_live and masked later
-      const int c = tid + i * 256;
-      const int row = t * 32 + c / (RS / 8);
-      const int from = row < M_s ? row : M_s - 1;
-      kreg[i] = *reinterpret_cast<const u32x4*>(kh + int64_t(from) * RS + (c % (RS / 8)) * 8);
-    }
+    for (int i = 0; i < CPT; ++i) kreg[i] = *reinterpret_cast<const u32x4*>(kt + (tid / 32 + i * 8) * rows * 8);
   };
   auto commit = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int c = tid + i * 256;
-      *reinterpret_cast<u32x4*>(&s_k[buf][(c / (RS / 8)) * RSP + (c % (RS / 8)) * 8]) = kreg[i];
-    }
+    for (int i = 0; i < CPT; ++i) *reinterpret_cast<u32x4*>(&s_k[buf][(tid + i * 256) * 8]) = kreg[i];
   };
   float m_row = LSE_START, z_row = 0.f;       // this lane's share of the row log-sum-exp of query sub-block i0 + n
   const int q_row = i0 + n;
@@ -299,16 +306,17 @@ score_lse_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict_
   //     give 2^-inf = 0; R == 8: a key block is split over the two lane halves, which therefore share the
   //     reference); then per key block the log of its summed exponentials.
   constexpr int NS = 3 * KS;                  // matrix instructions of a tile
+  const int lane_at = chunk_at<D>(0, half, 32, n);
   auto stage = [&](auto do_mm, auto do_ep, int t, int buf, f32x16& c0, f32x16& c1, float (&dn_next)[4], const f32x16& p0,
                    const f32x16& p1, const float (&dn_prev)[4], int tp) {
     constexpr bool MM = decltype(do_mm)::value, EP = decltype(do_ep)::value;
-    const uint16_t* krow = &s_k[buf][n * RSP + 8 * half];
+    const uint16_t* krow = &s_k[buf][lane_at];
     f16x8 fr[2][4];
     auto load_pair = [&](int p) {
-      fr[p & 1][0] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + 32 * p));
-      fr[p & 1][1] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + D + 32 * p));
-      fr[p & 1][2] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + 32 * p + 16));
-      fr[p & 1][3] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + D + 32 * p + 16));
+      fr[p & 1][0] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + chunk_at<D>(0, 4 * p, 32, 0)));
+      fr[p & 1][1] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + chunk_at<D>(1, 4 * p, 32, 0)));
+      fr[p & 1][2] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + chunk_at<D>(0, 4 * p + 2, 32, 0)));
+      fr[p & 1][3] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + chunk_at<D>(1, 4 * p + 2, 32, 0)));
     };
     float dp[4], c[16];
     float mt = 0.f, m_new = 0.f, zt = 0.f;
@@ -564,7 +572,7 @@ static size_t fs_lds(int M_v) { return size_t(FS_ROWS) * (256 + fs_stride(M_v)) 
 // above, except that a row's keys are summed by eight waves; so one kernel serves the calls that want scores (`score`) and
 // those that want lists (`kv_idx`), and both decide alike.  What bounds it is latency: a tile's rows, its product chain, three
 // barriers, the selection; it saves a launch and the way of T through memory.  256 fp32 tokens x 2 heads 18.6 -> 16.3 us a
-// refresh, 2 565 + 77 tokens x 12 heads, blocks of 64, 42.5 -> 38.6, 2 565 x 1 23.4 -> 21.0 (on one box each).
+// refresh, 2 565 + 77 tokens x 12 heads, blocks of 64, 39.2 -> 35.5 (on one box each).
 constexpr int SS_T = 512, SS_WAVES = SS_T / 64, SS_STRIDE = 33;
 template <int D, int R>
 __global__ void __launch_bounds__(SS_T) score_small_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict__ k_hat,
@@ -592,16 +600,17 @@ __global__ void __launch_bounds__(SS_T) score_small_kernel(const uint16_t* __res
     for (int p = 0; p < 2; ++p)
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk)
-        bq[p][kk] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(qh + int64_t(q_from) * RS + p * D + 16 * kk + 8 * half));
+        bq[p][kk] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(
+            qh + tile_at<D>(i0 / 32) + chunk_at<D>(p, 2 * kk + half, tile_rows(M_s, i0 / 32), q_from - i0)));
     float m_row = LSE_START, z_row = 0.f;
     for (int t = wave; t * 32 < n_live; t += SS_WAVES) {
-      const int k_from = t * 32 + n < M_s ? t * 32 + n : M_s - 1;        // beyond the last: masked below
-      const uint16_t* krow = kh + int64_t(k_from) * RS + 8 * half;
+      const int rows = tile_rows(M_s, t);
+      const uint16_t* kt = kh + tile_at<D>(t) + (n < rows ? n : rows - 1) * 8;          // beyond the last: masked below
       f16x8 ak[2][KS];
 #pragma unroll
       for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) ak[p][kk] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + p * D + 16 * kk));
+        for (int kk = 0; kk < KS; ++kk) ak[p][kk] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(kt + chunk_at<D>(p, 2 * kk + half, rows, 0)));
       float dn[4];
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
@@ -699,20 +708,20 @@ __global__ void __launch_bounds__(SS_T) score_small_kernel(const uint16_t* __res
   }
 }
 static size_t ss_lds(int M_v) { return (size_t(SS_WAVES) * 256 + size_t(M_v) * SS_STRIDE) * sizeof(uint32_t); }
-// Where the one kernel is the faster of the two ways.  A wave selects 4 / R .. 1 rows one after the other, and a tile's rows come
-// from memory lane by lane, the more so the longer they are.  Two kernels / one, us a refresh, bf16, one card:
-//   R = 8, d = 64: 250 blocks x 4 heads (252 work-groups) 1.03, x 5 (315) 0.94, 375 x 2 (188) 1.01, 44 x 12 1.13;
-//          d = 128: 16 x 24 1.13, 48 x 6 1.03, 48 x 24 (288) 0.96, 64 x 6 1.01, 72 x 6 1.01, 200 x 1 0.89
-//   R = 4, d = 64: 41 blocks of 64 x 12 1.09, 64 x 48 1.03, 96 x 12 1.04, 86 x 48 (528 work-groups) 0.99;
-//          d = 128: 32 x 24 1.05, 48 x 24 1.01, 64 x 6 0.995, 85 x 40 0.985
-//   R = 2, d = 64: 24 x 24 1.02, 48 x 24 0.99; d = 128: 8 x 6 1.08, 24 x 1 0.998, 48 x 1 0.96
-//   R = 1, d = 64: 16 x 24 1.03, 24 x 24 0.98; d = 128: 8 x 24 1.09, 16 x 1 0.99, 64 x 1 0.79
+// Where the one kernel is the faster of the two ways: a wave selects 4 / R .. 1 rows one after the other, and every 32 query
+// sub-blocks read all key tiles.  Time of the two kernels over that of the one, whole refresh calls in bf16 on one card:
+//   R = 8, d = 64: 16 blocks x 8 heads 1.30, 48 x 40 1.07, 200 x 8 1.04, 200 x 40 1.03, 313 x 1 1.09, 313 x 8 0.98;
+//          d = 128: 16 x 8 1.23, 88 x 40 0.99, 200 x 8 1.02, 200 x 40 1.00, 313 x 8 0.97
+//   R = 4, d = 64: 24 x 8 1.13, 138 x 48 1.00, 200 x 8 1.03, 313 x 1 1.08, 313 x 40 1.00; d = 128: 24 x 8 1.10, 138 x 40 1.00, 313 x 8 1.01, 313 x 40 1.00
+//   R = 2, d = 64: 8 x 8 1.12, 48 x 8 1.03, 72 x 8 1.01, 138 x 1 0.96; d = 128: 24 x 8 1.04, 48 x 8 1.00, 72 x 8 0.99
+//   R = 1: 8 x 8 1.04, 16 x 8 0.99 (d = 64) and 1.02 (128), 24 x 8 0.95 and 0.97, 138 x 1 0.78
 static bool score_small(const dfs_geom* g, const dfs_sizes& s) {
-  if (ss_lds(s.M_v) > 61440) return false;                 // 64 KB with the fixed part: 392 blocks
-  const int64_t work_groups = int64_t(g->heads) * ((s.M_s + 31) / 32);
-  if (s.r == 8) return work_groups <= 256 && (g->d == 64 || s.M_v <= 64);
-  if (s.r == 4) return work_groups <= 480 && s.M_v * g->d <= 6144;
-  return s.M_v * g->d <= (s.r == 2 ? 1536 : 1024);
+  switch (s.r) {
+    case 8: return s.M_v <= 256;
+    case 4: return s.M_v <= 320;                           // 52 KB of the 64 KB of LDS
+    case 2: return s.M_v * g->d <= 4096;
+    default: return s.M_v <= 12;
+  }
 }
 
 // Workspace: Q_hat, K_hat (two fp16 planes each, followed by the inverse scales of their row groups),

@@ -12,11 +12,10 @@ P = pytest.importorskip("paper_2605_23445_amd")
 from tests import gpu_util as G  # noqa: E402
 
 
-# blocks of 64; r = 8 is bounded by 256 work-groups of 32 sub-blocks (1024 blocks over the heads) and by 64 blocks at d = 128
-@pytest.mark.parametrize("d,r,M_v,heads", [(64, 1, 1, 3), (64, 1, 16, 2), (64, 1, 17, 2), (64, 2, 1, 1), (64, 2, 24, 2), (64, 2, 25, 2), (64, 4, 2, 2),
-                                           (64, 4, 65, 2), (64, 4, 96, 1), (64, 4, 97, 1), (64, 8, 1, 2), (64, 8, 392, 1), (64, 8, 393, 1), (64, 8, 64, 16),
-                                           (64, 8, 65, 16), (128, 1, 8, 2), (128, 1, 9, 2), (128, 2, 12, 2), (128, 2, 13, 2), (128, 4, 48, 2),
-                                           (128, 4, 49, 2), (128, 8, 64, 2), (128, 8, 65, 2), (128, 8, 5, 1)])
+@pytest.mark.parametrize("d,r,M_v,heads", [(64, 1, 1, 3), (64, 1, 12, 2), (64, 1, 13, 2), (64, 2, 1, 1), (64, 2, 64, 2), (64, 2, 65, 2), (64, 4, 2, 2),
+                                           (64, 4, 65, 2), (64, 4, 320, 1), (64, 4, 321, 1), (64, 8, 1, 2), (64, 8, 256, 1), (64, 8, 257, 1), (128, 1, 12, 2),
+                                           (128, 1, 13, 2), (128, 2, 32, 2), (128, 2, 33, 2), (128, 4, 320, 1), (128, 4, 321, 1), (128, 4, 9, 2),
+                                           (128, 8, 256, 1), (128, 8, 257, 1), (128, 8, 64, 2), (128, 8, 5, 1)])
 def test_scores_and_lists(d, r, M_v, heads):
     N_v = M_v * 64 - (64 // r % 64 + 3 if M_v % 2 else 0) if M_v > 1 else 41     # odd counts: a ragged last block, without its last sub-block if r > 1
     H, W = next((n // w, w) for n in range(N_v, 0, -1) for w in range(512, 0, -1) if n % w == 0 and n // w <= 512)
