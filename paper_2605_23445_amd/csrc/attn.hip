@@ -64,9 +64,13 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
 // KS: where the query blocks are too few to give every SIMD its two waves, KS groups of waves share one query block, each
 // with a KS-th of its tiles, tile buffers of its own and a softmax of its own; they merge through LDS at the end.  A lone
 // wave per SIMD reaches three fifths of the matrix rate, two together three quarters; see key_split below for the rule.
+//
+// SLIM (d = 128, 64 query rows): at 16 KB a tile, two buffers each for K and V leave room for two work-groups of two waves, one
+// wave per SIMD.  With one buffer each, whose halves take turns, four work-groups fit; a half is then requested a stage
+// ahead instead of a tile.  See `slim` below for the rule.
 template <int D, int BM, bool XLSE, int KS>
 constexpr int attn_waves() { return D == 64 && BM == 128 && !XLSE && KS == 1 ? 3 : 2; }
-template <int D, int BM, bool XLSE, int KS>
+template <int D, int BM, bool XLSE, int KS, bool SLIM = false>
 __global__ void __launch_bounds__(BM * 2 * KS)
 __attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE, KS>(), attn_waves<D, BM, XLSE, KS>())))
 attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -84,8 +88,9 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   constexpr int ESL = NF - 1;                      // matrix instructions the sixteen exponentials of a half tile are spread over
   constexpr float HEADROOM = 4.f, SUM_LIMIT = 2.25f;                      // see "A row's reference" below
   // Two K and two V tile buffers per group (tile t lives in the pair of parity t & 1), at fixed byte offsets.
-  __shared__ __attribute__((aligned(16))) uint16_t tiles[KS * 4 * TILE];
-  constexpr int K0 = 0, K1 = 2 * TILE, V0 = 4 * TILE, V1 = 6 * TILE;
+  static_assert(!SLIM || KS == 1, "the merge of wave groups wants all four buffers");
+  __shared__ __attribute__((aligned(16))) uint16_t tiles[KS * (SLIM ? 2 : 4) * TILE];
+  constexpr int K0 = 0, K1 = SLIM ? 0 : 2 * TILE, V0 = SLIM ? 2 * TILE : 4 * TILE, V1 = SLIM ? 2 * TILE : 6 * TILE;
 
   // Work-group to (head, query block).  Ids are dealt round-robin to the 8 XCDs, so id % 8 names the XCD
   // and id / 8 the order inside it.
@@ -446,9 +451,22 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     constexpr int k_nxt = ODD ? K0 : K1;             // K(t+1)
     constexpr int v_cur = ODD ? V1 : V0;             // V(t)
     constexpr int v_nxt = ODD ? V0 : V1;             // V(t-1); V(t+1) goes here
+    // SLIM: every stage requests a half of V(t) and a half of K(t+1), in its first slots, into the halves that the stage before
+    // has left; they are read in the next stage.
+    auto request = [&](int half) {
+      const uint64_t k_src = tile_src(kh, t + 1, b_nxt), v_src = tile_src(vh, t, b_cur);
+      return [&, half, k_src, v_src](int f) {
+        if (!SLIM || f >= NF / 2) return;
+#pragma unroll
+        for (int j = f * 2 * LPW / NF; j < (f + 1) * 2 * LPW / NF; ++j) {
+          if (LAST && j >= LPW / 2) return;
+          issue_one(j < LPW / 2 ? v_src : k_src, j < LPW / 2 ? V0 : K0, j < LPW / 2, half * LPW / 2 + j % (LPW / 2));
+        }
+      };
+    };
     // first half: products of (t-1, 1), logits of (t, 1), probabilities of (t, 0)
     float xsum;
-    stage(std::integral_constant<bool, !FIRST>{}, yes{}, v_nxt, 1, p1, k_cur, 1, s1, s0, p0, xsum, [](int) {});
+    stage(std::integral_constant<bool, !FIRST>{}, yes{}, v_nxt, 1, p1, k_cur, 1, s1, s0, p0, xsum, request(0));
     mask_pads(b_cur, t, 1, s1);
     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wave's parts of K(t+1) and V(t) landed
     __syncthreads();                                 // all parts landed; every wave is past the first half of tile t
@@ -459,12 +477,18 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // last tile K(t+2) is that tile once more, into a buffer that nothing reads.
     const int b_new = tile_block(t + 2 < n_tiles ? t + 2 : n_tiles - 1);
     const uint64_t k_src = tile_src(kh, t + 2, b_new), v_src = tile_src(vh, t + 1, b_nxt);
-    stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1, xsum, [&](int f) {
-      if (LAST) return;
+    if constexpr (SLIM) {
+      stage(yes{}, std::integral_constant<bool, !LAST>{}, V0, 0, p0, K0, 0, s0, s1, p1, xsum, request(1));
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
+    } else {
+      stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1, xsum, [&](int f) {
+        if (LAST) return;
 #pragma unroll
-      for (int j = f * 2 * LPW / NF; j < (f + 1) * 2 * LPW / NF; ++j)
-        issue_one(j < LPW ? v_src : k_src, j < LPW ? v_nxt : k_cur, j < LPW, j % LPW);
-    });
+        for (int j = f * 2 * LPW / NF; j < (f + 1) * 2 * LPW / NF; ++j)
+          issue_one(j < LPW ? v_src : k_src, j < LPW ? v_nxt : k_cur, j < LPW, j % LPW);
+      });
+    }
     settle(s1, p1, xsum);
     if (!LAST) mask_pads(b_nxt, t + 1, 0, s0);
     b_cur = b_nxt;
@@ -486,7 +510,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     b_cur = tile_block(0);
     b_nxt = n_tiles > 1 ? tile_block(1) : b_cur;
     issue(kh, K0, false, 0, b_cur);
-    issue(vh, V0, true, 0, b_cur);
+    if (!SLIM) issue(vh, V0, true, 0, b_cur);
     bf16x8 own_k[D / 16];
     {
       const u32x4* kp = reinterpret_cast<const u32x4*>(kh + q_row0 * D);
@@ -495,8 +519,9 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
-    if (n_tiles > 1) issue(kh, K1, false, 1, b_nxt);
+    if (!SLIM && n_tiles > 1) issue(kh, K1, false, 1, b_nxt);
     logits(K0, 0, s0);
+    if (SLIM) __syncthreads();                       // the first half of K(0) has been read
     mask_pads(b_cur, 0, 0, s0);
     m_run = half_max(s0);
     bool own = dense ? u - blk_first >= own_first && u - blk_first < own_first + own_blks : listed == u;
@@ -857,6 +882,13 @@ static int key_split(int d, int B, int64_t work_groups, int K_max) {
   return work_groups <= 256 ? 2 : 1;
 }
 
+// One tile buffer instead of two where the work-groups are more than two per CU (kernel's SLIM, d = 128, 64 rows).  Measured (two
+// buffers over one, whole calls): 528 work-groups x 14 of 88 blocks 53.9 -> 41.6 us, 1 056 78.8 -> 75.4, 6 600 x 42 of 275 763 ->
+// 733, dense 4 030 -> 3 700, 704 dense with log-sum-exp 1 072 -> 957; 328 work-groups 24.6 -> 27.6, 352 dense 97.5 -> 137.  Not for
+// sequences that all XCDs walk together (mapping 2), whose lists come from beyond L2: 2 364 work-groups x 178 of 1 182 blocks 1 028 ->
+// 1 055, 14 184 6 223 -> 7 374.
+static bool slim(int64_t work_groups, int ks, int mapping) { return ks == 1 && work_groups > 512 && mapping != 2; }
+
 // Work-groups per text block, and the key blocks each takes: about as many as a video row keeps (an eighth of all where
 // K_max does not tell), at least eight.  One where the video rows' work, in rounds of the chip's work-group slots, hides
 // the text rows, which start first.  Measured (us a reuse step, whole -> split), 17 550 video + 77 text tokens, 21 of 138
@@ -899,17 +931,20 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     dim3 grid(unsigned(8 * (mapping >= 2 ? text_slots + per_xcd : per_xcd)));
     int32_t* tickets = static_cast<int32_t*>(scratch);
     float* part = reinterpret_cast<float*>(static_cast<char*>(scratch) + align256(text_tickets(g, s) * sizeof(int32_t)));
-    const int ks = key_split(g->d, g->B, total + int64_t(g->heads) * s.M_x * (ts.splits - 1), K_max);
-#define ATTN_X(DD, BB, XX, KS)                                                                                                  \
-  attn_bf16_kernel<DD, BB, XX, KS><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
+    const int64_t work_groups = total + int64_t(g->heads) * s.M_x * (ts.splits - 1);
+    const int ks = key_split(g->d, g->B, work_groups, K_max);
+#define ATTN_X(DD, BB, XX, KS, SLIM)                                                                                            \
+  attn_bf16_kernel<DD, BB, XX, KS, SLIM><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
                                                         static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                 \
                                                         static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,         \
                                                         g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe, \
                                                         part, tickets, ts.splits, ts.blocks)
-#define ATTN(DD, BB, KS) do { if (lse) ATTN_X(DD, BB, true, KS); else ATTN_X(DD, BB, false, KS); } while (0)
-#define ATTN_KS(DD, BB) do { if (ks == 2) ATTN(DD, BB, 2); else ATTN(DD, BB, 1); } while (0)
+#define ATTN(DD, BB, KS, SLIM) do { if (lse) ATTN_X(DD, BB, true, KS, SLIM); else ATTN_X(DD, BB, false, KS, SLIM); } while (0)
+#define ATTN_KS(DD, BB) do { if (ks == 2) ATTN(DD, BB, 2, false); else ATTN(DD, BB, 1, false); } while (0)
     if (g->d == 64) { if (g->B == 64) ATTN_KS(64, 64); else ATTN_KS(64, 128); }
-    else            { if (g->B == 64) ATTN_KS(128, 64); else ATTN_KS(128, 128); }
+    else if (g->B == 128) ATTN_KS(128, 128);
+    else if (slim(work_groups, ks, mapping)) ATTN(128, 64, 1, true);
+    else ATTN_KS(128, 64);
 #undef ATTN_KS
 #undef ATTN
 #undef ATTN_X
