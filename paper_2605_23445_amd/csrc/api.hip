@@ -124,7 +124,7 @@ int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, cons
   // are reordered: by the pooling kernel on the way on a refresh step, by one gather on a reuse step.
   void *k_perm = base + L.kp, *v_perm = base + L.vp;
   int32_t* tickets = reinterpret_cast<int32_t*>(base + L.text);
-  const int n_tickets = int(text_tickets(g, s));
+  const int n_tickets = int(split_tickets(g, s));
   if (refresh) {
     float* score = reinterpret_cast<float*>(base + L.score);
     if ((rc = check_select(g, s, mode, sparsity, mass, st->K_max))) return rc;

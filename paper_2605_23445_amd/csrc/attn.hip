@@ -59,6 +59,7 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
 // Text rows keep every block and are many times longer than the others; where too few of the others follow to hide
 // them, SPLIT work-groups share one text block, each with a run of its list.  They leave their unnormalised sums in
 // `part`; the one that takes the last ticket merges them, in list order, so the result does not depend on who is last.
+// The query blocks of the last round of work-groups are shared in the same way where they would leave slots idle (tail_split).
 // (Only calls without log-sum-exp are given a `part`.)
 //
 // KS: where the query blocks are too few to give every SIMD its two waves, KS groups of waves share one query block, each
@@ -77,7 +78,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                  const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
                  float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
                  int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
-                 float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks) {
+                 float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows,
+                 int tail_splits) {
   constexpr int NW = BM / 32;                      // waves per group: one per 32 query rows
   constexpr int CH = D / 8;                        // 16-byte chunks per row
   constexpr int TILE = KN * D;                     // elements per tile
@@ -102,9 +104,16 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   //   mapping 1 (an eighth of a head would not fill an XCD): each XCD walks whole heads of its own,
   //     query blocks last-first so that the text blocks of a head start first.
   //   mapping 3: mapping 1 with the text blocks, split, of all heads in front as in mapping 2.
-  int head, u, split = 0;
+  // Behind slot tail_from, where the query blocks left would not fill the XCD once more, tail_splits work-groups share each.
+  int head, u, split = 0, splits = 1, slot = blockIdx.x / 8;
+  const int xcd = blockIdx.x % 8;
+  const bool tail = !XLSE && tail_splits > 1 && slot >= tail_from;
+  if (tail) {
+    splits = tail_splits;
+    split = (slot - tail_from) / tail_rows;
+    slot -= split * tail_rows;
+  }
   if (mapping >= 2) {
-    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int M_x = M - M_v, n_heads = total_wg / M;
     const int text_wgs = n_heads * M_x * text_splits, text_slots = (text_wgs + 7) / 8;
     if (slot < text_slots) {
@@ -112,6 +121,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       if (id >= text_wgs) return;
       u = M_v + id % M_x;
       split = id / M_x % text_splits;
+      splits = text_splits;
       head = id / M_x / text_splits;
     } else if (mapping == 2) {
       const int C = (M_v + 7) / 8, s2 = slot - text_slots;
@@ -125,8 +135,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       u = M_v - 1 - logical % M_v;
     }
   } else {
-    const int logical = (blockIdx.x % 8) * wg_per_xcd + blockIdx.x / 8;
-    if (logical >= total_wg) return;
+    const int logical = xcd * wg_per_xcd + slot;
+    if (slot >= wg_per_xcd || logical >= total_wg) return;
     head = logical / M;
     u = M - 1 - logical % M;
   }
@@ -146,10 +156,11 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   const int n = lane & 31, h = lane >> 5;
   const int cnt_in = kv_cnt[int64_t(head) * M + u];
   const bool dense = cnt_in >= M;
-  const bool shared_row = !XLSE && text_splits > 1 && u >= M_v;
-  const int blk_first = shared_row ? split * split_blocks : 0;            // this work-group's run of the list
+  const bool shared_row = !XLSE && splits > 1;
   int cnt = dense ? M : (cnt_in < 0 ? 0 : (cnt_in > K_max ? K_max : cnt_in));
-  if (shared_row) cnt = cnt - blk_first < 0 ? 0 : cnt - blk_first < split_blocks ? cnt - blk_first : split_blocks;
+  const int run = tail ? (cnt + splits - 1) / splits : split_blocks;
+  const int blk_first = shared_row ? split * run : 0;                     // this work-group's run of the list
+  if (shared_row) cnt = cnt - blk_first < 0 ? 0 : cnt - blk_first < run ? cnt - blk_first : run;
   const int32_t* idx = kv_idx + (int64_t(head) * M + u) * K_max + blk_first;
   const int64_t head_off = int64_t(head) * N_pad * D;
   const uint16_t* kh = k + head_off;
@@ -621,8 +632,11 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       auto put = [](float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
       auto get = [](const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
       constexpr int REGS = D / 2 + 2;                // of a lane: accumulators, reference, row sum
-      const int M_x = M - M_v, row = head * M_x + (u - M_v);
-      float* rows = part + (int64_t(row) * text_splits * NW + wave) * REGS * 64 + lane;
+      // tickets and partial rows: those of the text rows, then those of the tail
+      const int M_x = M - M_v, text_rows = total_wg / M * M_x, tail_row = xcd * tail_rows + slot - tail_from;
+      const int row = tail ? text_rows + tail_row : head * M_x + (u - M_v);
+      const int64_t first = tail ? int64_t(text_splits > 1 ? text_rows : 0) * text_splits + int64_t(tail_row) * splits : int64_t(row) * splits;
+      float* rows = part + (first * NW + wave) * REGS * 64 + lane;
       float* mine = rows + int64_t(split) * NW * REGS * 64;
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
@@ -635,19 +649,19 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       __syncthreads();                               // and every wave's, before the ticket is taken
       if (tid == 0) s_ticket = __hip_atomic_fetch_add(&tickets[row], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __syncthreads();
-      if (s_ticket != text_splits - 1) {
+      if (s_ticket != splits - 1) {
         probe_end();
         return;
       }
       float m_all = -INFINITY;
-      for (int sp = 0; sp < text_splits; ++sp) m_all = fmaxf(m_all, get(rows + (int64_t(sp) * NW * REGS + REGS - 2) * 64));
+      for (int sp = 0; sp < splits; ++sp) m_all = fmaxf(m_all, get(rows + (int64_t(sp) * NW * REGS + REGS - 2) * 64));
       const float ref = m_all == -INFINITY ? 0.f : m_all;
       l_run = 0.f;
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
-      for (int sp = 0; sp < text_splits; ++sp) {
+      for (int sp = 0; sp < splits; ++sp) {
         const float* p = rows + int64_t(sp) * NW * REGS * 64;
         const float share = __builtin_amdgcn_exp2f(get(p + (REGS - 2) * 64) - ref);
         l_run = fmaf(share, get(p + (REGS - 1) * 64), l_run);
@@ -906,12 +920,39 @@ static TextSplit text_split(const dfs_geom* g, const dfs_sizes& s, int K_max, si
   int blocks = int(2 * kept <= s.M ? kept : s.M / 8);
   if (blocks < 8) blocks = 8;
   const size_t row = size_t(g->B) * (g->d + 4) * sizeof(float) * s.M_x * g->heads;         // one split of every text block
-  const int64_t room = int64_t((scratch_bytes - align256(text_tickets(g, s) * sizeof(int32_t))) / row);
+  const int64_t room = int64_t((scratch_bytes - align256(split_tickets(g, s) * sizeof(int32_t))) / row);
   if ((s.M + blocks - 1) / blocks > room) {
     if (room < 2) return whole;
     blocks = int((s.M + room - 1) / room);
   }
   return {(s.M + blocks - 1) / blocks, blocks};
+}
+
+// The last round of work-groups: `rows` query blocks of an XCD from slot `from` on, shared by `splits` work-groups each where a
+// whole one would leave slots idle: a third of them and less at d = 128 with blocks of 128 (a lone wave per SIMD does most of
+// what two do), half and less elsewhere, pieces of four key blocks and more.  Within eight rounds: beyond, the last one is short
+// against the rest; two for the form with one buffer, whose work-groups end less evenly.  Measured (us, whole -> shared, kept of
+// blocks x heads): d = 128, 44 of 107 x 5 (1.04 rounds) 250 -> 207, 60 of 342 x 6 (4.0) 996 -> 933, 107 of 228 x 3 (1.34, two
+// pieces: whole by the rule) 573 -> 582; d = 64, 47 of 102 x 8 (1.06) 208 -> 175, 39 of 148 x 21 (4.05) 556 -> 535, blocks of 64, 63 of
+// 492 x 3 (1.44) 148 -> 132; d = 128, blocks of 64, 262 of 559 x 2 (1.09) 806 -> 667, 28 of 159 x 27 (4.19: whole by the rule) 353 -> 368.
+struct TailSplit { int from, rows, splits; };
+static TailSplit tail_split(const dfs_geom* g, const dfs_sizes& s, int32_t K_max, int order, int text_slots, const TextSplit& ts, bool one_buffer,
+                            size_t scratch_bytes) {
+  const TailSplit none = {0, 1, 1};
+  const int slots = 32 * (g->B == 128 ? (g->d == 64 ? 3 : 2) : g->d == 64 || one_buffer ? 4 : 2);     // resident work-groups of an XCD
+  const int full = order / slots * slots, rows = order - full;
+  if (scratch_bytes == 0 || int64_t(g->heads) * s.M < 512 || full == 0 || rows == 0 || full < text_slots) return none;
+  if (full > (one_buffer ? 2 : 8) * slots) return none;
+  const int64_t kept = K_max < s.M ? K_max : s.M, likely = kept == s.M ? kept / 3 : kept;     // as in text_split
+  int splits = slots / rows;
+  if (splits > 4) splits = 4;
+  const int pieces = int(likely / (full == slots ? 4 : 6));
+  if (splits > pieces) splits = pieces;
+  if (splits < (g->d == 128 && g->B == 128 ? 3 : 2)) return none;
+  const int64_t parts = 8 * int64_t(rows) * splits + (ts.splits > 1 ? int64_t(g->heads) * s.M_x * ts.splits : 0);
+  const size_t have = scratch_bytes - align256(split_tickets(g, s) * sizeof(int32_t));
+  if (size_t(parts) * g->B * (g->d + 4) * sizeof(float) > have) return none;
+  return {full, rows, splits};
 }
 
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
@@ -928,22 +969,25 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     const int mapping = chunk >= 64 ? 2 : ts.splits > 1 ? 3 : 1;
     const int text_slots = (g->heads * s.M_x * ts.splits + 7) / 8, video_slots = int((int64_t(g->heads) * s.M_v + 7) / 8);
     const int per_xcd = mapping == 2 ? g->heads * chunk : mapping == 3 ? video_slots : int((total + 7) / 8);
-    dim3 grid(unsigned(8 * (mapping >= 2 ? text_slots + per_xcd : per_xcd)));
     int32_t* tickets = static_cast<int32_t*>(scratch);
-    float* part = reinterpret_cast<float*>(static_cast<char*>(scratch) + align256(text_tickets(g, s) * sizeof(int32_t)));
+    float* part = reinterpret_cast<float*>(static_cast<char*>(scratch) + align256(split_tickets(g, s) * sizeof(int32_t)));
     const int64_t work_groups = total + int64_t(g->heads) * s.M_x * (ts.splits - 1);
     const int ks = key_split(g->d, g->B, work_groups, K_max);
+    const bool one_buffer = g->d == 128 && g->B == 64 && slim(work_groups, ks, mapping);
+    const int order = mapping >= 2 ? text_slots + per_xcd : per_xcd;     // slots of an XCD
+    const TailSplit tail = lse || ks > 1 ? TailSplit{0, 1, 1} : tail_split(g, s, K_max, order, mapping >= 2 ? text_slots : 0, ts, one_buffer, scratch_bytes);
+    dim3 grid(unsigned(8 * (order + tail.rows * (tail.splits - 1))));
 #define ATTN_X(DD, BB, XX, KS, SLIM)                                                                                            \
   attn_bf16_kernel<DD, BB, XX, KS, SLIM><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
                                                         static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                 \
                                                         static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,         \
                                                         g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe, \
-                                                        part, tickets, ts.splits, ts.blocks)
+                                                        part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits)
 #define ATTN(DD, BB, KS, SLIM) do { if (lse) ATTN_X(DD, BB, true, KS, SLIM); else ATTN_X(DD, BB, false, KS, SLIM); } while (0)
 #define ATTN_KS(DD, BB) do { if (ks == 2) ATTN(DD, BB, 2, false); else ATTN(DD, BB, 1, false); } while (0)
     if (g->d == 64) { if (g->B == 64) ATTN_KS(64, 64); else ATTN_KS(64, 128); }
     else if (g->B == 128) ATTN_KS(128, 128);
-    else if (slim(work_groups, ks, mapping)) ATTN(128, 64, 1, true);
+    else if (one_buffer) ATTN(128, 64, 1, true);
     else ATTN_KS(128, 64);
 #undef ATTN_KS
 #undef ATTN

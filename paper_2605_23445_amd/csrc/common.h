@@ -55,8 +55,11 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
                     const int32_t* row_index, void* scratch, size_t scratch_bytes, hipStream_t st);
 // row_index (may be NULL): Q and O in source order.  scratch (may be NULL): room to split text rows over work-groups; its
-// first text_tickets() words are zero when the kernel starts.
-inline size_t text_tickets(const dfs_geom* g, const dfs_sizes& s) { return size_t(g->heads) * s.M_x; }
+// first split_tickets() words are zero when the kernel starts: one per text block, and with 512 query blocks and more one for each
+// that the last round of work-groups may share (at most 127 per XCD).
+inline size_t split_tickets(const dfs_geom* g, const dfs_sizes& s) {
+  return size_t(g->heads) * s.M_x + (int64_t(g->heads) * s.M >= 512 ? 8 * 128 : 0);
+}
 int run_unperm(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* o_perm, const int32_t* inv, void* o,
                hipStream_t st);
 size_t ws_block_score(const dfs_geom* g, const dfs_sizes& s);
