@@ -54,18 +54,21 @@ __device__ __forceinline__ void group_scale(float gmax, float& up, float& down) 
   }
 }
 
-// Layout of Q_hat and K_hat: per head, tiles of 32 sub-blocks (the last one with what is left, `rows`), a tile chunk by chunk as
+// Layouts of Q_hat and K_hat.  For the two-kernel contraction, row after row, [2][D] fp16 (hi, lo planes).  For the one-kernel
+// form (`tiled`), per head, tiles of 32 sub-blocks (the last one with what is left, `rows`), a tile chunk by chunk as
 // the matrix instructions' operands want it, [2 D / 8][rows][8] fp16: chunks 0 .. D / 8 - 1 are features 8 c .. 8 c + 7 of the hi
-// plane, the others of the lo plane.  The lanes of an operand load, one row each, then read a kilobyte in one piece; with
-// whole rows behind one another they read 16 bytes of 32 rows.  A refresh
-// of 2 565 tokens x 12 heads, d = 64, blocks of 64, 36.5 -> 35.5 us; 75 600 tokens x 40 heads, sub-blocks of 16, 22.9 ms the same.
+// plane, the others of the lo plane.  The lanes of an operand load, one row each, then read a kilobyte
+// in one piece; with whole rows behind one another they read 16 bytes of 32 rows: 2 565 tokens x 12 heads, d = 64, blocks of 64,
+// 36.5 -> 35.5 us a refresh.  It costs the pooling, which writes rows of a tile in pieces of 64 bytes, 4 % where it is an HBM stream
+// (75 600 tokens x 40 heads 399 -> 418 us for Q and K), and the two-kernel contraction, which goes through LDS, would gain 2 %
+// (184 -> 181).
 __host__ __device__ __forceinline__ int tile_rows(int M_s, int t) { return M_s - 32 * t < 32 ? M_s - 32 * t : 32; }
 template <int D> __device__ __forceinline__ int64_t tile_at(int t) { return int64_t(t) * (32 * 2 * D); }      // elements
 template <int D> __device__ __forceinline__ int chunk_at(int p, int c, int rows, int n) { return ((p * (D / 8) + c) * rows + n) * 8; }
 
 // One wave per sub-block.  Lanes of a row sit side by side (16 bytes each); several rows are in
 // flight per load; partial sums of the row groups are folded with cross-lane exchanges.
-// Output: the hi and lo fp16 planes of the row times its group's scale (layout above); the inverse scale of group s / 4 goes
+// Output: the hi and lo fp16 planes of the row times its group's scale (layouts above); the inverse scale of group s / 4 goes
 // to q_down / k_down.
 // blockIdx.z: 0 pools Q, 1 pools K, 2 only reorders V.  With an index (the permutation) the tensors come in source
 // order and their rows are gathered; K (if k_out) and V are written out in the reordered layout on the way (pads as
@@ -79,7 +82,7 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in
                                                    uint16_t* __restrict__ q_hat, uint16_t* __restrict__ k_hat,
                                                    float* __restrict__ q_down, float* __restrict__ k_down,
                                                    const int32_t* __restrict__ index, void* __restrict__ k_out, void* __restrict__ v_out,
-                                                   int64_t N_src, int64_t N_pad, int64_t N_v, int Bs, int M_s, float q_scale,
+                                                   int64_t N_src, int64_t N_pad, int64_t N_v, int Bs, int M_s, float q_scale, bool tiled,
                                                    int32_t* __restrict__ zero, int n_zero) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
     for (int i = threadIdx.x; i < n_zero; i += 256) zero[i] = 0;
@@ -162,7 +165,8 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in
   if (threadIdx.x == 0) (blockIdx.z == 0 ? q_down : k_down)[int64_t(head) * ((M_s + 3) / 4) + blockIdx.x] = down;
   if (rg == 0) {
     const int in_tile = tile_rows(M_s, s / 32);
-    uint16_t* o = dst + int64_t(head) * M_s * (2 * D) + tile_at<D>(s / 32) + chunk_at<D>(0, c * EPL / 8, in_tile, s % 32) + c * EPL % 8;
+    uint16_t* o = dst + int64_t(head) * M_s * (2 * D) +
+                  (tiled ? tile_at<D>(s / 32) + chunk_at<D>(0, c * EPL / 8, in_tile, s % 32) + c * EPL % 8 : int64_t(s) * (2 * D) + c * EPL);
     uint16_t hi[EPL], lo[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) split2(acc[e] * up, hi[e], lo[e]);
@@ -174,7 +178,7 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in
       l2[e / 2] = uint32_t(lo[e]) | (uint32_t(lo[e + 1]) << 16);
     }
     *reinterpret_cast<pairs*>(o) = h2;
-    *reinterpret_cast<pairs*>(o + chunk_at<D>(1, 0, in_tile, 0)) = l2;
+    *reinterpret_cast<pairs*>(o + (tiled ? chunk_at<D>(1, 0, in_tile, 0) : D)) = l2;
   }
 }
 
@@ -227,10 +231,11 @@ score_lse_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict_
                  const float* __restrict__ k_down, float* __restrict__ tt, float* __restrict__ lse, int M_s, int n_live, int tiles_per_split, int ksplit,
                  int wgs_per_head, int total_wgs, int wgs_per_xcd) {
   constexpr int RS = 2 * D;                   // elements of a centroid row (hi, lo planes)
+  constexpr int RSP = RS + 8;                 // LDS row stride: 16 bytes of skew keep the row-per-lane reads conflict-free
   constexpr int KS = D / 16;                  // product steps of 16 features
-  constexpr int CPT = 32 * RS / 8 / 256;      // 16-byte chunks of a key tile per thread (4 at d = 128)
+  constexpr int CPT = 32 * RS / 8 / 256;      // 16-byte chunks of a key tile per thread (6 at d=128)
   constexpr int G = R < 4 ? R : 4;            // key sub-blocks of one key block that sit in consecutive registers
-  __shared__ __attribute__((aligned(16))) uint16_t s_k[2][32 * RS];      // chunk by chunk, 32 rows each
+  __shared__ __attribute__((aligned(16))) uint16_t s_k[2][32 * RSP];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = lane & 31, half = lane >> 5;
   // Work-group ids are dealt round-robin to the 8 XCDs, each with an L2 of its own.  Every XCD takes a contiguous
@@ -256,7 +261,7 @@ score_lse_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict_
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
         u32x4 v = {0u, 0u, 0u, 0u};
-        if (row < M_s) v = *reinterpret_cast<const u32x4*>(qh + tile_at<D>(i0 / 32) + chunk_at<D>(p, 2 * kk + half, tile_rows(M_s, i0 / 32), n));
+        if (row < M_s) v = *reinterpret_cast<const u32x4*>(qh + int64_t(row) * RS + p * D + 16 * kk + 8 * half);
         bq[p][kk] = __builtin_bit_cast(f16x8, v);
       }
   }
@@ -264,18 +269,24 @@ score_lse_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict_
   const int t_begin = split * tiles_per_split;
   const int t_end = t_begin + tiles_per_split < n_tiles ? t_begin + tiles_per_split : n_tiles;
 
-  // key tile t -> registers -> LDS
+  // key tile t (32 centroid rows, contiguous in memory) -> registers -> LDS
   u32x4 kreg[CPT];
   auto fetch = [&](int t) {
-    // rows at or beyond M_s re-read the last row instead (no branch): they are at or beyond n_live and masked later
-    const int rows = tile_rows(M_s, t), row = tid % 32 < rows ? tid % 32 : rows - 1;
-    const uint16_t* kt = kh + tile_at<D>(t) + row * 8;
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) kreg[i] = *reinterpret_cast<const u32x4*>(kt + (tid / 32 + i * 8) * rows * 8);
+    for (int i = 0; i < CPT; ++i) {
+      // rows at or beyond M_s re-read the last row instead (no branch): they are at or beyond n_live and masked later
+      const int c = tid + i * 256;
+      const int row = t * 32 + c / (RS / 8);
+      const int from = row < M_s ? row : M_s - 1;
+      kreg[i] = *reinterpret_cast<const u32x4*>(kh + int64_t(from) * RS + (c % (RS / 8)) * 8);
+    }
   };
   auto commit = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) *reinterpret_cast<u32x4*>(&s_k[buf][(tid + i * 256) * 8]) = kreg[i];
+    for (int i = 0; i < CPT; ++i) {
+      const int c = tid + i * 256;
+      *reinterpret_cast<u32x4*>(&s_k[buf][(c / (RS / 8)) * RSP + (c % (RS / 8)) * 8]) = kreg[i];
+    }
   };
   float m_row = LSE_START, z_row = 0.f;       // this lane's share of the row log-sum-exp of query sub-block i0 + n
   const int q_row = i0 + n;
@@ -306,17 +317,16 @@ score_lse_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict_
   //     give 2^-inf = 0; R == 8: a key block is split over the two lane halves, which therefore share the
   //     reference); then per key block the log of its summed exponentials.
   constexpr int NS = 3 * KS;                  // matrix instructions of a tile
-  const int lane_at = chunk_at<D>(0, half, 32, n);
   auto stage = [&](auto do_mm, auto do_ep, int t, int buf, f32x16& c0, f32x16& c1, float (&dn_next)[4], const f32x16& p0,
                    const f32x16& p1, const float (&dn_prev)[4], int tp) {
     constexpr bool MM = decltype(do_mm)::value, EP = decltype(do_ep)::value;
-    const uint16_t* krow = &s_k[buf][lane_at];
+    const uint16_t* krow = &s_k[buf][n * RSP + 8 * half];
     f16x8 fr[2][4];
     auto load_pair = [&](int p) {
-      fr[p & 1][0] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + chunk_at<D>(0, 4 * p, 32, 0)));
-      fr[p & 1][1] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + chunk_at<D>(1, 4 * p, 32, 0)));
-      fr[p & 1][2] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + chunk_at<D>(0, 4 * p + 2, 32, 0)));
-      fr[p & 1][3] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + chunk_at<D>(1, 4 * p + 2, 32, 0)));
+      fr[p & 1][0] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + 32 * p));
+      fr[p & 1][1] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + D + 32 * p));
+      fr[p & 1][2] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + 32 * p + 16));
+      fr[p & 1][3] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(krow + D + 32 * p + 16));
     };
     float dp[4], c[16];
     float mt = 0.f, m_new = 0.f, zt = 0.f;
@@ -801,7 +811,7 @@ int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
   const bool bf = dtype == DFS_BF16;
   // 1/sqrt(d) of Eq. 2 and the change to base 2 go into Q_hat, so that the logits come out of the contraction in base 2
   const float scale = 1.4426950408889634f / sqrtf(float(g->d));
-#define POOL(BF, DD) pool_kernel<BF, DD><<<pg, 256, 0, st>>>(q_perm, k_perm, v, q_hat, k_hat, q_down, k_down, index, k_out, v_out, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale, zero, n_zero)
+#define POOL(BF, DD) pool_kernel<BF, DD><<<pg, 256, 0, st>>>(q_perm, k_perm, v, q_hat, k_hat, q_down, k_down, index, k_out, v_out, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale, score_small(g, s), zero, n_zero)
   if (g->d == 64) { if (bf) POOL(true, 64); else POOL(false, 64); }
   else            { if (bf) POOL(true, 128); else POOL(false, 128); }
 #undef POOL
