@@ -59,7 +59,8 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
 // Text rows keep every block and are many times longer than the others; where too few of the others follow to hide
 // them, SPLIT work-groups share one text block, each with a run of its list.  They leave their unnormalised sums in
 // `part`; the one that takes the last ticket merges them, in list order, so the result does not depend on who is last.
-// The query blocks of the last round of work-groups are shared in the same way where they would leave slots idle (tail_split).
+// The query blocks of the last round of work-groups are shared in the same way where they would leave slots idle (tail_split),
+// by an instance of its own (TAIL): the work behind it costs every work-group some 0.3 us on its way to the list.
 // (Only calls without log-sum-exp are given a `part`.)
 //
 // KS: where the query blocks are too few to give every SIMD its two waves, KS groups of waves share one query block, each
@@ -71,7 +72,7 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
 // ahead instead of a tile.  See `slim` below for the rule.
 template <int D, int BM, bool XLSE, int KS>
 constexpr int attn_waves() { return D == 64 && BM == 128 && !XLSE && KS == 1 ? 3 : 2; }
-template <int D, int BM, bool XLSE, int KS, bool SLIM = false>
+template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL>
 __global__ void __launch_bounds__(BM * 2 * KS)
 __attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE, KS>(), attn_waves<D, BM, XLSE, KS>())))
 attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -91,6 +92,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   constexpr float HEADROOM = 4.f, SUM_LIMIT = 2.25f;                      // see "A row's reference" below
   // Two K and two V tile buffers per group (tile t lives in the pair of parity t & 1), at fixed byte offsets.
   static_assert(!SLIM || KS == 1, "the merge of wave groups wants all four buffers");
+  static_assert(!TAIL || (KS == 1 && !XLSE), "see run_sparse_attn");
   __shared__ __attribute__((aligned(16))) uint16_t tiles[KS * (SLIM ? 2 : 4) * TILE];
   constexpr int K0 = 0, K1 = SLIM ? 0 : 2 * TILE, V0 = SLIM ? 2 * TILE : 4 * TILE, V1 = SLIM ? 2 * TILE : 6 * TILE;
 
@@ -107,7 +109,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // Behind slot tail_from, where the query blocks left would not fill the XCD once more, tail_splits work-groups share each.
   int head, u, split = 0, splits = 1, slot = blockIdx.x / 8;
   const int xcd = blockIdx.x % 8;
-  const bool tail = !XLSE && tail_splits > 1 && slot >= tail_from;
+  const bool tail = TAIL && slot >= tail_from;
   if (tail) {
     splits = tail_splits;
     split = (slot - tail_from) / tail_rows;
@@ -977,19 +979,21 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     const int order = mapping >= 2 ? text_slots + per_xcd : per_xcd;     // slots of an XCD
     const TailSplit tail = lse || ks > 1 ? TailSplit{0, 1, 1} : tail_split(g, s, K_max, order, mapping >= 2 ? text_slots : 0, ts, one_buffer, scratch_bytes);
     dim3 grid(unsigned(8 * (order + tail.rows * (tail.splits - 1))));
-#define ATTN_X(DD, BB, XX, KS, SLIM)                                                                                            \
-  attn_bf16_kernel<DD, BB, XX, KS, SLIM><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
+#define ATTN_X(DD, BB, XX, KS, SLIM, TAIL)                                                                                            \
+  attn_bf16_kernel<DD, BB, XX, KS, SLIM, TAIL><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
                                                         static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                 \
                                                         static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,         \
                                                         g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe, \
                                                         part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits)
-#define ATTN(DD, BB, KS, SLIM) do { if (lse) ATTN_X(DD, BB, true, KS, SLIM); else ATTN_X(DD, BB, false, KS, SLIM); } while (0)
-#define ATTN_KS(DD, BB) do { if (ks == 2) ATTN(DD, BB, 2, false); else ATTN(DD, BB, 1, false); } while (0)
+#define ATTN(DD, BB, KS, SLIM) do { if (lse) ATTN_X(DD, BB, true, KS, SLIM, false); else ATTN_X(DD, BB, false, KS, SLIM, false); } while (0)
+#define ATTN_1(DD, BB, SLIM) do { if (tail.splits > 1) ATTN_X(DD, BB, false, 1, SLIM, true); else ATTN(DD, BB, 1, SLIM); } while (0)
+#define ATTN_KS(DD, BB) do { if (ks == 2) ATTN(DD, BB, 2, false); else ATTN_1(DD, BB, false); } while (0)
     if (g->d == 64) { if (g->B == 64) ATTN_KS(64, 64); else ATTN_KS(64, 128); }
     else if (g->B == 128) ATTN_KS(128, 128);
-    else if (one_buffer) ATTN(128, 64, 1, true);
+    else if (one_buffer) ATTN_1(128, 64, true);
     else ATTN_KS(128, 64);
 #undef ATTN_KS
+#undef ATTN_1
 #undef ATTN
 #undef ATTN_X
   } else {
