@@ -355,10 +355,12 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     l_acc = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(row_ones, __builtin_bit_cast(bf16x16, both), l_acc, row_pick, 0, 0);
   };
   // A half tile's weights pc have been added to the row sums l_acc; xsum: the sum of the unrounded ones.  If a row of the wave
-  // has outgrown its reference, the rows that have grown at all move (logits sx) and the half tile is summed again.
+  // has outgrown its reference, the rows that have grown at all move (logits sx) and the half tile is summed again.  The
+  // comparison is one that a NaN does not pass: where rows n and 16 + n both reach infinite weights, each sum holds the other's
+  // infinity times a stored zero.
   auto settle = [&](const f32x16& sx, u32x4 (&pc)[2], float xsum) __attribute__((always_inline)) {
     float l_new = l_acc[0] + l_acc[1];
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(l_new - l_run > SUM_LIMIT) != 0, 0)) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(l_new - l_run <= SUM_LIMIT)) != 0, 0)) {
       const float mx = fmaf(half_max(sx), c2, HEADROOM);
       const float m_new = mx > m_run ? mx : m_run;   // not fmaxf: a NaN leaves the reference where it is
       float alpha = __builtin_amdgcn_exp2f(m_run - m_new);

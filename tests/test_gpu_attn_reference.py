@@ -139,3 +139,51 @@ def test_large_values_under_steep_logits(d, B, jump):
     q, k, v = q.bfloat16(), k.bfloat16(), (v * 2.0 ** 100).bfloat16()
     want = torch.softmax(q.double() @ k.double().transpose(1, 2).contiguous() / math.sqrt(d), -1) @ v.double()
     assert _rel(_dense(g, q, k, v)[0], want) <= 7.5e-3
+
+
+@pytest.mark.parametrize("d,B", SHAPES)
+@pytest.mark.parametrize("heads", [1, 200])              # shared by wave groups or not; above 512 work-groups, one buffer each at (128, 64)
+@pytest.mark.parametrize("jump", [140, 200, 1000])
+def test_weights_that_overflow_in_every_row_at_once(d, B, heads, jump):
+    """A key block so far above the reference that all rows of a wave reach infinite weights in the same half tile: the row sums
+    multiply the weights of rows n and n + 16 by zeros of one another's, so that both come out as NaN, and the half tile has
+    to be done again all the same."""
+    g = P.Geom(1, 1, 3 * B, 0, heads, d, B, B // 4)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(jump)
+    q, k, v = (torch.randn(1, 3 * B, d, generator=gen, device="cuda") for _ in range(3))
+    q[:, :, 0] = 8.0
+    k[:, :, 0] = (torch.arange(3 * B, device="cuda") // B == 1) * jump * math.sqrt(d) / (8 * math.log2(math.e))
+    rows = torch.arange(3 * B, device="cuda") // B != 1  # the others' own block, where their reference starts, is the high one
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    logits = q[0].double() @ k[0].double().t().contiguous() / math.sqrt(d)
+    want, want_lse = torch.softmax(logits, -1) @ v[0].double(), torch.logsumexp(logits, -1)
+    q, k, v = (x.expand(heads, -1, -1).contiguous() for x in (q, k, v))
+    for with_lse in (True, False):
+        o, lse = _dense(g, q, k, v, with_lse)
+        for r in (rows, ~rows):
+            assert _rel(o[:, r], want[r].expand(heads, -1, -1)) <= 7.5e-3
+        if with_lse:                                       # the bound of the first test
+            assert float((lse.double() - want_lse).abs().max()) <= 1e-4 + 2.0 ** -20 * float(want_lse.abs().max())
+
+
+@pytest.mark.parametrize("jump", [140, 1000])
+def test_weights_that_overflow_where_the_last_round_is_shared(jump):
+    """As above through dfs_forward, 520 query blocks: eight of them are shared by several work-groups."""
+    g = P.Geom(5, 16, 64, 0, 13, 128, 128, 32)
+    s = P.dfs_geom_sizes(g)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(jump)
+    q, k, v = (torch.randn(13, s.N, 128, generator=gen, device="cuda") for _ in range(3))
+    perm_pad, inv, _ = G.gpu_perm(g)
+    q[:, :, 0] = 8.0
+    k[:, :, 0] = (inv // 128 % 20 == 11) * jump * math.sqrt(128) / (8 * math.log2(math.e))
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    st = P.MaskState(torch.zeros((13, s.M, s.M), dtype=torch.int32, device="cuda"), torch.full((13, s.M), s.M, dtype=torch.int32, device="cuda"),
+                     None, None, s.M)                      # K_max = M: three work-groups to each of the eight
+    o = torch.full_like(q, 7.0)
+    P.dfs_forward(g, P.DFS_BF16, q, k, v, perm_pad, inv, False, P.DFS_SELECT_TOPK, 0.5, 0.0, st, 128 ** -0.5, o,
+                  G.ws_tensor(P.dfs_workspace_bytes(g, P.DFS_WS_FORWARD_BF16)))
+    for h in range(13):
+        want = torch.softmax(q[h].double() @ k[h].double().t().contiguous() * 128 ** -0.5, -1) @ v[h].double()
+        assert _rel(o[h], want) <= 7.5e-3
