@@ -21,8 +21,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -191,18 +189,15 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // reference in the base-2 exponent's units (logit x c2), row sum, row sum of the unrounded probabilities (XLSE only)
   float m_run = 0.f, l_run = 0.f, x_run = 0.f;
   // Row sums of the probabilities as rounded to bf16 (numerator and denominator then use exactly the same weights, so
-  // a dominant key leaves no systematic rounding bias), on the matrix cores: one 16x16x64 product with a 2:4 sparse operand
-  // takes both B operands of a half tile's value products at once.  Lanes 16 g + n hold what it reads for column n; stored
-  // elements 0 .. 3 of a row of the sparse operand meet groups 0 and 2, elements 4 .. 7 groups 1 and 3, which are the query
-  // rows n and 16 + n.  With ones for the pair that holds the query row of the result's own group, and even result rows picking
-  // the first, odd ones the last two of every four weights, the first two registers of every lane's result add up to the sum over
-  // both lane halves of its own query row.  16 matrix cycles per half tile, and one result to wait for; two 16x16x32 products with
-  // ones took 32: 75 600 tokens, d = 128, dense 96.4 -> 94.7 ms, 60 of 591 blocks 11.57 -> 11.54, with log-sum-exp 11.77 ->
-  // 11.55; d = 64, 17 550 tokens x 48 heads 0.672 -> 0.670.
-  const uint32_t even_pair = ((lane >> 2) & 1) == 0 ? 0x3F803F80u : 0u, odd_pair = even_pair ^ 0x3F803F80u;
-  const bf16x8 row_ones = __builtin_bit_cast(bf16x8, u32x4{even_pair, even_pair, odd_pair, odd_pair});
-  const int row_pick = (lane & 1) ? 0xEEEE : 0x4444;
-  f32x4 l_acc = {0.f, 0.f, 0.f, 0.f};
+  // a dominant key leaves no systematic rounding bias), on the matrix cores: a 16x16x32 product takes the same B operand
+  // registers as the 32x32x16 one, but reads lanes 16 g + n as keys 8 g .. 8 g + 7 of column n.  With ones where the
+  // parity of the key group equals that of the result row's group, every lane's result is the sum over both lane
+  // halves of its own query row.  Every half tile is summed from zero and added to the row's sum on the vector unit: a matrix
+  // instruction that accumulates the row's sum rounds each weight against it, and a long row of small weights behind large
+  // ones loses 3e-4 to 5e-4 of the sum (131 072 keys; this form below 1.2e-4); it was one 2:4 sparse product of half the
+  // matrix cycles, 1.0 % faster on 75 600 tokens dense and on 60 of 591 blocks, 0.8 % at d = 64.
+  const uint32_t one_pair = (((lane >> 4) ^ (lane >> 2)) & 1) == 0 ? 0x3F803F80u : 0u;
+  const bf16x8 row_ones = __builtin_bit_cast(bf16x8, u32x4{one_pair, one_pair, one_pair, one_pair});
   const float c2 = scale * 1.4426950408889634f;     // softmax in base 2
 
   // Tile loads, global memory straight into LDS: instruction j of this wave fills the 64 consecutive
@@ -329,8 +324,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // A row's reference m_run is a maximum of its logits times 2^HEADROOM: to start with that of its first half tile and of
   // its own 32 keys, where many rows have their largest logit; later that of a half tile whose weights sum to more than
   // SUM_LIMIT.  32 weights of 2^-HEADROOM sum to 2, so a row moves when one weight has grown by 2^5.2 or many have by less,
-  // and raises its reference by at least an eighth.  The sums come from the matrix cores, so that watching them costs three
-  // vector instructions per half tile, two additions and a comparison (a running maximum and its factor: some fifteen), and
+  // and raises its reference by at least an eighth.  The sums come from the matrix cores, so that watching them costs two
+  // vector instructions per half tile, an addition and a comparison (a running maximum and its factor: some fifteen), and
   // `settle` does the half tile again when a row moves: about 1 % of the half tiles of a wave at 75 600 tokens, 2 % at
   // 17 550, 5 % in rows of 13 blocks of 64.
   // Weights are then below SUM_LIMIT whatever comes, and exact in bf16 where they are largest, which is what the reference
@@ -350,17 +345,15 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const bf16x2 pk = {(__bf16)a, (__bf16)b};
     return __builtin_bit_cast(uint32_t, pk);
   };
-  auto add_sums = [&](const u32x4 (&p)[2]) __attribute__((always_inline)) {
-    const u32x8 both = __builtin_shufflevector(p[0], p[1], 0, 1, 2, 3, 4, 5, 6, 7);
-    l_acc = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(row_ones, __builtin_bit_cast(bf16x16, both), l_acc, row_pick, 0, 0);
+  auto half_sum = [&](const u32x4& p, f32x4 sum) __attribute__((always_inline)) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, __builtin_bit_cast(bf16x8, p), sum, 0, 0, 0);
   };
-  // A half tile's weights pc have been added to the row sums l_acc; xsum: the sum of the unrounded ones.  If a row of the wave
-  // has outgrown its reference, the rows that have grown at all move (logits sx) and the half tile is summed again.  The
-  // comparison is one that a NaN does not pass: where rows n and 16 + n both reach infinite weights, each sum holds the other's
-  // infinity times a stored zero.
-  auto settle = [&](const f32x16& sx, u32x4 (&pc)[2], float xsum) __attribute__((always_inline)) {
-    float l_new = l_acc[0] + l_acc[1];
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(l_new - l_run <= SUM_LIMIT)) != 0, 0)) {
+  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  // Adds a half tile's sums (`sum` of the rounded weights pc, xsum of the unrounded) to the row's.  If a row of the wave has
+  // outgrown its reference, the rows that have grown at all move first (logits sx).  The comparison is one that a NaN does not
+  // pass: where rows n and 16 + n both reach infinite weights, each sum holds the other's infinity times a zero.
+  auto settle = [&](const f32x16& sx, u32x4 (&pc)[2], f32x4 sum, float xsum) __attribute__((always_inline)) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(sum[0] <= SUM_LIMIT)) != 0, 0)) {
       const float mx = fmaf(half_max(sx), c2, HEADROOM);
       const float m_new = mx > m_run ? mx : m_run;   // not fmaxf: a NaN leaves the reference where it is
       float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -387,16 +380,14 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         pc[i / 8][(i % 8) / 2] = pack(a, b);
         if (XLSE) xsum += a + b;
       }
-      l_acc = f32x4{l_run, 0.f, 0.f, 0.f};
-      add_sums(pc);
-      l_new = l_acc[0] + l_acc[1];
-      asm volatile("" : "+v"(l_acc));                 // one home as well
+      sum = half_sum(pc[1], half_sum(pc[0], zero4));
+      asm volatile("" : "+v"(sum));                   // one home as well
     }
-    l_run = l_new;
+    l_run += sum[0];
     if (XLSE) x_run += xsum;
   };
   auto stage = [&](auto do_pv, auto do_s, int vbuf, int pv_half, const u32x4 (&pp)[2], int kbuf,
-                   int s_half, f32x16& sn, const f32x16& sx, u32x4 (&pc)[2], float& xsum, auto mem) __attribute__((always_inline)) {
+                   int s_half, f32x16& sn, const f32x16& sx, u32x4 (&pc)[2], f32x4& sum, float& xsum, auto mem) __attribute__((always_inline)) {
     constexpr bool DO_PV = decltype(do_pv)::value, DO_S = decltype(do_s)::value;
     bf16x8 frag[NF];
     auto load = [&](int f) {
@@ -447,7 +438,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 #pragma unroll
         for (int i = (ESL - 1) * 16 / ESL; i < 16; ++i) asm volatile("" : "+v"(pc[i / 8][(i % 8) / 2]));
       }
-      if (f == NF - 1) add_sums(pc);
+      if (f == NF - 2) sum = half_sum(pc[0], zero4);
+      if (f == NF - 1) sum = half_sum(pc[1], sum);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -480,12 +472,13 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       };
     };
     // first half: products of (t-1, 1), logits of (t, 1), probabilities of (t, 0)
+    f32x4 sum;
     float xsum;
-    stage(std::integral_constant<bool, !FIRST>{}, yes{}, v_nxt, 1, p1, k_cur, 1, s1, s0, p0, xsum, request(0));
+    stage(std::integral_constant<bool, !FIRST>{}, yes{}, v_nxt, 1, p1, k_cur, 1, s1, s0, p0, sum, xsum, request(0));
     mask_pads(b_cur, t, 1, s1);
     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wave's parts of K(t+1) and V(t) landed
     __syncthreads();                                 // all parts landed; every wave is past the first half of tile t
-    settle(s0, p0, xsum);
+    settle(s0, p0, sum, xsum);
     // Second half: products of (t, 0), logits of (t+1, 0), probabilities of (t, 1); between its matrix instructions the
     // loads of K(t+2) and V(t+1) (in one run behind the barrier they kept the matrix cores waiting for some fifty
     // instructions: +2.0 % on lists that hit in L2, +2.5 % on scattered ones, +4.7 % dense at d = 128).  Behind the
@@ -493,18 +486,18 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int b_new = tile_block(t + 2 < n_tiles ? t + 2 : n_tiles - 1);
     const uint64_t k_src = tile_src(kh, t + 2, b_new), v_src = tile_src(vh, t + 1, b_nxt);
     if constexpr (SLIM) {
-      stage(yes{}, std::integral_constant<bool, !LAST>{}, V0, 0, p0, K0, 0, s0, s1, p1, xsum, request(1));
+      stage(yes{}, std::integral_constant<bool, !LAST>{}, V0, 0, p0, K0, 0, s0, s1, p1, sum, xsum, request(1));
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
     } else {
-      stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1, xsum, [&](int f) {
+      stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1, sum, xsum, [&](int f) {
         if (LAST) return;
 #pragma unroll
         for (int j = f * 2 * LPW / NF; j < (f + 1) * 2 * LPW / NF; ++j)
           issue_one(j < LPW ? v_src : k_src, j < LPW ? v_nxt : k_cur, j < LPW, j % LPW);
       });
     }
-    settle(s1, p1, xsum);
+    settle(s1, p1, sum, xsum);
     if (!LAST) mask_pads(b_nxt, t + 1, 0, s0);
     b_cur = b_nxt;
     b_nxt = b_new;

@@ -187,3 +187,31 @@ def test_weights_that_overflow_where_the_last_round_is_shared(jump):
     for h in range(13):
         want = torch.softmax(q[h].double() @ k[h].double().t().contiguous() * 128 ** -0.5, -1) @ v[h].double()
         assert _rel(o[h], want) <= 7.5e-3
+
+
+@pytest.mark.parametrize("d,B,below", [(64, 64, 20), (64, 64, 22), (64, 128, 19), (64, 128, 21), (128, 64, 20), (128, 64, 22), (128, 128, 19), (128, 128, 21)])
+def test_small_weights_behind_large_ones_are_counted(d, B, below):
+    """131 072 keys, those behind the first block 2^-below as heavy: each half tile of them weighs about as much as the last
+    place of the row's sum.  Only the first block has values, so that the outputs are inverse to the row sums.  4 096 half
+    tiles, each added with an error of half a last place, 2^-24 of the sum, at most; the outputs' own rounding averages out
+    over 8 192 rows."""
+    N = 131072
+    g = P.Geom(1, 256, 512, 0, 1, d, B, B // 4)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(below)
+    q, k = (0.3 * torch.randn(1, N, d, generator=gen, device="cuda") for _ in range(2))
+    q[:, :, 0] = 8.0
+    k[:, :, 0] = 0.0
+    k[:, B:, 0] = -below * math.sqrt(d) / (8 * math.log2(math.e))
+    v = 1 + torch.rand(1, N, d, generator=gen, device="cuda")
+    v[:, B:] = 0.0
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    kd, vd = k[0].double().t().contiguous(), v[0].double()
+    want = torch.cat([torch.softmax(x.double() @ kd / math.sqrt(d), -1) @ vd for x in q[0, :8192].split(2048)])
+    cnt = torch.full((1, N // B), N // B, dtype=torch.int32, device="cuda")
+    st = P.MaskState(torch.zeros((1, N // B, 1), dtype=torch.int32, device="cuda"), cnt, None, None, 1)
+    for with_lse in (False, True):
+        o = G.gpu_attn(g, P.DFS_BF16, q, k, v, st, want_lse=with_lse)[0]
+        off = float((o[0, :8192].double() / want - 1).mean())
+        print(f"d={d} B={B} below={below} lse={with_lse}: {off:+.2e}", flush=True)
+        assert abs(off) <= 4096 * 2.0 ** -24
