@@ -194,7 +194,9 @@ int dfs_select_mask_static(const dfs_geom* g, const float* score, int mode, doub
  * bf16: products on the matrix cores, fp32 accumulation and softmax, output rounded to bf16.
  * f32:  fp32 throughout.
  * A row whose kept logits are all -inf is zero in bf16 and NaN in f32, its lse -inf.  An infinite value of V gives an
- * infinite or NaN output in the rows that keep its block and nothing elsewhere.  The same call gives the same bits every
+ * infinite or NaN output in the rows that keep its block and nothing elsewhere.  A query row with a NaN logit is NaN, its
+ * lse -inf in bf16.  In bf16 it shares a matrix product with the row 16 before or behind it in its 32 rows of q_perm (pad
+ * rows count), whose output is then zero; the others of the 32 may round differently.  The same call gives the same bits every
  * time; the same head alone, in a batch, or with another K_max may differ by rounding, because the number of waves and
  * work-groups that share a row, and with it the order of its sums, follows from heads, M and K_max.
  *   q_perm, k_perm, v_perm [heads, N_pad, d] in;  o_perm [heads, N_pad, d] out (pad rows unspecified).
@@ -254,8 +256,11 @@ typedef struct {
  * One call of Algorithm 1 for one layer: reorder Q, K, V; if `refresh` is non-zero recompute the
  * block mask into `st` (scoring + selection as above), otherwise reuse it (Sec. 5.3: masks are
  * refreshed every Delta steps, outputs are recomputed every step); block-sparse attention; inverse
- * reorder.  perm_pad / inv come from dfs_hilbert_perm.  Text rows may differ from the staged calls' by rounding (their
- * keys are split over work-groups here).  `scale` is not checked: f32 tensors take any, bf16 tensors need it positive.
+ * reorder.  perm_pad / inv come from dfs_hilbert_perm.  bf16 rows may differ from the staged calls' by rounding where
+ * several work-groups share a query block's keys, which only this call has room for: text blocks (16 blocks and more in
+ * all), and, from 512 query blocks in all heads on, the video or text blocks that would be left over for a last round of
+ * work-groups with half and more of the chip idle.  Which these are follows from the geometry and K_max alone.
+ * `scale` is not checked: f32 tensors take any, bf16 tensors need it positive.
  *   q, k, v [heads, N, d] in;  o [heads, N, d] out.   ws: DFS_WS_FORWARD (f32) or DFS_WS_FORWARD_BF16.
  */
 int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, const void* v,

@@ -894,10 +894,10 @@ static int key_split(int d, int B, int64_t work_groups, int K_max) {
 }
 
 // One tile buffer instead of two where the work-groups are more than two per CU (kernel's SLIM, d = 128, 64 rows).  Measured (two
-// buffers over one, whole calls): 528 work-groups x 14 of 88 blocks 53.9 -> 41.6 us, 1 056 78.8 -> 75.4, 6 600 x 42 of 275 763 ->
-// 733, dense 4 030 -> 3 700, 704 dense with log-sum-exp 1 072 -> 957; 328 work-groups 24.6 -> 27.6, 352 dense 97.5 -> 137.  Not for
-// sequences that all XCDs walk together (mapping 2), whose lists come from beyond L2: 2 364 work-groups x 178 of 1 182 blocks 1 028 ->
-// 1 055, 14 184 6 223 -> 7 374.
+// buffers over one, whole calls): 528 work-groups x 14 of 88 blocks 48.3 -> 41.3 us, 1 056 76.5 -> 72.4, 6 600 x 42 of 275 765 ->
+// 711, dense 4 013 -> 3 630, 704 dense with log-sum-exp 182 -> 147; 328 work-groups x 14 of 82 30.5 -> 35.8, 352 dense 97 -> 136.  Not
+// for sequences that all XCDs walk together (mapping 2), whose lists come from beyond L2: 2 364 work-groups x 178 of 1 182 blocks
+// 1 049 -> 1 052, 14 184 8 104 -> 8 412.
 static bool slim(int64_t work_groups, int ks, int mapping) { return ks == 1 && work_groups > 512 && mapping != 2; }
 
 // Work-groups per text block, and the key blocks each takes: about as many as a video row keeps (an eighth of all where
@@ -929,9 +929,9 @@ static TextSplit text_split(const dfs_geom* g, const dfs_sizes& s, int K_max, si
 // whole one would leave slots idle: a third of them and less at d = 128 with blocks of 128 (a lone wave per SIMD does most of
 // what two do), half and less elsewhere, pieces of four key blocks and more.  Within eight rounds: beyond, the last one is short
 // against the rest; two for the form with one buffer, whose work-groups end less evenly.  Measured (us, whole -> shared, kept of
-// blocks x heads): d = 128, 44 of 107 x 5 (1.04 rounds) 250 -> 207, 60 of 342 x 6 (4.0) 996 -> 933, 107 of 228 x 3 (1.34, two
-// pieces: whole by the rule) 573 -> 582; d = 64, 47 of 102 x 8 (1.06) 208 -> 175, 39 of 148 x 21 (4.05) 556 -> 535, blocks of 64, 63 of
-// 492 x 3 (1.44) 148 -> 132; d = 128, blocks of 64, 262 of 559 x 2 (1.09) 806 -> 667, 28 of 159 x 27 (4.19: whole by the rule) 353 -> 368.
+// blocks x heads): d = 128, 44 of 107 x 5 (1.05 rounds) 253 -> 207, 60 of 342 x 6 (4.02) 1 006 -> 942, 107 of 228 x 3 (1.34, two
+// pieces: whole by the rule) 573 -> 582; d = 64, 47 of 102 x 8 (1.06) 211 -> 181, 39 of 148 x 21 (4.06) 559 -> 542, blocks of 64, 63 of
+// 492 x 3 (1.45) 142 -> 133; d = 128, blocks of 64, 130 of 279 x 4 (1.09) 391 -> 332, 28 of 159 x 27 (4.20: whole by the rule) 353 -> 368.
 struct TailSplit { int from, rows, splits; };
 static TailSplit tail_split(const dfs_geom* g, const dfs_sizes& s, int32_t K_max, int order, int text_slots, const TextSplit& ts, bool one_buffer,
                             size_t scratch_bytes) {
