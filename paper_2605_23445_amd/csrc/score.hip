@@ -579,10 +579,10 @@ static size_t fs_lds(int M_v) { return size_t(FS_ROWS) * (256 + fs_stride(M_v)) 
 
 // Scoring of small problems in one kernel: a work-group owns 32 query sub-blocks (32 / R query blocks) of a head, its eight
 // waves take key tiles in turn, straight from memory, and T and the row sums never leave LDS.  The same sums as the two kernels
-// above, except that a row's keys are summed by eight waves; so one kernel serves the calls that want scores (`score`) and
-// those that want lists (`kv_idx`), and both decide alike.  What bounds it is latency: a tile's rows, its product chain, three
-// barriers, the selection; it saves a launch and the way of T through memory.  256 fp32 tokens x 2 heads 18.6 -> 16.3 us a
-// refresh, 2 565 + 77 tokens x 12 heads, blocks of 64, 39.2 -> 35.5 (on one box each).
+// above, except that a row's keys are summed by eight waves and its reference and sum stay apart; so one kernel serves the
+// calls that want scores (`score`) and those that want lists (`kv_idx`), and both decide alike.  What bounds it is latency: a
+// tile's rows, its product chain, three barriers, the selection; it saves a launch and the way of T through memory.  256 fp32
+// tokens x 2 heads 18.4 -> 16.6 us a refresh, 2 565 + 77 tokens x 12 heads, blocks of 64, 39.1 -> 35.5 (both sides in turn).
 constexpr int SS_T = 512, SS_WAVES = SS_T / 64, SS_STRIDE = 33;
 template <int D, int R>
 __global__ void __launch_bounds__(SS_T) score_small_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict__ k_hat,
