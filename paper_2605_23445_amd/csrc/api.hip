@@ -120,11 +120,13 @@ int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, cons
     return fail(DFS_EWORKSPACE, "dfs_forward: workspace of %zu bytes needed (256-byte aligned), got %zu", L.total, ws_bytes);
   char* base = static_cast<char*>(ws);
   hipStream_t hs = as_stream(stream);
-  // Q is gathered where it is consumed (pooling, attention) and O is scattered by the attention kernel, so only K and V
-  // are reordered: by the pooling kernel on the way on a refresh step, by one gather on a reuse step.
+  // Q is gathered where it is consumed (pooling, attention) and O is scattered by the attention kernel, and for most bf16 calls
+  // the attention gathers K and V as well (`src`).  Else these are reordered: by the pooling kernel on the way on a refresh step, by
+  // one gather on a reuse step.
   void *k_perm = base + L.kp, *v_perm = base + L.vp;
   int32_t* tickets = reinterpret_cast<int32_t*>(base + L.text);
   const int n_tickets = int(split_tickets(g, s));
+  const bool src = attn_reads_source(g, s, dtype, k, v, o);
   if (refresh) {
     float* score = reinterpret_cast<float*>(base + L.score);
     if ((rc = check_select(g, s, mode, sparsity, mass, st->K_max))) return rc;
@@ -132,16 +134,16 @@ int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, cons
     const SelectPlan sel = {dfs_keep_count(sparsity, s.M_v), k_room < s.M_v ? k_room : s.M_v, mode == DFS_SELECT_MASS_ROW ? mass : 0.0,
                             st->mask, st->kv_idx, st->kv_cnt, st->K_max, st->k_head};
     const bool in_fold = can_select_in_fold(s, mode);
-    if ((rc = run_block_score(g, s, dtype, q, k, score, base + L.sub, perm_pad, k_perm, v, v_perm, tickets, n_tickets,
+    if ((rc = run_block_score(g, s, dtype, q, k, score, base + L.sub, perm_pad, true, src ? nullptr : k_perm, src ? nullptr : v, src ? nullptr : v_perm, tickets, n_tickets,
                               in_fold ? &sel : nullptr, hs)))
       return rc;
     if (!in_fold && (rc = run_select_mask(g, s, score, mode, sparsity, mass, st->mask, st->kv_idx, st->kv_cnt, st->K_max, st->k_head,
                                           base + L.sub, hs)))
       return rc;
-  } else if ((rc = run_permute(g, s, dtype, k, perm_pad, k_perm, v, v_perm, tickets, n_tickets, hs))) {
+  } else if (!src && (rc = run_permute(g, s, dtype, k, perm_pad, k_perm, v, v_perm, tickets, n_tickets, hs))) {
     return rc;
   }
-  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, st->kv_idx, st->kv_cnt, st->K_max, scale, o, nullptr, perm_pad,
+  return run_sparse_attn(g, s, dtype, q, src ? k : k_perm, src ? v : v_perm, st->kv_idx, st->kv_cnt, st->K_max, scale, o, nullptr, perm_pad, src, refresh || !src,
                          base + L.text, L.text_bytes, hs);
 }
 

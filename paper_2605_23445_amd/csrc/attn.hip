@@ -68,9 +68,13 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
 // SLIM (d = 128, 64 query rows): at 16 KB a tile, two buffers each for K and V leave room for two work-groups of two waves, one
 // wave per SIMD.  With one buffer each, whose halves take turns, four work-groups fit; a half is then requested a stage
 // ahead instead of a tile.  See `slim` below for the rule.
+//
+// SRC: keys and values come in source order, like the queries, and their tiles are gathered through row_index, so that nothing is
+// reordered in front of the kernel.  The rows of a block are 64 times 128 or 256 contiguous bytes either way; what it costs
+// is the lookup of positions and their way to the lanes.  See attn_reads_source below for the rule.
 template <int D, int BM, bool XLSE, int KS>
 constexpr int attn_waves() { return D == 64 && BM == 128 && !XLSE && KS == 1 ? 3 : 2; }
-template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL>
+template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL, bool SRC>
 __global__ void __launch_bounds__(BM * 2 * KS)
 __attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE, KS>(), attn_waves<D, BM, XLSE, KS>())))
 attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -91,6 +95,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // Two K and two V tile buffers per group (tile t lives in the pair of parity t & 1), at fixed byte offsets.
   static_assert(!SLIM || KS == 1, "the merge of wave groups wants all four buffers");
   static_assert(!TAIL || (KS == 1 && !XLSE), "see run_sparse_attn");
+  static_assert(!SRC || !XLSE, "see run_sparse_attn");
   __shared__ __attribute__((aligned(16))) uint16_t tiles[KS * (SLIM ? 2 : 4) * TILE];
   constexpr int K0 = 0, K1 = SLIM ? 0 : 2 * TILE, V0 = SLIM ? 2 * TILE : 4 * TILE, V1 = SLIM ? 2 * TILE : 6 * TILE;
 
@@ -162,7 +167,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   const int blk_first = shared_row ? split * run : 0;                     // this work-group's run of the list
   if (shared_row) cnt = cnt - blk_first < 0 ? 0 : cnt - blk_first < run ? cnt - blk_first : run;
   const int32_t* idx = kv_idx + (int64_t(head) * M + u) * K_max + blk_first;
-  const int64_t head_off = int64_t(head) * N_pad * D;
+  const int64_t head_off = int64_t(head) * (SRC ? N_src : N_pad) * D;
   const uint16_t* kh = k + head_off;
   const uint16_t* vh = v + head_off;
   const int64_t q_row0 = int64_t(u) * BM + wave * 32 + n;
@@ -219,7 +224,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   auto lane_off = [&](int j, bool is_v) {             // byte offset inside the tile of the chunk this lane fetches
     const int p = (j * NW + wave) * 64 + lane;
     const int row = p / CH, pc = p % CH;
-    return uint32_t(2 * (row * D + ((pc ^ (is_v ? swz_v<CH>(row) : swz_k<CH>(row))) * 8)));
+    return uint32_t(2 * ((SRC ? 0 : row * D) + ((pc ^ (is_v ? swz_v<CH>(row) : swz_k<CH>(row))) * 8)));
   };
   uint32_t k_off[PK], v_off[PV];
 #pragma unroll
@@ -251,6 +256,56 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint64_t src = tile_src(base, tile, blk);
 #pragma unroll
     for (int j = 0; j < LPW; ++j) issue_one(src, buf, is_v, j);
+  };
+
+  // SRC: tiles are gathered from the tensors in source order.  The lanes of a row of load j need that row's position; of four loads,
+  // the lanes of a quad look up one each and exchange them inside the quad, on the way of an addition that is needed anyway, so that a
+  // tile costs LQ lookups instead of LPW (75 600 tokens dense, d = 128, 1 % of the call; 60 of 591 blocks 1.5 %).  The
+  // requests go through a buffer descriptor of the head, whose bounds turn positions that are none (pads, -1; a damaged order) into
+  // zeros: their offsets, 2^32 - 2 D and more, lie behind any head that the host takes this way.  With a mask of the lanes in its
+  // place the calls took 2 to 5 % longer.
+  constexpr int LQ = (LPW + 3) / 4;
+  const int lane_row = 4 * ((lane % (LPW < 4 ? LPW : 4) * NW * 64 + wave * 64 + lane) / CH);             // bytes of row_index
+  auto descriptor = [&](const uint16_t* base) {
+    const uint64_t at = reinterpret_cast<uint64_t>(base);
+    return u32x4{uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(at))), uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(at >> 32))) & 0xFFFFu,
+                 uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(N_src * (2 * D)))), 0x00020000u};
+  };
+  const u32x4 k_desc = descriptor(kh), v_desc = descriptor(vh);
+  struct Rows { uint32_t at[LQ]; };
+  auto index_desc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(row_index), 0, int(N_pad * 4), 0x00020000);
+  auto look_up = [&](int step, int blk) {            // positions of tile `step` of block blk
+    Rows r;
+#pragma unroll
+    for (int i = 0; i < LQ; ++i) r.at[i] = __builtin_amdgcn_raw_buffer_load_b32(index_desc, lane_row + i * 16 * RJ, (blk * BM + step * KN) * 4, 0);
+    return r;
+  };
+  // The list entry of a tile further ahead, by a vector load: the wait at the tile's barrier covers it, while a scalar one is waited for
+  // on the spot, together with the operand reads in flight (d = 128, 17 550 tokens x 24 heads 565 -> 543 us).
+  auto list_desc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(idx), 0, dense ? 0 : cnt * 4, 0x00020000);
+  auto ask_block = [&](int tile) { return __builtin_amdgcn_raw_buffer_load_b32(list_desc, 0, (t_first + (tile < n_tiles ? tile : n_tiles - 1)) / STEPS * 4, 0); };
+  auto told_block = [&](int tile, uint32_t entry) {
+    const uint32_t blk = dense ? uint32_t(blk_first + (t_first + (tile < n_tiles ? tile : n_tiles - 1)) / STEPS) : uint32_t(__builtin_amdgcn_readfirstlane(entry));
+    return blk < uint32_t(M) ? int(blk) : 0;
+  };
+  auto offsets = [&](const Rows& r) {                // byte offsets of the rows inside the head
+    constexpr uint32_t OUT = 0xFFFFFFFFu / uint32_t(2 * D);
+    Rows o;
+#pragma unroll
+    for (int i = 0; i < LQ; ++i) o.at[i] = (r.at[i] < OUT ? r.at[i] : OUT) * uint32_t(2 * D);
+    return o;
+  };
+  auto gather_one = [&](const Rows& off, int buf, bool is_v, int j) {
+    const int x = int(off.at[j / 4]);
+    const int y = j % 4 == 0 ? __builtin_amdgcn_mov_dpp(x, 0x00, 0xF, 0xF, true) : j % 4 == 1 ? __builtin_amdgcn_mov_dpp(x, 0x55, 0xF, 0xF, true)
+                : j % 4 == 2 ? __builtin_amdgcn_mov_dpp(x, 0xAA, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp(x, 0xFF, 0xF, 0xF, true);
+    const uint32_t voff = uint32_t(y) + (is_v ? v_off[j % PV] : k_off[j % PK]);
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 ::"s"(lds_wave), "v"(voff), "s"(is_v ? v_desc : k_desc), "i"(buf + j * NW * 1024) : "memory", "m0", "scc");
+  };
+  auto gather = [&](const Rows& off, int buf, bool is_v) {
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) gather_one(off, buf, is_v, j);
   };
 
   // LDS byte addresses of this lane's operand reads in the first buffer, loop invariant: one per K fragment and one per
@@ -452,7 +507,12 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // read a full tile later.
   f32x16 s0, s1;
   u32x4 p0[2], p1[2];                              // probabilities as bf16 pairs: B operands of the products
-  int b_cur = 0, b_nxt = 0;                        // key blocks of tiles t and t + 1: one list lookup per tile (that of tile t + 2)
+  int b_cur = 0, b_nxt = 0;                        // key blocks of tiles t and t + 1 (a list lookup where tile t + 2 starts another)
+  // SRC: block of tile t + 2, list entry of tile t + 3, positions of the rows of K(t + 2), offsets of those of V(t + 1); SLIM: all a
+  // tile less.  Positions are looked up a tile before the tile is requested and two before it is read.
+  int b_far = 0;
+  uint32_t entry = 0;
+  Rows k_rows, v_rows;
   auto tile_step = [&](auto parity, auto first, auto last, int t) __attribute__((always_inline)) {
     constexpr bool ODD = decltype(parity)::value, FIRST = decltype(first)::value, LAST = decltype(last)::value;
     constexpr int k_cur = ODD ? K1 : K0;             // K(t); K(t+2) goes here
@@ -461,13 +521,24 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     constexpr int v_nxt = ODD ? V0 : V1;             // V(t-1); V(t+1) goes here
     // SLIM: every stage requests a half of V(t) and a half of K(t+1), in its first slots, into the halves that the stage before
     // has left; they are read in the next stage.
+    Rows next;
+    const int b_told = SRC && SLIM ? told_block(t + 2, entry) : 0;
+    if (SRC && SLIM) k_rows = offsets(k_rows);
     auto request = [&](int half) {
       const uint64_t k_src = tile_src(kh, t + 1, b_nxt), v_src = tile_src(vh, t, b_cur);
       return [&, half, k_src, v_src](int f) {
         if (!SLIM || f >= NF / 2) return;
+        if (SRC && f == 0 && half == 0 && !LAST) {
+          next = look_up(0, b_told);
+          entry = ask_block(t + 3);
+        }
 #pragma unroll
         for (int j = f * 2 * LPW / NF; j < (f + 1) * 2 * LPW / NF; ++j) {
           if (LAST && j >= LPW / 2) return;
+          if (SRC) {
+            gather_one(j < LPW / 2 ? v_rows : k_rows, j < LPW / 2 ? V0 : K0, j < LPW / 2, half * LPW / 2 + j % (LPW / 2));
+            continue;
+          }
           issue_one(j < LPW / 2 ? v_src : k_src, j < LPW / 2 ? V0 : K0, j < LPW / 2, half * LPW / 2 + j % (LPW / 2));
         }
       };
@@ -484,12 +555,34 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // loads of K(t+2) and V(t+1) (in one run behind the barrier they kept the matrix cores waiting for some fifty
     // instructions: +2.0 % on lists that hit in L2, +2.5 % on scattered ones, +4.7 % dense at d = 128).  Behind the
     // last tile K(t+2) is that tile once more, into a buffer that nothing reads.
-    const int b_new = tile_block(t + 2 < n_tiles ? t + 2 : n_tiles - 1);
+    const int b_new = SRC && SLIM ? b_told : SRC ? b_far : STEPS == 2 && ODD ? b_nxt : tile_block(t + 2 < n_tiles ? t + 2 : n_tiles - 1);
     const uint64_t k_src = tile_src(kh, t + 2, b_new), v_src = tile_src(vh, t + 1, b_nxt);
     if constexpr (SLIM) {
       stage(yes{}, std::integral_constant<bool, !LAST>{}, V0, 0, p0, K0, 0, s0, s1, p1, sum, xsum, request(1));
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
+      if (SRC) {
+        v_rows = k_rows;
+        if (!LAST) k_rows = next;
+      }
+    } else if constexpr (SRC) {
+      const int b_pos = STEPS == 2 && !ODD ? b_far : told_block(t + 3, entry);
+      k_rows = offsets(k_rows);
+      stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1, sum, xsum, [&](int f) {
+        if (LAST) return;
+        if (f == 0) {
+          next = look_up(STEPS == 2 && !ODD, b_pos);
+          if (STEPS == 1 || !ODD) entry = ask_block(t + 4);
+        }
+#pragma unroll
+        for (int j = f * 2 * LPW / NF; j < (f + 1) * 2 * LPW / NF; ++j) {
+          if (j < LPW) gather_one(v_rows, v_nxt, true, j);
+          else gather_one(k_rows, k_cur, false, j - LPW);
+        }
+      });
+      v_rows = k_rows;
+      if (!LAST) k_rows = next;
+      b_far = b_pos;
     } else {
       stage(yes{}, std::integral_constant<bool, !LAST>{}, v_cur, 0, p0, k_nxt, 0, s0, s1, p1, sum, xsum, [&](int f) {
         if (LAST) return;
@@ -518,17 +611,37 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int listed = !dense && lane < own_blks ? idx[own_first + lane] : -1;
     b_cur = tile_block(0);
     b_nxt = n_tiles > 1 ? tile_block(1) : b_cur;
-    issue(kh, K0, false, 0, b_cur);
-    if (!SLIM) issue(vh, V0, true, 0, b_cur);
+    if constexpr (SRC) {
+      Rows rows_0 = look_up(0, b_cur);
+      k_rows = look_up(STEPS - 1, b_nxt);            // behind a lone tile its block once more, into a buffer that nothing reads
+      if (SLIM) {
+        entry = ask_block(2);
+        v_rows = offsets(rows_0);
+        gather(v_rows, K0, false);
+      } else {
+        v_rows = k_rows;
+        b_far = tile_block(n_tiles > 2 ? 2 : n_tiles - 1);
+        k_rows = look_up(0, b_far);
+        if (STEPS == 1) entry = ask_block(3);
+        rows_0 = offsets(rows_0);
+        gather(rows_0, K0, false);
+        gather(rows_0, V0, true);
+        v_rows = offsets(v_rows);
+        gather(v_rows, K1, false);
+      }
+    } else {
+      issue(kh, K0, false, 0, b_cur);
+      if (!SLIM) issue(vh, V0, true, 0, b_cur);
+    }
     bf16x8 own_k[D / 16];
     {
-      const u32x4* kp = reinterpret_cast<const u32x4*>(kh + q_row0 * D);
+      const u32x4* kp = reinterpret_cast<const u32x4*>(kh + (SRC ? io_row < 0 ? 0 : io_row : q_row0) * D);
 #pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk) own_k[kk] = __builtin_bit_cast(bf16x8, kp[2 * kk + h]);
+      for (int kk = 0; kk < D / 16; ++kk) own_k[kk] = __builtin_bit_cast(bf16x8, SRC && io_row < 0 ? u32x4{0u, 0u, 0u, 0u} : kp[2 * kk + h]);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
-    if (!SLIM && n_tiles > 1) issue(kh, K1, false, 1, b_nxt);
+    if (!SRC && !SLIM && n_tiles > 1) issue(kh, K1, false, 1, b_nxt);
     logits(K0, 0, s0);
     if (SLIM) __syncthreads();                       // the first half of K(0) has been read
     mask_pads(b_cur, 0, 0, s0);
@@ -878,6 +991,12 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(const float* __restrict__
     lse[int64_t(head) * N_pad + q_row] = l_all > 0.f ? (ref + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f : -INFINITY;
 }
 
+// The tickets of shared rows, for calls with no kernel in front that clears them on its way (a launch of 3 us; a memset may not be
+// recorded into a graph).
+__global__ void __launch_bounds__(256) clear_tickets_kernel(int32_t* __restrict__ tickets, int n) {
+  for (int i = threadIdx.x; i < n; i += 256) tickets[i] = 0;
+}
+
 static unsigned long long* g_clock_probe = nullptr;   // set by dfs_attn_clock_probe (diagnostic)
 
 // Groups of waves that share a query block (kernel's KS): two where the work-groups leave SIMDs with less than one wave
@@ -953,9 +1072,31 @@ static TailSplit tail_split(const dfs_geom* g, const dfs_sizes& s, int32_t K_max
   return {full, rows, splits};
 }
 
+// Whether dfs_forward's attention gathers keys and values itself (kernel's SRC) instead of having them reordered in front.  It saves
+// the reorder's way through memory, and on a reuse step its launch; it costs a tile's loads some ten instructions, which is 1 to 2 %
+// of a long dense call.  Measured (us a call, reordered -> gathered), reuse steps: d = 64, 512 tokens x 8 heads 13.0 -> 9.1,
+// 2 565 + 77 x 12, blocks of 64, 30.0 -> 22.4, 17 550 x 48, 21 of 138 blocks, 676 -> 616; d = 128, 5 632 x 24 121 -> 92, 17 550 x 24
+// 620 -> 550, 75 600 x 40, 60 of 591 blocks, 11 610 -> 11 000; refresh steps: 17 550 x 48, d = 64, 715 -> 679, 75 600 x 40 11 997 ->
+// 11 580; dense: 17 550 x 12, d = 64, 969 -> 960, 75 600 x 40 96.89 -> 96.96 ms.  Not for sequences that all XCDs walk together
+// (mapping 2) at d = 64 or in blocks of 64, where the reorder is a smaller part: 75 600 tokens, d = 64, dense x 8 11 155 -> 11 236,
+// 48 of 591 blocks x 10 3 022 -> 3 030; d = 128, blocks of 64, dense x 2 6 458 -> 6 918.  The host does not know whether a call is
+// dense, so the line lies where dense calls break even.
+// Not where the output lies over the keys or values either: they are then reordered before the first row is written.
+bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* k, const void* v, const void* o) {
+  if (dtype != DFS_BF16) return false;
+  if (s.N > int64_t(0xFFFFFFFFu / uint32_t(2 * g->d))) return false;    // offsets inside a head are 32 bits
+  if ((s.M_v + 7) / 8 >= 64 && !(g->d == 128 && g->B == 128)) return false;
+  const uintptr_t bytes = uintptr_t(g->heads) * s.N * g->d * 2, out = reinterpret_cast<uintptr_t>(o);
+  for (const void* p : {k, v}) {
+    const uintptr_t in = reinterpret_cast<uintptr_t>(p);
+    if (in < out + bytes && out < in + bytes) return false;
+  }
+  return true;
+}
+
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
-                    const int32_t* row_index, void* scratch, size_t scratch_bytes, hipStream_t st) {
+                    const int32_t* row_index, bool kv_src, bool zeroed, void* scratch, size_t scratch_bytes, hipStream_t st) {
   if (K_max < 1) return fail(DFS_ESHAPE, "dfs_sparse_attn_fwd: K_max=%d must be positive", K_max);
   if (dtype == DFS_BF16) {
     const int64_t total = int64_t(g->heads) * s.M;
@@ -974,23 +1115,28 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     const bool one_buffer = g->d == 128 && g->B == 64 && slim(work_groups, ks, mapping);
     const int order = mapping >= 2 ? text_slots + per_xcd : per_xcd;     // slots of an XCD
     const TailSplit tail = lse || ks > 1 ? TailSplit{0, 1, 1} : tail_split(g, s, K_max, order, mapping >= 2 ? text_slots : 0, ts, one_buffer, scratch_bytes);
+    if (!zeroed && (ts.splits > 1 || tail.splits > 1)) clear_tickets_kernel<<<1, 256, 0, st>>>(tickets, int(split_tickets(g, s)));
     dim3 grid(unsigned(8 * (order + tail.rows * (tail.splits - 1))));
-#define ATTN_X(DD, BB, XX, KS, SLIM, TAIL)                                                                                            \
-  attn_bf16_kernel<DD, BB, XX, KS, SLIM, TAIL><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
+#define ATTN_X(DD, BB, XX, KS, SLIM, TAIL, SRC)                                                                                            \
+  attn_bf16_kernel<DD, BB, XX, KS, SLIM, TAIL, SRC><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
                                                         static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                 \
                                                         static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,         \
                                                         g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe, \
                                                         part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits)
-#define ATTN(DD, BB, KS, SLIM) do { if (lse) ATTN_X(DD, BB, true, KS, SLIM, false); else ATTN_X(DD, BB, false, KS, SLIM, false); } while (0)
-#define ATTN_1(DD, BB, SLIM) do { if (tail.splits > 1) ATTN_X(DD, BB, false, 1, SLIM, true); else ATTN(DD, BB, 1, SLIM); } while (0)
-#define ATTN_KS(DD, BB) do { if (ks == 2) ATTN(DD, BB, 2, false); else ATTN_1(DD, BB, false); } while (0)
+#define ATTN_LSE(DD, BB, KS, SLIM) do { if (lse) ATTN_X(DD, BB, true, KS, SLIM, false, false); else ATTN_X(DD, BB, false, KS, SLIM, false, false); } while (0)
+#define ATTN_WHOLE(DD, BB, KS, SLIM) do { if (kv_src) ATTN_X(DD, BB, false, KS, SLIM, false, true); else ATTN_LSE(DD, BB, KS, SLIM); } while (0)
+#define ATTN_TAIL(DD, BB, SLIM) do { if (kv_src) ATTN_X(DD, BB, false, 1, SLIM, true, true); else ATTN_X(DD, BB, false, 1, SLIM, true, false); } while (0)
+#define ATTN_1(DD, BB, SLIM) do { if (tail.splits > 1) ATTN_TAIL(DD, BB, SLIM); else ATTN_WHOLE(DD, BB, 1, SLIM); } while (0)
+#define ATTN_KS(DD, BB) do { if (ks == 2) ATTN_WHOLE(DD, BB, 2, false); else ATTN_1(DD, BB, false); } while (0)
     if (g->d == 64) { if (g->B == 64) ATTN_KS(64, 64); else ATTN_KS(64, 128); }
     else if (g->B == 128) ATTN_KS(128, 128);
     else if (one_buffer) ATTN_1(128, 64, true);
     else ATTN_KS(128, 64);
 #undef ATTN_KS
 #undef ATTN_1
-#undef ATTN
+#undef ATTN_TAIL
+#undef ATTN_WHOLE
+#undef ATTN_LSE
 #undef ATTN_X
   } else {
     if (g->heads > 65535) return fail(DFS_ESHAPE, "heads=%d exceeds 65535", g->heads);
@@ -1026,7 +1172,7 @@ extern "C" int dfs_sparse_attn_fwd(const dfs_geom* g, int dtype, const void* q_p
   if (misaligned(16, {q_perm, k_perm, v_perm, o_perm}) || misaligned(4, {kv_idx, kv_cnt, lse}))
     return fail(DFS_EINVAL, "dfs_sparse_attn_fwd: tensors must be 16-byte aligned, index and fp32 arrays 4-byte aligned");
   if (!(scale > 0.f)) return fail(DFS_EINVAL, "dfs_sparse_attn_fwd: scale must be positive");
-  return run_sparse_attn(g, s, dtype, q_perm, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o_perm, lse, nullptr, nullptr, 0, as_stream(stream));
+  return run_sparse_attn(g, s, dtype, q_perm, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o_perm, lse, nullptr, false, false, nullptr, 0, as_stream(stream));
 }
 
 extern "C" int dfs_sparse_attn_fwd_src(const dfs_geom* g, int dtype, const void* q, const int32_t* perm_pad, const void* k_perm,
@@ -1040,5 +1186,5 @@ extern "C" int dfs_sparse_attn_fwd_src(const dfs_geom* g, int dtype, const void*
   if (misaligned(16, {q, k_perm, v_perm, o}) || misaligned(4, {perm_pad, kv_idx, kv_cnt, lse}))
     return fail(DFS_EINVAL, "dfs_sparse_attn_fwd_src: tensors must be 16-byte aligned, index and fp32 arrays 4-byte aligned");
   if (!(scale > 0.f)) return fail(DFS_EINVAL, "dfs_sparse_attn_fwd_src: scale must be positive");
-  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o, lse, perm_pad, nullptr, 0, as_stream(stream));
+  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o, lse, perm_pad, false, false, nullptr, 0, as_stream(stream));
 }

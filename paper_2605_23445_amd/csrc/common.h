@@ -39,11 +39,11 @@ struct SelectPlan {
   int32_t K_max;
   int32_t* k_head;
 };
-// index (may be NULL): the permutation; Q is then read in source order and gathered while pooling.  With k_out K comes
-// in source order too and is written out reordered, and so is V with v_out (which needs k_out).  n_zero words at `zero`
-// are cleared on the way.  With sel the block lists are written instead of the scores (`score` may be NULL then).
+// index (may be NULL): the permutation; Q is then read in source order and gathered while pooling, and so is K with k_src.
+// With k_out (which needs k_src) K is written out reordered on the way, and so is V with v_out (which needs k_out).  n_zero words at
+// `zero` are cleared on the way.  With sel the block lists are written instead of the scores (`score` may be NULL then).
 int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q_perm, const void* k_perm,
-                    float* score, void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, int32_t* zero,
+                    float* score, void* ws, const int32_t* index, bool k_src, void* k_out, const void* v, void* v_out, int32_t* zero,
                     int n_zero, const SelectPlan* sel, hipStream_t st);
 // Whether the scoring can select on the way: the rule needs one row's scores only and eight rows fit in 64 KB of LDS.
 bool can_select_in_fold(const dfs_sizes& s, int mode);
@@ -53,9 +53,11 @@ int run_select_mask(const dfs_geom* g, const dfs_sizes& s, const float* score, i
                     int32_t* k_head, void* ws, hipStream_t st);
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
-                    const int32_t* row_index, void* scratch, size_t scratch_bytes, hipStream_t st);
+                    const int32_t* row_index, bool kv_src, bool zeroed, void* scratch, size_t scratch_bytes, hipStream_t st);
+// Whether dfs_forward hands the attention K and V in source order (kv_src below) instead of reordering them.
+bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* k, const void* v, const void* o);
 // row_index (may be NULL): Q and O in source order.  scratch (may be NULL): room to split text rows over work-groups; its
-// first split_tickets() words are zero when the kernel starts: one per text block, and with 512 query blocks and more one for each
+// first split_tickets() words are zero when the kernel starts, already (zeroed) or by a launch of its own: one per text block, and with 512 query blocks and more one for each
 // that the last round of work-groups may share (at most 127 per XCD).
 inline size_t split_tickets(const dfs_geom* g, const dfs_sizes& s) {
   return size_t(g->heads) * s.M_x + (int64_t(g->heads) * s.M >= 512 ? 8 * 128 : 0);

@@ -70,7 +70,7 @@ template <int D> __device__ __forceinline__ int chunk_at(int p, int c, int rows,
 // flight per load; partial sums of the row groups are folded with cross-lane exchanges.
 // Output: the hi and lo fp16 planes of the row times its group's scale (layouts above); the inverse scale of group s / 4 goes
 // to q_down / k_down.
-// blockIdx.z: 0 pools Q, 1 pools K, 2 only reorders V.  With an index (the permutation) the tensors come in source
+// blockIdx.z: 0 pools Q, 1 pools K, 2 only reorders V.  With an index (the permutation) Q, K (if k_src) and V come in source
 // order and their rows are gathered; K (if k_out) and V are written out in the reordered layout on the way (pads as
 // zeros, text rows too), so that a step that refreshes the mask reads and writes each of them once, in one launch.
 // An HBM stream; a wave requests up to eight row groups (the positions first, then the rows) before it uses one,
@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in
                                                    uint16_t* __restrict__ q_hat, uint16_t* __restrict__ k_hat,
                                                    float* __restrict__ q_down, float* __restrict__ k_down,
                                                    const int32_t* __restrict__ index, void* __restrict__ k_out, void* __restrict__ v_out,
-                                                   int64_t N_src, int64_t N_pad, int64_t N_v, int Bs, int M_s, float q_scale, bool tiled,
+                                                   int64_t N_src, int64_t N_pad, int64_t N_v, int Bs, int M_s, float q_scale, bool tiled, bool k_src,
                                                    int32_t* __restrict__ zero, int n_zero) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
     for (int i = threadIdx.x; i < n_zero; i += 256) zero[i] = 0;
@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in
   const bool pooled = s < M_s && blockIdx.z < 2;             // this wave has a sub-block to pool
   void* out = blockIdx.z == 0 ? nullptr : blockIdx.z == 1 ? k_out : v_out;
   const bool copied = out != nullptr && int64_t(s) * Bs < N_pad;
-  const bool gather = index != nullptr && (blockIdx.z == 0 || out != nullptr);   // K without k_out is in the reordered layout
+  const bool gather = index != nullptr && (blockIdx.z != 1 || k_src);
   const int head = blockIdx.y;
   const void* src = blockIdx.z == 0 ? q_in : blockIdx.z == 1 ? k_in : v_in;
   uint16_t* dst = blockIdx.z == 0 ? q_hat : k_hat;
@@ -799,7 +799,7 @@ static void launch_score(const dfs_geom* g, const dfs_sizes& s, const uint16_t* 
 bool can_select_in_fold(const dfs_sizes& s, int mode) { return mode != DFS_SELECT_MASS_HEAD && fs_lds(s.M_v) <= 65536; }
 
 int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q_perm, const void* k_perm, float* score,
-                    void* ws, const int32_t* index, void* k_out, const void* v, void* v_out, int32_t* zero, int n_zero, const SelectPlan* sel,
+                    void* ws, const int32_t* index, bool k_src, void* k_out, const void* v, void* v_out, int32_t* zero, int n_zero, const SelectPlan* sel,
                     hipStream_t st) {
   if (g->heads > 65535) return fail(DFS_ESHAPE, "heads=%d exceeds 65535", g->heads);
   if ((s.M_v + 31) / 32 > 65535) return fail(DFS_ESHAPE, "M_v=%d is too large for the scoring grid", s.M_v);
@@ -815,7 +815,7 @@ int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
   const bool bf = dtype == DFS_BF16;
   // 1/sqrt(d) of Eq. 2 and the change to base 2 go into Q_hat, so that the logits come out of the contraction in base 2
   const float scale = 1.4426950408889634f / sqrtf(float(g->d));
-#define POOL(BF, DD) pool_kernel<BF, DD><<<pg, 256, 0, st>>>(q_perm, k_perm, v, q_hat, k_hat, q_down, k_down, index, k_out, v_out, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale, score_small(g, s), zero, n_zero)
+#define POOL(BF, DD) pool_kernel<BF, DD><<<pg, 256, 0, st>>>(q_perm, k_perm, v, q_hat, k_hat, q_down, k_down, index, k_out, v_out, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale, score_small(g, s), k_src, zero, n_zero)
   if (g->d == 64) { if (bf) POOL(true, 64); else POOL(false, 64); }
   else            { if (bf) POOL(true, 128); else POOL(false, 128); }
 #undef POOL
@@ -850,7 +850,7 @@ extern "C" int dfs_block_score(const dfs_geom* g, int dtype, const void* q_perm,
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q_perm, k_perm, score, ws, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, as_stream(stream));
+  return run_block_score(g, s, dtype, q_perm, k_perm, score, ws, nullptr, false, nullptr, nullptr, nullptr, nullptr, 0, nullptr, as_stream(stream));
 }
 
 extern "C" int dfs_block_score_src(const dfs_geom* g, int dtype, const void* q, const int32_t* perm_pad, const void* k_perm,
@@ -865,7 +865,7 @@ extern "C" int dfs_block_score_src(const dfs_geom* g, int dtype, const void* q, 
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score_src: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q, k_perm, score, ws, perm_pad, nullptr, nullptr, nullptr, nullptr, 0, nullptr, as_stream(stream));
+  return run_block_score(g, s, dtype, q, k_perm, score, ws, perm_pad, false, nullptr, nullptr, nullptr, nullptr, 0, nullptr, as_stream(stream));
 }
 
 extern "C" int dfs_block_score_fused(const dfs_geom* g, int dtype, const void* q, const void* k, const int32_t* perm_pad,
@@ -881,5 +881,5 @@ extern "C" int dfs_block_score_fused(const dfs_geom* g, int dtype, const void* q
   const size_t need = ws_block_score(g, s);
   if (!ws || (uintptr_t(ws) & 255) || ws_bytes < need)
     return fail(DFS_EWORKSPACE, "dfs_block_score_fused: workspace of %zu bytes needed (256-byte aligned), got %zu", need, ws_bytes);
-  return run_block_score(g, s, dtype, q, k, score, ws, perm_pad, k_perm, nullptr, nullptr, nullptr, 0, nullptr, as_stream(stream));
+  return run_block_score(g, s, dtype, q, k, score, ws, perm_pad, true, k_perm, nullptr, nullptr, nullptr, 0, nullptr, as_stream(stream));
 }
