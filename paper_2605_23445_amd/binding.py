@@ -1,4 +1,4 @@
-"""ctypes binding of the C ABI in include/dfsattn.h (argument marshalling only)."""
+"""Binding of the C ABI in include/dfsattn.h through ctypes (argument marshalling only)."""
 from __future__ import annotations
 
 import ctypes as C
@@ -90,6 +90,9 @@ def _load():
 
 
 _lib = _load()
+from . import _calls  # noqa: E402   the hottest calls without marshalling in Python; links to the library loaded above
+
+_calls.set_geom_type(Geom)
 EXPORTS = ("dfs_geom_sizes", "dfs_workspace_bytes", "dfs_last_error", "dfs_keep_count", "dfs_hilbert_perm", "dfs_permute",
            "dfs_block_score", "dfs_select_mask", "dfs_sparse_attn_fwd", "dfs_unperm", "dfs_forward", "dfs_token_order", "dfs_recall",
            "dfs_schedule", "dfs_block_score_src", "dfs_sparse_attn_fwd_src", "dfs_attn_clock_probe", "dfs_block_score_fused", "dfs_probe_mfma", "dfs_probe_copy", "dfs_probe_read",
@@ -102,9 +105,9 @@ def _check(rc: int):
         raise DfsError(rc, _lib.dfs_last_error().decode())
 
 
-# Small calls are bound by what happens here between two launches (a refresh on 256 fp32 tokens 22.1 -> 18.8 us; the
-# token order of a geometry 9.5 -> 6.3 us), so pointers and the stream go to the library as plain integers and a geometry by itself (ctypes
-# passes its address), and the checks of a tensor are one attribute each.
+# Small calls are bound by what happens between two launches, so pointers and the stream go to the library as plain integers and a
+# geometry by itself (ctypes passes its address), the checks of a tensor are one attribute each, and the calls of every step go
+# through _calls (csrc/calls.cpp), which does what follows here for plain arguments without Python.
 
 
 def _ptr(t: torch.Tensor | None, dtype=None, numel=0, name="tensor"):
@@ -158,6 +161,11 @@ def _ws_args(ws: torch.Tensor | None):
 
 
 def dfs_hilbert_perm(g: Geom, perm_pad, inv, blk_valid, ws):
+    rc = _calls.token_order(g, DFS_ORDER_HILBERT3D, perm_pad, inv, blk_valid, ws)
+    if rc == 0:
+        return
+    if rc is not None:
+        _check(rc)
     s = dfs_geom_sizes(g)
     wp, wb = _ws_args(ws)
     _check(_lib.dfs_hilbert_perm(g, _ptr(perm_pad, torch.int32, s.N_pad, "perm_pad"),
@@ -166,6 +174,11 @@ def dfs_hilbert_perm(g: Geom, perm_pad, inv, blk_valid, ws):
 
 
 def dfs_token_order(g: Geom, order: int, perm_pad, inv, blk_valid, ws):
+    rc = _calls.token_order(g, order, perm_pad, inv, blk_valid, ws)
+    if rc == 0:
+        return
+    if rc is not None:
+        _check(rc)
     s = dfs_geom_sizes(g)
     wp, wb = _ws_args(ws)
     _check(_lib.dfs_token_order(g, int(order), _ptr(perm_pad, torch.int32, s.N_pad, "perm_pad"),
@@ -304,6 +317,11 @@ def dfs_unperm(g: Geom, dtype: int, o_perm, inv, o):
 
 def dfs_forward(g: Geom, dtype: int, q, k, v, perm_pad, inv, refresh: bool, mode: int, sparsity: float, mass: float,
                 st: MaskState, scale: float, o, ws):
+    rc = _calls.forward(g, dtype, q, k, v, perm_pad, inv, refresh, mode, sparsity, mass, st, scale, o, ws)
+    if rc == 0:
+        return
+    if rc is not None:
+        _check(rc)
     s = dfs_geom_sizes(g)
     td = _torch_dtype(dtype)
     n = g.heads * s.N * g.d

@@ -1,22 +1,36 @@
-"""Builds libdfsattn.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libdfsattn.so (HIP kernels + C ABI) for gfx950 with hipcc and _calls.so (its calls from Python) with g++, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdfsattn.so")
 SOURCES = ["api.hip", "hilbert.hip", "permute.hip", "score.hip", "select.hip", "attn.hip", "recall.hip", "probe.hip"]
+CALLS = os.path.join(HERE, "_calls.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]
 
 
+def _calls_command() -> list[str]:
+    import torch
+    from torch.utils import cpp_extension
+    rocm = os.path.dirname(os.path.dirname(HIPCC)) if os.path.isabs(HIPCC) else "/opt/rocm"
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    include = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], os.path.join(rocm, "include")]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *(f"-isystem{d}" for d in include),
+            os.path.join(CSRC, "calls.cpp"), "-o", CALLS, f"-L{HERE}", "-l:" + os.path.basename(LIB), f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+            "-Wl,-rpath,$ORIGIN"]
+
+
 def build_library(verbose: bool = False, jobs: int = 6) -> str:
-    """Compiles every translation unit and links the shared library; returns its path."""
+    """Compiles every translation unit and links the shared library and the module of its calls; returns the library's path."""
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     procs = []
@@ -36,6 +50,7 @@ def build_library(verbose: bool = False, jobs: int = 6) -> str:
     out = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if out.returncode != 0:
         raise RuntimeError("link failed:\n" + out.stdout)
+    _wait(("calls.cpp", subprocess.Popen(_calls_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)), verbose)
     return LIB
 
 
@@ -45,7 +60,7 @@ def _wait(item, verbose):
     # the host pass does not know the device-only target feature and says so; that is harmless
     lines = [l for l in out.splitlines() if "packed-fp32-ops" not in l and l.strip()]
     if proc.returncode != 0:
-        raise RuntimeError(f"hipcc failed on {src}:\n" + "\n".join(lines))
+        raise RuntimeError(f"compilation failed on {src}:\n" + "\n".join(lines))
     if verbose and lines:
         print("\n".join(lines), flush=True)
 
