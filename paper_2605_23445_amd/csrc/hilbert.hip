@@ -4,9 +4,9 @@
 // No keys are sorted or counted.  A token's rank among the cells of the grid has a closed form under every
 // order: walking down the levels of the curve, the cells that come before it are those of the sibling octants the
 // curve visits earlier, and an octant clipped by the grid holds the product of its three clipped extents.  So one
-// kernel without scratch memory gives perm, inverse and block sizes.  75 600 tokens take 5.8 us, of which the launch
-// is half; the six kernels before (keys marked in a bitmap over the enclosing cube, its prefix sum in three launches,
-// keys turned into ranks) took 26 us with the gaps between them, the call as a whole now 6.2.  Run once per geometry.
+// kernel without scratch memory gives perm, inverse and block sizes.  75 600 tokens take 3.4 us a call among
+// others, of which the launch is half; the six kernels before (keys marked in a bitmap over the enclosing cube, its prefix sum in three
+// launches, keys turned into ranks) took 26 us with the gaps between them.  Run once per geometry.
 #include "common.h"
 
 namespace dfs {
@@ -14,59 +14,74 @@ namespace dfs {
 // Rank of cell x among the cells of the grid [0, dim[0]) x ... in ascending order of their Hilbert index: the Butz
 // curve in Skilling's transpose form on the enclosing cube of 2^b cells per axis, axis 0 the high bit of a digit.
 // At level j the bits of the cell are read through the axis order and reflections that the levels above left
-// behind (a set bit reflects axis 0 below this level, a clear one exchanges axis 0 with that axis); their running
-// parities, all inverted where `fix` says so, are the digit of the index, and a set digit bit means that the whole
-// half of the sub-cube with that bit clear comes before the cell.
+// behind (a set bit reflects axis 0 below this level, a clear one exchanges axis 0 with that axis); their parity,
+// running over the axes and the levels, is the next bit of the index, and a set one means that the whole half of the
+// sub-cube with that bit clear comes before the cell.
+// A wave is alone on its SIMD here (75 600 tokens are 1 182 waves) and issues a vector instruction every eight cycles or so, so
+// what bounds the kernel is their number, some fifty a level: an axis keeps its coordinate and the reflected one in one word, which is
+// exchanged in one piece, and the extent of the present sub-cube inside the grid, which is halved with it; volumes are at most
+// 2^23, their factors at most 2^18, so the products are 24-bit ones, at four times the rate.  With the extents worked out anew from
+// the grid, reflections apart and 32-bit products and divisions a call took 4.13 us, now 3.36 (75 600 tokens; 64
+// tokens 2.12 and 1.75).
 template <int N>
-__device__ __forceinline__ uint32_t hilbert_rank(uint32_t (&x)[N], uint32_t (&dim)[N], int b) {
-  uint32_t flip[N] = {};
-  uint32_t fix = 0, rank = 0;
+__device__ __forceinline__ uint32_t hilbert_rank(const uint32_t (&x)[N], const uint32_t (&dim)[N], int b) {
+  constexpr int REFLECTED = 16;                      // first bit of the reflected coordinate
+  uint32_t w[N], ext[N];
+#pragma unroll
+  for (int a = 0; a < N; ++a) {
+    w[a] = x[a] | x[a] << REFLECTED;
+    ext[a] = dim[a];
+  }
+  uint32_t digit = 0, rank = 0;                      // digit: bit of the index, running over the axes and levels
   for (int j = b - 1; j >= 0; --j) {
     const uint32_t side = 1u << j;
-    uint32_t bit[N], mine[N], other[N];             // extents inside the grid of the half with this cell and of its sibling
+    bool bit[N];
+    uint32_t mine[N], before[N];                     // extents of the half with this cell, and of the other if that comes first
 #pragma unroll
     for (int a = 0; a < N; ++a) {
-      const uint32_t raw = (x[a] >> j) & 1u;
-      const uint32_t room = dim[a] - ((x[a] >> j) >> 1 << (j + 1));             // > 0: the cell itself is inside
-      const uint32_t lower = room < side ? room : side, rest = room - lower;
-      const uint32_t upper = rest < side ? rest : side;
-      mine[a] = raw ? upper : lower;
-      other[a] = raw ? lower : upper;
-      bit[a] = raw ^ flip[a];
+      bit[a] = (w[a] >> (REFLECTED + j)) & 1u;
+      digit ^= bit[a];
+      const uint32_t lower = ext[a] < side ? ext[a] : side;
+      mine[a] = (w[a] >> j) & 1u ? ext[a] - lower : lower;
+      before[a] = digit ? ext[a] - mine[a] : 0u;
     }
-    uint32_t parity = 0, same = 1;                   // same: cells that agree with this one on the axes before
+    uint32_t same = 1;                               // cells that agree with this one on the axes before
 #pragma unroll
     for (int a = 0; a < N; ++a) {
-      parity ^= bit[a];
-      uint32_t before = same * other[a];
+      uint32_t v = same;
 #pragma unroll
-      for (int c = a + 1; c < N; ++c) before *= mine[c] + other[c];
-      rank += (parity ^ fix) ? before : 0u;
-      same *= mine[a];
+      for (int c = a + 1; c < N; ++c) v = __umul24(v, ext[c]);
+      rank += __umul24(before[a], v);
+      same = __umul24(same, mine[a]);
     }
-    fix ^= parity;
+#pragma unroll
+    for (int a = 0; a < N; ++a) ext[a] = mine[a];
 #pragma unroll
     for (int a = 0; a < N; ++a) {
       if (bit[a]) {
-        flip[0] ^= 1u;
+        w[0] ^= 0xFFFFu << REFLECTED;
       } else {
-        uint32_t tmp = x[0]; x[0] = x[a]; x[a] = tmp;
-        tmp = dim[0]; dim[0] = dim[a]; dim[a] = tmp;
-        tmp = flip[0]; flip[0] = flip[a]; flip[a] = tmp;
+        uint32_t tmp = w[0]; w[0] = w[a]; w[a] = tmp;
+        tmp = ext[0]; ext[0] = ext[a]; ext[a] = tmp;
       }
     }
   }
   return rank;
 }
 
-// Rank of video token n (< 2^23, see check_geom) under a traversal order:
+// Division of n < 2^23 (65 536 blocks, see check_geom) by d <= 512, by the high half of a product with ceil(2^32 / d): it exceeds
+// 2^32 n / d by less than 2^23 x 512 / d, so that the floor is right.  0 stands for d = 1.
+static uint32_t reciprocal(int d) { return d == 1 ? 0u : uint32_t((0x100000000ull + d - 1) / d); }
+__device__ __forceinline__ uint32_t quotient(uint32_t n, uint32_t recip) { return recip ? __umulhi(n, recip) : n; }
+
+// Rank of video token n under a traversal order:
 //   hilbert3d  3D Hilbert index of (t,h,w) in the enclosing cube (Sec. 5.1)
 //   raster     n itself (per-frame row-major, the model's own order)
 //   hilbert2d  frame index, then the 2D Hilbert index of (h,w) (ablation of Sec. 6.3)
 //   block3d    4x4x4 cubes in raster order of the cubes, raster inside a cube (ablation of Sec. 6.3)
-__device__ __forceinline__ uint32_t token_rank(uint32_t n, int order, uint32_t T, uint32_t H, uint32_t W, int b, int b2) {
-  const uint32_t w = n % W, th = n / W;
-  const uint32_t t = th / H, h = th % H;
+__device__ __forceinline__ uint32_t token_rank(uint32_t n, int order, uint32_t T, uint32_t H, uint32_t W, uint32_t by_H, uint32_t by_W, int b, int b2) {
+  const uint32_t th = quotient(n, by_W), w = n - __umul24(th, W);
+  const uint32_t t = quotient(th, by_H), h = th - __umul24(t, H);
   switch (order) {
     case DFS_ORDER_RASTER: return n;
     case DFS_ORDER_HILBERT2D: {
@@ -86,12 +101,12 @@ __device__ __forceinline__ uint32_t token_rank(uint32_t n, int order, uint32_t T
 }
 
 // Every video token writes itself at its rank; text tokens and pads are filled in beside them.
-__global__ void __launch_bounds__(256) token_order_kernel(uint32_t N_v, int n_text, int order, int T, int H, int W, int b, int b2, int B,
-                                                          int M_v, int64_t N_pad, int32_t* __restrict__ perm_pad,
+__global__ void __launch_bounds__(256) token_order_kernel(uint32_t N_v, int n_text, int order, int T, int H, int W, uint32_t by_H, uint32_t by_W, int b,
+                                                          int b2, int B, int M_v, int64_t N_pad, int32_t* __restrict__ perm_pad,
                                                           int32_t* __restrict__ inv, int32_t* __restrict__ blk_valid) {
   const uint32_t i = blockIdx.x * 256u + threadIdx.x;
   if (i < N_v) {
-    const uint32_t rank = token_rank(i, order, uint32_t(T), uint32_t(H), uint32_t(W), b, b2);
+    const uint32_t rank = token_rank(i, order, uint32_t(T), uint32_t(H), uint32_t(W), by_H, by_W, b, b2);
     perm_pad[rank] = int32_t(i);
     inv[i] = int32_t(rank);
   }
@@ -146,8 +161,8 @@ size_t ws_hilbert(const dfs_geom* g, const dfs_sizes& s) {   // enough for every
 static int run_token_order(const dfs_geom* g, const dfs_sizes& s, int order, int32_t* perm_pad, int32_t* inv, int32_t* blk_valid,
                            hipStream_t st) {
   const int b2 = bits_for(g->H > g->W ? g->H : g->W);
-  token_order_kernel<<<dim3(unsigned((s.N_pad + 255) / 256)), 256, 0, st>>>(uint32_t(s.N_v), g->n_text, order, g->T, g->H, g->W, s.bits, b2,
-                                                                          g->B, s.M_v, s.N_pad, perm_pad, inv, blk_valid);
+  token_order_kernel<<<dim3(unsigned((s.N_pad + 255) / 256)), 256, 0, st>>>(uint32_t(s.N_v), g->n_text, order, g->T, g->H, g->W, reciprocal(g->H),
+                                                                          reciprocal(g->W), s.bits, b2, g->B, s.M_v, s.N_pad, perm_pad, inv, blk_valid);
   return launch_status("dfs_token_order");
 }
 
