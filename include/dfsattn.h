@@ -260,7 +260,7 @@ typedef struct {
  * several work-groups share a query block's keys, which only this call has room for: text blocks (16 blocks and more in
  * all), and, from 512 query blocks in all heads on, the video or text blocks that would be left over for a last round of
  * work-groups with half and more of the chip idle.  Which these are follows from the geometry and K_max alone.
- * `scale` is not checked: f32 tensors take any, bf16 tensors need it positive.
+ * `scale` is not checked: f32 tensors take any, bf16 tensors need it positive.  At most 65 535 heads (DFS_ESHAPE).
  *   q, k, v [heads, N, d] in;  o [heads, N, d] out.   ws: DFS_WS_FORWARD (f32) or DFS_WS_FORWARD_BF16.
  */
 int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, const void* v,

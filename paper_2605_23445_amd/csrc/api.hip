@@ -140,6 +140,8 @@ int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, cons
     if (!in_fold && (rc = run_select_mask(g, s, score, mode, sparsity, mass, st->mask, st->kv_idx, st->kv_cnt, st->K_max, st->k_head,
                                           base + L.sub, hs)))
       return rc;
+  } else if (g->heads > 65535) {                     // a limit of the reorder's and the scoring's grids: what is refused does not follow from the route
+    return fail(DFS_ESHAPE, "heads=%d exceeds 65535", g->heads);
   } else if (!src && (rc = run_permute(g, s, dtype, k, perm_pad, k_perm, v, v_perm, tickets, n_tickets, hs))) {
     return rc;
   }

@@ -90,6 +90,28 @@ def test_argument_errors_come_before_any_launch():
     assert lib.dfs_block_score(C.byref(g), 0, fake, odd8, fake, fake, 1 << 30, None) == -1
 
 
+@pytest.mark.parametrize("refresh", [0, 1])
+@pytest.mark.parametrize("dtype,kind", [(P.DFS_F32, P.DFS_WS_FORWARD), (P.DFS_BF16, P.DFS_WS_FORWARD_BF16)])
+def test_forward_refuses_more_heads_than_a_grid_holds(dtype, kind, refresh):
+    """On every step and for both types alike, before anything is launched (no GPU is present here)."""
+    lib = C.CDLL(P.lib_path())
+    lib.dfs_last_error.restype = C.c_char_p
+    vp = C.c_void_p
+
+    class State(C.Structure):
+        _fields_ = [(n, vp) for n in ("kv_idx", "kv_cnt", "mask", "k_head")] + [("K_max", C.c_int32)]
+
+    lib.dfs_forward.argtypes = [C.POINTER(P.Geom), C.c_int, vp, vp, vp, vp, vp, C.c_int, C.c_int, C.c_double, C.c_double, C.POINTER(State), C.c_float,
+                                vp, vp, C.c_size_t, vp]
+    g = P.Geom(1, 1, 1, 0, 65536, 64, 64, 64)
+    # addresses that are never read: the output behind the keys and values, the rest anywhere
+    q, k, v, o, other = (vp(i << 32) for i in range(1, 6))
+    st = State(other, other, None, None, 1)
+    assert lib.dfs_forward(C.byref(g), dtype, q, k, v, other, other, refresh, 0, 0.0, 0.0, C.byref(st), 0.125, o, other,
+                           P.dfs_workspace_bytes(g, kind), None) == -2
+    assert b"65535" in lib.dfs_last_error()
+
+
 def test_binding_refuses_host_tensors():
     import torch
     g = P.Geom(4, 8, 8, 0, 2, 64, 64, 16)
