@@ -1,8 +1,10 @@
-"""Binding of the C ABI in include/dfsattn.h through ctypes (argument marshalling only)."""
+"""Binding of the C ABI in include/dfsattn.h (argument marshalling only): through ctypes, and the calls of every step through a
+module built beside the library (csrc/calls.cpp) where that fits the running Python and torch."""
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from dataclasses import dataclass
 
 import torch
@@ -89,10 +91,25 @@ def _load():
     return lib
 
 
-_lib = _load()
-from . import _calls  # noqa: E402   the hottest calls without marshalling in Python; links to the library loaded above
+def _load_calls():
+    """forward and token_order of the _calls module.  They do in native code what dfs_forward and the token orders do below, for plain
+    arguments, and return None for what they leave to these: as the stand-ins do for every call where the module is not there or
+    was built against another torch, whose classes it reads (another Python does not find it: its name holds the version)."""
+    try:
+        from . import _calls                         # links to the library loaded above
+        if getattr(_calls, "torch_version", None) == torch.__version__:
+            _calls.set_geom_type(Geom)
+            return _calls.forward, _calls.token_order
+        why = "built for another torch"
+    except ImportError as e:
+        why = str(e)
+    warnings.warn(f"the module of the hottest calls cannot be used ({why}): they go through Python, some 2 us slower each; "
+                  "run `python -c 'import __graft_entry__ as g; g.build()'`", RuntimeWarning, stacklevel=3)
+    return lambda *a: None, lambda *a: None
 
-_calls.set_geom_type(Geom)
+
+_lib = _load()
+_plain_forward, _plain_token_order = _load_calls()
 EXPORTS = ("dfs_geom_sizes", "dfs_workspace_bytes", "dfs_last_error", "dfs_keep_count", "dfs_hilbert_perm", "dfs_permute",
            "dfs_block_score", "dfs_select_mask", "dfs_sparse_attn_fwd", "dfs_unperm", "dfs_forward", "dfs_token_order", "dfs_recall",
            "dfs_schedule", "dfs_block_score_src", "dfs_sparse_attn_fwd_src", "dfs_attn_clock_probe", "dfs_block_score_fused", "dfs_probe_mfma", "dfs_probe_copy", "dfs_probe_read",
@@ -106,8 +123,8 @@ def _check(rc: int):
 
 
 # Small calls are bound by what happens between two launches, so pointers and the stream go to the library as plain integers and a
-# geometry by itself (ctypes passes its address), the checks of a tensor are one attribute each, and the calls of every step go
-# through _calls (csrc/calls.cpp), which does what follows here for plain arguments without Python.
+# geometry by itself (ctypes passes its address), the checks of a tensor are one attribute each, and the calls of every step are tried
+# without Python first (_load_calls).
 
 
 def _ptr(t: torch.Tensor | None, dtype=None, numel=0, name="tensor"):
@@ -161,7 +178,7 @@ def _ws_args(ws: torch.Tensor | None):
 
 
 def dfs_hilbert_perm(g: Geom, perm_pad, inv, blk_valid, ws):
-    rc = _calls.token_order(g, DFS_ORDER_HILBERT3D, perm_pad, inv, blk_valid, ws)
+    rc = _plain_token_order(g, DFS_ORDER_HILBERT3D, perm_pad, inv, blk_valid, ws)
     if rc == 0:
         return
     if rc is not None:
@@ -174,7 +191,7 @@ def dfs_hilbert_perm(g: Geom, perm_pad, inv, blk_valid, ws):
 
 
 def dfs_token_order(g: Geom, order: int, perm_pad, inv, blk_valid, ws):
-    rc = _calls.token_order(g, order, perm_pad, inv, blk_valid, ws)
+    rc = _plain_token_order(g, order, perm_pad, inv, blk_valid, ws)
     if rc == 0:
         return
     if rc is not None:
@@ -317,7 +334,7 @@ def dfs_unperm(g: Geom, dtype: int, o_perm, inv, o):
 
 def dfs_forward(g: Geom, dtype: int, q, k, v, perm_pad, inv, refresh: bool, mode: int, sparsity: float, mass: float,
                 st: MaskState, scale: float, o, ws):
-    rc = _calls.forward(g, dtype, q, k, v, perm_pad, inv, refresh, mode, sparsity, mass, st, scale, o, ws)
+    rc = _plain_forward(g, dtype, q, k, v, perm_pad, inv, refresh, mode, sparsity, mass, st, scale, o, ws)
     if rc == 0:
         return
     if rc is not None:

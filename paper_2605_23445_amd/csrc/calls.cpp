@@ -5,6 +5,7 @@
 // among others, in Python -> here): token order of 75 600 tokens 6.2 -> 4.2, of 64 tokens 5.6 -> 3.3, reuse step of 512 tokens x 8
 // heads 8.6 -> 6.9; a refresh step of 256 fp32 tokens stays at 16.7, which its kernels take.
 //
+// The module holds the version of the torch it was built against, whose classes it reads: binding.py uses it with no other.
 // A call goes to the library only if every argument is of the plain kind and passes every check of binding.py; else None is returned,
 // nothing has happened, and binding.py does the call, or raises, in its own way.
 #include <torch/csrc/autograd/python_variable.h>
@@ -158,5 +159,7 @@ PyMODINIT_FUNC PyInit__calls() {
   s_mask = PyUnicode_InternFromString("mask");
   s_k_head = PyUnicode_InternFromString("k_head");
   s_K_max = PyUnicode_InternFromString("K_max");
-  return PyModule_Create(&module);
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "torch_version", DFS_TORCH_VERSION) != 0) Py_CLEAR(m);
+  return m;
 }

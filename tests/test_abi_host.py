@@ -156,3 +156,52 @@ def test_build_entry_does_not_need_a_built_library():
     # and build.py itself imports nothing from the package
     src = open(os.path.join(root, "paper_2605_23445_amd", "build.py")).read()
     assert "paper_2605_23445_amd" not in src.replace("paper_2605_23445_amd/build.py", "")
+
+
+@pytest.mark.parametrize("module", ["built", "missing", "damaged", "other torch"])
+def test_binding_works_without_the_module_of_its_calls(module, tmp_path):
+    """libdfsattn.so alone is enough, whatever became of _calls: the calls then go through ctypes, and a warning says so."""
+    import shutil
+    import subprocess
+    import sys
+    import sysconfig
+    src, pkg = os.path.dirname(P.__file__), tmp_path / "paper_2605_23445_amd"
+    pkg.mkdir()
+    for name in ("__init__.py", "binding.py", "libdfsattn.so"):
+        os.symlink(os.path.join(src, name), pkg / name)
+    calls = "_calls" + sysconfig.get_config_var("EXT_SUFFIX")
+    if module == "damaged":
+        (pkg / calls).write_bytes(b"\x7fELF, cut short")
+    elif module != "missing":
+        shutil.copy(os.path.join(src, calls), pkg / calls)
+    code = f"""
+import warnings, torch
+if {module == "other torch"}: torch.__version__ = "0.1"
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    import paper_2605_23445_amd as P
+print(sum("g.build()" in str(w.message) for w in seen))
+g, x = P.Geom(2, 3, 5, 0, 1, 64, 64, 16), torch.zeros(64, dtype=torch.int32)
+print(P.dfs_geom_sizes(g).N)
+for call in (P.dfs_hilbert_perm, lambda *a: P.dfs_token_order(a[0], 1, *a[1:])):
+    try: call(g, x, x, x, x)
+    except ValueError as e: print(e)
+try: P.dfs_forward(g, P.DFS_BF16, x, x, x, x, x, True, 0, 0.5, 0.0, P.MaskState(x, x, None, None, 1), 0.125, x, x)
+except ValueError as e: print(e)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    lines = r.stdout.split("\n")
+    assert lines[:2] == ["0" if module == "built" else "1", "30"]
+    assert len(lines) == 6 and all("must be a contiguous device tensor" in x for x in lines[2:5]), lines
+
+
+@pytest.mark.parametrize("header", ["Python.h", "torch/csrc/autograd/python_variable.h", "c10/hip/HIPStream.h"])
+def test_build_leaves_the_module_out_where_its_headers_are_missing(header, monkeypatch):
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("_dfs_build", os.path.join(ROOT, "paper_2605_23445_amd", "build.py"))
+    build = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(build)
+    exists = os.path.exists
+    monkeypatch.setattr(os.path, "exists", lambda p: not str(p).endswith(header) and exists(p))
+    assert build._calls_command() is None
