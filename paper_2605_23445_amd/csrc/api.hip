@@ -38,7 +38,7 @@ int check_geom(const dfs_geom* g, dfs_sizes* s) {
   int64_t N_v = int64_t(g->T) * g->H * g->W;
   int64_t N = N_v + g->n_text;
   int64_t M_v = (N_v + g->B - 1) / g->B, M_x = (int64_t(g->n_text) + g->B - 1) / g->B;
-  if (M_v + M_x > 65536) return fail(DFS_ESHAPE, "M=%lld blocks exceeds 65536", (long long)(M_v + M_x));
+  if (M_v + M_x > MAX_BLOCKS) return fail(DFS_ESHAPE, "M=%lld blocks exceeds %d", (long long)(M_v + M_x), MAX_BLOCKS);
   if ((M_v + M_x) * g->B * int64_t(g->heads) >= (int64_t(1) << 40))
     return fail(DFS_ESHAPE, "heads*N_pad too large");
   int mx = g->T > g->H ? g->T : g->H;

@@ -262,7 +262,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // the lanes of a quad look up one each and exchange them inside the quad, on the way of an addition that is needed anyway, so that a
   // tile costs LQ lookups instead of LPW (75 600 tokens dense, d = 128, 1 % of the call; 60 of 591 blocks 1.5 %).  The
   // requests go through a buffer descriptor of the head, whose bounds turn positions that are none (pads, -1; a damaged order) into
-  // zeros: their offsets, 2^32 - 2 D and more, lie behind any head that the host takes this way.  With a mask of the lanes in its
+  // zeros: their offsets, 2^32 - 2 D and more, lie behind any head.  With a mask of the lanes in its
   // place the calls took 2 to 5 % longer.
   constexpr int LQ = (LPW + 3) / 4;
   const int lane_row = 4 * ((lane % (LPW < 4 ? LPW : 4) * NW * 64 + wave * 64 + lane) / CH);             // bytes of row_index
@@ -290,6 +290,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   };
   auto offsets = [&](const Rows& r) {                // byte offsets of the rows inside the head
     constexpr uint32_t OUT = 0xFFFFFFFFu / uint32_t(2 * D);
+    static_assert(int64_t(MAX_BLOCKS) * BM <= OUT, "no row of a head lies at the offset of a position that is none, or behind 32 bits");
     Rows o;
 #pragma unroll
     for (int i = 0; i < LQ; ++i) o.at[i] = (r.at[i] < OUT ? r.at[i] : OUT) * uint32_t(2 * D);
@@ -1072,6 +1073,11 @@ static TailSplit tail_split(const dfs_geom* g, const dfs_sizes& s, int32_t K_max
   return {full, rows, splits};
 }
 
+// Whether all XCDs walk one head together (kernel's mapping 2), an eighth of its video blocks each: once that fills the XCD's 64
+// work-group slots (measured +3..6 % on the 75 600- and 118 800-token shapes, -4 % on the 17 550-token one, which stays on mapping 1).
+static int xcd_blocks(const dfs_sizes& s) { return (s.M_v + 7) / 8; }
+static bool walked_together(const dfs_sizes& s) { return xcd_blocks(s) >= 64; }
+
 // Whether dfs_forward's attention gathers keys and values itself (kernel's SRC) instead of having them reordered in front.  It saves
 // the reorder's way through memory, and on a reuse step its launch; it costs a tile's loads some ten instructions, which is 1 to 2 %
 // of a long dense call.  Measured (us a call, reordered -> gathered), reuse steps: d = 64, 512 tokens x 8 heads 13.0 -> 9.1,
@@ -1084,8 +1090,7 @@ static TailSplit tail_split(const dfs_geom* g, const dfs_sizes& s, int32_t K_max
 // Not where the output lies over the keys or values either: they are then reordered before the first row is written.
 bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* k, const void* v, const void* o) {
   if (dtype != DFS_BF16) return false;
-  if (s.N > int64_t(0xFFFFFFFFu / uint32_t(2 * g->d))) return false;    // offsets inside a head are 32 bits
-  if ((s.M_v + 7) / 8 >= 64 && !(g->d == 128 && g->B == 128)) return false;
+  if (walked_together(s) && !(g->d == 128 && g->B == 128)) return false;
   const uintptr_t bytes = uintptr_t(g->heads) * s.N * g->d * 2, out = reinterpret_cast<uintptr_t>(o);
   for (const void* p : {k, v}) {
     const uintptr_t in = reinterpret_cast<uintptr_t>(p);
@@ -1101,11 +1106,9 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
   if (dtype == DFS_BF16) {
     const int64_t total = int64_t(g->heads) * s.M;
     if (total > (int64_t(1) << 30)) return fail(DFS_ESHAPE, "dfs_sparse_attn_fwd: heads*M too large");
-    // an eighth of a head's video blocks per XCD once that fills the XCD's 64 work-group slots (measured
-    // +3..6 % on the 75 600- and 118 800-token shapes, -4 % on the 17 550-token one, which stays on mapping 1)
-    const int chunk = (s.M_v + 7) / 8;
+    const int chunk = xcd_blocks(s);
     const TextSplit ts = lse ? TextSplit{1, s.M} : text_split(g, s, K_max, scratch_bytes);
-    const int mapping = chunk >= 64 ? 2 : ts.splits > 1 ? 3 : 1;
+    const int mapping = walked_together(s) ? 2 : ts.splits > 1 ? 3 : 1;
     const int text_slots = (g->heads * s.M_x * ts.splits + 7) / 8, video_slots = int((int64_t(g->heads) * s.M_v + 7) / 8);
     const int per_xcd = mapping == 2 ? g->heads * chunk : mapping == 3 ? video_slots : int((total + 7) / 8);
     int32_t* tickets = static_cast<int32_t*>(scratch);

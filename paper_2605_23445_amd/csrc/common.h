@@ -8,6 +8,8 @@
 
 namespace dfs {
 
+constexpr int MAX_BLOCKS = 65536;                   // of a sequence (check_geom): at most 2^23 rows
+
 // Records `msg` as the calling thread's last error and returns `code`.
 int fail(int code, const char* fmt, ...);
 // Validates a geometry (sets the error on failure) and fills the derived sizes.
@@ -51,14 +53,15 @@ int check_select(const dfs_geom* g, const dfs_sizes& s, int mode, double sparsit
 int run_select_mask(const dfs_geom* g, const dfs_sizes& s, const float* score, int mode, double sparsity,
                     double mass, uint8_t* mask, int32_t* kv_idx, int32_t* kv_cnt, int32_t K_max,
                     int32_t* k_head, void* ws, hipStream_t st);
+// row_index (may be NULL): Q and O in source order, and K and V as well with kv_src.  scratch (may be NULL): room to split text rows
+// over work-groups; its first split_tickets() words are zero when the kernel starts, already (zeroed) or by a launch of its own.
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
                     const int32_t* row_index, bool kv_src, bool zeroed, void* scratch, size_t scratch_bytes, hipStream_t st);
-// Whether dfs_forward hands the attention K and V in source order (kv_src below) instead of reordering them.
+// Whether dfs_forward hands the attention K and V in source order (kv_src above) instead of reordering them.
 bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* k, const void* v, const void* o);
-// row_index (may be NULL): Q and O in source order.  scratch (may be NULL): room to split text rows over work-groups; its
-// first split_tickets() words are zero when the kernel starts, already (zeroed) or by a launch of its own: one per text block, and with 512 query blocks and more one for each
-// that the last round of work-groups may share (at most 127 per XCD).
+// One per text block, and with 512 query blocks and more one for each that the last round of work-groups may share (at most 127
+// per XCD).
 inline size_t split_tickets(const dfs_geom* g, const dfs_sizes& s) {
   return size_t(g->heads) * s.M_x + (int64_t(g->heads) * s.M >= 512 ? 8 * 128 : 0);
 }
