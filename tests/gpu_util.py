@@ -2,7 +2,9 @@
 hand results back as numpy arrays.  No arithmetic of the method lives here."""
 from __future__ import annotations
 
+import ctypes as C
 import math
+import re
 
 import numpy as np
 import torch
@@ -124,3 +126,36 @@ def gpu_unperm(g, dtype, op, inv):
 def as_f64_dev(t: torch.Tensor) -> np.ndarray:
     """Exact up-conversion of a device tensor (bf16 or fp32) to a float64 numpy array."""
     return t.to(torch.float32).cpu().numpy().astype(np.float64)
+
+
+class _KernelNodeParams(C.Structure):
+    """hipKernelNodeParams"""
+    _fields_ = [("block", C.c_uint * 3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", C.c_uint * 3), ("args", C.c_void_p),
+                ("lds", C.c_uint)]
+
+
+def kernels_of(call) -> list[str]:
+    """The library's kernels that `call` launches, in order, as "name" or "name<template arguments>" (captured, not run)."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    hip = C.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))     # the one that torch uses
+    hip.hipKernelNameRefByPtr.restype, hip.hipKernelNameRefByPtr.argtypes = C.c_char_p, [C.c_void_p, C.c_void_p]
+    n = C.c_size_t()
+    raw = C.c_void_p(graph.raw_cuda_graph())
+    assert hip.hipGraphGetNodes(raw, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, C.byref(n)) == 0
+    names = []
+    for node in nodes:
+        kind, p = C.c_int(-1), _KernelNodeParams()
+        assert hip.hipGraphNodeGetType(C.c_void_p(node), C.byref(kind)) == 0
+        if kind.value != 0:                                # copies of the caller's
+            continue
+        assert hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(p)) == 0
+        own = re.match(r"_ZN3dfs\d+([a-z_0-9]+?_kernel)(?:I((?:L[a-z]\d+E)+)E)?", hip.hipKernelNameRefByPtr(p.func, None).decode())
+        if own is None:                                    # torch's
+            continue
+        head, args = own.groups()
+        names.append(head + (f"<{', '.join(re.findall(r'L[a-z]([0-9]+)E', args))}>" if args else ""))
+    return names

@@ -1,5 +1,7 @@
-"""dfs_forward, whose pooling kernel reorders K and V on the way, against the staged calls, bit for bit, at the sub-block sizes
-that make its row groups in flight one short pass, whole passes and several, with ragged last sub-blocks and text."""
+"""dfs_forward against the staged calls, bit for bit, at the sub-block sizes that make the pooling kernel's row groups in flight one
+short pass, whole passes and several, with ragged last sub-blocks and text: with an output of its own (bf16 tensors: the attention gathers
+K and V) and with one over the keys or the values, where a refresh step's pooling reorders both on the way before the first row is
+written, and a reuse step's gather does (fp32 tensors: always)."""
 import math
 
 import pytest
@@ -32,7 +34,15 @@ def test_forward_equals_staged_calls(dtype, d, B, Bs, W, n_text):
     st2 = G.gpu_select(g, G.gpu_score(g, dtype, qp, kp), P.DFS_SELECT_TOPK, 0.5)
     want = G.gpu_unperm(g, dtype, G.gpu_attn(g, dtype, qp, kp, vp, st2, want_lse=False)[0], inv)
     for refresh in (True, False):
-        o = torch.full_like(q, float("nan"))
-        P.dfs_forward(g, dtype, q, k, v, perm_pad, inv, refresh, P.DFS_SELECT_TOPK, 0.5, 0.0, st, 1.0 / math.sqrt(d), o, ws)
-        assert torch.equal(st.kv_cnt, st2.kv_cnt)
-        assert torch.equal(o.view(torch.uint8), want.view(torch.uint8)), refresh
+        for over in (None, "k", "v"):
+            x = [q, k, v]
+            o = torch.full_like(q, float("nan"))
+            if over:
+                x["qkv".index(over)] = o
+                o.copy_(k if over == "k" else v)
+            kernels = G.kernels_of(lambda: P.dfs_forward(g, dtype, *x, perm_pad, inv, refresh, P.DFS_SELECT_TOPK, 0.5, 0.0, st, 1.0 / math.sqrt(d), o, ws))
+            assert not any("gather_rows" in name for name in kernels) or not refresh
+            assert dtype == P.DFS_F32 or kernels[-1].endswith(", 0>" if over else ", 1>")        # from the reordered copies, or gathered
+            P.dfs_forward(g, dtype, *x, perm_pad, inv, refresh, P.DFS_SELECT_TOPK, 0.5, 0.0, st, 1.0 / math.sqrt(d), o, ws)
+            assert torch.equal(st.kv_cnt, st2.kv_cnt)
+            assert torch.equal(o.view(torch.uint8), want.view(torch.uint8)), (refresh, over)
