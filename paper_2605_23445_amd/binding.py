@@ -103,7 +103,7 @@ def _load_calls():
         why = "built for another torch"
     except ImportError as e:
         why = str(e)
-    warnings.warn(f"the module of the hottest calls cannot be used ({why}): they go through Python, some 2 us slower each; "
+    warnings.warn(f"the module of the hottest calls cannot be used ({why}): they go through Python, 2.5 to 5 us of host time more each; "
                   "run `python -c 'import __graft_entry__ as g; g.build()'`", RuntimeWarning, stacklevel=3)
     return lambda *a: None, lambda *a: None
 

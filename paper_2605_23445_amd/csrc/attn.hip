@@ -508,7 +508,10 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // read a full tile later.
   f32x16 s0, s1;
   u32x4 p0[2], p1[2];                              // probabilities as bf16 pairs: B operands of the products
-  int b_cur = 0, b_nxt = 0;                        // key blocks of tiles t and t + 1 (a list lookup where tile t + 2 starts another)
+  // Key blocks of tiles t and t + 1; the list is looked up where tile t + 2 starts another block.  (With a lookup for every tile, K and V
+  // reordered, blocks of 128: d = 64, 17 550 tokens x 48 heads, 21 of 138 blocks, 627 -> 621 us; d = 128, 75 600 x 40, 60 of 591, 11 331 -> 11 298,
+  // x 8 dense 20 105 -> 19 994, x 4 dense with log-sum-exp 10 981 -> 10 892.)
+  int b_cur = 0, b_nxt = 0;
   // SRC: block of tile t + 2, list entry of tile t + 3, positions of the rows of K(t + 2), offsets of those of V(t + 1); SLIM: all a
   // tile less.  Positions are looked up a tile before the tile is requested and two before it is read.
   int b_far = 0;
@@ -992,8 +995,8 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(const float* __restrict__
     lse[int64_t(head) * N_pad + q_row] = l_all > 0.f ? (ref + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f : -INFINITY;
 }
 
-// The tickets of shared rows, for calls with no kernel in front that clears them on its way (a launch of 3 us; a memset may not be
-// recorded into a graph).
+// The tickets of shared rows, for calls with no kernel in front that clears them on its way (1.4 us at the least under the profiler, 5.5
+// on average; a memset may not be recorded into a graph).
 __global__ void __launch_bounds__(256) clear_tickets_kernel(int32_t* __restrict__ tickets, int n) {
   for (int i = threadIdx.x; i < n; i += 256) tickets[i] = 0;
 }
@@ -1079,14 +1082,16 @@ static int xcd_blocks(const dfs_sizes& s) { return (s.M_v + 7) / 8; }
 static bool walked_together(const dfs_sizes& s) { return xcd_blocks(s) >= 64; }
 
 // Whether dfs_forward's attention gathers keys and values itself (kernel's SRC) instead of having them reordered in front.  It saves
-// the reorder's way through memory, and on a reuse step its launch; it costs a tile's loads some ten instructions, which is 1 to 2 %
-// of a long dense call.  Measured (us a call, reordered -> gathered), reuse steps: d = 64, 512 tokens x 8 heads 13.0 -> 9.1,
-// 2 565 + 77 x 12, blocks of 64, 30.0 -> 22.4, 17 550 x 48, 21 of 138 blocks, 676 -> 616; d = 128, 5 632 x 24 121 -> 92, 17 550 x 24
-// 620 -> 550, 75 600 x 40, 60 of 591 blocks, 11 610 -> 11 000; refresh steps: 17 550 x 48, d = 64, 715 -> 679, 75 600 x 40 11 997 ->
-// 11 580; dense: 17 550 x 12, d = 64, 969 -> 960, 75 600 x 40 96.89 -> 96.96 ms.  Not for sequences that all XCDs walk together
-// (mapping 2) at d = 64 or in blocks of 64, where the reorder is a smaller part: 75 600 tokens, d = 64, dense x 8 11 155 -> 11 236,
-// 48 of 591 blocks x 10 3 022 -> 3 030; d = 128, blocks of 64, dense x 2 6 458 -> 6 918.  The host does not know whether a call is
-// dense, so the line lies where dense calls break even.
+// the reorder's way through memory, and on a reuse step its launch; it costs a tile's loads some ten instructions, 0.3 % of a long dense
+// call.  Measured (us a call, reordered -> gathered; medians of three runs each, in turn on one card, whose spread is 0.1 to 1 %),
+// reuse steps: d = 64, 512 tokens x 8 heads 11.9 -> 8.7, 2 565 + 77 x 12, blocks of 64, 30.0 -> 22.6, 17 550 x 48, 21 of 138 blocks,
+// 689 -> 631; d = 128, 5 632 x 24, 9 of 44 blocks, 131 -> 99, 17 550 x 24, 21 of 138, 634 -> 573, 75 600 x 40, 60 of 591, 11 874 ->
+// 11 319; refresh steps, whose pooling reorders on its way: 2 565 + 77 x 12 36.8 -> 35.5, 17 550 x 48, d = 64, 730 -> 692, 75 600 x 40
+// 12 258 -> 11 982, 118 800 + 256 x 24, 93 of 929, 18 023 -> 17 850; dense: 17 550 x 12, d = 64, 988 -> 987, 75 600 x 40 98.8 ->
+// 99.1 ms.  Not for sequences that all XCDs walk together at d = 64 or in blocks of 64, where the reorder is a smaller part: 75 600 tokens, dense, d = 64
+// x 8 11 307 -> 11 476, d = 128, blocks of 64, x 2 6 633 -> 7 203, 119 of 1 182 blocks x 10 3 746 -> 3 854; d = 64 would win 2 to 3 %
+// on short lists (48 of 591 blocks x 10 1 305 -> 1 267, 119 of 1 182 of 64 x 10 1 859 -> 1 824).  The host does not know whether a
+// call is dense, so the line lies where dense calls break even.
 // Not where the output lies over the keys or values either: they are then reordered before the first row is written.
 bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* k, const void* v, const void* o) {
   if (dtype != DFS_BF16) return false;

@@ -1,9 +1,9 @@
 // The calls of a small problem from Python without the cost of marshalling them in Python: dfs_forward and the token orders take their
 // arguments straight from the objects.  A launch costs the host some 3 us and its kernel often less, so what bounds
-// such calls is what Python does between two of them: some fifty attribute lookups of tensors and a ctypes call, 6 of the 10 us that a
-// reuse step takes the host.  Here it takes 4 in all (one launch), a refresh step 9 instead of 16 (three).  Measured (us a call
-// among others, in Python -> here): token order of 75 600 tokens 6.2 -> 4.2, of 64 tokens 5.6 -> 3.3, reuse step of 512 tokens x 8
-// heads 8.6 -> 6.9; a refresh step of 256 fp32 tokens stays at 16.7, which its kernels take.
+// such calls is what Python does between two of them: some fifty attribute lookups of tensors and a ctypes call.  Measured (us, in Python ->
+// here).  The host's time of a call in a burst of eight: reuse step (one launch) 10.0 -> 4.9, refresh step of 256 fp32 tokens
+// (three) 17.2 -> 13.0, token order 6.5 -> 4.1.  A call among others: token order of 75 600 or 64 tokens 6.2 -> 3.6, reuse step of
+// 512 tokens x 8 heads, d = 64, 9.4 -> 8.7, of which its kernel takes 8.5; the refresh step stays at 16.5, which its kernels take.
 //
 // The module holds the version of the torch it was built against, whose classes it reads: binding.py uses it with no other.
 // A call goes to the library only if every argument is of the plain kind and passes every check of binding.py; else None is returned,

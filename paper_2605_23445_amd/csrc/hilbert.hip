@@ -4,9 +4,10 @@
 // No keys are sorted or counted.  A token's rank among the cells of the grid has a closed form under every
 // order: walking down the levels of the curve, the cells that come before it are those of the sibling octants the
 // curve visits earlier, and an octant clipped by the grid holds the product of its three clipped extents.  So one
-// kernel without scratch memory gives perm, inverse and block sizes.  75 600 tokens take 3.4 us a call among
-// others, of which the launch is half; the six kernels before (keys marked in a bitmap over the enclosing cube, its prefix sum in three
-// launches, keys turned into ranks) took 26 us with the gaps between them.  Run once per geometry.
+// kernel without scratch memory gives perm, inverse and block sizes.  75 600 tokens take 3.4 us a launch among
+// others in a graph, of which the launch itself is half, and 3.6 us a call from Python, whose host side is then the longer
+// one; the six kernels before (keys marked in a bitmap over the enclosing cube, its prefix sum in three launches, keys turned
+// into ranks) took 26 us with the gaps between them.  Run once per geometry.
 #include "common.h"
 
 namespace dfs {
@@ -21,8 +22,8 @@ namespace dfs {
 // what bounds the kernel is their number, some fifty a level: an axis keeps its coordinate and the reflected one in one word, which is
 // exchanged in one piece, and the extent of the present sub-cube inside the grid, which is halved with it; volumes are at most
 // 2^23, their factors at most 2^18, so the products are 24-bit ones, at four times the rate.  With the extents worked out anew from
-// the grid, reflections apart and 32-bit products and divisions a call took 4.13 us, now 3.36 (75 600 tokens; 64
-// tokens 2.12 and 1.75).
+// the grid, reflections apart and 32-bit products and divisions a launch among others in a graph took 4.11 us, now 3.39 (75 600
+// tokens; 64 tokens 1.96 and 1.76).
 template <int N>
 __device__ __forceinline__ uint32_t hilbert_rank(const uint32_t (&x)[N], const uint32_t (&dim)[N], int b) {
   constexpr int REFLECTED = 16;                      // first bit of the reflected coordinate
