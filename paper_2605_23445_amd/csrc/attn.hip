@@ -1139,7 +1139,9 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     if (g->d == 64) { if (g->B == 64) ATTN_KS(64, 64); else ATTN_KS(64, 128); }
     else if (g->B == 128) ATTN_KS(128, 128);
     else if (one_buffer) ATTN_1(128, 64, true);
-    else ATTN_KS(128, 64);
+    else if (tail.splits > 1) ATTN_X(128, 64, false, 1, false, true, false);      // only sequences that all XCDs walk together: none is gathered
+    else if (ks == 2) ATTN_WHOLE(128, 64, 2, false);
+    else ATTN_WHOLE(128, 64, 1, false);
 #undef ATTN_KS
 #undef ATTN_1
 #undef ATTN_TAIL
