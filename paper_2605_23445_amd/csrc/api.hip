@@ -145,7 +145,7 @@ int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, cons
   } else if (!src && (rc = run_permute(g, s, dtype, k, perm_pad, k_perm, v, v_perm, tickets, n_tickets, hs))) {
     return rc;
   }
-  return run_sparse_attn(g, s, dtype, q, src ? k : k_perm, src ? v : v_perm, st->kv_idx, st->kv_cnt, st->K_max, scale, o, nullptr, perm_pad, src, refresh || !src,
+  return run_sparse_attn(g, s, dtype, q, src ? k : k_perm, src ? v : v_perm, st->kv_idx, st->kv_cnt, st->K_max, scale, o, nullptr, perm_pad, src, !refresh || (mode == DFS_SELECT_TOPK && dfs_keep_count(sparsity, s.M_v) == s.M_v), refresh || !src,
                          base + L.text, L.text_bytes, hs);
 }
 

@@ -74,21 +74,54 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
 // is the lookup of positions and their way to the lanes.  See attn_reads_source below for the rule.
 template <int D, int BM, bool XLSE, int KS>
 constexpr int attn_waves() { return D == 64 && BM == 128 && !XLSE && KS == 1 ? 3 : 2; }
+// Pairs of query blocks that attn_pairs_kernel takes, and in which order.  A pair is two neighbouring video blocks of a head (the last
+// one may be alone) or two text blocks.  Slots of an XCD: the text pairs of all heads in turn with the other XCDs, then its eighth of
+// the video pairs of head 0, of head 1, ... as in mapping 2.  Its PAIR_WGS work-groups take a slot each per round.
+constexpr int PAIR_WGS = 32;
+__host__ __device__ __forceinline__ int pair_text_slots(int M_v, int M, int n_heads) { return (n_heads * ((M - M_v + 1) / 2) + 7) / 8; }
+__host__ __device__ __forceinline__ int pair_chunk(int M_v) { return ((M_v + 1) / 2 + 7) / 8; }        // video pairs of a head and XCD
+// First block of the pair in a slot, -1 for none.
+__device__ __forceinline__ int pair_at(int xcd, int slot, int M_v, int M, int n_heads, int& head) {
+  const int XP = (M - M_v + 1) / 2, C = pair_chunk(M_v), text_slots = pair_text_slots(M_v, M, n_heads);
+  if (slot < text_slots) {
+    const int id = slot * 8 + xcd;
+    head = XP > 0 ? id / XP : 0;
+    return head < n_heads && XP > 0 ? M_v + 2 * (id % XP) : -1;
+  }
+  const int s2 = slot - text_slots, u = 2 * (xcd * C + s2 % C);
+  head = s2 / C;
+  return head < n_heads && u < M_v ? u : -1;
+}
+// Whether the pair's rows are dense.  Text rows always are; they go with the head's first video rows, so that they run beside what
+// takes as long.
+__device__ __forceinline__ bool pair_dense(const int32_t* __restrict__ kv_cnt, int head, int u, int M_v, int M) {
+  const int32_t* cnt = kv_cnt + int64_t(head) * M;
+  const int end = u < M_v ? M_v : M, v1 = M_v > 1 ? 1 : 0;
+  return cnt[u] >= M && cnt[u + 1 < end ? u + 1 : u] >= M && (u < M_v || (cnt[0] >= M && cnt[v1] >= M));
+}
+__device__ __forceinline__ bool in_pairs(const int32_t* __restrict__ kv_cnt, int head, int u, int M_v, int M, int n_heads, int rounds) {
+  const int u0 = u < M_v ? u & ~1 : M_v + ((u - M_v) & ~1), C = pair_chunk(M_v);
+  const int slot = u < M_v ? pair_text_slots(M_v, M, n_heads) + head * C + u0 / 2 % C : (head * ((M - M_v + 1) / 2) + (u0 - M_v) / 2) / 8;
+  return slot < rounds * PAIR_WGS && pair_dense(kv_cnt, head, u0, M_v, M);
+}
+
+// What a work-group does: the query block u of `head` (BM = 256: blocks u and u + 1, which keep every key block), or with TAIL and
+// for text rows the share `split` of it; xcd and slot name it among the tail's.
 template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL, bool SRC>
-__global__ void __launch_bounds__(BM * 2 * KS)
-__attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE, KS>(), attn_waves<D, BM, XLSE, KS>())))
-attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                 const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
-                 float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
-                 int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
-                 float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows,
-                 int tail_splits) {
+__device__ __forceinline__ void
+attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+          const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
+          float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
+          int M_v, int M, int total_wg, float scale, unsigned long long* __restrict__ clock_probe, float* __restrict__ part,
+          int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows, int pair_rounds, int head, int u, int split,
+          int splits, int xcd, int slot, bool tail) {
   constexpr int NW = BM / 32;                      // waves per group: one per 32 query rows
   constexpr int CH = D / 8;                        // 16-byte chunks per row
   constexpr int TILE = KN * D;                     // elements per tile
   constexpr int LPW = KN * CH / (64 * NW);         // load instructions per wave and tile
   constexpr int RJ = NW * 64 / CH;                 // tile rows between two load instructions of a wave
-  constexpr int STEPS = BM / KN;                   // tiles per key block
+  constexpr int BK = BM > 128 ? 128 : BM;          // rows of a block
+  constexpr int STEPS = BK / KN;                   // tiles per key block
   constexpr int NF = D / 8;                        // operand fragments per stage: D/16 of V^T, D/16 of K
   constexpr int ESL = NF - 1;                      // matrix instructions the sixteen exponentials of a half tile are spread over
   constexpr float HEADROOM = 4.f, SUM_LIMIT = 2.25f;                      // see "A row's reference" below
@@ -96,55 +129,10 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   static_assert(!SLIM || KS == 1, "the merge of wave groups wants all four buffers");
   static_assert(!TAIL || (KS == 1 && !XLSE), "see run_sparse_attn");
   static_assert(!SRC || !XLSE, "see run_sparse_attn");
+  constexpr bool PAIR = BM > 128;
+  static_assert(!PAIR || (KS == 1 && !SLIM && !TAIL), "see attn_pairs_kernel");
   __shared__ __attribute__((aligned(16))) uint16_t tiles[KS * (SLIM ? 2 : 4) * TILE];
   constexpr int K0 = 0, K1 = SLIM ? 0 : 2 * TILE, V0 = SLIM ? 2 * TILE : 4 * TILE, V1 = SLIM ? 2 * TILE : 6 * TILE;
-
-  // Work-group to (head, query block).  Ids are dealt round-robin to the 8 XCDs, so id % 8 names the XCD
-  // and id / 8 the order inside it.
-  //   mapping 2 (long sequences): every XCD takes its own eighth of the query blocks of head 0, then of
-  //     head 1, ...  All XCDs are on the same head at the same time, so the key/value working set of the
-  //     chip is one or two heads and stays in the memory-side cache, while the blocks that meet in one
-  //     L2 are neighbours on the curve, which share key blocks.  The dense text blocks of all heads, the
-  //     longest work-groups, come first.
-  //   mapping 1 (an eighth of a head would not fill an XCD): each XCD walks whole heads of its own,
-  //     query blocks last-first so that the text blocks of a head start first.
-  //   mapping 3: mapping 1 with the text blocks, split, of all heads in front as in mapping 2.
-  // Behind slot tail_from, where the query blocks left would not fill the XCD once more, tail_splits work-groups share each.
-  int head, u, split = 0, splits = 1, slot = blockIdx.x / 8;
-  const int xcd = blockIdx.x % 8;
-  const bool tail = TAIL && slot >= tail_from;
-  if (tail) {
-    splits = tail_splits;
-    split = (slot - tail_from) / tail_rows;
-    slot -= split * tail_rows;
-  }
-  if (mapping >= 2) {
-    const int M_x = M - M_v, n_heads = total_wg / M;
-    const int text_wgs = n_heads * M_x * text_splits, text_slots = (text_wgs + 7) / 8;
-    if (slot < text_slots) {
-      const int id = slot * 8 + xcd;
-      if (id >= text_wgs) return;
-      u = M_v + id % M_x;
-      split = id / M_x % text_splits;
-      splits = text_splits;
-      head = id / M_x / text_splits;
-    } else if (mapping == 2) {
-      const int C = (M_v + 7) / 8, s2 = slot - text_slots;
-      head = s2 / C;
-      u = xcd * C + s2 % C;
-      if (head >= n_heads || u >= M_v) return;
-    } else {
-      const int logical = xcd * wg_per_xcd + slot - text_slots;
-      if (slot - text_slots >= wg_per_xcd || logical >= n_heads * M_v) return;
-      head = logical / M_v;
-      u = M_v - 1 - logical % M_v;
-    }
-  } else {
-    const int logical = xcd * wg_per_xcd + slot;
-    if (slot >= wg_per_xcd || logical >= total_wg) return;
-    head = logical / M;
-    u = M - 1 - logical % M;
-  }
 
   // diagnostic: shader-clock cycles and constant-rate (100 MHz) ticks this work-group lives for
   const unsigned long long probe_c0 = clock_probe ? clock64() : 0, probe_w0 = clock_probe ? wall_clock64() : 0;
@@ -156,11 +144,15 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
   };
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;
+  if (PAIR) asm volatile("" : "+v"(tid));             // see attn_pairs_kernel
+  const int lane = tid & 63;
   const int grp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / (64 * NW)), wave = (tid >> 6) - grp * NW;
   const int n = lane & 31, h = lane >> 5;
-  const int cnt_in = kv_cnt[int64_t(head) * M + u];
-  const bool dense = cnt_in >= M;
+  const int cnt_in = PAIR ? M : kv_cnt[int64_t(head) * M + u];
+  const bool dense = PAIR || cnt_in >= M;
+  constexpr bool PAIRABLE = D == 128 && BM == 128 && KS == 1;            // see pair_rounds
+  if (PAIRABLE && dense && pair_rounds > 0 && in_pairs(kv_cnt, head, u, M_v, M, total_wg / M, pair_rounds)) return;     // attn_pairs_kernel has done it
   const bool shared_row = !XLSE && splits > 1;
   int cnt = dense ? M : (cnt_in < 0 ? 0 : (cnt_in > K_max ? K_max : cnt_in));
   const int run = tail ? (cnt + splits - 1) / splits : split_blocks;
@@ -170,11 +162,14 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   const int64_t head_off = int64_t(head) * (SRC ? N_src : N_pad) * D;
   const uint16_t* kh = k + head_off;
   const uint16_t* vh = v + head_off;
-  const int64_t q_row0 = int64_t(u) * BM + wave * 32 + n;
+  const int64_t q_row0 = int64_t(u) * BK + wave * 32 + n;
+  // PAIR: this wave's block, and whether there is one (the last video or text block may be alone)
+  const int u_wave = PAIR ? u + wave / (BK / 32) : u;
+  const bool owned = !PAIR || u_wave < (u < M_v ? M_v : M);
 
   // Where this lane's query rows live.  With row_index (the permutation) Q is read from, and O written to,
   // the tensors in source order, which spares the reorder passes of Q and O; -1 marks a pad row.
-  int64_t io_row = row_index ? int64_t(row_index[q_row0]) : q_row0;
+  int64_t io_row = !owned ? -1 : row_index ? int64_t(row_index[q_row0]) : q_row0;
   if (row_index && io_row >= N_src) io_row = -1;
   const int64_t io_off = int64_t(head) * (row_index ? N_src : N_pad) * D;
 
@@ -241,7 +236,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   const uint32_t lds_tiles = uint32_t(reinterpret_cast<uintptr_t>((LDS_PTR(void))(tiles))) + uint32_t(grp * 8 * TILE);
   const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_tiles + uint32_t(wave * 1024));
   auto tile_src = [&](const uint16_t* base, int tile, int blk) {
-    return reinterpret_cast<uint64_t>(base + (int64_t(blk) * BM + (tile % STEPS) * KN) * D);
+    return reinterpret_cast<uint64_t>(base + (int64_t(blk) * BK + (tile % STEPS) * KN) * D);
   };
   auto issue_one = [&](uint64_t src, int buf, bool is_v, int j) {
     const int P = is_v ? PV : PK;
@@ -277,7 +272,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   auto look_up = [&](int step, int blk) {            // positions of tile `step` of block blk
     Rows r;
 #pragma unroll
-    for (int i = 0; i < LQ; ++i) r.at[i] = __builtin_amdgcn_raw_buffer_load_b32(index_desc, lane_row + i * 16 * RJ, (blk * BM + step * KN) * 4, 0);
+    for (int i = 0; i < LQ; ++i) r.at[i] = __builtin_amdgcn_raw_buffer_load_b32(index_desc, lane_row + i * 16 * RJ, (blk * BK + step * KN) * 4, 0);
     return r;
   };
   // The list entry of a tile further ahead, by a vector load: the wait at the tile's barrier covers it, while a scalar one is waited for
@@ -290,7 +285,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   };
   auto offsets = [&](const Rows& r) {                // byte offsets of the rows inside the head
     constexpr uint32_t OUT = 0xFFFFFFFFu / uint32_t(2 * D);
-    static_assert(int64_t(MAX_BLOCKS) * BM <= OUT, "no row of a head lies at the offset of a position that is none, or behind 32 bits");
+    static_assert(int64_t(MAX_BLOCKS) * BK <= OUT, "no row of a head lies at the offset of a position that is none, or behind 32 bits");
     Rows o;
 #pragma unroll
     for (int i = 0; i < LQ; ++i) o.at[i] = (r.at[i] < OUT ? r.at[i] : OUT) * uint32_t(2 * D);
@@ -358,9 +353,9 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   // block; their ids and real-row counts are worked out once, so that the check per half tile is two scalar compares
   // on a block id that is already at hand (measured: the 64-bit arithmetic of the general form, twice per tile, cost
   // 2 % of the kernel).
-  const int real_v_last = block_real_rows(M_v - 1, BM, M_v, N_v, n_text);
-  const int real_x_last = M > M_v ? block_real_rows(M - 1, BM, M_v, N_v, n_text) : BM;
-  const int ragged_v = real_v_last < BM ? M_v - 1 : -1, ragged_x = real_x_last < BM ? M - 1 : -1;
+  const int real_v_last = block_real_rows(M_v - 1, BK, M_v, N_v, n_text);
+  const int real_x_last = M > M_v ? block_real_rows(M - 1, BK, M_v, N_v, n_text) : BK;
+  const int ragged_v = real_v_last < BK ? M_v - 1 : -1, ragged_x = real_x_last < BK ? M - 1 : -1;
   auto mask_pads = [&](int blk, int tile, int half, f32x16& sx) {
     if (__builtin_expect(blk == ragged_v || blk == ragged_x, 0)) {
       asm volatile("");                               // keeps this a branch: turned into selects it would run on every half tile
@@ -639,7 +634,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
     bf16x8 own_k[D / 16];
     {
-      const u32x4* kp = reinterpret_cast<const u32x4*>(kh + (SRC ? io_row < 0 ? 0 : io_row : q_row0) * D);
+      const u32x4* kp = reinterpret_cast<const u32x4*>(kh + (SRC ? io_row < 0 ? 0 : io_row : owned ? q_row0 : 0) * D);
 #pragma unroll
       for (int kk = 0; kk < D / 16; ++kk) own_k[kk] = __builtin_bit_cast(bf16x8, SRC && io_row < 0 ? u32x4{0u, 0u, 0u, 0u} : kp[2 * kk + h]);
     }
@@ -650,7 +645,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     if (SLIM) __syncthreads();                       // the first half of K(0) has been read
     mask_pads(b_cur, 0, 0, s0);
     m_run = half_max(s0);
-    bool own = dense ? u - blk_first >= own_first && u - blk_first < own_first + own_blks : listed == u;
+    bool own = dense ? u_wave - blk_first >= own_first && u_wave - blk_first < own_first + own_blks : listed == u;
     if (!dense)
       for (int i = 64 + lane; i < own_blks; i += 64) own |= idx[own_first + i] == u;
     if (__builtin_amdgcn_ballot_w64(own) != 0) {     // as logits and mask_pads, with the keys from registers
@@ -658,11 +653,11 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
       for (int i = 0; i < 16; ++i) s1[i] = 0.f;
 #pragma unroll
       for (int kk = 0; kk < D / 16; ++kk) s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(own_k[kk], qf[kk], s1, 0, 0, 0);
-      if (u == ragged_v || u == ragged_x) {
-        const int real = u == ragged_v ? real_v_last : real_x_last;
+      if (u_wave == ragged_v || u_wave == ragged_x) {
+        const int real = u_wave == ragged_v ? real_v_last : real_x_last;
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if (wave * 32 + 8 * (i / 4) + 4 * h + (i % 4) >= real) s1[i] = -INFINITY;
+          if (wave % (BK / 32) * 32 + 8 * (i / 4) + 4 * h + (i % 4) >= real) s1[i] = -INFINITY;
       }
       m_run = fmaxf(m_run, half_max(s1));
     }
@@ -805,8 +800,102 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
   }
   if (XLSE) {
     const float x_tot = x_run + __shfl_xor(x_run, 32, 64);
-    if (lse && h == 0)
+    if (lse && h == 0 && owned)
       lse[int64_t(head) * N_pad + q_row0] = x_tot > 0.f ? (m_run + __builtin_amdgcn_logf(x_tot)) * 0.6931471805599453f : -INFINITY;
+  }
+}
+
+template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL, bool SRC>
+__global__ void __launch_bounds__(BM * 2 * KS)
+__attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE, KS>(), attn_waves<D, BM, XLSE, KS>())))
+attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                 const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
+                 float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
+                 int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
+                 float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows,
+                 int tail_splits, int pair_rounds) {
+  // Work-group to (head, query block).  Ids are dealt round-robin to the 8 XCDs, so id % 8 names the XCD
+  // and id / 8 the order inside it.
+  //   mapping 2 (long sequences): every XCD takes its own eighth of the query blocks of head 0, then of
+  //     head 1, ...  All XCDs are on the same head at the same time, so the key/value working set of the
+  //     chip is one or two heads and stays in the memory-side cache, while the blocks that meet in one
+  //     L2 are neighbours on the curve, which share key blocks.  The dense text blocks of all heads, the
+  //     longest work-groups, come first.
+  //   mapping 1 (an eighth of a head would not fill an XCD): each XCD walks whole heads of its own,
+  //     query blocks last-first so that the text blocks of a head start first.
+  //   mapping 3: mapping 1 with the text blocks, split, of all heads in front as in mapping 2.
+  // Behind slot tail_from, where the query blocks left would not fill the XCD once more, tail_splits work-groups share each.
+  int head, u, split = 0, splits = 1, slot = blockIdx.x / 8;
+  const int xcd = blockIdx.x % 8;
+  const bool tail = TAIL && slot >= tail_from;
+  if (tail) {
+    splits = tail_splits;
+    split = (slot - tail_from) / tail_rows;
+    slot -= split * tail_rows;
+  }
+  if (mapping >= 2) {
+    const int M_x = M - M_v, n_heads = total_wg / M;
+    const int text_wgs = n_heads * M_x * text_splits, text_slots = (text_wgs + 7) / 8;
+    if (slot < text_slots) {
+      const int id = slot * 8 + xcd;
+      if (id >= text_wgs) return;
+      u = M_v + id % M_x;
+      split = id / M_x % text_splits;
+      splits = text_splits;
+      head = id / M_x / text_splits;
+    } else if (mapping == 2) {
+      const int C = (M_v + 7) / 8, s2 = slot - text_slots;
+      head = s2 / C;
+      u = xcd * C + s2 % C;
+      if (head >= n_heads || u >= M_v) return;
+    } else {
+      const int logical = xcd * wg_per_xcd + slot - text_slots;
+      if (slot - text_slots >= wg_per_xcd || logical >= n_heads * M_v) return;
+      head = logical / M_v;
+      u = M_v - 1 - logical % M_v;
+    }
+  } else {
+    const int logical = xcd * wg_per_xcd + slot;
+    if (slot >= wg_per_xcd || logical >= total_wg) return;
+    head = logical / M;
+    u = M - 1 - logical % M;
+  }
+  attn_rows<D, BM, XLSE, KS, SLIM, TAIL, SRC>(q, k, v, kv_idx, kv_cnt, K_max, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, total_wg, scale,
+                                              clock_probe, part, tickets, text_splits, split_blocks, tail_from, tail_rows, pair_rounds, head, u,
+                                              split, splits, xcd, slot, tail);
+}
+
+// Dense rows (the first quarter of a sampling run's steps): two neighbouring query blocks of 128 rows that keep every key block, in one
+// work-group of eight waves, so that a tile is brought into LDS once for both.  What bounds them is the clock that the chip grants, and
+// it pays for every byte on its way: half the tile loads are 4.5 % (75 600 tokens x 40 heads 102.4 -> 97.7 ms, 1.15 -> 1.20 PFLOP/s on one
+// card), the same bits.  The kernel looks the counts up and leaves if no pair is dense; its work-groups, one per CU, walk
+// their slots in step.  The blocks behind the last full round, pairs that are not dense and single blocks are the other kernel's, in a
+// launch behind this one.
+template <int D, bool XLSE, bool SRC>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+attn_pairs_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                  const int32_t* __restrict__ kv_cnt, uint16_t* __restrict__ o, float* __restrict__ lse, const int32_t* __restrict__ row_index,
+                  int64_t N_src, int64_t N_pad, int64_t N_v, int n_text, int M_v, int M, int n_heads, float scale,
+                  unsigned long long* __restrict__ clock_probe, int rounds) {
+  const int xcd = blockIdx.x % 8, first = blockIdx.x / 8, lane = threadIdx.x & 63;
+  for (int r0 = 0; r0 < rounds; r0 += 64) {
+    int head, u = -1;
+    if (r0 + lane < rounds) {
+      u = pair_at(xcd, (r0 + lane) * PAIR_WGS + first, M_v, M, n_heads, head);
+      if (u >= 0 && !pair_dense(kv_cnt, head, u, M_v, M)) u = -1;
+    }
+    unsigned long long todo = __builtin_amdgcn_ballot_w64(u >= 0);         // the same in every wave
+    while (todo != 0) {
+      const int r = r0 + __builtin_ctzll(todo);
+      todo &= todo - 1;
+      u = pair_at(xcd, r * PAIR_WGS + first, M_v, M, n_heads, head);
+      // What a pair needs is worked out anew for each: kept from pair to pair, forty registers of it would be spilled.
+      asm volatile("" : "+s"(q), "+s"(k), "+s"(v), "+s"(o), "+s"(lse), "+s"(row_index), "+s"(N_src), "+s"(N_pad), "+s"(N_v), "+s"(n_text), "+s"(scale),
+                   "+s"(head), "+s"(u));
+      attn_rows<D, 256, XLSE, 1, false, false, SRC>(q, k, v, nullptr, kv_cnt, 0, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, n_heads * M, scale,
+                                                    clock_probe, nullptr, nullptr, 1, M, 0, 1, 0, head, u, 0, 1, xcd, 0, false);
+      __syncthreads();                               // every wave is done with the tiles
+    }
   }
 }
 
@@ -1104,9 +1193,21 @@ bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const v
   return true;
 }
 
+// Rounds of attn_pairs_kernel, full ones; what is left is the other kernel's, whose work-groups are half as long.  The kernel is launched
+// where lists may be dense, the host does not know, and costs a call whose lists are not 4.5 us (10 heads of 138 blocks, 7 kept, 100 -> 102.6
+// us): so from 2 048 query blocks on, four rounds of work-groups.  Measured (ms, blocks one by one -> in pairs; all 591 kept): 3 heads 7.78 ->
+// 7.56, 4 10.57 -> 10.15, 8 20.7 -> 19.9, 40 102.4 -> 97.7; 929 + 2 text blocks x 4 25.8 -> 25.25; with log-sum-exp, 4 heads of 591, recall's
+// two calls and what is around them 12.26 -> 11.92; 60 of 591 kept x 40 11.05 -> 11.11, two runs of one side as far apart.  Not for
+// sequences that an XCD takes whole (mapping 1): the blocks left over are then one XCD's (138 blocks x 24 heads, all kept, 3.33 -> 5.29).  At d
+// = 64 eight waves would leave the CU two per SIMD instead of three (138 blocks x 48 heads, all kept, 3.74 -> 4.07).
+static int pair_rounds(const dfs_geom* g, const dfs_sizes& s) {
+  if (g->d != 128 || g->B != 128 || !walked_together(s) || int64_t(g->heads) * s.M < 2048) return 0;
+  return (pair_text_slots(s.M_v, s.M, g->heads) + g->heads * pair_chunk(s.M_v)) / PAIR_WGS;
+}
+
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
-                    const int32_t* row_index, bool kv_src, bool zeroed, void* scratch, size_t scratch_bytes, hipStream_t st) {
+                    const int32_t* row_index, bool kv_src, bool maybe_dense, bool zeroed, void* scratch, size_t scratch_bytes, hipStream_t st) {
   if (K_max < 1) return fail(DFS_ESHAPE, "dfs_sparse_attn_fwd: K_max=%d must be positive", K_max);
   if (dtype == DFS_BF16) {
     const int64_t total = int64_t(g->heads) * s.M;
@@ -1124,13 +1225,24 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     const int order = mapping >= 2 ? text_slots + per_xcd : per_xcd;     // slots of an XCD
     const TailSplit tail = lse || ks > 1 ? TailSplit{0, 1, 1} : tail_split(g, s, K_max, order, mapping >= 2 ? text_slots : 0, ts, one_buffer, scratch_bytes);
     if (!zeroed && (ts.splits > 1 || tail.splits > 1)) clear_tickets_kernel<<<1, 256, 0, st>>>(tickets, int(split_tickets(g, s)));
+    const int pairs = maybe_dense ? pair_rounds(g, s) : 0;
+    if (pairs > 0) {
+#define ATTN_PAIRS(XX, SRC)                                                                                                            \
+  attn_pairs_kernel<128, XX, SRC><<<8 * PAIR_WGS, 512, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),            \
+                                                                static_cast<const uint16_t*>(v), kv_cnt, static_cast<uint16_t*>(o), lse, row_index, \
+                                                                s.N, s.N_pad, s.N_v, g->n_text, s.M_v, s.M, g->heads, scale, g_clock_probe, pairs)
+      if (kv_src) ATTN_PAIRS(false, true);
+      else if (lse) ATTN_PAIRS(true, false);
+      else ATTN_PAIRS(false, false);
+#undef ATTN_PAIRS
+    }
     dim3 grid(unsigned(8 * (order + tail.rows * (tail.splits - 1))));
 #define ATTN_X(DD, BB, XX, KS, SLIM, TAIL, SRC)                                                                                            \
   attn_bf16_kernel<DD, BB, XX, KS, SLIM, TAIL, SRC><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
                                                         static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                 \
                                                         static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,         \
                                                         g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe, \
-                                                        part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits)
+                                                        part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits, pairs)
 #define ATTN_LSE(DD, BB, KS, SLIM) do { if (lse) ATTN_X(DD, BB, true, KS, SLIM, false, false); else ATTN_X(DD, BB, false, KS, SLIM, false, false); } while (0)
 #define ATTN_WHOLE(DD, BB, KS, SLIM) do { if (kv_src) ATTN_X(DD, BB, false, KS, SLIM, false, true); else ATTN_LSE(DD, BB, KS, SLIM); } while (0)
 #define ATTN_TAIL(DD, BB, SLIM) do { if (kv_src) ATTN_X(DD, BB, false, 1, SLIM, true, true); else ATTN_X(DD, BB, false, 1, SLIM, true, false); } while (0)
@@ -1182,7 +1294,7 @@ extern "C" int dfs_sparse_attn_fwd(const dfs_geom* g, int dtype, const void* q_p
   if (misaligned(16, {q_perm, k_perm, v_perm, o_perm}) || misaligned(4, {kv_idx, kv_cnt, lse}))
     return fail(DFS_EINVAL, "dfs_sparse_attn_fwd: tensors must be 16-byte aligned, index and fp32 arrays 4-byte aligned");
   if (!(scale > 0.f)) return fail(DFS_EINVAL, "dfs_sparse_attn_fwd: scale must be positive");
-  return run_sparse_attn(g, s, dtype, q_perm, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o_perm, lse, nullptr, false, false, nullptr, 0, as_stream(stream));
+  return run_sparse_attn(g, s, dtype, q_perm, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o_perm, lse, nullptr, false, true, false, nullptr, 0, as_stream(stream));
 }
 
 extern "C" int dfs_sparse_attn_fwd_src(const dfs_geom* g, int dtype, const void* q, const int32_t* perm_pad, const void* k_perm,
@@ -1196,5 +1308,5 @@ extern "C" int dfs_sparse_attn_fwd_src(const dfs_geom* g, int dtype, const void*
   if (misaligned(16, {q, k_perm, v_perm, o}) || misaligned(4, {perm_pad, kv_idx, kv_cnt, lse}))
     return fail(DFS_EINVAL, "dfs_sparse_attn_fwd_src: tensors must be 16-byte aligned, index and fp32 arrays 4-byte aligned");
   if (!(scale > 0.f)) return fail(DFS_EINVAL, "dfs_sparse_attn_fwd_src: scale must be positive");
-  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o, lse, perm_pad, false, false, nullptr, 0, as_stream(stream));
+  return run_sparse_attn(g, s, dtype, q, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o, lse, perm_pad, false, true, false, nullptr, 0, as_stream(stream));
 }

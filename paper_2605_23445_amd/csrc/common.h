@@ -57,7 +57,7 @@ int run_select_mask(const dfs_geom* g, const dfs_sizes& s, const float* score, i
 // over work-groups; its first split_tickets() words are zero when the kernel starts, already (zeroed) or by a launch of its own.
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
-                    const int32_t* row_index, bool kv_src, bool zeroed, void* scratch, size_t scratch_bytes, hipStream_t st);
+                    const int32_t* row_index, bool kv_src, bool maybe_dense, bool zeroed, void* scratch, size_t scratch_bytes, hipStream_t st);
 // Whether dfs_forward hands the attention K and V in source order (kv_src above) instead of reordering them.
 bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* k, const void* v, const void* o);
 // One per text block, and with 512 query blocks and more one for each that the last round of work-groups may share (at most 127
