@@ -1114,7 +1114,10 @@ static int key_split(int d, int B, int64_t work_groups, int K_max) {
 static bool slim(int64_t work_groups, int ks, int mapping) { return ks == 1 && work_groups > 512 && mapping != 2; }
 
 // Work-groups per text block, and the key blocks each takes: about as many as a video row keeps (an eighth of all where
-// K_max does not tell), at least eight.  One where the video rows' work, in rounds of the chip's work-group slots, hides
+// K_max does not tell), at least eight; five eighths of that where all start at once, because the merge of a text row, some 4 us,
+// would come behind the last video row (us a call, pieces as long as a video row -> five eighths of it: 2 565 + 77 x 12, d = 64, blocks of 64,
+// 15 kept, a refresh 35.4 -> 33.9, x 4, 19 kept, a reuse step 18.6 -> 15.8, 6 300 + 300 x 3, 18 kept, d = 64 43.2 -> 38.4, d = 128 58.2 ->
+// 52.5; with several rounds of work-groups they end early as it is: 17 550 + 77 x 12, 15 kept, 155.9 -> 157.5).  One where the video rows' work, in rounds of the chip's work-group slots, hides
 // the text rows, which start first.  Measured (us a reuse step, whole -> split), 17 550 video + 77 text tokens, 21 of 138
 // blocks kept: d = 64 x 2 heads 194 -> 58, x 12 331 -> 199, x 40 679 -> 618; d = 128 x 2 264 -> 88, x 12 519 -> 348, x 40
 // 1 187 -> 1 142 (work of 1.7 text rows: whole by the rule, which is drawn for lists of the room they are given);
@@ -1127,7 +1130,7 @@ static TextSplit text_split(const dfs_geom* g, const dfs_sizes& s, int K_max, si
   const int64_t slots = g->B == 128 ? 512 : 1024, kept = K_max < s.M ? K_max : s.M;
   const int64_t likely = kept == s.M ? kept / 3 : kept;                  // adaptive lists are given room for all
   if (int64_t(g->heads) * s.M_v * likely * 5 >= 4 * slots * s.M) return whole;
-  int blocks = int(2 * kept <= s.M ? kept : s.M / 8);
+  int blocks = int(2 * kept <= s.M ? int64_t(g->heads) * s.M <= slots ? kept * 5 / 8 : kept : s.M / 8);
   if (blocks < 8) blocks = 8;
   const size_t row = size_t(g->B) * (g->d + 4) * sizeof(float) * s.M_x * g->heads;         // one split of every text block
   const int64_t room = int64_t((scratch_bytes - align256(split_tickets(g, s) * sizeof(int32_t))) / row);

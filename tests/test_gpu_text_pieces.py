@@ -1,0 +1,37 @@
+"""Text rows of problems whose work-groups all start at once, dealt in pieces of five eighths of a video row: lists at which the pieces are the
+least, a little more, and leave a last one of a single block; against float64 on the same tensors."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+P = pytest.importorskip("paper_2605_23445_amd")
+from tests import gpu_util as G  # noqa: E402
+
+
+@pytest.mark.parametrize("d,B,H,W,n_text,heads,kept", [
+    (64, 64, 32, 80, 77, 3, 13), (64, 64, 45, 57, 1, 20, 15), (128, 64, 32, 80, 130, 2, 17), (64, 128, 64, 80, 200, 3, 14), (128, 128, 64, 81, 128, 3, 18)])
+def test_text_rows_in_short_pieces(d, B, H, W, n_text, heads, kept):
+    g = P.Geom(1, H, W, n_text, heads, d, B, B // 4)
+    s = P.dfs_geom_sizes(g)
+    sparsity = 1 - kept / s.M_v
+    K_max = kept + s.M_x
+    assert P.dfs_keep_count(sparsity, s.M_v) == kept and 2 * K_max <= s.M and s.M >= 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + kept)
+    q, k, v = (torch.randn(heads, s.N, d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    perm_pad, inv, _ = G.gpu_perm(g)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    st = P.MaskState(torch.zeros((heads, s.M, K_max), **i32), torch.zeros((heads, s.M), **i32), None, None, K_max)
+    ws = G.ws_tensor(P.dfs_workspace_bytes(g, P.DFS_WS_FORWARD_BF16))
+    outs = []
+    for refresh in (True, False, False):
+        out = torch.full_like(q, float("nan"))
+        P.dfs_forward(g, P.DFS_BF16, q, k, v, perm_pad, inv, refresh, P.DFS_SELECT_TOPK, sparsity, 0.0, st, d ** -0.5, out, ws)
+        outs.append(out)
+    assert torch.isfinite(outs[0].float()).all() and all(torch.equal(outs[0], o) for o in outs[1:])
+    qf, kf, vf = (x.double().cpu() for x in (q[:, s.N_v:], k, v))
+    want = torch.softmax(qf @ kf.transpose(1, 2) * d ** -0.5, -1) @ vf
+    got = outs[0][:, s.N_v:].double().cpu()
+    # weights and result are rounded to bf16, 1.9e-3 of the result in 2-norm: four times that, the suite's bound
+    assert float((got - want).norm() / want.norm()) <= 7.5e-3
