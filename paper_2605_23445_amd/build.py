@@ -11,7 +11,7 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdfsattn.so")
-SOURCES = ["api.hip", "hilbert.hip", "permute.hip", "score.hip", "select.hip", "attn.hip", "recall.hip", "probe.hip"]
+SOURCES = ["api.hip", "hilbert.hip", "permute.hip", "score.hip", "select.hip", "attn.hip", "recall.hip", "probe.hip", "small.hip"]
 CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))      # another Python does not take it for its own
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ROCM = os.path.dirname(os.path.dirname(HIPCC)) if os.path.isabs(HIPCC) else "/opt/rocm"

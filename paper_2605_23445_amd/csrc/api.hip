@@ -52,6 +52,12 @@ int check_geom(const dfs_geom* g, dfs_sizes* s) {
   return DFS_OK;
 }
 
+// Whether two tensors in source order have no byte in common.
+bool apart(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* a, const void* b) {
+  const uintptr_t bytes = uintptr_t(g->heads) * s.N * g->d * elem_size(dtype), x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x >= y + bytes || y >= x + bytes;
+}
+
 struct FwdLayout { size_t kp, vp, text, text_bytes, score, sub, total; };
 
 static FwdLayout forward_layout(const dfs_geom* g, const dfs_sizes& s, int dtype) {
@@ -122,17 +128,19 @@ int dfs_forward(const dfs_geom* g, int dtype, const void* q, const void* k, cons
   hipStream_t hs = as_stream(stream);
   // Q is gathered where it is consumed (pooling, attention) and O is scattered by the attention kernel, and for most bf16 calls
   // the attention gathers K and V as well (`src`).  Else these are reordered: by the pooling kernel on the way on a refresh step, by
-  // one gather on a reuse step.
+  // one gather on a reuse step.  Small fp32 calls gather on reuse steps; their refresh steps are one kernel.
   void *k_perm = base + L.kp, *v_perm = base + L.vp;
   int32_t* tickets = reinterpret_cast<int32_t*>(base + L.text);
   const int n_tickets = int(split_tickets(g, s));
-  const bool src = attn_reads_source(g, s, dtype, k, v, o);
+  const bool src = (dtype == DFS_BF16 || !refresh) && attn_reads_source(g, s, dtype, k, v, o);
   if (refresh) {
     float* score = reinterpret_cast<float*>(base + L.score);
     if ((rc = check_select(g, s, mode, sparsity, mass, st->K_max))) return rc;
     const int k_room = st->K_max - s.M_x;
     const SelectPlan sel = {dfs_keep_count(sparsity, s.M_v), k_room < s.M_v ? k_room : s.M_v, mode == DFS_SELECT_MASS_ROW ? mass : 0.0,
                             st->mask, st->kv_idx, st->kv_cnt, st->K_max, st->k_head};
+    if (forward_small_fits(g, s, dtype, mode, q, k, v, o))
+      return run_forward_small(g, s, q, k, v, perm_pad, sel, scale, o, hs);
     const bool in_fold = can_select_in_fold(s, mode);
     if ((rc = run_block_score(g, s, dtype, q, k, score, base + L.sub, perm_pad, true, src ? nullptr : k_perm, src ? nullptr : v, src ? nullptr : v_perm, tickets, n_tickets,
                               in_fold ? &sel : nullptr, hs)))

@@ -12,12 +12,10 @@
 #include <math.h>
 #include <type_traits>
 
-#include "common.h"
+#include "attn_f32.h"
 
 namespace dfs {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -27,11 +25,6 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 constexpr int KN = 64;   // key rows per LDS tile
-
-__device__ __forceinline__ int block_real_rows(int blk, int B, int M_v, int64_t N_v, int n_text) {
-  int64_t real = blk < M_v ? N_v - int64_t(blk) * B : int64_t(n_text) - int64_t(blk - M_v) * B;
-  return real >= B ? B : (real <= 0 ? 0 : int(real));
-}
 
 // XOR swizzles of the 16-byte chunks inside a tile row.  Tiles are stored without padding (the
 // direct-to-LDS load writes 64 consecutive chunks per wave instruction); the swizzle, applied on the
@@ -899,189 +892,23 @@ attn_pairs_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// fp32 kernel.  A work-group owns 32 query rows of one (head, query block); its eight waves split the kept keys, 32 at a
-// time in turn, each with a softmax of its own, and merge through LDS at the end, because calls on fp32 tensors are
-// small (a few thousand tokens) and have few query rows to fill the chip with, so what bounds them is one row's serial
-// walk through its keys.  Both products run on the fp32 matrix instruction (32x32x2: full fp32, the chip's fastest fp32
-// rate), transposed as in the bf16 kernel, with operands straight from memory: no key is shared between waves.  The
-// order of the summed features and of the output features is free, so lanes load 16 bytes of a key row (features
-// 8 c + 4 h ..) and D / 32 consecutive value features each.
-// Measured against one thread per query row with operands from LDS (which at d = 128 spilled its rows): 256 tokens x
-// 2 heads, d = 64, 2 of 4 blocks 89 -> 9 us; 3 600 tokens + 30 text rows x 6 heads, d = 128, 9 of 29 blocks 6 670 ->
-// 268 us (16 and 330 without the requests ahead of their use); error against 64 bits a half to a ninth of that kernel's
-// (3.2e-7 instead of 2.1e-6 at d = 128), since a row's sums are now eight shorter ones.
-template <int D>
-__global__ void __launch_bounds__(512) attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                       const float* __restrict__ v, const int32_t* __restrict__ kv_idx,
-                                                       const int32_t* __restrict__ kv_cnt, int K_max, float* __restrict__ o,
-                                                       float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src,
-                                                       int64_t N_pad, int64_t N_v, int n_text, int M_v, int M, int B, float scale) {
-  constexpr int NW = 8, DT = D / 32;
-  typedef float vrow __attribute__((ext_vector_type(DT)));
-  __shared__ float s_m[NW][32], s_l[NW][32];
-  __shared__ float s_o[NW / 2][DT * 16 * 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = lane & 31, h = lane >> 5;
-  const int log_parts = B == 128 ? 2 : 1, parts = 1 << log_parts;        // per block: groups of 32 query rows, runs of 32 keys
-  const int head = blockIdx.y, u = M - 1 - int(blockIdx.x >> log_parts); // the dense text rows start first
-  const int cnt_in = kv_cnt[int64_t(head) * M + u];
-  const bool dense = cnt_in >= M;
-  const int cnt = dense ? M : (cnt_in < 0 ? 0 : (cnt_in > K_max ? K_max : cnt_in));
-  const int32_t* idx = kv_idx + (int64_t(head) * M + u) * K_max;
-  const float* kh = k + int64_t(head) * N_pad * D;
-  const float* vh = v + int64_t(head) * N_pad * D;
-  const int64_t q_row = int64_t(u) * B + int(blockIdx.x) % parts * 32 + n;
-  int64_t io_row = row_index ? int64_t(row_index[q_row]) : q_row;        // see the bf16 kernel
-  if (row_index && io_row >= N_src) io_row = -1;
-  const int64_t io_off = int64_t(head) * (row_index ? N_src : N_pad) * D;
-  f32x4 qf[D / 8];
-#pragma unroll
-  for (int c = 0; c < D / 8; ++c)                    // a pad row reads row 0; it is not written
-    qf[c] = *reinterpret_cast<const f32x4*>(q + io_off + (io_row < 0 ? 0 : io_row) * D + 8 * c + 4 * h);
-  // Softmax in base 2.  The factor is positive, so that masked logits (-inf) stay what they are and a row's maximum is the
-  // largest exponent; the sign of a scale that is not goes to Q (0 as well: every logit is 0 then).
-  float c2 = scale * 1.4426950408889634f;
-  if (!(scale > 0.f)) {
-    const float sign = scale < 0.f ? -1.f : scale;
-    c2 = scale < 0.f ? -c2 : 1.f;
-#pragma unroll
-    for (int c = 0; c < D / 8; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) qf[c][e] *= sign;
-  }
-  f32x16 oacc[DT];
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;              // reference in the exponent's units, this lane half's share of the sum
-  // This wave's next run of keys, skipping what lies wholly behind the real rows of a ragged block.
-  const int runs = cnt << log_parts;
-  int64_t row = 0;                                   // first key row of the run, the real ones among its 32
-  int real = 1;
-  auto next_run = [&](int j) {
-    for (; j < runs; j += NW) {
-      int blk = dense ? j >> log_parts : idx[j >> log_parts];
-      blk = unsigned(blk) < unsigned(M) ? blk : 0;   // a corrupt list must not read out of bounds
-      const int r0 = j % parts * 32;
-      const int left = block_real_rows(blk, B, M_v, N_v, n_text) - r0;
-      if (left <= 0) continue;
-      row = int64_t(blk) * B + r0;
-      real = left < 32 ? left : 32;
-      break;
-    }
-    return j;
-  };
-  // pad rows are never read: their keys and values repeat the last real one and are masked
-  f32x4 kf[D / 8];
-  vrow vf[16];
-  auto load_k = [&](const float* base, uint32_t off, int c) { kf[c] = *reinterpret_cast<const f32x4*>(base + off + 8 * c); };
-  int j = next_run(wave);
-  if (j < runs) {
-#pragma unroll
-    for (int c = 0; c < D / 8; ++c) load_k(kh + row * D, uint32_t(n < real ? n : real - 1) * D + 4 * h, c);
-  }
-  while (j < runs) {
-    const float* vb = vh + row * D;
-    const int here = real;
-    f32x16 s;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = 0.f;
-    // the values are requested while the logits are formed, the keys of the next run during the value products
-#pragma unroll
-    for (int c = 0; c < D / 8; ++c) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[c][e], qf[c][e], s, 0, 0, 0);
-#pragma unroll
-      for (int i = c * 128 / D; i < (c + 1) * 128 / D; ++i) {
-        const int key = 8 * (i / 4) + 4 * h + i % 4;
-        vf[i] = *reinterpret_cast<const vrow*>(vb + (uint32_t(key < here ? key : here - 1) * D + DT * n));
-      }
-    }
-    j = next_run(j + NW);
-    // s[i]: key 8 (i / 4) + 4 h + i % 4 of the run against query row n
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      if (8 * (i / 4) + 4 * h + i % 4 >= here) s[i] = -INFINITY;
-      mx = fmaxf(mx, s[i]);
-    }
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-    const float m_new = fmaxf(m_run, fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c2);
-    const float ref = m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
-    m_run = m_new;
-    l_run *= alpha;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], c2, -ref));
-      l_run += s[i];
-    }
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
-    const float* kb = kh + row * D;                  // behind the last run: that run once more
-    const uint32_t k_off = uint32_t(n < real ? n : real - 1) * D + 4 * h;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const bool pad = 8 * (i / 4) + 4 * h + i % 4 >= here;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(pad ? 0.f : vf[i][dt], s[i], oacc[dt], 0, 0, 0);
-#pragma unroll
-      for (int c = i * D / 128; c < (i + 1) * D / 128; ++c) load_k(kb, k_off, c);
-    }
-  }
-  // merge: a common reference, then the sums, wave onto wave in a tree
-  const auto lw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-  s_m[wave][n] = m_run;
-  s_l[wave][n] = __uint_as_float(lw[0]) + __uint_as_float(lw[1]);
-  __syncthreads();
-  float m_all = s_m[0][n], l_all = 0.f;
-#pragma unroll
-  for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, s_m[w][n]);
-  const float ref = m_all == -INFINITY ? 0.f : m_all;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) l_all += s_l[w][n] * __builtin_amdgcn_exp2f(s_m[w][n] - ref);
-  const float share = __builtin_amdgcn_exp2f(m_run - ref);
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) oacc[dt][i] *= share;
-#pragma unroll
-  for (int half = NW / 2; half >= 1; half /= 2) {
-    if (runs <= half) continue;                      // the upper waves had no run: nothing to add
-    if (wave >= half && wave < 2 * half) {
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s_o[wave - half][(dt * 16 + i) * 64 + lane] = oacc[dt][i];
-    }
-    __syncthreads();
-    if (wave < half) {
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[dt][i] += s_o[wave][(dt * 16 + i) * 64 + lane];
-    }
-    __syncthreads();
-  }
-  if (wave != 0) return;
-  // no keys: a zero row; keys whose weights all vanish (logits of -inf only): undefined, NaN as 0 / 0
-  const float inv = l_all > 0.f ? 1.0f / l_all : cnt > 0 ? NAN : 0.f;
-  if (io_row >= 0) {
-    float* orow = o + io_off + io_row * D + DT * 4 * h;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      vrow w;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) w[dt] = oacc[dt][i] * inv;
-      *reinterpret_cast<vrow*>(orow + DT * (8 * (i / 4) + i % 4)) = w;
-    }
-  }
-  if (lse && h == 0)
-    lse[int64_t(head) * N_pad + q_row] = l_all > 0.f ? (ref + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f : -INFINITY;
+// Attention of fp32 tensors (attn_f32.h).
+template <int D, bool SRC>
+__global__ void __launch_bounds__(64 * AF_WAVES) attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+                                                                 const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max,
+                                                                 float* __restrict__ o, float* __restrict__ lse, const int32_t* __restrict__ row_index,
+                                                                 int64_t N_src, int64_t N_pad, int64_t N_v, int n_text, int M_v, int M, int B,
+                                                                 float scale) {
+  __shared__ AttnF32Room<D, SRC || D == 128> room;
+  const int parts = B / 32, head = blockIdx.y, u = M - 1 - int(blockIdx.x) / parts;      // the dense text rows start first
+  const int64_t row = int64_t(head) * M + u;
+  const int part = int(blockIdx.x) % parts, cnt = kv_cnt[row];
+  const int64_t q_row = int64_t(u) * B + part * 32 + (threadIdx.x & 31), head_rows = row_index ? N_src : N_pad;
+  QueryRow<D> query;
+  query.load(q, head_rows, head, row_index ? int64_t(row_index[q_row]) : q_row);       // see the bf16 kernel
+  attn_f32_rows<D, SRC>(
+      room, query, k, v, [&](int i) { return kv_idx[row * K_max + i]; }, cnt, K_max, o, lse, head_rows, [&](int64_t at) { return row_index[at]; }, N_src,
+      N_pad, N_v, n_text, M_v, M, B, scale, head, u, part);
 }
 
 // The tickets of shared rows, for calls with no kernel in front that clears them on its way (1.4 us at the least under the profiler, 5.5
@@ -1186,14 +1013,12 @@ static bool walked_together(const dfs_sizes& s) { return xcd_blocks(s) >= 64; }
 // call is dense, so the line lies where dense calls break even.
 // Not where the output lies over the keys or values either: they are then reordered before the first row is written.
 bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* k, const void* v, const void* o) {
-  if (dtype != DFS_BF16) return false;
-  if (walked_together(s) && !(g->d == 128 && g->B == 128)) return false;
-  const uintptr_t bytes = uintptr_t(g->heads) * s.N * g->d * 2, out = reinterpret_cast<uintptr_t>(o);
-  for (const void* p : {k, v}) {
-    const uintptr_t in = reinterpret_cast<uintptr_t>(p);
-    if (in < out + bytes && out < in + bytes) return false;
-  }
-  return true;
+  if (dtype == DFS_BF16 && walked_together(s) && !(g->d == 128 && g->B == 128)) return false;
+  // fp32 tensors (on reuse steps, see dfs_forward): calls of 2^31 operations and less with every block kept, whose reorder is a launch more than it
+  // is work.  (us) 256 tokens x 2 heads, d = 64, 11.0 -> 8.9; 1 024 x 3, d = 64 17.5 -> 14.2, d = 128 29.8 -> 24.7; 1 920 x 1, d = 64, dense 46.5 ->
+  // 45.7; larger ones lose, the rows of a run lying apart: 1 920 + 30 x 6, d = 128, 127 -> 131, 3 968 x 8 236 -> 252.
+  if (dtype == DFS_F32 && 4 * int64_t(g->heads) * g->d * double(s.N_pad) * double(s.N_pad) > 2147483648.0) return false;
+  return apart(g, s, dtype, k, o) && apart(g, s, dtype, v, o);
 }
 
 // Rounds of attn_pairs_kernel, full ones; what is left is the other kernel's, whose work-groups are half as long.  The kernel is launched
@@ -1266,11 +1091,12 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
   } else {
     if (g->heads > 65535) return fail(DFS_ESHAPE, "heads=%d exceeds 65535", g->heads);
     dim3 grid(unsigned(s.M * (g->B / 32)), unsigned(g->heads));
-#define ATTN_F32(DD)                                                                                                            \
-  attn_f32_kernel<DD><<<grid, 512, 0, st>>>(static_cast<const float*>(q), static_cast<const float*>(k),                         \
+#define ATTN_F32(DD, SRC)                                                                                                       \
+  attn_f32_kernel<DD, SRC><<<grid, 512, 0, st>>>(static_cast<const float*>(q), static_cast<const float*>(k),                         \
                                             static_cast<const float*>(v), kv_idx, kv_cnt, K_max, static_cast<float*>(o), lse,   \
                                             row_index, s.N, s.N_pad, s.N_v, g->n_text, s.M_v, s.M, g->B, scale)
-    if (g->d == 64) ATTN_F32(64); else ATTN_F32(128);
+    if (g->d == 64) { if (kv_src) ATTN_F32(64, true); else ATTN_F32(64, false); }
+    else            { if (kv_src) ATTN_F32(128, true); else ATTN_F32(128, false); }
 #undef ATTN_F32
   }
   return launch_status("dfs_sparse_attn_fwd");

@@ -47,6 +47,12 @@ struct SelectPlan {
 int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q_perm, const void* k_perm,
                     float* score, void* ws, const int32_t* index, bool k_src, void* k_out, const void* v, void* v_out, int32_t* zero,
                     int n_zero, const SelectPlan* sel, hipStream_t st);
+// Whether one kernel scores a problem of this size behind the pooling.
+bool score_small(const dfs_geom* g, const dfs_sizes& s);
+// A refresh step of a small fp32 problem in one kernel, and whether a call is one.
+bool forward_small_fits(const dfs_geom* g, const dfs_sizes& s, int dtype, int mode, const void* q, const void* k, const void* v, const void* o);
+int run_forward_small(const dfs_geom* g, const dfs_sizes& s, const void* q, const void* k, const void* v, const int32_t* perm_pad, const SelectPlan& sel,
+                      float scale, void* o, hipStream_t st);
 // Whether the scoring can select on the way: the rule needs one row's scores only and eight rows fit in 64 KB of LDS.
 bool can_select_in_fold(const dfs_sizes& s, int mode);
 int check_select(const dfs_geom* g, const dfs_sizes& s, int mode, double sparsity, double mass, int32_t K_max);
@@ -58,6 +64,8 @@ int run_select_mask(const dfs_geom* g, const dfs_sizes& s, const float* score, i
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
                     const int32_t* row_index, bool kv_src, bool maybe_dense, bool zeroed, void* scratch, size_t scratch_bytes, hipStream_t st);
+// Whether two tensors in source order have no byte in common.
+bool apart(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* a, const void* b);
 // Whether dfs_forward hands the attention K and V in source order (kv_src above) instead of reordering them.
 bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* k, const void* v, const void* o);
 // One per text block, and with 512 query blocks and more one for each that the last round of work-groups may share (at most 127

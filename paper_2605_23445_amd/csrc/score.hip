@@ -18,53 +18,12 @@
 //   score_small_kernel : all of it behind the pooling, for small problems.
 #include <type_traits>
 
+#include "score_small.h"
 #include "select_row.h"
 
 namespace dfs {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
 // ------------------------------------------------------------------------------------ pooling
-
-// x (already scaled so that its group's largest magnitude is in [2^11, 2^12)) -> (hi, lo) with hi = fp16(x),
-// lo = fp16(x - hi).  The subtraction is exact and |x - hi| <= 2^-11 |x|, so x = hi + lo to within 2^-22 |x| as long
-// as lo is a normal fp16 number, which it is for |x| >= 2^-3: an element more than 2^14 times smaller than the
-// largest of its group is kept to 2^-25 absolute instead, i.e. to 2^-36 of that largest one.
-__device__ __forceinline__ void split2(float x, uint16_t& hi, uint16_t& lo) {
-  const _Float16 h = (_Float16)x;
-  const _Float16 l = (_Float16)(x - (float)h);
-  hi = __builtin_bit_cast(uint16_t, h);
-  lo = __builtin_bit_cast(uint16_t, l);
-}
-// Rows are scaled in groups of four consecutive sub-blocks (the four waves of a pooling work-group) by a power of
-// two that brings the group's largest magnitude into [2^11, 2^12); `down` is the inverse.  Powers of two: exact.
-constexpr int SHIFT_MAX = 126;                 // keeps both factors finite and normal for groups of vanishing magnitude
-                                               // (the largest finite fp32 needs a shift of -116)
-__device__ __forceinline__ void group_scale(float gmax, float& up, float& down) {
-  up = 1.0f; down = 1.0f;
-  if (gmax > 0.f && gmax < INFINITY) {
-    int ex;
-    (void)frexpf(gmax, &ex);                   // gmax = m 2^ex, m in [0.5, 1)
-    int sh = 12 - ex;
-    sh = sh > SHIFT_MAX ? SHIFT_MAX : (sh < -SHIFT_MAX ? -SHIFT_MAX : sh);
-    up = ldexpf(1.0f, sh);
-    down = ldexpf(1.0f, -sh);
-  }
-}
-
-// Layouts of Q_hat and K_hat.  For the two-kernel contraction, row after row, [2][D] fp16 (hi, lo planes).  For the one-kernel
-// form (`tiled`), per head, tiles of 32 sub-blocks (the last one with what is left, `rows`), a tile chunk by chunk as
-// the matrix instructions' operands want it, [2 D / 8][rows][8] fp16: chunks 0 .. D / 8 - 1 are features 8 c .. 8 c + 7 of the hi
-// plane, the others of the lo plane.  The lanes of an operand load, one row each, then read a kilobyte
-// in one piece; with whole rows behind one another they read 16 bytes of 32 rows: 2 565 tokens x 12 heads, d = 64, blocks of 64,
-// 36.5 -> 35.5 us a refresh.  It costs the pooling, which writes rows of a tile in pieces of 64 bytes, 4 % where it is an HBM stream
-// (75 600 tokens x 40 heads 399 -> 418 us for Q and K), and the two-kernel contraction, which goes through LDS, would gain 2 %
-// (184 -> 181).
-__host__ __device__ __forceinline__ int tile_rows(int M_s, int t) { return M_s - 32 * t < 32 ? M_s - 32 * t : 32; }
-template <int D> __device__ __forceinline__ int64_t tile_at(int t) { return int64_t(t) * (32 * 2 * D); }      // elements
-template <int D> __device__ __forceinline__ int chunk_at(int p, int c, int rows, int n) { return ((p * (D / 8) + c) * rows + n) * 8; }
 
 // One wave per sub-block.  Lanes of a row sit side by side (16 bytes each); several rows are in
 // flight per load; partial sums of the row groups are folded with cross-lane exchanges.
@@ -189,32 +148,10 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in
 __host__ __device__ inline int t_cols(int M_s) { return (M_s + 127) / 128 * 128; }
 __host__ __device__ inline int t_rows(int M_s, int R) { return (M_s + 31) / 32 * (32 / R); }
 
-constexpr float LSE_START = -1.0e30f;          // finite stand-in for "nothing seen yet" (keeps differences finite)
-
 __device__ __forceinline__ float vmax3(float a, float b, float c) {
   float r;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
-}
-
-// The value of the other lane half (lane ^ 32) beside this lane's own, through the vector unit (a shuffle through
-// LDS would make the wave wait for every LDS read in flight).  Returns {lower half's value, upper half's value}.
-__device__ __forceinline__ void both_halves(float x, float& lo, float& hi) {
-  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  lo = __uint_as_float(sw[0]);
-  hi = __uint_as_float(sw[1]);
-}
-
-// Running base-2 log-sum-exp (reference m, sum z of 2^(x - m)): add one term, merge two partial sums.
-__device__ __forceinline__ void lse_add(float& m, float& z, float x) {
-  const float mn = fmaxf(m, x);
-  z = z * __builtin_amdgcn_exp2f(m - mn) + __builtin_amdgcn_exp2f(x - mn);
-  m = mn;
-}
-__device__ __forceinline__ void lse_merge(float& m, float& z, float m2, float z2) {
-  const float mn = fmaxf(m, m2);
-  z = z * __builtin_amdgcn_exp2f(m - mn) + z2 * __builtin_amdgcn_exp2f(m2 - mn);
-  m = mn;
 }
 
 // Pass 1 (the contraction, once).  A work-group owns 128 query sub-blocks (32 per wave) and one of KSPLIT
@@ -583,115 +520,28 @@ static size_t fs_lds(int M_v) { return size_t(FS_ROWS) * (256 + fs_stride(M_v)) 
 // calls that want scores (`score`) and those that want lists (`kv_idx`), and both decide alike.  What bounds it is latency: a
 // tile's rows, its product chain, three barriers, the selection; it saves a launch and the way of T through memory.  256 fp32
 // tokens x 2 heads 18.4 -> 16.6 us a refresh, 2 565 + 77 tokens x 12 heads, blocks of 64, 39.1 -> 35.5 (both sides in turn).
-constexpr int SS_T = 512, SS_WAVES = SS_T / 64, SS_STRIDE = 33;
 template <int D, int R>
 __global__ void __launch_bounds__(SS_T) score_small_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict__ k_hat,
                                                            const float* __restrict__ q_down, const float* __restrict__ k_down,
                                                            float* __restrict__ score, int M_s, int M_v, int M_x, int n_live, int k_fixed,
                                                            int k_cap, double mass, uint8_t* __restrict__ mask, int32_t* __restrict__ kv_idx,
                                                            int32_t* __restrict__ kv_cnt, int K_max, int32_t* __restrict__ k_head) {
-  constexpr int RS = 2 * D, KS = D / 16, ROWS = 32 / R;
-  constexpr int G = R < 4 ? R : 4, NG = 16 / G;            // as in score_lse_kernel
+  constexpr int RS = 2 * D, ROWS = 32 / R;
   extern __shared__ unsigned long long lds64[];
   uint32_t* hists = reinterpret_cast<uint32_t*>(lds64);                  // 256 words per wave
   float* s_t = reinterpret_cast<float*>(hists + SS_WAVES * 256);         // T [M_v][SS_STRIDE], then keys in the first of R
   __shared__ float s_m[SS_WAVES][32], s_z[SS_WAVES][32], s_ref[32], s_inv[32];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = lane & 31, half = lane >> 5;
   const int head = blockIdx.y, u0 = blockIdx.x * ROWS, i0 = blockIdx.x * 32, M = M_v + M_x;
   if (u0 < M_v) {
     const uint16_t* qh = q_hat + int64_t(head) * M_s * RS;
     const uint16_t* kh = k_hat + int64_t(head) * M_s * RS;
     const int G4 = (M_s + 3) / 4;
-    const int q_from = i0 + n < M_s ? i0 + n : M_s - 1;    // rows beyond the last repeat it; nothing reads their results
-    const float q_dn = q_down[int64_t(head) * G4 + q_from / 4];
-    f16x8 bq[2][KS];
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk)
-        bq[p][kk] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(
-            qh + tile_at<D>(i0 / 32) + chunk_at<D>(p, 2 * kk + half, tile_rows(M_s, i0 / 32), q_from - i0)));
-    float m_row = LSE_START, z_row = 0.f;
-    for (int t = wave; t * 32 < n_live; t += SS_WAVES) {
-      const int rows = tile_rows(M_s, t);
-      const uint16_t* kt = kh + tile_at<D>(t) + (n < rows ? n : rows - 1) * 8;          // beyond the last: masked below
-      f16x8 ak[2][KS];
-#pragma unroll
-      for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) ak[p][kk] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(kt + chunk_at<D>(p, 2 * kk + half, rows, 0)));
-      float dn[4];
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        const int grp = 8 * t + 2 * gq + half;
-        dn[gq] = k_down[int64_t(head) * G4 + (grp < G4 ? grp : G4 - 1)] * q_dn;
-      }
-      f32x16 c0, c1;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) { c0[i] = 0.f; c1[i] = 0.f; }
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {                    // hi.hi, hi.lo, lo.hi, dealt to the accumulators as there
-        f32x16& a = kk % 2 ? c1 : c0;
-        f32x16& b = kk % 2 ? c0 : c1;
-        a = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[0][kk], bq[0][kk], a, 0, 0, 0);
-        b = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[0][kk], bq[1][kk], b, 0, 0, 0);
-        a = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[1][kk], bq[0][kk], a, 0, 0, 0);
-      }
-      float c[16], mt = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        c[i] = (c0[i] + c1[i]) * dn[i / 4];
-        if (t * 32 + 8 * (i / 4) + 4 * half + (i % 4) >= n_live) c[i] = -INFINITY;
-        mt = fmaxf(mt, c[i]);
-      }
-      if (R == 8) {                                        // a key block is split over the lane halves: one reference
-        float lo, hi;
-        both_halves(mt, lo, hi);
-        mt = fmaxf(lo, hi);
-      }
-      const float m_new = fmaxf(m_row, mt);
-      z_row *= __builtin_amdgcn_exp2f(m_row - m_new);
-      m_row = m_new;
-#pragma unroll
-      for (int gi = 0; gi < NG; ++gi) {
-        float sg = 0.f;
-#pragma unroll
-        for (int e = 0; e < G; ++e) sg += __builtin_amdgcn_exp2f(c[gi * G + e] - m_new);
-        z_row += sg;
-        if (R == 8) {
-          float lo, hi;
-          both_halves(sg, lo, hi);
-          sg = lo + hi;
-        }
-        const int first = gi * G, v = (t * 32 + 8 * (first / 4) + (R == 8 ? 0 : 4 * half) + first % 4) / R;
-        if (v < M_v) s_t[v * SS_STRIDE + n] = m_new + __builtin_amdgcn_logf(sg);  // R == 8: both halves store the same
-      }
-    }
-    const float m2 = __shfl_xor(m_row, 32, 64), z2 = __shfl_xor(z_row, 32, 64);
-    lse_merge(m_row, z_row, m2, z2);
-    if (half == 0) {
-      s_m[wave][n] = m_row;
-      s_z[wave][n] = z_row;
-    }
-    __syncthreads();
-    if (tid < 32) {
-      float m = s_m[0][tid], z = s_z[0][tid];
-#pragma unroll
-      for (int w = 1; w < SS_WAVES; ++w) lse_merge(m, z, s_m[w][tid], s_z[w][tid]);
-      // Reference and sum stay apart: their log-sum-exp in one number, of magnitude log2(M_s) and more, would be rounded by up
-      // to 2^-21 there (error of the scores, 2-norm: 2.8e-7 at 688 sub-blocks, the two kernels with their key ranges 1.6e-7).
-      const bool any = i0 + tid < n_live && z > 0.f;                                         // an empty query sub-block scores nothing
-      s_ref[tid] = any ? m : INFINITY;
-      s_inv[tid] = any ? 1.f / z : 0.f;
-    }
-    __syncthreads();
+    small_scores<D, R>(MemoryOperands<D>{qh, kh, q_down + int64_t(head) * G4, k_down + int64_t(head) * G4, M_s, i0}, s_t, s_m, s_z, s_ref, s_inv, M_v, n_live, i0);
     for (int x = tid; x < ROWS * M_v; x += SS_T) {
       const int r = x / M_v, v = x % M_v;
       float* t = s_t + v * SS_STRIDE + r * R;
-      float acc = 0.f;
-#pragma unroll
-      for (int a = 0; a < R; ++a) acc = fmaf(__builtin_amdgcn_exp2f(t[a] - s_ref[r * R + a]), s_inv[r * R + a], acc);
+      const float acc = small_score<R>(t, s_ref + r * R, s_inv + r * R);
       if (score) {
         if (u0 + r < M_v) score[(int64_t(head) * M_v + u0 + r) * M_v + v] = acc;
       } else {
@@ -729,7 +579,7 @@ static size_t ss_lds(int M_v) { return (size_t(SS_WAVES) * 256 + size_t(M_v) * S
 //   R = 4, d = 64: 24 x 8 1.13, 138 x 48 1.00, 200 x 8 1.03, 313 x 1 1.08, 313 x 40 1.00; d = 128: 24 x 8 1.10, 138 x 40 1.00, 313 x 8 1.01, 313 x 40 1.00
 //   R = 2, d = 64: 8 x 8 1.12, 48 x 8 1.03, 72 x 8 1.01, 138 x 1 0.96; d = 128: 24 x 8 1.04, 48 x 8 1.00, 72 x 8 0.99
 //   R = 1: 8 x 8 1.04, 16 x 8 0.99 (d = 64) and 1.02 (128), 24 x 8 0.95 and 0.97, 138 x 1 0.78
-static bool score_small(const dfs_geom* g, const dfs_sizes& s) {
+bool score_small(const dfs_geom* g, const dfs_sizes& s) {
   switch (s.r) {
     case 8: return s.M_v <= 256;
     case 4: return s.M_v <= 320;                           // 52 KB of the 64 KB of LDS
