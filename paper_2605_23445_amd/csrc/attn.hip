@@ -100,7 +100,7 @@ __device__ __forceinline__ bool in_pairs(const int32_t* __restrict__ kv_cnt, int
 
 // What a work-group does: the query block u of `head` (BM = 256: blocks u and u + 1, which keep every key block), or with TAIL and
 // for text rows the share `split` of it; xcd and slot name it among the tail's.
-template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL, bool SRC>
+template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL, bool SRC, bool REST>
 __device__ __forceinline__ void
 attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
           const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
@@ -144,8 +144,7 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
   const int n = lane & 31, h = lane >> 5;
   const int cnt_in = PAIR ? M : kv_cnt[int64_t(head) * M + u];
   const bool dense = PAIR || cnt_in >= M;
-  constexpr bool PAIRABLE = D == 128 && BM == 128 && KS == 1;            // see pair_rounds
-  if (PAIRABLE && dense && pair_rounds > 0 && in_pairs(kv_cnt, head, u, M_v, M, total_wg / M, pair_rounds)) return;     // attn_pairs_kernel has done it
+  if (REST && dense && in_pairs(kv_cnt, head, u, M_v, M, total_wg / M, pair_rounds)) return;     // attn_pairs_kernel has done it
   const bool shared_row = !XLSE && splits > 1;
   int cnt = dense ? M : (cnt_in < 0 ? 0 : (cnt_in > K_max ? K_max : cnt_in));
   const int run = tail ? (cnt + splits - 1) / splits : split_blocks;
@@ -685,7 +684,7 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
     };
     static_assert(TILE * 2 == (D / 32) * 16 * 64 * 4, "one tile buffer holds the accumulators of one wave");
     if (rounds == 0) {
-      if (grp > 0) return;
+      if (grp > 0) __builtin_amdgcn_endpgm();
     } else {
       if (n_tiles == 0) m_run = -INFINITY;
       __syncthreads();                               // every wave is done with the tiles
@@ -700,7 +699,9 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
         s_part[grp][wave][2][lane] = x_run;
       }
       __syncthreads();
-      if (grp > 0) return;
+      // The end of the wave itself: as a return, a way to the end of the kernel, it kept the accumulators of the first group in scratch (187 registers
+      // spilled with log-sum-exp, d = 128, blocks of 128, instead of 15; recall's calls on one head of 44 blocks 174 us instead of 153).
+      if (grp > 0) __builtin_amdgcn_endpgm();
       float m_all = m_run;
 #pragma unroll
       for (int g = 1; g < KS; ++g) m_all = fmaxf(m_all, s_part[g][wave][0][lane]);
@@ -798,15 +799,15 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
   }
 }
 
-template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL, bool SRC>
-__global__ void __launch_bounds__(BM * 2 * KS)
-__attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE, KS>(), attn_waves<D, BM, XLSE, KS>())))
-attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                 const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
-                 float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
-                 int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
-                 float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows,
-                 int tail_splits, int pair_rounds) {
+// REST: what attn_pairs_kernel, launched in front, has done is left out.
+template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL, bool SRC, bool REST>
+__device__ __forceinline__ void
+attn_work_group(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
+                float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
+                int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
+                float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows,
+                int tail_splits, int pair_rounds) {
   // Work-group to (head, query block).  Ids are dealt round-robin to the 8 XCDs, so id % 8 names the XCD
   // and id / 8 the order inside it.
   //   mapping 2 (long sequences): every XCD takes its own eighth of the query blocks of head 0, then of
@@ -853,9 +854,37 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     head = logical / M;
     u = M - 1 - logical % M;
   }
-  attn_rows<D, BM, XLSE, KS, SLIM, TAIL, SRC>(q, k, v, kv_idx, kv_cnt, K_max, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, total_wg, scale,
-                                              clock_probe, part, tickets, text_splits, split_blocks, tail_from, tail_rows, pair_rounds, head, u,
-                                              split, splits, xcd, slot, tail);
+  attn_rows<D, BM, XLSE, KS, SLIM, TAIL, SRC, REST>(q, k, v, kv_idx, kv_cnt, K_max, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, total_wg,
+                                                    scale, clock_probe, part, tickets, text_splits, split_blocks, tail_from, tail_rows, pair_rounds,
+                                                    head, u, split, splits, xcd, slot, tail);
+}
+
+template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL, bool SRC>
+__global__ void __launch_bounds__(BM * 2 * KS)
+__attribute__((amdgpu_waves_per_eu(attn_waves<D, BM, XLSE, KS>(), attn_waves<D, BM, XLSE, KS>())))
+attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                 const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
+                 float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
+                 int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
+                 float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows,
+                 int tail_splits) {
+  attn_work_group<D, BM, XLSE, KS, SLIM, TAIL, SRC, false>(q, k, v, kv_idx, kv_cnt, K_max, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, total_wg,
+                                                          wg_per_xcd, mapping, scale, clock_probe, part, tickets, text_splits, split_blocks, tail_from,
+                                                          tail_rows, tail_splits, 0);
+}
+
+// The same behind attn_pairs_kernel (its look at the pairs costs a work-group 0.3 us on its way to the list).
+template <int D, int BM, bool XLSE, bool TAIL, bool SRC>
+__global__ void __launch_bounds__(BM * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
+attn_rest_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                 const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
+                 float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
+                 int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
+                 float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows,
+                 int tail_splits, int pair_rounds) {
+  attn_work_group<D, BM, XLSE, 1, false, TAIL, SRC, true>(q, k, v, kv_idx, kv_cnt, K_max, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, total_wg,
+                                                         wg_per_xcd, mapping, scale, clock_probe, part, tickets, text_splits, split_blocks, tail_from,
+                                                         tail_rows, tail_splits, pair_rounds);
 }
 
 // Dense rows (the first quarter of a sampling run's steps): two neighbouring query blocks of 128 rows that keep every key block, in one
@@ -885,7 +914,7 @@ attn_pairs_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
       // What a pair needs is worked out anew for each: kept from pair to pair, forty registers of it would be spilled.
       asm volatile("" : "+s"(q), "+s"(k), "+s"(v), "+s"(o), "+s"(lse), "+s"(row_index), "+s"(N_src), "+s"(N_pad), "+s"(N_v), "+s"(n_text), "+s"(scale),
                    "+s"(head), "+s"(u));
-      attn_rows<D, 256, XLSE, 1, false, false, SRC>(q, k, v, nullptr, kv_cnt, 0, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, n_heads * M, scale,
+      attn_rows<D, 256, XLSE, 1, false, false, SRC, false>(q, k, v, nullptr, kv_cnt, 0, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, n_heads * M, scale,
                                                     clock_probe, nullptr, nullptr, 1, M, 0, 1, 0, head, u, 0, 1, xcd, 0, false);
       __syncthreads();                               // every wave is done with the tiles
     }
@@ -1070,13 +1099,25 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
                                                         static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                 \
                                                         static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,         \
                                                         g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe, \
-                                                        part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits, pairs)
+                                                        part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits)
+#define ATTN_REST(XX, TAIL, SRC)                                                                                                           \
+  attn_rest_kernel<128, 128, XX, TAIL, SRC><<<grid, 256, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),               \
+                                                                  static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                         \
+                                                                  static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,                 \
+                                                                  g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe,      \
+                                                                  part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits, pairs)
 #define ATTN_LSE(DD, BB, KS, SLIM) do { if (lse) ATTN_X(DD, BB, true, KS, SLIM, false, false); else ATTN_X(DD, BB, false, KS, SLIM, false, false); } while (0)
 #define ATTN_WHOLE(DD, BB, KS, SLIM) do { if (kv_src) ATTN_X(DD, BB, false, KS, SLIM, false, true); else ATTN_LSE(DD, BB, KS, SLIM); } while (0)
 #define ATTN_TAIL(DD, BB, SLIM) do { if (kv_src) ATTN_X(DD, BB, false, 1, SLIM, true, true); else ATTN_X(DD, BB, false, 1, SLIM, true, false); } while (0)
 #define ATTN_1(DD, BB, SLIM) do { if (tail.splits > 1) ATTN_TAIL(DD, BB, SLIM); else ATTN_WHOLE(DD, BB, 1, SLIM); } while (0)
 #define ATTN_KS(DD, BB) do { if (ks == 2) ATTN_WHOLE(DD, BB, 2, false); else ATTN_1(DD, BB, false); } while (0)
-    if (g->d == 64) { if (g->B == 64) ATTN_KS(64, 64); else ATTN_KS(64, 128); }
+    if (pairs > 0) {
+      if (lse) ATTN_REST(true, false, false);
+      else if (tail.splits > 1) { if (kv_src) ATTN_REST(false, true, true); else ATTN_REST(false, true, false); }
+      else if (kv_src) ATTN_REST(false, false, true);
+      else ATTN_REST(false, false, false);
+    }
+    else if (g->d == 64) { if (g->B == 64) ATTN_KS(64, 64); else ATTN_KS(64, 128); }
     else if (g->B == 128) ATTN_KS(128, 128);
     else if (one_buffer) ATTN_1(128, 64, true);
     else if (tail.splits > 1) ATTN_X(128, 64, false, 1, false, true, false);      // only sequences that all XCDs walk together: none is gathered
@@ -1087,6 +1128,7 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
 #undef ATTN_TAIL
 #undef ATTN_WHOLE
 #undef ATTN_LSE
+#undef ATTN_REST
 #undef ATTN_X
   } else {
     if (g->heads > 65535) return fail(DFS_ESHAPE, "heads=%d exceeds 65535", g->heads);

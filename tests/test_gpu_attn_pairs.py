@@ -37,7 +37,7 @@ def test_same_bits_as_one_by_one(T, H, W, n_text, heads, mixed):
         o, want = (torch.full_like(q, float("nan")) for _ in range(2))
         lse, want_l = (torch.full((heads, s.N_pad), float("nan"), device="cuda") if want_lse else None for _ in range(2))
         names = G.kernels_of(lambda: call(g, P.DFS_BF16, q, k, v, idx, cnt, K_max, scale, o, lse))
-        assert names == [f"attn_pairs_kernel<128, {int(want_lse)}, 0>", f"attn_bf16_kernel<128, 128, {int(want_lse)}, 1, 0, 0, 0>"]
+        assert names == [f"attn_pairs_kernel<128, {int(want_lse)}, 0>", f"attn_rest_kernel<128, 128, {int(want_lse)}, 0, 0>"]
         call(g, P.DFS_BF16, q, k, v, idx, cnt, K_max, scale, o, lse)
         for h in range(heads):
             assert not any("pairs" in n for n in G.kernels_of(lambda: call(one, P.DFS_BF16, q[h:h + 1], k[h:h + 1], v[h:h + 1], idx[h:h + 1], cnt[h:h + 1], K_max,
@@ -55,6 +55,6 @@ def test_same_bits_as_one_by_one(T, H, W, n_text, heads, mixed):
     st = P.MaskState(idx, cnt, None, None, K_max)
     out = torch.full_like(src[0], float("nan"))
     step = lambda: P.dfs_forward(g, P.DFS_BF16, *src, perm_pad, inv, False, P.DFS_SELECT_TOPK, 0.0, 0.0, st, scale, out, ws)  # noqa: E731
-    assert G.kernels_of(step) == ["attn_pairs_kernel<128, 0, 1>", "attn_bf16_kernel<128, 128, 0, 1, 0, 0, 1>"]
+    assert G.kernels_of(step) == ["attn_pairs_kernel<128, 0, 1>", "attn_rest_kernel<128, 128, 0, 0, 1>"]
     step()
     assert torch.equal(out.view(torch.int16), G.gpu_unperm(g, P.DFS_BF16, want, inv).view(torch.int16))
