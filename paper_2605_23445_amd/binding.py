@@ -91,25 +91,29 @@ def _load():
     return lib
 
 
-def _load_calls():
-    """forward and token_order of the _calls module.  They do in native code what dfs_forward and the token orders do below, for plain
+def _load_calls(names=("forward", "token_order", "permute", "unperm", "block_score", "select_mask", "sparse_attn", "recall")):
+    """The calls of the _calls module.  They do in native code what those of the same names do below, for plain
     arguments, and return None for what they leave to these: as the stand-ins do for every call where the module is not there or
     was built against another torch, whose classes it reads (another Python does not find it: its name holds the version)."""
     try:
         from . import _calls                         # links to the library loaded above
-        if getattr(_calls, "torch_version", None) == torch.__version__:
+        if getattr(_calls, "torch_version", None) != torch.__version__:
+            why = "built for another torch"
+        elif not all(hasattr(_calls, name) for name in names):
+            why = "older than this file"
+        else:
             _calls.set_geom_type(Geom)
-            return _calls.forward, _calls.token_order
-        why = "built for another torch"
+            return [getattr(_calls, name) for name in names]
     except ImportError as e:
         why = str(e)
     warnings.warn(f"the module of the hottest calls cannot be used ({why}): they go through Python, 2.5 to 5 us of host time more each; "
                   "run `python -c 'import __graft_entry__ as g; g.build()'`", RuntimeWarning, stacklevel=3)
-    return lambda *a: None, lambda *a: None
+    return [lambda *a: None] * len(names)
 
 
 _lib = _load()
-_plain_forward, _plain_token_order = _load_calls()
+(_plain_forward, _plain_token_order, _plain_permute, _plain_unperm, _plain_block_score, _plain_select_mask, _plain_sparse_attn,
+ _plain_recall) = _load_calls()
 EXPORTS = ("dfs_geom_sizes", "dfs_workspace_bytes", "dfs_last_error", "dfs_keep_count", "dfs_hilbert_perm", "dfs_permute",
            "dfs_block_score", "dfs_select_mask", "dfs_sparse_attn_fwd", "dfs_unperm", "dfs_forward", "dfs_token_order", "dfs_recall",
            "dfs_schedule", "dfs_block_score_src", "dfs_sparse_attn_fwd_src", "dfs_attn_clock_probe", "dfs_block_score_fused", "dfs_probe_mfma", "dfs_probe_copy", "dfs_probe_read",
@@ -204,6 +208,11 @@ def dfs_token_order(g: Geom, order: int, perm_pad, inv, blk_valid, ws):
 
 
 def dfs_recall(g: Geom, lse_sparse, lse_dense, recall):
+    rc = _plain_recall(g, lse_sparse, lse_dense, recall)
+    if rc == 0:
+        return
+    if rc is not None:
+        _check(rc)
     s = dfs_geom_sizes(g)
     n = g.heads * s.N_pad
     _check(_lib.dfs_recall(g, _ptr(lse_sparse, torch.float32, n, "lse_sparse"), _ptr(lse_dense, torch.float32, n, "lse_dense"),
@@ -219,6 +228,11 @@ def dfs_schedule(total_steps: int, t: int, delta: int = 12, cached_keep: float |
 
 
 def dfs_permute(g: Geom, dtype: int, x, perm_pad, x_perm):
+    rc = _plain_permute(g, dtype, x, perm_pad, x_perm)
+    if rc == 0:
+        return
+    if rc is not None:
+        _check(rc)
     s = dfs_geom_sizes(g)
     td = _torch_dtype(dtype)
     _check(_lib.dfs_permute(g, dtype, _ptr(x, td, g.heads * s.N * g.d, "x"),
@@ -227,6 +241,11 @@ def dfs_permute(g: Geom, dtype: int, x, perm_pad, x_perm):
 
 
 def dfs_block_score(g: Geom, dtype: int, q_perm, k_perm, score, ws):
+    rc = _plain_block_score(g, dtype, q_perm, k_perm, score, ws)
+    if rc == 0:
+        return
+    if rc is not None:
+        _check(rc)
     s = dfs_geom_sizes(g)
     td = _torch_dtype(dtype)
     n = g.heads * s.N_pad * g.d
@@ -237,6 +256,11 @@ def dfs_block_score(g: Geom, dtype: int, q_perm, k_perm, score, ws):
 
 def dfs_select_mask(g: Geom, score, mode: int, sparsity: float, mass: float, mask, kv_idx, kv_cnt, K_max: int,
                     k_head, ws):
+    rc = _plain_select_mask(g, score, mode, sparsity, mass, mask, kv_idx, kv_cnt, K_max, k_head, ws)
+    if rc == 0:
+        return
+    if rc is not None:
+        _check(rc)
     s = dfs_geom_sizes(g)
     wp, wb = _ws_args(ws)
     _check(_lib.dfs_select_mask(g, _ptr(score, torch.float32, g.heads * s.M_v * s.M_v, "score"), mode,
@@ -257,6 +281,11 @@ def dfs_select_mask_static(g: Geom, score, mode: int, sparsity: float, mass: flo
 
 def dfs_sparse_attn_fwd(g: Geom, dtype: int, q_perm, k_perm, v_perm, kv_idx, kv_cnt, K_max: int, scale: float,
                         o_perm, lse=None):
+    rc = _plain_sparse_attn(g, dtype, q_perm, k_perm, v_perm, kv_idx, kv_cnt, K_max, scale, o_perm, lse)
+    if rc == 0:
+        return
+    if rc is not None:
+        _check(rc)
     s = dfs_geom_sizes(g)
     td = _torch_dtype(dtype)
     n = g.heads * s.N_pad * g.d
@@ -326,6 +355,11 @@ def dfs_probe_read(src: torch.Tensor, work_groups: int, pieces_per_wg: int, sink
 
 
 def dfs_unperm(g: Geom, dtype: int, o_perm, inv, o):
+    rc = _plain_unperm(g, dtype, o_perm, inv, o)
+    if rc == 0:
+        return
+    if rc is not None:
+        _check(rc)
     s = dfs_geom_sizes(g)
     td = _torch_dtype(dtype)
     _check(_lib.dfs_unperm(g, dtype, _ptr(o_perm, td, g.heads * s.N_pad * g.d, "o_perm"),

@@ -1,9 +1,11 @@
-// The calls of a small problem from Python without the cost of marshalling them in Python: dfs_forward and the token orders take their
-// arguments straight from the objects.  A launch costs the host some 3 us and its kernel often less, so what bounds
+// The calls of a small problem from Python without the cost of marshalling them in Python: dfs_forward, the token orders and the staged calls
+// of a quality check take their arguments straight from the objects.  A launch costs the host some 3 us and its kernel often less, so what bounds
 // such calls is what Python does between two of them: some fifty attribute lookups of tensors and a ctypes call.  Measured (us, in Python ->
 // here).  The host's time of a call in a burst of eight: reuse step (one launch) 10.0 -> 4.9, refresh step of 256 fp32 tokens
 // (three) 17.2 -> 13.0, token order 6.5 -> 4.1.  A call among others: token order of 75 600 or 64 tokens 6.2 -> 3.6, reuse step of
 // 512 tokens x 8 heads, d = 64, 9.4 -> 8.7, of which its kernel takes 8.5; the refresh step stays at 16.5, which its kernels take.
+// A quality check in staged calls (nine of them and two of torch), 675 tokens x 2 heads, d = 64, 73 -> 53, 1 575 x 2 73 -> 62; larger ones
+// take what their kernels take (2 625 x 4, d = 128, 111).
 //
 // The module holds the version of the torch it was built against, whose classes it reads: binding.py uses it with no other.
 // A call goes to the library only if every argument is of the plain kind and passes every check of binding.py; else None is returned,
@@ -137,6 +139,100 @@ PyObject* token_order(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
+// The staged calls.  Their arguments as binding.py passes them on, None where it takes None.
+void* to_ptr_or_null(PyObject* x, at::ScalarType type, int64_t numel, int64_t* bytes = nullptr) {
+  return x == Py_None ? nullptr : to_ptr(x, type, numel, bytes);
+}
+at::ScalarType tensor_type(int dtype) { return dtype == DFS_BF16 ? at::kBFloat16 : at::kFloat; }
+struct Problem {
+  dfs_geom g;
+  dfs_sizes s;
+  explicit Problem(PyObject* x) : g(to_geom(x)) { need(dfs_geom_sizes(&g, &s) == DFS_OK); }
+  int64_t source() const { return int64_t(g.heads) * s.N * g.d; }
+  int64_t ordered() const { return int64_t(g.heads) * s.N_pad * g.d; }
+  int64_t scores() const { return int64_t(g.heads) * s.M_v * s.M_v; }
+  int64_t rows() const { return int64_t(g.heads) * s.M; }
+};
+template <class F>
+int without_gil(F f) {
+  PyThreadState* gil = PyEval_SaveThread();
+  const int rc = f();
+  PyEval_RestoreThread(gil);
+  return rc;
+}
+
+template <bool BACK>
+PyObject* reorder(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return guarded([&]() -> int {
+    need(n == 5);
+    const Problem p(a[0]);
+    const int dtype = to_int(a[1]);
+    const auto type = tensor_type(dtype);
+    const void* x = to_ptr(a[2], type, BACK ? p.ordered() : p.source());
+    const auto* index = static_cast<const int32_t*>(to_ptr(a[3], at::kInt, BACK ? p.s.N : p.s.N_pad));
+    void *y = to_ptr(a[4], type, BACK ? p.source() : p.ordered()), *st = stream();
+    return without_gil([&] { return BACK ? dfs_unperm(&p.g, dtype, x, index, y, st) : dfs_permute(&p.g, dtype, x, index, y, st); });
+  });
+}
+
+PyObject* block_score(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return guarded([&]() -> int {
+    need(n == 6);
+    const Problem p(a[0]);
+    const int dtype = to_int(a[1]);
+    const void *q = to_ptr(a[2], tensor_type(dtype), p.ordered()), *k = to_ptr(a[3], tensor_type(dtype), p.ordered());
+    auto* score = static_cast<float*>(to_ptr(a[4], at::kFloat, p.scores()));
+    int64_t ws_bytes = 0;
+    void *ws = to_ptr(a[5], at::ScalarType::Undefined, 0, &ws_bytes), *st = stream();
+    return without_gil([&] { return dfs_block_score(&p.g, dtype, q, k, score, ws, size_t(ws_bytes), st); });
+  });
+}
+
+PyObject* select_mask(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return guarded([&]() -> int {
+    need(n == 11);
+    const Problem p(a[0]);
+    const auto* score = static_cast<const float*>(to_ptr(a[1], at::kFloat, p.scores()));
+    const int mode = to_int(a[2]), K_max = to_int(a[8]);
+    const double sparsity = to_double(a[3]), mass = to_double(a[4]);
+    auto* mask = static_cast<uint8_t*>(to_ptr_or_null(a[5], at::kByte, p.rows() * p.s.M));
+    auto *kv_idx = static_cast<int32_t*>(to_ptr(a[6], at::kInt, p.rows() * K_max)), *kv_cnt = static_cast<int32_t*>(to_ptr(a[7], at::kInt, p.rows()));
+    auto* k_head = static_cast<int32_t*>(to_ptr_or_null(a[9], at::kInt, p.g.heads));
+    int64_t ws_bytes = 0;
+    void *ws = to_ptr_or_null(a[10], at::ScalarType::Undefined, 0, &ws_bytes), *st = stream();
+    return without_gil([&] { return dfs_select_mask(&p.g, score, mode, sparsity, mass, mask, kv_idx, kv_cnt, K_max, k_head, ws, size_t(ws_bytes), st); });
+  });
+}
+
+PyObject* sparse_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return guarded([&]() -> int {
+    need(n == 11);
+    const Problem p(a[0]);
+    const int dtype = to_int(a[1]), K_max = to_int(a[7]);
+    const auto type = tensor_type(dtype);
+    const void *q = to_ptr(a[2], type, p.ordered()), *k = to_ptr(a[3], type, p.ordered()), *v = to_ptr(a[4], type, p.ordered());
+    const auto *kv_idx = static_cast<const int32_t*>(to_ptr(a[5], at::kInt, p.rows() * K_max)),
+               *kv_cnt = static_cast<const int32_t*>(to_ptr(a[6], at::kInt, p.rows()));
+    const float scale = float(to_double(a[8]));
+    void* o = to_ptr(a[9], type, p.ordered());
+    auto* lse = static_cast<float*>(to_ptr_or_null(a[10], at::kFloat, int64_t(p.g.heads) * p.s.N_pad));
+    void* st = stream();
+    return without_gil([&] { return dfs_sparse_attn_fwd(&p.g, dtype, q, k, v, kv_idx, kv_cnt, K_max, scale, o, lse, st); });
+  });
+}
+
+PyObject* recall(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return guarded([&]() -> int {
+    need(n == 4);
+    const Problem p(a[0]);
+    const int64_t rows = int64_t(p.g.heads) * p.s.N_pad;
+    const auto *kept = static_cast<const float*>(to_ptr(a[1], at::kFloat, rows)), *all = static_cast<const float*>(to_ptr(a[2], at::kFloat, rows));
+    auto* out = static_cast<float*>(to_ptr(a[3], at::kFloat, p.g.heads));
+    void* st = stream();
+    return without_gil([&] { return dfs_recall(&p.g, kept, all, out, st); });
+  });
+}
+
 PyObject* set_geom_type(PyObject*, PyObject* type) {
   Py_INCREF(type);
   g_geom_type = type;
@@ -146,6 +242,12 @@ PyObject* set_geom_type(PyObject*, PyObject* type) {
 PyMethodDef methods[] = {
     {"forward", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(forward)), METH_FASTCALL, nullptr},
     {"token_order", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(token_order)), METH_FASTCALL, nullptr},
+    {"permute", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(reorder<false>)), METH_FASTCALL, nullptr},
+    {"unperm", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(reorder<true>)), METH_FASTCALL, nullptr},
+    {"block_score", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(block_score)), METH_FASTCALL, nullptr},
+    {"select_mask", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(select_mask)), METH_FASTCALL, nullptr},
+    {"sparse_attn", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(sparse_attn)), METH_FASTCALL, nullptr},
+    {"recall", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(recall)), METH_FASTCALL, nullptr},
     {"set_geom_type", set_geom_type, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 
