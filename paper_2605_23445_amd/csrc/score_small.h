@@ -108,15 +108,25 @@ __device__ __forceinline__ void small_scores(const Operands& x, float* s_t, floa
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) bq[p][kk] = x.q(p, 2 * kk + half, n);
   float m_row = LSE_START, z_row = 0.f;
-  for (int t = wave; t * 32 < n_live; t += SS_WAVES) {
-    f16x8 ak[2][KS];
+  // At d = 64 a tile's operands are requested as soon as the matrix instructions have taken those of the tile before, in front of its
+  // exponentials; at d = 128 the registers that this takes would leave a CU one work-group instead of two.
+  constexpr bool AHEAD = D == 64;
+  f16x8 ak[2][KS];
+  float k_dn[4];
+  auto ask = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) ak[p][kk] = x.k(t, p, 2 * kk + half, n);
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) k_dn[gq] = x.k_inverse(8 * t + 2 * gq + half);
+  };
+  if (AHEAD && wave * 32 < n_live) ask(wave);
+  for (int t = wave; t * 32 < n_live; t += SS_WAVES) {
+    if (!AHEAD) ask(t);
     float dn[4];
 #pragma unroll
-    for (int gq = 0; gq < 4; ++gq) dn[gq] = x.k_inverse(8 * t + 2 * gq + half) * q_dn;
+    for (int gq = 0; gq < 4; ++gq) dn[gq] = k_dn[gq] * q_dn;
     f32x16 c0, c1;
 #pragma unroll
     for (int i = 0; i < 16; ++i) { c0[i] = 0.f; c1[i] = 0.f; }
@@ -127,6 +137,10 @@ __device__ __forceinline__ void small_scores(const Operands& x, float* s_t, floa
       a = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[0][kk], bq[0][kk], a, 0, 0, 0);
       b = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[0][kk], bq[1][kk], b, 0, 0, 0);
       a = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[1][kk], bq[0][kk], a, 0, 0, 0);
+    }
+    if (AHEAD) {
+      if ((t + SS_WAVES) * 32 < n_live) ask(t + SS_WAVES);
+      __builtin_amdgcn_sched_barrier(0);
     }
     float c[16], mt = -INFINITY;
 #pragma unroll

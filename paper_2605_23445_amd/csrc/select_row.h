@@ -97,13 +97,54 @@ __device__ __forceinline__ int mass_count_row(Keys keys, unsigned long long* bin
   return int(n_above + (need + at - 1) / at);
 }
 
+// The row in registers, NK keys a lane: the k-th largest key a bit at a time from the top, the count of the keys that reach it from ballots and scalar
+// additions.  Then its kept columns in ascending order, ties at the threshold the lowest first.
+template <int NK, class Keys>
+__device__ __forceinline__ void select_in_registers(Keys keys, int M_v, int k, uint8_t* mrow, int32_t* idx) {
+  const int lane = threadIdx.x & 63;
+  uint32_t key[NK];
+#pragma unroll
+  for (int i = 0; i < NK; ++i) key[i] = 64 * i + lane < M_v ? keys[64 * i + lane] : 0u;     // zeros reach no threshold that is tried
+  uint32_t T = 0;
+  constexpr int BITS = NK <= 3 ? 2 : 1;                // two at a time where the chain from count to count is longer than the counting
+  for (int shift = 32 - BITS; shift >= 0; shift -= BITS) {
+    uint32_t digit = 0;                              // the counts fall from digit to digit
+#pragma unroll
+    for (uint32_t x = 1; x < 1u << BITS; ++x) {
+      int reached = 0;
+#pragma unroll
+      for (int i = 0; i < NK; ++i) reached += __popcll(__ballot(key[i] >= (T | x << shift)));
+      digit += reached >= k ? 1 : 0;
+    }
+    T |= digit << shift;
+  }
+  int above = 0;
+#pragma unroll
+  for (int i = 0; i < NK; ++i) above += __popcll(__ballot(64 * i + lane < M_v && key[i] > T));
+  const unsigned long long below_me = (1ull << lane) - 1ull;
+  int ties_left = k - above, written = 0;
+#pragma unroll
+  for (int i = 0; i < NK; ++i) {
+    const int j = 64 * i + lane;
+    const bool is_tie = j < M_v && key[i] == T;
+    const unsigned long long ties = __ballot(is_tie);
+    const bool keep = j < M_v && (key[i] > T || (is_tie && __popcll(ties & below_me) < ties_left));
+    const unsigned long long kept = __ballot(keep);
+    if (keep) idx[written + __popcll(kept & below_me)] = j;
+    if (mrow && j < M_v) mrow[j] = keep ? 1 : 0;
+    ties_left -= __popcll(ties) < ties_left ? __popcll(ties) : ties_left;
+    written += __popcll(kept);
+  }
+}
+
 // Top-k of a row: kept columns in ascending order into idx, the text blocks behind them, the mask row if there is one.
-// The k-th largest key is found a byte at a time from the top: a 256-bin histogram of the next byte of the keys that
-// still match the bytes fixed so far, then the bin in which the count from the top reaches what is still wanted.  Four
-// passes instead of one per bit; counts are integers, so the result is the same key.  A row of up to 64 columns is ranked
-// outright, each lane counting the columns ahead of its own (keys four at a time, the same for all lanes): with the fold, 4 columns
-// 5.3 -> 3.0 us, 41 columns 7.4 -> 7.1.
-template <class Keys>
+// Rows of up to 640 columns are selected in registers.  In longer ones the k-th largest key is found a byte at a time from the top: a 256-bin
+// histogram of the next byte of the keys that still match the bytes fixed so far, then the bin in which the count from the top
+// reaches what is still wanted; counts are integers, so it is the same key.
+// With the histogram for rows of more than 64 columns and a rank of every column below (us a launch, under the profiler): 41 columns x 12 heads with
+// the scoring 7.6 -> 6.2, 138 x 48 35.0 -> 31.2 (d = 64, with the operands ahead), 591 x 40 with the fold 78 -> 72.
+// MOST: rows have no more columns than that (the ways for longer ones are left out).
+template <int MOST = 1 << 30, class Keys>
 __device__ __forceinline__ void select_row(Keys keys, uint32_t* hist /*[256]*/, int M_v, int M_x, int k, uint8_t* mrow,
                                            int32_t* idx, int32_t* cnt) {
   const int lane = threadIdx.x & 63;
@@ -112,7 +153,7 @@ __device__ __forceinline__ void select_row(Keys keys, uint32_t* hist /*[256]*/, 
     if (mrow) mrow[M_v + j] = 1;
   }
   if (lane == 0) *cnt = k + M_x;
-  if (M_v <= 64) {
+  if (MOST <= 16 || M_v <= 16) {                     // ranked outright, each lane counting the columns ahead of its own
     const uint32_t key = lane < M_v ? keys[lane] : 0u;
     int ahead = 0;
     for (int i0 = 0; i0 < M_v; i0 += 4) {
@@ -129,6 +170,10 @@ __device__ __forceinline__ void select_row(Keys keys, uint32_t* hist /*[256]*/, 
     if (mrow && lane < M_v) mrow[lane] = keep ? 1 : 0;
     return;
   }
+  if (MOST <= 64 || M_v <= 64) return select_in_registers<1>(keys, M_v, k, mrow, idx);
+  if (M_v <= 192) return select_in_registers<3>(keys, M_v, k, mrow, idx);
+  if (MOST <= 320 || M_v <= 320) return select_in_registers<5>(keys, M_v, k, mrow, idx);
+  if (M_v <= 640) return select_in_registers<10>(keys, M_v, k, mrow, idx);
   uint32_t T = 0, fixed = 0, want = uint32_t(k);      // want: rank of the key looked for among the keys matching T on `fixed`
   for (int shift = 24; shift >= 0; shift -= 8) {
     for (int b = lane; b < 256; b += 64) hist[b] = 0u;

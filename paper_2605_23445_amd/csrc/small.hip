@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(SS_T) forward_small_kernel(const float* __rest
       } else if (k_head && u == 0 && part == 0 && lane == 0) {
         k_head[head] = n;
       }
-      select_row(row, x.hist, M_v, M - M_v, n, mrow, room.list, &room.cnt);
+      select_row<16>(row, x.hist, M_v, M - M_v, n, mrow, room.list, &room.cnt);
     }
   } else if (wave == 0) {
     select_text_row(M, mrow, &room.cnt);
