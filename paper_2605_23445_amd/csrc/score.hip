@@ -141,6 +141,91 @@ __global__ void __launch_bounds__(256) pool_kernel(const void* __restrict__ q_in
   }
 }
 
+// Pooling of bf16 tensors that nothing is written out of on the way: one wave per scale group of four sub-blocks, so that what follows the sums
+// (row groups folded, magnitude, scale, split) is done once for four, each row of sixteen lanes with a sub-block of its own, and without a way
+// through LDS; the same sums in the same order as above.  An HBM stream that was bound by the issue of some 240 instructions per
+// sub-block beside its loads (counted from the source), now some 130.  See pool_reads_groups for the rule and what it measured.
+template <int D>
+__global__ void __launch_bounds__(256) pool_read_kernel(const uint16_t* __restrict__ q_in, const uint16_t* __restrict__ k_in, uint16_t* __restrict__ q_hat,
+                                                        uint16_t* __restrict__ k_hat, float* __restrict__ q_down, float* __restrict__ k_down,
+                                                        const int32_t* __restrict__ index, int64_t N_src, int64_t N_pad, int64_t N_v, int Bs, int M_s,
+                                                        float q_scale, bool tiled, bool k_src, int32_t* __restrict__ zero, int n_zero) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+    for (int i = threadIdx.x; i < n_zero; i += 256) zero[i] = 0;
+  constexpr int TPR = D / 8, RPP = 64 / TPR, AHEAD = 4, CR = RPP * AHEAD;        // lanes per row, rows per pass, passes in flight of each sub-block
+  constexpr int NP = 4 * CR / 64;                            // positions a lane looks up for them
+  const int lane = threadIdx.x & 63, g = blockIdx.x * 4 + (threadIdx.x >> 6), G4 = (M_s + 3) / 4;
+  if (g >= G4) return;
+  const int c = lane % TPR, rg = lane / TPR, head = blockIdx.y;
+  const bool keys = blockIdx.z == 1, gather = index != nullptr && (!keys || k_src);
+  const int64_t limit = gather ? N_src : N_pad, row0 = int64_t(4 * g) * Bs;
+  const u32x4* base = reinterpret_cast<const u32x4*>(keys ? k_in : q_in) + int64_t(head) * limit * TPR + c;
+  float acc[4][8];
+#pragma unroll
+  for (int sb = 0; sb < 4; ++sb)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[sb][e] = 0.f;
+  for (int i0 = 0; i0 < Bs; i0 += CR) {
+    int pos[NP];
+#pragma unroll
+    for (int m = 0; m < NP; ++m) {
+      const int x = m * 64 + lane, i = i0 + x % CR;
+      const int64_t row = row0 + x / CR * Bs + i;
+      pos[m] = i >= Bs || row >= N_v ? -1 : gather ? index[row] : int(row);
+      if (pos[m] >= limit) pos[m] = -1;
+    }
+    u32x4 val[4][AHEAD];
+#pragma unroll
+    for (int sb = 0; sb < 4; ++sb)
+#pragma unroll
+      for (int p = 0; p < AHEAD; ++p) {
+        const int x = sb * CR + p * RPP, from = __shfl(pos[x / 64], x % 64 + rg, 64);
+        val[sb][p] = u32x4{0u, 0u, 0u, 0u};
+        if (from >= 0) val[sb][p] = __builtin_nontemporal_load(base + int64_t(from) * TPR);
+      }
+#pragma unroll
+    for (int sb = 0; sb < 4; ++sb)
+#pragma unroll
+      for (int p = 0; p < AHEAD; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {                        // zeros change no sum that starts from zero
+          acc[sb][2 * e] += __uint_as_float(val[sb][p][e] << 16);
+          acc[sb][2 * e + 1] += __uint_as_float(val[sb][p][e] & 0xFFFF0000u);
+        }
+  }
+  const int sb = lane >> 4, s = 4 * g + sb;                  // this lane's sub-block from here on
+  const int64_t left = N_v - int64_t(s) * Bs;
+  const float cnt = left <= 0 ? 0.f : float(left < Bs ? int(left) : Bs), by = left <= 0 ? 0.f : (keys ? 1.0f : q_scale) / cnt;
+  float own[8], mx = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    if (RPP == 8) {                                          // two row groups in sixteen lanes
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc[x][e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[x][e]), 0x128, 0xF, 0xF, true));
+    }
+    own[e] = sum_32(sum_16(acc[0][e], acc[1][e]), sum_16(acc[2][e], acc[3][e])) * by;
+    mx = fmaxf(mx, fabsf(own[e]));
+  }
+  float up, down;
+  group_scale(max_32(max_16(max_of_16(mx))), up, down);
+  if (lane == 0) (keys ? k_down : q_down)[int64_t(head) * G4 + g] = down;
+  if (s >= M_s || (lane & 15) >= TPR) return;
+  const int in_tile = tile_rows(M_s, s / 32);
+  uint16_t* o = (keys ? k_hat : q_hat) + int64_t(head) * M_s * (2 * D) +
+                (tiled ? tile_at<D>(s / 32) + chunk_at<D>(0, c, in_tile, s % 32) : int64_t(s) * (2 * D) + c * 8);
+  uint16_t hi[8], lo[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) split2(own[e] * up, hi[e], lo[e]);
+  u32x4 h4, l4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    h4[e] = uint32_t(hi[2 * e]) | (uint32_t(hi[2 * e + 1]) << 16);
+    l4[e] = uint32_t(lo[2 * e]) | (uint32_t(lo[2 * e + 1]) << 16);
+  }
+  *reinterpret_cast<u32x4*>(o) = h4;
+  *reinterpret_cast<u32x4*>(o + (tiled ? chunk_at<D>(1, 0, in_tile, 0) : D)) = l4;
+}
+
 // ------------------------------------------------------------------------------------ scoring
 
 // T is stored with its rows padded to whole query groups (128 sub-blocks) and its row count to whole key tiles,
@@ -650,6 +735,14 @@ static void launch_score(const dfs_geom* g, const dfs_sizes& s, const uint16_t* 
 
 bool can_select_in_fold(const dfs_sizes& s, int mode) { return mode != DFS_SELECT_MASS_HEAD && fs_lds(s.M_v) <= 65536; }
 
+// Where a wave pools four sub-blocks: rows that it can have in flight together, and enough groups to fill the chip with as long waves
+// all the same.  Measured (us, one sub-block a wave -> four): pooling under the profiler, 17 550 tokens x 48 heads, d = 64, sub-blocks of 32, 42.6 -> 35.4,
+// 2 565 x 12, of 16, 5.5 -> 5.1, 75 600 x 40, d = 128, of 32, 272 -> 272 (HBM); refresh steps: 38 400 x 5, d = 64, of 32, 138.8 -> 134.5, 7 200 x 6, d = 128, of
+// 8, 58.0 -> 55.6, 1 024 x 8, d = 64, of 16 (128 groups), 16.1 -> 16.6, 3 072 x 8, d = 128, of 64, 27.6 -> 31.2.
+static bool pool_reads_groups(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* k_out) {
+  return dtype == DFS_BF16 && !k_out && g->Bs <= 32 && int64_t(g->heads) * ((s.M_s + 3) / 4) >= 384;
+}
+
 int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q_perm, const void* k_perm, float* score,
                     void* ws, const int32_t* index, bool k_src, void* k_out, const void* v, void* v_out, int32_t* zero, int n_zero, const SelectPlan* sel,
                     hipStream_t st) {
@@ -668,8 +761,11 @@ int run_block_score(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
   // 1/sqrt(d) of Eq. 2 and the change to base 2 go into Q_hat, so that the logits come out of the contraction in base 2
   const float scale = 1.4426950408889634f / sqrtf(float(g->d));
 #define POOL(BF, DD) pool_kernel<BF, DD><<<pg, 256, 0, st>>>(q_perm, k_perm, v, q_hat, k_hat, q_down, k_down, index, k_out, v_out, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale, score_small(g, s), k_src, zero, n_zero)
-  if (g->d == 64) { if (bf) POOL(true, 64); else POOL(false, 64); }
-  else            { if (bf) POOL(true, 128); else POOL(false, 128); }
+#define POOL_READ(DD) pool_read_kernel<DD><<<dim3(unsigned(((s.M_s + 3) / 4 + 3) / 4), unsigned(g->heads), 2), 256, 0, st>>>(static_cast<const uint16_t*>(q_perm), static_cast<const uint16_t*>(k_perm), q_hat, k_hat, q_down, k_down, index, s.N, s.N_pad, s.N_v, g->Bs, s.M_s, scale, score_small(g, s), k_src, zero, n_zero)
+  if (pool_reads_groups(g, s, dtype, k_out)) { if (g->d == 64) POOL_READ(64); else POOL_READ(128); }
+  else if (g->d == 64) { if (bf) POOL(true, 64); else POOL(false, 64); }
+  else                 { if (bf) POOL(true, 128); else POOL(false, 128); }
+#undef POOL_READ
 #undef POOL
   const int n_live = int((s.N_v + g->Bs - 1) / g->Bs);
 #define SCORE(DD, RR) launch_score<DD, RR>(g, s, q_hat, k_hat, q_down, k_down, tt, lse, score, sel, n_live, st)

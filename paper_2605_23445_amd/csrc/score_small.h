@@ -59,6 +59,35 @@ __device__ __forceinline__ void both_halves(float x, float& lo, float& hi) {
   hi = __uint_as_float(sw[1]);
 }
 
+// x' and y' hold the lower and the upper lanes' (of 32, of 64) values of a pair: x' + y' is x summed over the pair in its lower lanes and y
+// in its upper ones.
+__device__ __forceinline__ float sum_16(float x, float y) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ float sum_32(float x, float y) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ float max_16(float x) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+__device__ __forceinline__ float max_32(float x) {
+  float lo, hi;
+  both_halves(x, lo, hi);
+  return fmaxf(lo, hi);
+}
+template <int CTRL> __device__ __forceinline__ float dpp_max(float x) {
+  return fmaxf(x, __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), CTRL, 0xF, 0xF, true)));
+}
+__device__ __forceinline__ float max_of_16(float x) {        // over each row of sixteen lanes
+  x = dpp_max<0xB1>(x);                                       // lanes 1 0 3 2
+  x = dpp_max<0x4E>(x);                                       // lanes 2 3 0 1
+  x = dpp_max<0x141>(x);                                      // eight, mirrored
+  return dpp_max<0x140>(x);                                   // sixteen, mirrored
+}
+
 // Running base-2 log-sum-exp (reference m, sum z of 2^(x - m)): add one term, merge two partial sums.
 __device__ __forceinline__ void lse_add(float& m, float& z, float x) {
   const float mn = fmaxf(m, x);

@@ -29,35 +29,6 @@ template <int D> struct SmallRoom {                   // LDS
   int32_t list[FS_BLOCKS], cnt;
 };
 
-// x' and y' hold the lower and the upper lanes' (of 32, of 64) values of a pair: x' + y' is x summed over the pair in its lower lanes and y
-// in its upper ones.
-__device__ __forceinline__ float sum_16(float x, float y) {
-  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
-}
-__device__ __forceinline__ float sum_32(float x, float y) {
-  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
-}
-__device__ __forceinline__ float max_16(float x) {
-  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
-}
-__device__ __forceinline__ float max_32(float x) {
-  float lo, hi;
-  both_halves(x, lo, hi);
-  return fmaxf(lo, hi);
-}
-template <int CTRL> __device__ __forceinline__ float dpp_max(float x) {
-  return fmaxf(x, __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), CTRL, 0xF, 0xF, true)));
-}
-__device__ __forceinline__ float max_of_16(float x) {        // over each row of sixteen lanes
-  x = dpp_max<0xB1>(x);                                       // lanes 1 0 3 2
-  x = dpp_max<0x4E>(x);                                       // lanes 2 3 0 1
-  x = dpp_max<0x141>(x);                                      // eight, mirrored
-  return dpp_max<0x140>(x);                                   // sixteen, mirrored
-}
-
 // One wave: the centroids of groups first, first + step, ... < groups, four sub-blocks each, as pool_kernel forms them, the same sums in the same
 // order.  A group's rows are requested while the group before is finished.  rows_of(g): the tensor's head and the factor; put(g, sb, c, up, hi, lo):
 // features 4 c .. 4 c + 3 of sub-block sb of the group, and inverse(g, x).
