@@ -1062,6 +1062,20 @@ static int pair_rounds(const dfs_geom* g, const dfs_sizes& s) {
   return (pair_text_slots(s.M_v, s.M, g->heads) + g->heads * pair_chunk(s.M_v)) / PAIR_WGS;
 }
 
+// Behind the pairs: the query blocks that they leave over, the last of every XCD, shared as tail_split has it where there is room (dfs_forward).
+// Fewer than 64 an XCD, so that a whole one each would leave half of the chip's slots idle and more for as long as a dense row takes.  Measured (ms,
+// whole -> shared): 591 blocks, all kept, x 40 heads (16 left an XCD) 94.4 -> 93.6, x 8 19.28 -> 18.76; 60 of 591 kept x 40 10.67 -> 10.66, 929
+// blocks, 93 kept, x 24 16.26 -> 16.28, which two runs of one side differ by.
+static TailSplit pairs_tail(const dfs_geom* g, const dfs_sizes& s, int order, int text_slots, int pairs, const TextSplit& ts, size_t scratch_bytes) {
+  const TailSplit none = {0, 1, 1};
+  const int from = text_slots + 2 * (pairs * PAIR_WGS - pair_text_slots(s.M_v, s.M, g->heads)), rows = order - from;
+  if (scratch_bytes == 0 || from < text_slots || rows < 1 || rows > 32) return none;
+  const int splits = 64 / rows < 4 ? 64 / rows : 4;
+  const int64_t parts = 8 * int64_t(rows) * splits + (ts.splits > 1 ? int64_t(g->heads) * s.M_x * ts.splits : 0);
+  if (size_t(parts) * g->B * (g->d + 4) * sizeof(float) > scratch_bytes - align256(split_tickets(g, s) * sizeof(int32_t))) return none;
+  return {from, rows, splits};
+}
+
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
                     const int32_t* kv_idx, const int32_t* kv_cnt, int32_t K_max, float scale, void* o, float* lse,
                     const int32_t* row_index, bool kv_src, bool maybe_dense, bool zeroed, void* scratch, size_t scratch_bytes, hipStream_t st) {
@@ -1080,9 +1094,9 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     const int ks = key_split(g->d, g->B, work_groups, K_max);
     const bool one_buffer = g->d == 128 && g->B == 64 && slim(work_groups, ks, mapping);
     const int order = mapping >= 2 ? text_slots + per_xcd : per_xcd;     // slots of an XCD
-    const TailSplit tail = lse || ks > 1 ? TailSplit{0, 1, 1} : tail_split(g, s, K_max, order, mapping >= 2 ? text_slots : 0, ts, one_buffer, scratch_bytes);
-    if (!zeroed && (ts.splits > 1 || tail.splits > 1)) clear_tickets_kernel<<<1, 256, 0, st>>>(tickets, int(split_tickets(g, s)));
     const int pairs = maybe_dense ? pair_rounds(g, s) : 0;
+    const TailSplit tail = lse || ks > 1 ? TailSplit{0, 1, 1} : pairs > 0 ? pairs_tail(g, s, order, text_slots, pairs, ts, scratch_bytes) : tail_split(g, s, K_max, order, mapping >= 2 ? text_slots : 0, ts, one_buffer, scratch_bytes);
+    if (!zeroed && (ts.splits > 1 || tail.splits > 1)) clear_tickets_kernel<<<1, 256, 0, st>>>(tickets, int(split_tickets(g, s)));
     if (pairs > 0) {
 #define ATTN_PAIRS(XX, SRC)                                                                                                            \
   attn_pairs_kernel<128, XX, SRC><<<8 * PAIR_WGS, 512, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),            \
