@@ -259,8 +259,8 @@ typedef struct {
  * reorder.  perm_pad / inv come from dfs_hilbert_perm.  bf16 rows may differ from the staged calls' by rounding where
  * several work-groups share a query block's keys, which only this call has room for: text blocks (16 blocks and more in
  * all), and, from 512 query blocks in all heads on, the video or text blocks that would be left over for a last round of
- * work-groups with half and more of the chip idle.  Which these are follows from the geometry, K_max and, from 2 048 query
- * blocks on, whether the lists come from this call (a top-k that drops blocks, a mass rule) or may keep every block.
+ * work-groups with half and more of the chip idle.  Which these are follows from the geometry and K_max, and for rows that keep
+ * every block, from 2 048 query blocks on, from whether a call's lists may all do so (a reuse step, a top-k that drops none).
  * `scale` is not checked: f32 tensors take any, bf16 tensors need it positive.  At most 65 535 heads (DFS_ESHAPE).
  *   q, k, v [heads, N, d] in;  o [heads, N, d] out.   ws: DFS_WS_FORWARD (f32) or DFS_WS_FORWARD_BF16.
  */

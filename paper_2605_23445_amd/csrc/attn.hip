@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "attn_f32.h"
+#include "attn_pairs.h"
 
 namespace dfs {
 
@@ -67,24 +68,6 @@ constexpr int swz_period(int step, int mod) {    // smallest P with (P * step) %
 // is the lookup of positions and their way to the lanes.  See attn_reads_source below for the rule.
 template <int D, int BM, bool XLSE, int KS>
 constexpr int attn_waves() { return D == 64 && BM == 128 && !XLSE && KS == 1 ? 3 : 2; }
-// Pairs of query blocks that attn_pairs_kernel takes, and in which order.  A pair is two neighbouring video blocks of a head (the last
-// one may be alone) or two text blocks.  Slots of an XCD: the text pairs of all heads in turn with the other XCDs, then its eighth of
-// the video pairs of head 0, of head 1, ... as in mapping 2.  Its PAIR_WGS work-groups take a slot each per round.
-constexpr int PAIR_WGS = 32;
-__host__ __device__ __forceinline__ int pair_text_slots(int M_v, int M, int n_heads) { return (n_heads * ((M - M_v + 1) / 2) + 7) / 8; }
-__host__ __device__ __forceinline__ int pair_chunk(int M_v) { return ((M_v + 1) / 2 + 7) / 8; }        // video pairs of a head and XCD
-// First block of the pair in a slot, -1 for none.
-__device__ __forceinline__ int pair_at(int xcd, int slot, int M_v, int M, int n_heads, int& head) {
-  const int XP = (M - M_v + 1) / 2, C = pair_chunk(M_v), text_slots = pair_text_slots(M_v, M, n_heads);
-  if (slot < text_slots) {
-    const int id = slot * 8 + xcd;
-    head = XP > 0 ? id / XP : 0;
-    return head < n_heads && XP > 0 ? M_v + 2 * (id % XP) : -1;
-  }
-  const int s2 = slot - text_slots, u = 2 * (xcd * C + s2 % C);
-  head = s2 / C;
-  return head < n_heads && u < M_v ? u : -1;
-}
 // Whether the pair's rows are dense.  Text rows always are; they go with the head's first video rows, so that they run beside what
 // takes as long.
 __device__ __forceinline__ bool pair_dense(const int32_t* __restrict__ kv_cnt, int head, int u, int M_v, int M) {
@@ -92,10 +75,9 @@ __device__ __forceinline__ bool pair_dense(const int32_t* __restrict__ kv_cnt, i
   const int end = u < M_v ? M_v : M, v1 = M_v > 1 ? 1 : 0;
   return cnt[u] >= M && cnt[u + 1 < end ? u + 1 : u] >= M && (u < M_v || (cnt[0] >= M && cnt[v1] >= M));
 }
-__device__ __forceinline__ bool in_pairs(const int32_t* __restrict__ kv_cnt, int head, int u, int M_v, int M, int n_heads, int rounds) {
-  const int u0 = u < M_v ? u & ~1 : M_v + ((u - M_v) & ~1), C = pair_chunk(M_v);
-  const int slot = u < M_v ? pair_text_slots(M_v, M, n_heads) + head * C + u0 / 2 % C : (head * ((M - M_v + 1) / 2) + (u0 - M_v) / 2) / 8;
-  return slot < rounds * PAIR_WGS && pair_dense(kv_cnt, head, u0, M_v, M);
+// Whether a dense row is in such a pair in front of slot `end`.
+__device__ __forceinline__ bool in_pairs(const int32_t* __restrict__ kv_cnt, int head, int u, int M_v, int M, int n_heads, int end) {
+  return pair_slot(head, u, M_v, M, n_heads) < end && pair_dense(kv_cnt, head, pair_of(u, M_v), M_v, M);
 }
 
 // What a work-group does: the query block u of `head` (BM = 256: blocks u and u + 1, which keep every key block), or with TAIL and
@@ -106,7 +88,7 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
           const int32_t* __restrict__ kv_idx, const int32_t* __restrict__ kv_cnt, int K_max, uint16_t* __restrict__ o,
           float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
           int M_v, int M, int total_wg, float scale, unsigned long long* __restrict__ clock_probe, float* __restrict__ part,
-          int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows, int pair_rounds, int head, int u, int split,
+          int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows, int pairs_end, int head, int u, int split,
           int splits, int xcd, int slot, bool tail) {
   constexpr int NW = BM / 32;                      // waves per group: one per 32 query rows
   constexpr int CH = D / 8;                        // 16-byte chunks per row
@@ -144,7 +126,7 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
   const int n = lane & 31, h = lane >> 5;
   const int cnt_in = PAIR ? M : kv_cnt[int64_t(head) * M + u];
   const bool dense = PAIR || cnt_in >= M;
-  if (REST && dense && in_pairs(kv_cnt, head, u, M_v, M, total_wg / M, pair_rounds)) return;     // attn_pairs_kernel has done it
+  if (REST && dense && in_pairs(kv_cnt, head, u, M_v, M, total_wg / M, pairs_end)) return;       // another work-group's
   const bool shared_row = !XLSE && splits > 1;
   int cnt = dense ? M : (cnt_in < 0 ? 0 : (cnt_in > K_max ? K_max : cnt_in));
   const int run = tail ? (cnt + splits - 1) / splits : split_blocks;
@@ -799,7 +781,8 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
   }
 }
 
-// REST: what attn_pairs_kernel, launched in front, has done is left out.
+// REST: behind attn_pairs_kernel.  Dense pairs in front of slot pairs_end are left out, which it has done or, behind its `pair_rounds`, the work-groups
+// from slot left_from on do: left_rows / 2 pairs an XCD, whose blocks left_splits work-groups share each.
 template <int D, int BM, bool XLSE, int KS, bool SLIM, bool TAIL, bool SRC, bool REST>
 __device__ __forceinline__ void
 attn_work_group(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -807,7 +790,7 @@ attn_work_group(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, 
                 float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
                 int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
                 float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows,
-                int tail_splits, int pair_rounds) {
+                int tail_splits, int pair_rounds, int pairs_end, int left_from, int left_rows, int left_splits) {
   // Work-group to (head, query block).  Ids are dealt round-robin to the 8 XCDs, so id % 8 names the XCD
   // and id / 8 the order inside it.
   //   mapping 2 (long sequences): every XCD takes its own eighth of the query blocks of head 0, then of
@@ -821,13 +804,30 @@ attn_work_group(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, 
   // Behind slot tail_from, where the query blocks left would not fill the XCD once more, tail_splits work-groups share each.
   int head, u, split = 0, splits = 1, slot = blockIdx.x / 8;
   const int xcd = blockIdx.x % 8;
-  const bool tail = TAIL && slot >= tail_from;
-  if (tail) {
+  const bool left = REST && TAIL && slot >= left_from;
+  bool tail = TAIL && slot >= tail_from;
+  if (tail && !left) {
     splits = tail_splits;
     split = (slot - tail_from) / tail_rows;
     slot -= split * tail_rows;
   }
-  if (mapping >= 2) {
+  if (left) {
+    const int row = (slot - left_from) % left_rows;
+    splits = left_splits;
+    split = (slot - left_from) / left_rows;
+    u = pair_at(xcd, pair_rounds * PAIR_WGS + row / 2, M_v, M, total_wg / M, head);
+    if (u < 0 || !pair_dense(kv_cnt, head, u, M_v, M)) return;
+    u += row & 1;
+    if (u >= M_v) return;
+    // their tickets and partial rows lie behind the tail's
+    tickets += 8 * tail_rows;
+    part += int64_t(8 * tail_rows * tail_splits) * (BM * (D + 4));
+    tail = true;
+    tail_from = 0;
+    tail_rows = left_rows;
+    slot = row;
+    pairs_end = 0;
+  } else if (mapping >= 2) {
     const int M_x = M - M_v, n_heads = total_wg / M;
     const int text_wgs = n_heads * M_x * text_splits, text_slots = (text_wgs + 7) / 8;
     if (slot < text_slots) {
@@ -855,7 +855,7 @@ attn_work_group(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, 
     u = M - 1 - logical % M;
   }
   attn_rows<D, BM, XLSE, KS, SLIM, TAIL, SRC, REST>(q, k, v, kv_idx, kv_cnt, K_max, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, total_wg,
-                                                    scale, clock_probe, part, tickets, text_splits, split_blocks, tail_from, tail_rows, pair_rounds,
+                                                    scale, clock_probe, part, tickets, text_splits, split_blocks, tail_from, tail_rows, pairs_end,
                                                     head, u, split, splits, xcd, slot, tail);
 }
 
@@ -870,7 +870,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                  int tail_splits) {
   attn_work_group<D, BM, XLSE, KS, SLIM, TAIL, SRC, false>(q, k, v, kv_idx, kv_cnt, K_max, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, total_wg,
                                                           wg_per_xcd, mapping, scale, clock_probe, part, tickets, text_splits, split_blocks, tail_from,
-                                                          tail_rows, tail_splits, 0);
+                                                          tail_rows, tail_splits, 0, 0, 0, 0, 0);
 }
 
 // The same behind attn_pairs_kernel (its look at the pairs costs a work-group 0.3 us on its way to the list).
@@ -881,10 +881,10 @@ attn_rest_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                  float* __restrict__ lse, const int32_t* __restrict__ row_index, int64_t N_src, int64_t N_pad, int64_t N_v, int n_text,
                  int M_v, int M, int total_wg, int wg_per_xcd, int mapping, float scale, unsigned long long* __restrict__ clock_probe,
                  float* __restrict__ part, int32_t* __restrict__ tickets, int text_splits, int split_blocks, int tail_from, int tail_rows,
-                 int tail_splits, int pair_rounds) {
+                 int tail_splits, int pair_rounds, int pairs_end, int left_from, int left_rows, int left_splits) {
   attn_work_group<D, BM, XLSE, 1, false, TAIL, SRC, true>(q, k, v, kv_idx, kv_cnt, K_max, o, lse, row_index, N_src, N_pad, N_v, n_text, M_v, M, total_wg,
                                                          wg_per_xcd, mapping, scale, clock_probe, part, tickets, text_splits, split_blocks, tail_from,
-                                                         tail_rows, tail_splits, pair_rounds);
+                                                         tail_rows, tail_splits, pair_rounds, pairs_end, left_from, left_rows, left_splits);
 }
 
 // Dense rows (the first quarter of a sampling run's steps): two neighbouring query blocks of 128 rows that keep every key block, in one
@@ -1059,21 +1059,23 @@ bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const v
 // = 64 eight waves would leave the CU two per SIMD instead of three (138 blocks x 48 heads, all kept, 3.74 -> 4.07).
 static int pair_rounds(const dfs_geom* g, const dfs_sizes& s) {
   if (g->d != 128 || g->B != 128 || !walked_together(s) || int64_t(g->heads) * s.M < 2048) return 0;
-  return (pair_text_slots(s.M_v, s.M, g->heads) + g->heads * pair_chunk(s.M_v)) / PAIR_WGS;
+  return pair_slots(s.M_v, s.M, g->heads) / PAIR_WGS;
 }
 
-// Behind the pairs: the query blocks that they leave over, the last of every XCD, shared as tail_split has it where there is room (dfs_forward).
-// Fewer than 64 an XCD, so that a whole one each would leave half of the chip's slots idle and more for as long as a dense row takes.  Measured (ms,
-// whole -> shared): 591 blocks, all kept, x 40 heads (16 left an XCD) 94.4 -> 93.6, x 8 19.28 -> 18.76; 60 of 591 kept x 40 10.67 -> 10.66, 929
-// blocks, 93 kept, x 24 16.26 -> 16.28, which two runs of one side differ by.
-static TailSplit pairs_tail(const dfs_geom* g, const dfs_sizes& s, int order, int text_slots, int pairs, const TextSplit& ts, size_t scratch_bytes) {
-  const TailSplit none = {0, 1, 1};
-  const int from = text_slots + 2 * (pairs * PAIR_WGS - pair_text_slots(s.M_v, s.M, g->heads)), rows = order - from;
-  if (scratch_bytes == 0 || from < text_slots || rows < 1 || rows > 32) return none;
+// The dense pairs behind the last full round: their blocks, `rows` an XCD, shared by `splits` work-groups each where there is room (dfs_forward) and
+// up to 32 are left, so that a whole one each would leave half of the XCD's slots and more idle for as long as a dense row takes.  Two
+// pieces are worth their merge here, other than in tail_split, which shares masked rows behind pairs as elsewhere.  Measured (ms, whole
+// -> shared; all kept): 591 blocks x 40 heads (16 rows left an XCD) 94.4 -> 93.6, x 8 19.28 -> 18.76, 520 x 5 (10) 9.58 -> 9.01; in two pieces
+// 591 x 16 (32) 37.97 -> 37.15, 600 x 40 (32) 96.4 -> 96.0, 929 + 2 x 24 (22) 139.3 -> 138.9.  Masked calls that find nothing to share: 520 x 5, 52 kept,
+// 1.020 -> 1.022, 929 + 2 x 24, 93 kept, 17.1 -> 17.1, two runs of one side as far apart.
+struct PairsLeft { int rows, splits; };
+static PairsLeft pairs_left(const dfs_geom* g, const dfs_sizes& s, int pairs, const TailSplit& tail, const TextSplit& ts, size_t scratch_bytes) {
+  const int rows = 2 * (pair_slots(s.M_v, s.M, g->heads) - pairs * PAIR_WGS);
+  if (scratch_bytes == 0 || rows == 0 || rows > 32) return {0, 1};
   const int splits = 64 / rows < 4 ? 64 / rows : 4;
-  const int64_t parts = 8 * int64_t(rows) * splits + (ts.splits > 1 ? int64_t(g->heads) * s.M_x * ts.splits : 0);
-  if (size_t(parts) * g->B * (g->d + 4) * sizeof(float) > scratch_bytes - align256(split_tickets(g, s) * sizeof(int32_t))) return none;
-  return {from, rows, splits};
+  const int64_t parts = 8 * (int64_t(rows) * splits + int64_t(tail.rows) * tail.splits) + (ts.splits > 1 ? int64_t(g->heads) * s.M_x * ts.splits : 0);
+  if (size_t(parts) * g->B * (g->d + 4) * sizeof(float) > scratch_bytes - align256(split_tickets(g, s) * sizeof(int32_t))) return {0, 1};
+  return {rows, splits};
 }
 
 int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void* q, const void* k, const void* v,
@@ -1095,8 +1097,10 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
     const bool one_buffer = g->d == 128 && g->B == 64 && slim(work_groups, ks, mapping);
     const int order = mapping >= 2 ? text_slots + per_xcd : per_xcd;     // slots of an XCD
     const int pairs = maybe_dense ? pair_rounds(g, s) : 0;
-    const TailSplit tail = lse || ks > 1 ? TailSplit{0, 1, 1} : pairs > 0 ? pairs_tail(g, s, order, text_slots, pairs, ts, scratch_bytes) : tail_split(g, s, K_max, order, mapping >= 2 ? text_slots : 0, ts, one_buffer, scratch_bytes);
-    if (!zeroed && (ts.splits > 1 || tail.splits > 1)) clear_tickets_kernel<<<1, 256, 0, st>>>(tickets, int(split_tickets(g, s)));
+    TailSplit tail = lse || ks > 1 ? TailSplit{0, 1, 1} : tail_split(g, s, K_max, order, mapping >= 2 ? text_slots : 0, ts, one_buffer, scratch_bytes);
+    const PairsLeft left = lse || pairs == 0 ? PairsLeft{0, 1} : pairs_left(g, s, pairs, tail, ts, scratch_bytes);
+    if (left.rows > 0 && tail.splits == 1) tail = {order, 0, 1};         // nothing but what the pairs leave is shared
+    if (!zeroed && (ts.splits > 1 || tail.splits > 1 || left.splits > 1)) clear_tickets_kernel<<<1, 256, 0, st>>>(tickets, int(split_tickets(g, s)));
     if (pairs > 0) {
 #define ATTN_PAIRS(XX, SRC)                                                                                                            \
   attn_pairs_kernel<128, XX, SRC><<<8 * PAIR_WGS, 512, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),            \
@@ -1107,7 +1111,8 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
       else ATTN_PAIRS(false, false);
 #undef ATTN_PAIRS
     }
-    dim3 grid(unsigned(8 * (order + tail.rows * (tail.splits - 1))));
+    const int walked = order + tail.rows * (tail.splits - 1);
+    dim3 grid(unsigned(8 * (walked + left.rows * left.splits)));
 #define ATTN_X(DD, BB, XX, KS, SLIM, TAIL, SRC)                                                                                            \
   attn_bf16_kernel<DD, BB, XX, KS, SLIM, TAIL, SRC><<<grid, BB * 2 * KS, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), \
                                                         static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                 \
@@ -1119,7 +1124,8 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
                                                                   static_cast<const uint16_t*>(v), kv_idx, kv_cnt, K_max,                         \
                                                                   static_cast<uint16_t*>(o), lse, row_index, s.N, s.N_pad, s.N_v,                 \
                                                                   g->n_text, s.M_v, s.M, int(total), per_xcd, mapping, scale, g_clock_probe,      \
-                                                                  part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits, pairs)
+                                                                  part, tickets, ts.splits, ts.blocks, tail.from, tail.rows, tail.splits, pairs,     \
+                                                                  left.rows > 0 ? pair_slots(s.M_v, s.M, g->heads) : pairs * PAIR_WGS, walked, left.rows, left.splits)
 #define ATTN_LSE(DD, BB, KS, SLIM) do { if (lse) ATTN_X(DD, BB, true, KS, SLIM, false, false); else ATTN_X(DD, BB, false, KS, SLIM, false, false); } while (0)
 #define ATTN_WHOLE(DD, BB, KS, SLIM) do { if (kv_src) ATTN_X(DD, BB, false, KS, SLIM, false, true); else ATTN_LSE(DD, BB, KS, SLIM); } while (0)
 #define ATTN_TAIL(DD, BB, SLIM) do { if (kv_src) ATTN_X(DD, BB, false, 1, SLIM, true, true); else ATTN_X(DD, BB, false, 1, SLIM, true, false); } while (0)
@@ -1127,7 +1133,7 @@ int run_sparse_attn(const dfs_geom* g, const dfs_sizes& s, int dtype, const void
 #define ATTN_KS(DD, BB) do { if (ks == 2) ATTN_WHOLE(DD, BB, 2, false); else ATTN_1(DD, BB, false); } while (0)
     if (pairs > 0) {
       if (lse) ATTN_REST(true, false, false);
-      else if (tail.splits > 1) { if (kv_src) ATTN_REST(false, true, true); else ATTN_REST(false, true, false); }
+      else if (tail.splits > 1 || left.splits > 1) { if (kv_src) ATTN_REST(false, true, true); else ATTN_REST(false, true, false); }
       else if (kv_src) ATTN_REST(false, false, true);
       else ATTN_REST(false, false, false);
     }
