@@ -605,7 +605,6 @@ static size_t fs_lds(int M_v) { return size_t(FS_ROWS) * (256 + fs_stride(M_v)) 
 // calls that want scores (`score`) and those that want lists (`kv_idx`), and both decide alike.  What bounds it is latency: a
 // tile's rows, its product chain, three barriers, the selection; it saves a launch and the way of T through memory.  256 fp32
 // tokens x 2 heads 18.4 -> 16.6 us a refresh, 2 565 + 77 tokens x 12 heads, blocks of 64, 39.1 -> 35.5 (both sides in turn).
-constexpr int ss_most(int r) { return r >= 4 ? 320 : r == 2 ? 64 : 16; }          // key blocks, see score_small
 template <int D, int R>
 __global__ void __launch_bounds__(SS_T) score_small_kernel(const uint16_t* __restrict__ q_hat, const uint16_t* __restrict__ k_hat,
                                                            const float* __restrict__ q_down, const float* __restrict__ k_down,
@@ -654,7 +653,7 @@ __global__ void __launch_bounds__(SS_T) score_small_kernel(const uint16_t* __res
     } else if (k_head && u == 0 && lane == 0) {
       k_head[head] = k;
     }
-    select_row<ss_most(R)>(row, hist, M_v, M_x, k, mrow, kv_idx + out * K_max, kv_cnt + out);
+    select_row<ss_columns(R, D)>(row, hist, M_v, M_x, k, mrow, kv_idx + out * K_max, kv_cnt + out);
   }
 }
 static size_t ss_lds(int M_v) { return (size_t(SS_WAVES) * 256 + size_t(M_v) * SS_STRIDE) * sizeof(uint32_t); }
@@ -665,15 +664,7 @@ static size_t ss_lds(int M_v) { return (size_t(SS_WAVES) * 256 + size_t(M_v) * S
 //   R = 4, d = 64: 24 x 8 1.13, 138 x 48 1.00, 200 x 8 1.03, 313 x 1 1.08, 313 x 40 1.00; d = 128: 24 x 8 1.10, 138 x 40 1.00, 313 x 8 1.01, 313 x 40 1.00
 //   R = 2, d = 64: 8 x 8 1.12, 48 x 8 1.03, 72 x 8 1.01, 138 x 1 0.96; d = 128: 24 x 8 1.04, 48 x 8 1.00, 72 x 8 0.99
 //   R = 1: 8 x 8 1.04, 16 x 8 0.99 (d = 64) and 1.02 (128), 24 x 8 0.95 and 0.97, 138 x 1 0.78
-bool score_small(const dfs_geom* g, const dfs_sizes& s) {
-  if (s.M_v > ss_most(s.r)) return false;
-  switch (s.r) {
-    case 8: return s.M_v <= 256;
-    case 4: return s.M_v <= 320;                           // 52 KB of the 64 KB of LDS
-    case 2: return s.M_v * g->d <= 4096;
-    default: return s.M_v <= 12;
-  }
-}
+bool score_small(const dfs_geom* g, const dfs_sizes& s) { return s.M_v <= ss_columns(s.r, g->d); }   // at 320, R = 4, 52 KB of the 64 KB of LDS
 
 // Workspace: Q_hat, K_hat (two fp16 planes each, followed by the inverse scales of their row groups),
 // T [heads][t_rows][t_cols] fp32 (padded, see t_cols), row log-sum-exp [heads][KSPLIT_MAX][M_s] fp32.

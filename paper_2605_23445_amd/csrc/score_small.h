@@ -120,6 +120,9 @@ template <int D> struct MemoryOperands {
   }
 };
 
+// Key blocks up to which one kernel scores a head behind the pooling, see score_small.
+__host__ __device__ constexpr int ss_columns(int r, int d) { return r == 8 ? 256 : r == 4 ? 320 : r == 2 ? 4096 / d : 12; }
+
 // T of the query sub-blocks i0 .. i0 + 31 of a head, [M_v][SS_STRIDE] in LDS, and their references and inverse sums: the waves take key
 // tiles in turn.  Ends behind a barrier.
 constexpr int SS_T = 512, SS_WAVES = SS_T / 64, SS_STRIDE = 33;
@@ -138,8 +141,10 @@ __device__ __forceinline__ void small_scores(const Operands& x, float* s_t, floa
     for (int kk = 0; kk < KS; ++kk) bq[p][kk] = x.q(p, 2 * kk + half, n);
   float m_row = LSE_START, z_row = 0.f;
   // At d = 64 a tile's operands are requested as soon as the matrix instructions have taken those of the tile before, in front of its
-  // exponentials; at d = 128 the registers that this takes would leave a CU one work-group instead of two.
-  constexpr bool AHEAD = D == 64;
+  // exponentials; at d = 128 the registers that this takes would leave a CU one work-group instead of two.  Rows of R <= 2 are at most a
+  // tile for each wave: without room for a next one R = 1 takes 88 registers instead of 139, two work-groups a CU instead of one (us a launch, 12
+  // blocks x 1 024 heads 20.8 -> 14.7, x 512 10.4 -> 7.7, x 200 5.9 -> 6.1; with no operand ahead of its use 17.5, 9.1 and 7.5).
+  constexpr bool AHEAD = D == 64, ONE = AHEAD && ss_columns(R, D) * R <= 32 * SS_WAVES;
   f16x8 ak[2][KS];
   float k_dn[4];
   auto ask = [&](int t) __attribute__((always_inline)) {
@@ -151,6 +156,7 @@ __device__ __forceinline__ void small_scores(const Operands& x, float* s_t, floa
     for (int gq = 0; gq < 4; ++gq) k_dn[gq] = x.k_inverse(8 * t + 2 * gq + half);
   };
   if (AHEAD && wave * 32 < n_live) ask(wave);
+  if (ONE) __builtin_amdgcn_sched_barrier(0);          // all of them, not in turn with the products
   for (int t = wave; t * 32 < n_live; t += SS_WAVES) {
     if (!AHEAD) ask(t);
     float dn[4];
@@ -167,7 +173,7 @@ __device__ __forceinline__ void small_scores(const Operands& x, float* s_t, floa
       b = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[0][kk], bq[1][kk], b, 0, 0, 0);
       a = __builtin_amdgcn_mfma_f32_32x32x16_f16(ak[1][kk], bq[0][kk], a, 0, 0, 0);
     }
-    if (AHEAD) {
+    if (AHEAD && !ONE) {
       if ((t + SS_WAVES) * 32 < n_live) ask(t + SS_WAVES);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -200,6 +206,7 @@ __device__ __forceinline__ void small_scores(const Operands& x, float* s_t, floa
       const int first = gi * G, v = (t * 32 + 8 * (first / 4) + (R == 8 ? 0 : 4 * half) + first % 4) / R;
       if (v < M_v) s_t[v * SS_STRIDE + n] = m_new + __builtin_amdgcn_logf(sg);  // R == 8: both halves store the same
     }
+    if (ONE) break;
   }
   const float m2 = __shfl_xor(m_row, 32, 64), z2 = __shfl_xor(z_row, 32, 64);
   lse_merge(m_row, z_row, m2, z2);

@@ -134,8 +134,8 @@ class _KernelNodeParams(C.Structure):
                 ("lds", C.c_uint)]
 
 
-def kernels_of(call) -> list[str]:
-    """The library's kernels that `call` launches, in order, as "name" or "name<template arguments>" (captured, not run)."""
+def _launches_of(call):
+    """What `call` launches of the library's, in order (captured, not run): "name" or "name<template arguments>", the node's parameters and the runtime."""
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
         call()
@@ -146,7 +146,6 @@ def kernels_of(call) -> list[str]:
     assert hip.hipGraphGetNodes(raw, None, C.byref(n)) == 0
     nodes = (C.c_void_p * n.value)()
     assert hip.hipGraphGetNodes(raw, nodes, C.byref(n)) == 0
-    names = []
     for node in nodes:
         kind, p = C.c_int(-1), _KernelNodeParams()
         assert hip.hipGraphNodeGetType(C.c_void_p(node), C.byref(kind)) == 0
@@ -157,5 +156,19 @@ def kernels_of(call) -> list[str]:
         if own is None:                                    # torch's
             continue
         head, args = own.groups()
-        names.append(head + (f"<{', '.join(re.findall(r'L[a-z]([0-9]+)E', args))}>" if args else ""))
-    return names
+        yield head + (f"<{', '.join(re.findall(r'L[a-z]([0-9]+)E', args))}>" if args else ""), p, hip
+
+
+def kernels_of(call) -> list[str]:
+    """The library's kernels that `call` launches, in order."""
+    return [name for name, _, _ in _launches_of(call)]
+
+
+def resident_of(call) -> dict[str, int]:
+    """The library's kernels that `call` launches and how many of their work-groups a CU holds."""
+    found = {}
+    for name, p, hip in _launches_of(call):
+        n = C.c_int(-1)
+        assert hip.hipOccupancyMaxActiveBlocksPerMultiprocessor(C.byref(n), C.c_void_p(p.func), p.block[0] * p.block[1] * p.block[2], C.c_size_t(p.lds)) == 0
+        found[name] = n.value
+    return found

@@ -61,3 +61,14 @@ def test_scores_are_as_accurate_as_their_parts(d, B, r, M_v):
     err = float((G.gpu_score(g, P.DFS_BF16, q, k).double() - want).norm() / want.norm())
     print(f"d={d} r={r} M_v={M_v}: {err:.2e}", flush=True)
     assert err <= 2.0 ** -22
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("r", [1, 2, 4, 8])
+def test_two_work_groups_a_cu(d, r):
+    g = P.Geom(1, 12, 64, 0, 2, d, 64, 64 // r)
+    s = P.dfs_geom_sizes(g)
+    q = torch.zeros(2, s.N_pad, d, dtype=torch.bfloat16, device="cuda")
+    score = torch.empty(2, s.M_v, s.M_v, device="cuda")
+    ws = G.ws_tensor(P.dfs_workspace_bytes(g, P.DFS_WS_BLOCK_SCORE))
+    assert G.resident_of(lambda: P.dfs_block_score(g, P.DFS_BF16, q, q, score, ws))[f"score_small_kernel<{d}, {r}>"] >= 2
