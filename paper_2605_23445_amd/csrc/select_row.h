@@ -143,6 +143,9 @@ __device__ __forceinline__ void select_in_registers(Keys keys, int M_v, int k, u
 // reaches what is still wanted; counts are integers, so it is the same key.
 // With the histogram for rows of more than 64 columns and a rank of every column below (us a launch, under the profiler): 41 columns x 12 heads with
 // the scoring 7.6 -> 6.2, 138 x 48 35.0 -> 31.2 (d = 64, with the operands ahead), 591 x 40 with the fold 78 -> 72.
+// Where the lines lie (histogram -> registers, with the fold, x 24 heads): seven keys a lane 330 columns 22.1 -> 20.6, 360 28.8 -> 25.5, 448 36.3
+// -> 31.9 (ten: 24.4, 29.4, 35.8, so up to 360 slower than the histogram); ten 470 41.3 -> 39.3, 576 41.9 -> 37.6, 640 48.3 -> 42.6.  Fifteen would lose
+// again at 704 (x 40 heads 106 -> 108, x 8 31 -> 33) and win at 929 (97 -> 89 in 18 ms).
 // MOST: rows have no more columns than that (the ways for longer ones are left out).
 template <int MOST = 1 << 30, class Keys>
 __device__ __forceinline__ void select_row(Keys keys, uint32_t* hist /*[256]*/, int M_v, int M_x, int k, uint8_t* mrow,
@@ -173,6 +176,7 @@ __device__ __forceinline__ void select_row(Keys keys, uint32_t* hist /*[256]*/, 
   if (MOST <= 64 || M_v <= 64) return select_in_registers<1>(keys, M_v, k, mrow, idx);
   if (M_v <= 192) return select_in_registers<3>(keys, M_v, k, mrow, idx);
   if (MOST <= 320 || M_v <= 320) return select_in_registers<5>(keys, M_v, k, mrow, idx);
+  if (M_v <= 448) return select_in_registers<7>(keys, M_v, k, mrow, idx);
   if (M_v <= 640) return select_in_registers<10>(keys, M_v, k, mrow, idx);
   uint32_t T = 0, fixed = 0, want = uint32_t(k);      // want: rank of the key looked for among the keys matching T on `fixed`
   for (int shift = 24; shift >= 0; shift -= 8) {

@@ -10,7 +10,7 @@ P = pytest.importorskip("paper_2605_23445_amd")
 from tests import gpu_util as G  # noqa: E402
 
 
-@pytest.mark.parametrize("M_v", [1, 3, 16, 17, 63, 64, 65, 128, 192, 193, 320, 321, 640, 641, 900])
+@pytest.mark.parametrize("M_v", [1, 3, 16, 17, 63, 64, 65, 128, 192, 193, 320, 321, 448, 449, 640, 641, 900])
 def test_rows_of_every_length(M_v):
     H, W = next((n // w, w) for n in range(M_v * 64, (M_v - 1) * 64, -1) for w in range(512, 0, -1) if n % w == 0 and n // w <= 512)
     g = P.Geom(1, H, W, 70, 2, 64, 64, 16)
