@@ -595,7 +595,7 @@ __global__ void __launch_bounds__(FS_T) fold_select_kernel(const float* __restri
   } else if (k_head && uw == 0 && (threadIdx.x & 63) == 0) {
     k_head[head] = k;
   }
-  select_row(row, hist, M_v, M_x, k, mrow, kv_idx + out * K_max, kv_cnt + out);
+  select_row<1 << 30, ss_columns(R, 128)>(row, hist, M_v, M_x, k, mrow, kv_idx + out * K_max, kv_cnt + out);     // shorter rows are score_small_kernel's
 }
 static size_t fs_lds(int M_v) { return size_t(FS_ROWS) * (256 + fs_stride(M_v)) * sizeof(uint32_t); }
 

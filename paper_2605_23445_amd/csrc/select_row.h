@@ -146,8 +146,8 @@ __device__ __forceinline__ void select_in_registers(Keys keys, int M_v, int k, u
 // Where the lines lie (histogram -> registers, with the fold, x 24 heads): seven keys a lane 330 columns 22.1 -> 20.6, 360 28.8 -> 25.5, 448 36.3
 // -> 31.9 (ten: 24.4, 29.4, 35.8, so up to 360 slower than the histogram); ten 470 41.3 -> 39.3, 576 41.9 -> 37.6, 640 48.3 -> 42.6.  Fifteen would lose
 // again at 704 (x 40 heads 106 -> 108, x 8 31 -> 33) and win at 929 (97 -> 89 in 18 ms).
-// MOST: rows have no more columns than that (the ways for longer ones are left out).
-template <int MOST = 1 << 30, class Keys>
+// MOST: rows have no more columns than that, LEAST: they have more (the ways for longer and shorter ones are left out).
+template <int MOST = 1 << 30, int LEAST = 0, class Keys>
 __device__ __forceinline__ void select_row(Keys keys, uint32_t* hist /*[256]*/, int M_v, int M_x, int k, uint8_t* mrow,
                                            int32_t* idx, int32_t* cnt) {
   const int lane = threadIdx.x & 63;
@@ -156,7 +156,7 @@ __device__ __forceinline__ void select_row(Keys keys, uint32_t* hist /*[256]*/, 
     if (mrow) mrow[M_v + j] = 1;
   }
   if (lane == 0) *cnt = k + M_x;
-  if (MOST <= 16 || M_v <= 16) {                     // ranked outright, each lane counting the columns ahead of its own
+  if (LEAST < 16 && (MOST <= 16 || M_v <= 16)) {                   // ranked outright, each lane counting the columns ahead of its own
     const uint32_t key = lane < M_v ? keys[lane] : 0u;
     int ahead = 0;
     for (int i0 = 0; i0 < M_v; i0 += 4) {
@@ -173,9 +173,9 @@ __device__ __forceinline__ void select_row(Keys keys, uint32_t* hist /*[256]*/, 
     if (mrow && lane < M_v) mrow[lane] = keep ? 1 : 0;
     return;
   }
-  if (MOST <= 64 || M_v <= 64) return select_in_registers<1>(keys, M_v, k, mrow, idx);
-  if (M_v <= 192) return select_in_registers<3>(keys, M_v, k, mrow, idx);
-  if (MOST <= 320 || M_v <= 320) return select_in_registers<5>(keys, M_v, k, mrow, idx);
+  if (LEAST < 64 && (MOST <= 64 || M_v <= 64)) return select_in_registers<1>(keys, M_v, k, mrow, idx);
+  if (LEAST < 192 && M_v <= 192) return select_in_registers<3>(keys, M_v, k, mrow, idx);
+  if (LEAST < 320 && (MOST <= 320 || M_v <= 320)) return select_in_registers<5>(keys, M_v, k, mrow, idx);
   if (M_v <= 448) return select_in_registers<7>(keys, M_v, k, mrow, idx);
   if (M_v <= 640) return select_in_registers<10>(keys, M_v, k, mrow, idx);
   uint32_t T = 0, fixed = 0, want = uint32_t(k);      // want: rank of the key looked for among the keys matching T on `fixed`
