@@ -1,5 +1,5 @@
 """Text rows of problems whose work-groups all start at once, dealt in pieces of five eighths of a video row: lists at which the pieces are the
-least, a little more, and leave a last one of a single block; against float64 on the same tensors."""
+least, a little more, and leave a last one of a single block, by the number of work-groups; against float64 on the same tensors."""
 import pytest
 import torch
 
@@ -9,14 +9,19 @@ P = pytest.importorskip("paper_2605_23445_amd")
 from tests import gpu_util as G  # noqa: E402
 
 
-@pytest.mark.parametrize("d,B,H,W,n_text,heads,kept", [
-    (64, 64, 32, 80, 77, 3, 13), (64, 64, 45, 57, 1, 20, 15), (128, 64, 32, 80, 130, 2, 17), (64, 128, 64, 80, 200, 3, 14), (128, 128, 64, 81, 128, 3, 18)])
-def test_text_rows_in_short_pieces(d, B, H, W, n_text, heads, kept):
+@pytest.mark.parametrize("d,B,H,W,n_text,heads,kept,piece,last", [
+    (64, 64, 32, 80, 77, 3, 10, 8, 2),                     # five eighths of 12 blocks are 7: the least piece instead
+    (64, 64, 32, 80, 77, 3, 11, 8, 2), (64, 64, 32, 80, 77, 3, 13, 9, 6), (64, 64, 45, 57, 193, 20, 14, 11, 1), (64, 64, 45, 57, 1, 20, 15, 10, 2),
+    (128, 64, 32, 80, 130, 2, 17, 12, 7), (64, 128, 64, 80, 200, 3, 14, 10, 2), (128, 128, 64, 81, 128, 3, 18, 11, 9), (128, 128, 64, 81, 400, 3, 14, 11, 1)])
+def test_text_rows_in_short_pieces(d, B, H, W, n_text, heads, kept, piece, last):
     g = P.Geom(1, H, W, n_text, heads, d, B, B // 4)
     s = P.dfs_geom_sizes(g)
     sparsity = 1 - kept / s.M_v
     K_max = kept + s.M_x
-    assert P.dfs_keep_count(sparsity, s.M_v) == kept and 2 * K_max <= s.M and s.M >= 16
+    assert P.dfs_keep_count(sparsity, s.M_v) == kept and 2 * K_max <= s.M and s.M >= 16 and heads * s.M <= (512 if B == 128 else 1024)
+    pieces = -(-s.M // piece)
+    assert piece == max(8, K_max * 5 // 8) and last == s.M - (pieces - 1) * piece
+    probe = torch.zeros(3, dtype=torch.int64, device="cuda")
     gen = torch.Generator(device="cuda")
     gen.manual_seed(d + kept)
     q, k, v = (torch.randn(heads, s.N, d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
@@ -27,7 +32,13 @@ def test_text_rows_in_short_pieces(d, B, H, W, n_text, heads, kept):
     outs = []
     for refresh in (True, False, False):
         out = torch.full_like(q, float("nan"))
-        P.dfs_forward(g, P.DFS_BF16, q, k, v, perm_pad, inv, refresh, P.DFS_SELECT_TOPK, sparsity, 0.0, st, d ** -0.5, out, ws)
+        P.dfs_attn_clock_probe(probe.zero_())
+        try:
+            P.dfs_forward(g, P.DFS_BF16, q, k, v, perm_pad, inv, refresh, P.DFS_SELECT_TOPK, sparsity, 0.0, st, d ** -0.5, out, ws)
+            torch.cuda.synchronize()
+        finally:
+            P.dfs_attn_clock_probe(None)
+        assert int(probe[2]) == heads * (s.M_v + s.M_x * pieces)
         outs.append(out)
     assert torch.isfinite(outs[0].float()).all() and all(torch.equal(outs[0], o) for o in outs[1:])
     qf, kf, vf = (x.double().cpu() for x in (q[:, s.N_v:], k, v))
