@@ -104,7 +104,7 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
   static_assert(!SLIM || KS == 1, "the merge of wave groups wants all four buffers");
   static_assert(!TAIL || (KS == 1 && !XLSE), "see run_sparse_attn");
   static_assert(!SRC || !XLSE, "see run_sparse_attn");
-  constexpr bool PAIR = BM > 128;
+  constexpr bool PAIR = BM > 128, END_WAVE = XLSE || (D == 128 && BM == 128);
   static_assert(!PAIR || (KS == 1 && !SLIM && !TAIL), "see attn_pairs_kernel");
   __shared__ __attribute__((aligned(16))) uint16_t tiles[KS * (SLIM ? 2 : 4) * TILE];
   constexpr int K0 = 0, K1 = SLIM ? 0 : 2 * TILE, V0 = SLIM ? 2 * TILE : 4 * TILE, V1 = SLIM ? 2 * TILE : 6 * TILE;
@@ -666,7 +666,10 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
     };
     static_assert(TILE * 2 == (D / 32) * 16 * 64 * 4, "one tile buffer holds the accumulators of one wave");
     if (rounds == 0) {
-      if (grp > 0) __builtin_amdgcn_endpgm();
+      if (grp > 0) {
+        if constexpr (END_WAVE) __builtin_amdgcn_endpgm();
+        return;
+      }
     } else {
       if (n_tiles == 0) m_run = -INFINITY;
       __syncthreads();                               // every wave is done with the tiles
@@ -681,9 +684,14 @@ attn_rows(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const 
         s_part[grp][wave][2][lane] = x_run;
       }
       __syncthreads();
-      // The end of the wave itself: as a return, a way to the end of the kernel, it kept the accumulators of the first group in scratch (187 registers
-      // spilled with log-sum-exp, d = 128, blocks of 128, instead of 15; recall's calls on one head of 44 blocks 174 us instead of 153).
-      if (grp > 0) __builtin_amdgcn_endpgm();
+      // With END_WAVE the end of the wave itself: as a return, a way to the end of the kernel, it kept the accumulators of the first group in scratch
+      // (187 registers spilled with log-sum-exp, d = 128, blocks of 128, instead of 15; recall's calls on one head of 44 blocks 174 us instead of 153).
+      // Where none are spilled the return is the faster one (us a reuse step of 2 048 tokens: x 8 heads, d = 128, blocks of 64, 16.23 -> 15.97, x 3 20.65
+      // -> 20.42, x 8, d = 64, 9.20 -> 9.12).
+      if (grp > 0) {
+        if constexpr (END_WAVE) __builtin_amdgcn_endpgm();
+        return;
+      }
       float m_all = m_run;
 #pragma unroll
       for (int g = 1; g < KS; ++g) m_all = fmaxf(m_all, s_part[g][wave][0][lane]);
