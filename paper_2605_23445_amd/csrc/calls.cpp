@@ -1,9 +1,9 @@
 // The calls of a small problem from Python without the cost of marshalling them in Python: dfs_forward, the token orders and the staged calls
 // of a quality check take their arguments straight from the objects.  A launch costs the host some 3 us and its kernel often less, so what bounds
 // such calls is what Python does between two of them: some fifty attribute lookups of tensors and a ctypes call.  Measured (us, in Python ->
-// here).  The host's time of a call in a burst of eight: reuse step (one launch) 10.0 -> 4.9, refresh step of 256 fp32 tokens
-// (three) 17.2 -> 13.0, token order 6.5 -> 4.1.  A call among others: token order of 75 600 or 64 tokens 6.2 -> 3.6, reuse step of
-// 512 tokens x 8 heads, d = 64, 9.4 -> 8.7, of which its kernel takes 8.5; the refresh step stays at 16.5, which its kernels take.
+// here).  The host's time of a call in a burst of eight: refresh and reuse step of 256 fp32 tokens (one launch each) 9.7 -> 4.7 and 9.9 -> 5.0, token
+// order 6.4 -> 3.9.  A call among others: token order of 75 600 or 64 tokens 6.2 -> 3.6, reuse step of 512 tokens x 8 heads, d = 64,
+// 9.4 -> 7.3, of 256 fp32 tokens 9.2 -> 8.7; the refresh step of these stays at 12.4, which its kernel takes.
 // A quality check in staged calls (nine of them and two of torch), 675 tokens x 2 heads, d = 64, 73 -> 53, 1 575 x 2 73 -> 62; larger ones
 // take what their kernels take (2 625 x 4, d = 128, 111).
 //

@@ -4,7 +4,7 @@
 // its own query block, scores and selects that block's row, and attends.  What it repeats of other work-groups' work (the pooled
 // keys, once per work-group; the row, once per 32 query rows of a block) costs less than the two launches as long as a head is small; see
 // forward_small_fits.  The same sums in the same order as the kernels of their own, so the same lists and the same output, bit for bit.
-// 256 tokens x 2 heads, d = 64: 16.7 -> 12.75 us.
+// 256 tokens x 2 heads, d = 64: 16.4 -> 12.4 us.
 #include "attn_f32.h"
 #include "score_small.h"
 #include "select_row.h"
@@ -197,9 +197,11 @@ __global__ void __launch_bounds__(SS_T) forward_small_kernel(const float* __rest
 }
 
 // Small enough that what every work-group repeats costs less than the launches do, in one round of work-groups.  Measured (us, three kernels
-// -> one): d = 64, 256 tokens x 2 heads 16.7 -> 12.75, x 8 17.5 -> 12.8, 512 + 40 x 1 26.7 -> 17.9, 512 x 8 22.0 -> 17.1, with 64 sub-blocks 21.1 -> 17.7,
-// 1 024 x 1 22.8 -> 21.3, x 4, blocks of 128, 24.2 -> 21.8, x 1 with 128 sub-blocks 22.6 -> 24.6; d = 128, 256 x 8 24.8 -> 21.3, 512 x 8 34.5 ->
-// 32.2.  The output must not lie over the queries either, whose neighbours' rows a work-group pools where a block has fewer than four sub-blocks.
+// -> one, half the blocks kept; in brackets a first pass over new inputs, waited for, medians of 180): d = 64, 256 tokens x 2 heads 16.4 -> 12.4 (32.5 ->
+// 27.7), x 8 18.0 -> 12.6 (34 -> 28.5), 512 + 40 x 1 26.5 -> 18.9 (42 -> 34), 512 x 8 with 64 sub-blocks 21.1 -> 19.4 (38 -> 34), 1 024 x 1 25.2 -> 24.8 (40.7 ->
+// 40.1), x 4, blocks of 128, 26.9 -> 26.6 (43.4 -> 42.3), x 1 with 128 sub-blocks 22.6 -> 24.6; d = 128, 256 x 8 25.2 -> 22.5 (41.2 -> 38.3), 512 x 8
+// 31.1 -> 30.7 (48 -> 48), x 1 29.2 -> 28.9 (44.0 -> 45.8).  The output must not lie over the queries either, whose neighbours' rows a work-group
+// pools where a block has fewer than four sub-blocks.
 bool forward_small_fits(const dfs_geom* g, const dfs_sizes& s, int dtype, int mode, const void* q, const void* k, const void* v, const void* o) {
   return dtype == DFS_F32 && mode != DFS_SELECT_MASS_HEAD && s.N_v * g->d <= FS_NUMEL && s.M_s <= FS_SUBS && s.N_pad <= FS_ROWS_MAX && score_small(g, s) &&
          int64_t(g->heads) * s.M * (g->B / 32) <= 256 && apart(g, s, dtype, q, o) && apart(g, s, dtype, k, o) && apart(g, s, dtype, v, o);
