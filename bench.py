@@ -36,19 +36,19 @@ PEAK_HBM_GBS = 8000.0
 MEASURED_MFMA_TFLOPS = 2141.0
 MEASURED_COPY_GBS = 5830.0
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "wan90_attention_counters.txt")
-ATTN_SOURCE = os.path.join(ROOT, "paper_2605_23445_amd", "csrc", "attn.hip")
+ATTN_SOURCES = [os.path.join(ROOT, "paper_2605_23445_amd", "csrc", name) for name in ("attn.hip", "attn_pairs.h")]
 
 
 def recorded_traffic(workload, sparsity):
     """HBM-side bytes of the attention kernel per launch as recorded under profiles/ (rocprofv3 --pmc FETCH_SIZE
     and WRITE_SIZE, already scaled by the copy calibration).  The record names the workload it was taken on and
-    the SHA-256 of the kernel source it was taken with; it is used only if both match what runs now, so a
+    the SHA-256 of the kernel's sources it was taken with; it is used only if both match what runs now, so a
     changed kernel reports no traffic instead of a stale one."""
     import hashlib
     import re
     try:
         text = open(TRAFFIC_PROFILE).read()
-        digest = hashlib.sha256(open(ATTN_SOURCE, "rb").read()).hexdigest()
+        digest = hashlib.sha256(b"".join(open(p, "rb").read() for p in ATTN_SOURCES)).hexdigest()
     except OSError:
         return None, "no traffic record under profiles/"
     m = re.search(r"^record: workload=(\S+) sparsity=(\S+) attn_source_sha256=(\S+) fetch_bytes=(\S+) write_bytes=(\S+)", text, re.M)

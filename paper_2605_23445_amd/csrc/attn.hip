@@ -977,11 +977,34 @@ static int key_split(int d, int B, int64_t work_groups, int K_max) {
 // 1 049 -> 1 052, 14 184 8 104 -> 8 412.
 static bool slim(int64_t work_groups, int ks, int mapping) { return ks == 1 && work_groups > 512 && mapping != 2; }
 
+// Whether all XCDs walk one head together (kernel's mapping 2), an eighth of its video blocks each: once that fills the XCD's 64
+// work-group slots (measured +3..6 % on the 75 600- and 118 800-token shapes, -4 % on the 17 550-token one, which stays on mapping 1).
+static int xcd_blocks(const dfs_sizes& s) { return (s.M_v + 7) / 8; }
+static bool walked_together(const dfs_sizes& s) { return xcd_blocks(s) >= 64; }
+
+// Text rows in pieces of `blocks` key blocks, as long as a video row, or of five eighths of that: the merge of a text row, some 4 us, comes behind the
+// last video row where all work-groups start at once.  For that all of them must, in the form that they had (key_split, slim): in blocks of 128 up to 512, no more
+// of them on a CU than before; in blocks of 64, which lose from some 800 on, up to 768, at most 64 more than before, and a piece must lose three blocks and more
+// for each that a row gains, which the merge reads.  Measured (us a reuse step, long -> short): 2 560 + 30 x 4, 20 kept, d = 64, blocks of 64, 17.6 -> 15.5,
+// 2 560 + 77 x 8, 21 kept, d = 128 38.6 -> 32.1, 5 120 + 259 x 2, 16 kept, blocks of 128, d = 64 29.1 -> 25.0, d = 128 43.6 -> 36.3; not so, blocks of 64, d = 64:
+// 960 + 259 x 20, 10 -> 8 blocks a piece, 500 -> 600 work-groups, 17.4 -> 21.1 (another form), 1 344 + 259 x 15, 11 -> 8, 540 -> 615, 20.5 -> 21.6, 2 624 + 259 x 12, 12 -> 8,
+// 732 -> 852, 22.7 -> 25.0, 4 480 + 30 x 2, 12 -> 8, six -> nine pieces, 16.8 -> 17.3; blocks of 128, d = 128: 3 712 + 256 x 7, 15 -> 9, 245 -> 259, 45.2 -> 50.4.  592
+// shapes in all: the 440 taken 0.98 to 1.21 times as fast, 1.077 in the mean; the others would be 0.82 to 1.11 times, 0.996.
+static int shorter_pieces(const dfs_geom* g, const dfs_sizes& s, int K_max, int blocks) {
+  const int shorter = blocks * 5 / 8 < 8 ? 8 : blocks * 5 / 8, pieces = (s.M + blocks - 1) / blocks, more = (s.M + shorter - 1) / shorter;
+  const auto groups = [&](int n) { return int64_t(g->heads) * (s.M_v + int64_t(s.M_x) * n); };
+  const auto form = [&](int n) {
+    const int ks = key_split(g->d, g->B, groups(n), K_max);
+    return 2 * ks + (g->d == 128 && g->B == 64 && slim(groups(n), ks, walked_together(s) ? 2 : 3) ? 1 : 0);
+  };
+  const int64_t few = groups(pieces), many = groups(more);
+  if (form(pieces) != form(more)) return blocks;
+  if (g->B == 128) return many <= 512 && (few + 255) / 256 == (many + 255) / 256 ? shorter : blocks;
+  return many <= 768 && many - few <= 64 && blocks - shorter >= 3 * (more - pieces) ? shorter : blocks;
+}
+
 // Work-groups per text block, and the key blocks each takes: about as many as a video row keeps (an eighth of all where
-// K_max does not tell), at least eight; five eighths of that where all start at once, because the merge of a text row, some 4 us,
-// would come behind the last video row (us a call, pieces as long as a video row -> five eighths of it: 2 565 + 77 x 12, d = 64, blocks of 64,
-// 15 kept, a refresh 35.4 -> 33.9, x 4, 19 kept, a reuse step 18.6 -> 15.8, 6 300 + 300 x 3, 18 kept, d = 64 43.2 -> 38.4, d = 128 58.2 ->
-// 52.5; with several rounds of work-groups they end early as it is: 17 550 + 77 x 12, 15 kept, 155.9 -> 157.5).  One where the video rows' work, in rounds of the chip's work-group slots, hides
+// K_max does not tell), at least eight, or fewer (shorter_pieces).  One where the video rows' work, in rounds of the chip's work-group slots, hides
 // the text rows, which start first.  Measured (us a reuse step, whole -> split), 17 550 video + 77 text tokens, 21 of 138
 // blocks kept: d = 64 x 2 heads 194 -> 58, x 12 331 -> 199, x 40 679 -> 618; d = 128 x 2 264 -> 88, x 12 519 -> 348, x 40
 // 1 187 -> 1 142 (work of 1.7 text rows: whole by the rule, which is drawn for lists of the room they are given);
@@ -994,8 +1017,9 @@ static TextSplit text_split(const dfs_geom* g, const dfs_sizes& s, int K_max, si
   const int64_t slots = g->B == 128 ? 512 : 1024, kept = K_max < s.M ? K_max : s.M;
   const int64_t likely = kept == s.M ? kept / 3 : kept;                  // adaptive lists are given room for all
   if (int64_t(g->heads) * s.M_v * likely * 5 >= 4 * slots * s.M) return whole;
-  int blocks = int(2 * kept <= s.M ? int64_t(g->heads) * s.M <= slots ? kept * 5 / 8 : kept : s.M / 8);
+  int blocks = int(2 * kept <= s.M ? kept : s.M / 8);
   if (blocks < 8) blocks = 8;
+  if (2 * kept <= s.M) blocks = shorter_pieces(g, s, K_max, blocks);
   const size_t row = size_t(g->B) * (g->d + 4) * sizeof(float) * s.M_x * g->heads;         // one split of every text block
   const int64_t room = int64_t((scratch_bytes - align256(split_tickets(g, s) * sizeof(int32_t))) / row);
   if ((s.M + blocks - 1) / blocks > room) {
@@ -1031,11 +1055,6 @@ static TailSplit tail_split(const dfs_geom* g, const dfs_sizes& s, int32_t K_max
   if (size_t(parts) * g->B * (g->d + 4) * sizeof(float) > have) return none;
   return {full, rows, splits};
 }
-
-// Whether all XCDs walk one head together (kernel's mapping 2), an eighth of its video blocks each: once that fills the XCD's 64
-// work-group slots (measured +3..6 % on the 75 600- and 118 800-token shapes, -4 % on the 17 550-token one, which stays on mapping 1).
-static int xcd_blocks(const dfs_sizes& s) { return (s.M_v + 7) / 8; }
-static bool walked_together(const dfs_sizes& s) { return xcd_blocks(s) >= 64; }
 
 // Whether dfs_forward's attention gathers keys and values itself (kernel's SRC) instead of having them reordered in front.  It saves
 // the reorder's way through memory, and on a reuse step its launch; it costs a tile's loads some ten instructions, 0.3 % of a long dense
