@@ -1073,6 +1073,8 @@ bool attn_reads_source(const dfs_geom* g, const dfs_sizes& s, int dtype, const v
   // fp32 tensors (on reuse steps, see dfs_forward): calls of 2^31 operations and less with every block kept, whose reorder is a launch more than it
   // is work.  (us) 256 tokens x 2 heads, d = 64, 11.0 -> 8.9; 1 024 x 3, d = 64 17.5 -> 14.2, d = 128 29.8 -> 24.7; 1 920 x 1, d = 64, dense 46.5 ->
   // 45.7; larger ones lose, the rows of a run lying apart: 1 920 + 30 x 6, d = 128, 127 -> 131, 3 968 x 8 236 -> 252.
+  // One head dense at d = 128, a lone wave per SIMD at the most, loses all the same (768 tokens 39.0 -> 40.4, 2 048 87.7 -> 91.6) where its masked steps win (768, 2
+  // of 12 blocks, 18.0 -> 14.8, half 26.5 -> 25.3, 2 048, half, 52.5 -> 51.5): the host does not know which they are.
   if (dtype == DFS_F32 && 4 * int64_t(g->heads) * g->d * double(s.N_pad) * double(s.N_pad) > 2147483648.0) return false;
   return apart(g, s, dtype, k, o) && apart(g, s, dtype, v, o);
 }

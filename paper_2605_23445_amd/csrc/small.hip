@@ -11,8 +11,8 @@
 
 namespace dfs {
 
-// The most of a head: video tokens times d (256 KB of keys), sub-blocks, rows in the order, blocks.
-constexpr int FS_NUMEL = 65536, FS_SUBS = 64, FS_ROWS_MAX = 2048, FS_BLOCKS = FS_ROWS_MAX / 64;
+// The most of a head: video tokens times d (256 KB of keys), sub-blocks, rows in the order, blocks; of a sub-block: tokens times d.
+constexpr int FS_NUMEL = 65536, FS_SUBS = 64, FS_ROWS_MAX = 2048, FS_BLOCKS = FS_ROWS_MAX / 64, FS_SUB = 8192;
 
 template <int D> struct SmallRoom {                   // LDS
   static constexpr int V_BLOCKS = FS_NUMEL / D / 64;
@@ -200,10 +200,11 @@ __global__ void __launch_bounds__(SS_T) forward_small_kernel(const float* __rest
 // -> one, half the blocks kept; in brackets a first pass over new inputs, waited for, medians of 180): d = 64, 256 tokens x 2 heads 16.4 -> 12.4 (32.5 ->
 // 27.7), x 8 18.0 -> 12.6 (34 -> 28.5), 512 + 40 x 1 26.5 -> 18.9 (42 -> 34), 512 x 8 with 64 sub-blocks 21.1 -> 19.4 (38 -> 34), 1 024 x 1 25.2 -> 24.8 (40.7 ->
 // 40.1), x 4, blocks of 128, 26.9 -> 26.6 (43.4 -> 42.3), x 1 with 128 sub-blocks 22.6 -> 24.6; d = 128, 256 x 8 25.2 -> 22.5 (41.2 -> 38.3), 512 x 8
-// 31.1 -> 30.7 (48 -> 48), x 1 29.2 -> 28.9 (44.0 -> 45.8).  The output must not lie over the queries either, whose neighbours' rows a work-group
+// 31.1 -> 30.7 (48 -> 48), x 1 29.2 -> 28.9 (44.0 -> 45.8).  Sub-blocks of 128 rows at d = 128, a wave's serial way through 64 KB, lose: 128 x 1 34.8 -> 36.2, 256 x 4
+// 36.0 -> 37.1, 512 x 1 44.3 -> 45.5 (of 64 rows 35.4 -> 34.5, of 128 at d = 64 27.7 -> 24.8).  The output must not lie over the queries either, whose neighbours' rows a work-group
 // pools where a block has fewer than four sub-blocks.
 bool forward_small_fits(const dfs_geom* g, const dfs_sizes& s, int dtype, int mode, const void* q, const void* k, const void* v, const void* o) {
-  return dtype == DFS_F32 && mode != DFS_SELECT_MASS_HEAD && s.N_v * g->d <= FS_NUMEL && s.M_s <= FS_SUBS && s.N_pad <= FS_ROWS_MAX && score_small(g, s) &&
+  return dtype == DFS_F32 && mode != DFS_SELECT_MASS_HEAD && s.N_v * g->d <= FS_NUMEL && s.M_s <= FS_SUBS && s.N_pad <= FS_ROWS_MAX && g->Bs * g->d <= FS_SUB && score_small(g, s) &&
          int64_t(g->heads) * s.M * (g->B / 32) <= 256 && apart(g, s, dtype, q, o) && apart(g, s, dtype, k, o) && apart(g, s, dtype, v, o);
 }
 

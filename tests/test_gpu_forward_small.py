@@ -33,7 +33,8 @@ def _state(g, s, K_max, fill=-1):
     (1, 23, 29, 1344, 1, 64, 64, 1, True),                 # 2 048 rows, most of them text
     (1, 23, 29, 1345, 1, 64, 64, 1, False),
     (1, 21, 24, 0, 16, 128, 128, 8, True), (1, 21, 24, 0, 17, 128, 128, 8, False),                 # 256 work-groups and more
-    (3, 7, 11, 70, 5, 128, 64, 8, True), (1, 9, 70, 129, 2, 64, 128, 2, True)])
+    (3, 7, 11, 70, 5, 128, 64, 8, True), (1, 9, 70, 129, 2, 64, 128, 2, True),
+    (1, 16, 30, 40, 2, 128, 128, 2, True), (1, 16, 30, 40, 2, 64, 128, 1, True), (1, 16, 30, 40, 2, 128, 128, 1, False)])      # the longest sub-blocks
 def test_same_as_staged(T, H, W, n_text, heads, d, B, r, small):
     g = P.Geom(T, H, W, n_text, heads, d, B, B // r)
     s = P.dfs_geom_sizes(g)
