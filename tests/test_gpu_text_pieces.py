@@ -13,7 +13,8 @@ from tests import gpu_util as G  # noqa: E402
     (64, 64, 32, 42, 30, 4, 10, 8), (64, 128, 64, 80, 200, 3, 10, 8),      # five eighths of 11 and 12 blocks are 6 and 7: the least piece instead
     (64, 64, 32, 80, 77, 3, 13, 9), (128, 64, 32, 80, 130, 2, 17, 12), (64, 128, 64, 80, 200, 3, 14, 10), (128, 128, 64, 81, 128, 3, 18, 11),
     (128, 128, 64, 81, 400, 3, 14, 11), (64, 64, 32, 80, 300, 2, 13, 11),  # the last piece is one block
-    (64, 64, 32, 80, 77, 3, 10, 12), (64, 64, 32, 80, 77, 3, 11, 13),      # two pieces more for four and five blocks
+    (64, 64, 32, 80, 77, 3, 10, 12), (64, 64, 32, 80, 77, 3, 11, 13), (128, 64, 32, 80, 77, 3, 10, 8),     # two pieces more for four and five blocks
+    (64, 128, 64, 81, 30, 12, 19, 12),                     # 528 work-groups -> 540
     (64, 64, 45, 57, 1, 16, 15, 10), (64, 64, 45, 57, 1, 17, 15, 16),      # 736 work-groups with them, 782
     (64, 64, 32, 42, 259, 15, 6, 11), (64, 64, 24, 40, 259, 20, 5, 10),    # 75 work-groups more, 500 -> 600: one wave group instead of two
     (128, 128, 64, 58, 256, 7, 13, 15), (128, 128, 64, 58, 256, 6, 13, 9)])      # 245 -> 259, a second one on some CUs; 210 -> 222
