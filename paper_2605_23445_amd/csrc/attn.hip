@@ -986,10 +986,10 @@ static bool walked_together(const dfs_sizes& s) { return xcd_blocks(s) >= 64; }
 // last video row where all work-groups start at once.  For that all of them must, in the form that they had (key_split, slim): in blocks of 128 no more of them on
 // a CU than before (query blocks: 512 at the most); in blocks of 64 up to the chip's 1 024 slots and at most 64 more than before, and a piece must lose a block and more
 // for each that a row gains, which the merge reads; at d = 64, where a block is half the work, up to 768 and three blocks.
-// Measured (us a reuse step, long -> short): 2 560 + 30 x 4, 20 kept, d = 64, blocks of 64, 17.6 -> 15.5,
-// 2 560 + 77 x 8, 21 kept, d = 128 38.6 -> 32.1, 5 120 + 259 x 2, 16 kept, blocks of 128, d = 64 29.1 -> 25.0, d = 128 43.6 -> 36.3; not so, blocks of 64, d = 64:
-// 960 + 259 x 20, 10 -> 8 blocks a piece, 500 -> 600 work-groups, 17.4 -> 21.1 (another form), 1 344 + 259 x 15, 11 -> 8, 540 -> 615, 20.5 -> 21.6, 2 624 + 259 x 12, 12 -> 8,
-// 732 -> 852, 22.7 -> 25.0, 4 480 + 30 x 2, 12 -> 8, six -> nine pieces, 16.8 -> 17.3; blocks of 128, d = 128: 3 712 + 256 x 7, 15 -> 9, 245 -> 259, 45.2 -> 50.4.  592
+// Measured (us a reuse step, long -> short): 2 624 + 30 x 4, 20 kept, d = 64, blocks of 64, 17.6 -> 15.5,
+// 2 624 + 77 x 8, 21 kept, d = 128 38.6 -> 32.1, 5 248 + 259 x 2, 16 kept, blocks of 128, d = 64 29.1 -> 25.0, d = 128 43.6 -> 36.3; not so, blocks of 64, d = 64:
+// 960 + 259 x 20, 10 -> 8 blocks a piece, 500 -> 600 work-groups, 17.4 -> 21.1 (another form), 1 344 + 300 x 15, 11 -> 8, 540 -> 615, 20.5 -> 21.6, 2 624 + 259 x 12, 12 -> 8,
+// 732 -> 852, 22.7 -> 25.0, 4 480 + 30 x 2, 12 -> 8, six -> nine pieces, 16.8 -> 17.3; blocks of 128, d = 128: 3 712 + 200 x 7, 15 -> 9, 245 -> 259, 45.2 -> 50.4.  592
 // shapes in all: the 489 taken 0.98 to 1.21 times as fast, 1.073 in the mean; the others would be 0.82 to 1.11 times, 0.978.
 static int shorter_pieces(const dfs_geom* g, const dfs_sizes& s, int K_max, int blocks) {
   const int shorter = blocks * 5 / 8 < 8 ? 8 : blocks * 5 / 8, pieces = (s.M + blocks - 1) / blocks, more = (s.M + shorter - 1) / shorter;
